@@ -44,7 +44,11 @@ constexpr uint8_t kDead = 255;  // species byte of a particle removed by recombi
     (acc)[(k) - kPhaseCollideGather] += t_ - (acc##_t); \
     acc##_t = t_;                        \
   } while (0)
+#define HCAO_CLK_PARAM , uint64_t (&wclk)[5], uint64_t &wclk_t
+#define HCAO_CLK_ARG , wclk, wclk_t
 #else
+#define HCAO_CLK_PARAM
+#define HCAO_CLK_ARG
 #define HCAO_PHASE_MARK(k) \
   do {                     \
   } while (0)
@@ -104,6 +108,15 @@ struct RngT {
     block += 1;
     used = 0;
   }
+  // word i of the current block, selected by value: a conditional over the
+  // members themselves becomes a choice of addresses, which put the whole
+  // generator into scratch memory (every draw of the mixed form then waited
+  // for memory: 0.52 against 0.38 ms per step of 65,536 cells)
+  __device__ __forceinline__ uint32_t word(uint32_t i) const {
+    const uint32_t x0 = w0, x1 = w1, x2 = w2, x3 = w3;
+    const uint32_t lo = (i & 1u) ? x1 : x0, hi = (i & 1u) ? x3 : x2;
+    return (i & 2u) ? hi : lo;
+  }
   __device__ __forceinline__ uint64_t next64() {
     if (used >= 4) refill();
     uint64_t r = (used == 0) ? (((uint64_t)w1 << 32) | w0) : (((uint64_t)w3 << 32) | w2);
@@ -112,7 +125,7 @@ struct RngT {
   }
   __device__ __forceinline__ uint32_t next32() {
     if (used >= 4) refill();
-    const uint32_t r = used == 0 ? w0 : (used == 1 ? w1 : (used == 2 ? w2 : w3));
+    const uint32_t r = word(used);
     used += 1;
     return r;
   }
@@ -121,6 +134,49 @@ struct RngT {
     return (double)(next64() >> 11) * 0x1p-53;
   }
   __device__ __forceinline__ float uniform_f() { return (float)(next32() >> 8) * 0x1p-24f; }
+  // The next two uniforms of this form as raw words (64-bit in the fp64 form,
+  // low word first; 32-bit in the mixed form), with one block computation for
+  // both. The fp64 form's pair always needs exactly one new block (two words
+  // are left or none), so its lanes never diverge here.
+  __device__ __forceinline__ void next_two(uint64_t &a, uint64_t &b) {
+    if constexpr (MIX) {
+      if (used >= 3) {
+        const bool one = used == 3;
+        const uint32_t last = w3;
+        refill();
+        const uint32_t first = w0, second = w1;
+        a = one ? last : first;
+        b = one ? first : second;
+        used = one ? 1u : 2u;
+      } else {
+        a = word(used);
+        b = word(used + 1);
+        used += 2;
+      }
+    } else {
+      const bool left = used == 2;
+      const uint64_t last = ((uint64_t)w3 << 32) | w2;
+      refill();
+      const uint64_t lo = ((uint64_t)w1 << 32) | w0, hi = ((uint64_t)w3 << 32) | w2;
+      a = left ? last : lo;
+      b = left ? lo : hi;
+      used = left ? 2u : 4u;
+    }
+  }
+  // a word of next_two as the uniform itself, and in single precision (the
+  // fp64 form's estimate: within 2^-32 + 2^-24 u of it)
+  static __device__ __forceinline__ double exact_of(uint64_t w) {
+    if constexpr (MIX)
+      return (double)((float)((uint32_t)w >> 8) * 0x1p-24f);
+    else
+      return (double)(w >> 11) * 0x1p-53;
+  }
+  static __device__ __forceinline__ float single_of(uint64_t w) {
+    if constexpr (MIX)
+      return (float)((uint32_t)w >> 8) * 0x1p-24f;
+    else
+      return (float)(uint32_t)(w >> 32) * 0x1p-32f;
+  }
   // passes over the next n uniforms of this form without using them (blocks
   // wholly passed over are not computed)
   __device__ __forceinline__ void skip(uint32_t n) {
@@ -189,8 +245,12 @@ __device__ __forceinline__ uint64_t checked_index(uint64_t i, uint64_t n, uint32
   return 0;
 }
 #define HCAO_IDX(i, n, err) checked_index((i), (n), (err))
+#define HCAO_ERR_PARAM , uint32_t *err
+#define HCAO_ERR_ARG(e) , e
 #else
 #define HCAO_IDX(i, n, err) (i)
+#define HCAO_ERR_PARAM
+#define HCAO_ERR_ARG(e)
 #endif
 
 template <bool MIX>
@@ -381,6 +441,44 @@ __device__ __forceinline__ void tree_sum(double (&y)[N]) {
   for (int x = 0; x < N; ++x) y[x] = y[x] + tree_down<1>(y[x]);
 }
 
+// The same tree over six values at once, packed as it shrinks: the 32- and
+// 16-lane swaps take two registers each and leave the two values' halves side
+// by side, so that one addition serves both, and the 8-lane level puts the
+// last register into the upper halves of the rows. Every addition is the one
+// tree_sum makes (lane t's partial sum plus lane t + s's), 10 of them instead
+// of 36. tree6_value(lane) tells where each value ends;
+// what the other lanes hold is of no use.
+__device__ __forceinline__ double swap_add32(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+__device__ __forceinline__ double swap_add16(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((uint32_t)__double2loint(a), (uint32_t)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b), false, false);
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+// lanes 0-7 of each row: a; lanes 8-15: b of the lane eight below
+__device__ __forceinline__ uint32_t upper_half(uint32_t a, uint32_t b) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)a, (int)b, 0x118, 0xF, 0xC, false);
+}
+__device__ __forceinline__ double tree_sum6(double y0, double y1, double y2, double y3, double y4, double y5) {
+  const double s01 = swap_add32(y0, y1), s23 = swap_add32(y2, y3), s45 = swap_add32(y4, y5);
+  double a = swap_add16(s01, s23);  // rows: y0 y2 y1 y3
+  double b = swap_add16(s45, s45);  // rows: y4 y4 y5 y5
+  a = a + tree_down<8>(a);
+  b = b + tree_down<8>(b);
+  double c = __hiloint2double((int)upper_half((uint32_t)__double2hiint(a), (uint32_t)__double2hiint(b)),
+                              (int)upper_half((uint32_t)__double2loint(a), (uint32_t)__double2loint(b)));
+  c = c + tree_down<4>(c);
+  c = c + tree_down<2>(c);
+  return c + tree_down<1>(c);
+}
+// which value a lane holds after tree_sum6 (6: none)
+__device__ __forceinline__ uint32_t tree6_value(uint32_t lane) {
+  return lane == 0 ? 0u : lane == 32 ? 1u : lane == 16 ? 2u : lane == 48 ? 3u : lane == 8 ? 4u : lane == 40 ? 5u : 6u;
+}
+
 constexpr double kFilter = 1e-4;
 
 __device__ __forceinline__ double pow_estimate(double x, double y) {
@@ -459,11 +557,64 @@ struct PermReg {
     else
       once_r<16>(l, r);
   }
+  // i = l m + r. Below 2^24 the quotient comes from a single-precision
+  // estimate, off by at most one and put right by its remainder (an integer
+  // division takes three times the instructions).
+  __device__ __forceinline__ void divide(uint32_t i, uint32_t &l, uint32_t &r) const {
+    if (n <= (1u << 24)) {
+      l = (uint32_t)((float)i * __builtin_amdgcn_rcpf((float)m));
+      r = i - l * m;
+      if ((int32_t)r < 0) {
+        l -= 1u;
+        r += m;
+      } else if (r >= m) {
+        l += 1u;
+        r -= m;
+      }
+    } else {
+      l = i / m;
+      r = i - l * m;
+    }
+  }
   __device__ __forceinline__ uint32_t operator()(uint32_t i) const {
-    uint32_t l = i / m, r = i - l * m;
+    uint32_t l, r;
+    divide(i, l, r);
     once(l, r);
     while (l * m + r >= n) once(l, r);
     return l * m + r;
+  }
+  // the images a, b of 2k and 2k + 1. The two first evaluations run side by
+  // side; then one walk serves both: a lane steps whichever of its two
+  // values still lies outside [0, n). Two walks after one another each
+  // lasted until the slowest lane of the wave was inside (at 300 particles
+  // per cell about 2.6 evaluations each, 5.2 per 64 pairs; now 3.8).
+  __device__ __forceinline__ void pair(uint32_t k, uint32_t &a, uint32_t &b) const {
+    uint32_t l0, r0;
+    divide(2 * k, l0, r0);
+    uint32_t l1 = l0, r1 = r0 + 1u;
+    if (r1 == m) {
+      l1 += 1u;
+      r1 = 0;
+    }
+    once(l0, r0);
+    once(l1, r1);
+    a = l0 * m + r0;
+    b = l1 * m + r1;
+    while (a >= n || b >= n) {
+      const bool first = a >= n;
+      uint32_t l = first ? l0 : l1, r = first ? r0 : r1;
+      once(l, r);
+      const uint32_t x = l * m + r;
+      if (first) {
+        l0 = l;
+        r0 = r;
+        a = x;
+      } else {
+        l1 = l;
+        r1 = r;
+        b = x;
+      }
+    }
   }
 };
 
@@ -515,22 +666,63 @@ __device__ __forceinline__ double mode_energy(const SpeciesTab &S, const double 
 
 __device__ __forceinline__ double vib_energy(const SpeciesTab &S, const double *lev, const uint16_t *lv,
                                              uint32_t stride) {
+  // bends, then stretches: two plain loops whose table reads do not wait for
+  // the running sum
   double e = 0.0;
-  for (uint32_t m = 0; m < S.n_modes; ++m) e = e + mode_energy(S, lev, m, lv[m * stride]);
+  const uint32_t nb = S.n_bend, nm = S.n_modes;
+#pragma unroll 2
+  for (uint32_t m = 0; m < nb; ++m) e = e + ((double)lv[m * stride] + 0.5) * S.kt[m];
+#pragma unroll 2
+  for (uint32_t m = nb; m < nm; ++m) e = e + lev[S.lev_off[m] + lv[m * stride]];
   return e;
 }
 
-// top quantum number a mode may be proposed at, given the energy e it may hold
-__device__ __forceinline__ uint32_t mode_top(const SpeciesTab &S, const double *lev, uint32_t m, double e) {
-  if (m < S.n_bend) {
-    double fi = floor(e / S.kt[m] - 0.5);
-    fi = fi < 0.0 ? 0.0 : fi;
-    fi = fi > 65535.0 ? 65535.0 : fi;
-    return (uint32_t)fi;
+// top quantum number of a bend of energy quantum kt that may hold energy e:
+// floor(e / kt - 1/2) clamped to 0..65535. The quotient's single-precision
+// estimate is within 3e-7 (x + 1); only one within 1e-6 (x + 1) of an
+// integer evaluates the fp64 division, so the level is the fp64
+// expression's.
+__device__ __forceinline__ uint32_t bend_top(double kt, float inv_kt, double e) {
+  const float x = (float)e * inv_kt - 0.5f;
+  if (fabsf(x - rintf(x)) > 1e-6f * (fabsf(x) + 1.0f)) {
+    const float f = floorf(x);
+    return f < 0.0f ? 0u : (f > 65535.0f ? 65535u : (uint32_t)f);
   }
-  // highest level strictly below e (the table increases strictly), at least 0
+  double fi = floor(e / kt - 0.5);
+  fi = fi < 0.0 ? 0.0 : fi;
+  fi = fi > 65535.0 ? 65535.0 : fi;
+  return (uint32_t)fi;
+}
+
+// highest level of stretch m strictly below e (the ladder increases
+// strictly), at least 0, and its energy. A Morse ladder is inverted in
+// single precision, v = 2 t / (1 + sqrt(1 - 4 x_e t)) with t = e / (h c w_e)
+// (SpeciesTab::guess: the host has checked v against every level of the
+// ladder), and three levels around the guess, read together, settle it;
+// other ladders are bisected (five dependent reads for 22 levels).
+__device__ __forceinline__ uint32_t stretch_top(const SpeciesTab &S, const double *lev, uint32_t m, double e,
+                                                double &e_top) {
   const double *L = lev + S.lev_off[m];
-  uint32_t lo = 0, hi = S.idiss[m];
+  const uint32_t d = S.idiss[m];
+  if ((S.guess >> m) & 1u) {
+    const float t = (float)e * S.inv[m];
+    const float v = (t + t) * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_sqrtf(fmaxf(1.0f - S.anharm4[m] * t, 0.0f)));
+    const float f = fminf(fmaxf(v - 0.5f, 0.0f), (float)d);
+    const uint32_t g = (uint32_t)f;
+    const uint32_t up = g < d ? g + 1u : d, dn = g ? g - 1u : 0u;
+    const double eg = L[g], eu = L[up], ed = L[dn];
+    if (g < d && eu < e) {
+      e_top = eu;
+      return up;
+    }
+    if (g && !(eg < e)) {
+      e_top = ed;
+      return dn;
+    }
+    e_top = eg;
+    return g;
+  }
+  uint32_t lo = 0, hi = d;
   while (lo < hi) {
     const uint32_t mid = (lo + hi + 1) >> 1;
     if (L[mid] < e)
@@ -538,7 +730,15 @@ __device__ __forceinline__ uint32_t mode_top(const SpeciesTab &S, const double *
     else
       hi = mid - 1;
   }
+  e_top = L[lo];
   return lo;
+}
+
+// top quantum number a mode may be proposed at, given the energy e it may hold
+__device__ __forceinline__ uint32_t mode_top(const SpeciesTab &S, const double *lev, uint32_t m, double e) {
+  if (m < S.n_bend) return bend_top(S.kt[m], S.inv[m], e);
+  double unused;
+  return stretch_top(S, lev, m, e, unused);
 }
 
 // uniform level on 0..top from one draw: min(floor(u (top + 1)), top)
@@ -608,6 +808,51 @@ __device__ __forceinline__ double exact_slope(const SpeciesTab &S, const double 
   }
   return sl;
 }
+
+// Gibbs proposal and acceptance in the form's own arithmetic. de_top = E_top
+// - E_0, den = E_c - E_0; slope tells whether the linear envelope applies.
+__device__ __forceinline__ double gibbs_slope(bool slope, double q, double de_top, uint32_t top, double den) {
+  return slope ? (q * de_top) / ((double)top * den) : 0.0;
+}
+template <bool MIX>
+__device__ __forceinline__ uint32_t gibbs_level(double u, bool slope, double q, double de_top, uint32_t top,
+                                                double den) {
+  const double c = gibbs_slope(slope, q, de_top, top, den);
+  const double z = ((double)top + 1.0) * (1.0 - (0.5 * c) * (double)top);
+  const double h = 1.0 + 0.5 * c;
+  const double hh = h * h, c2 = 2.0 * c;
+  if constexpr (MIX) {
+    const float sv = (float)u * (float)z;
+    const float k = (2.0f * sv) / ((float)h + sqrtf((float)hh - (float)c2 * sv));
+    const float fi = floorf(k);
+    return fi > (float)top ? top : (uint32_t)fi;
+  } else {
+    const double sv = u * z;
+    const double k = (2.0 * sv) / (h + sqrt(hh - c2 * sv));
+    const double fi = floor(k);
+    return fi > (double)top ? top : (uint32_t)fi;
+  }
+}
+template <bool MIX>
+__device__ __forceinline__ bool gibbs_accept(double ua, bool slope, double q, double de_top, uint32_t top, double den,
+                                             uint32_t i, double ec, double ei) {
+  const double c = gibbs_slope(slope, q, de_top, top, den);
+  if (!(ei < ec)) return false;
+  if constexpr (MIX) {
+    const float w = 1.0f - (float)c * (float)i;
+    return lb_accept<MIX>((double)((float)ua * w), ec - ei, den, q);
+  } else {
+    return lb_accept<MIX>(ua * (1.0 - c * (double)i), ec - ei, den, q);
+  }
+}
+// When a single-precision Gibbs trial is clear of a boundary. The estimates
+// of c, z and h carry a few 1e-7 each, and the inverse's square root turns
+// the error d of its argument into d / (2 sqrt(arg)): above kGibbsDisc the
+// inverse k is within 6e-6 (k + 1) of the exact one, the product u w within
+// 1e-6, the power within 2e-6 of itself.
+constexpr float kGibbsTol = 3e-5f;
+constexpr float kGibbsDisc = 0.05f;
+constexpr float kGibbsBand = 5e-5f;
 
 // Larsen-Borgnakke relaxation of one molecule (levels at lv[m * stride]);
 // e_tr is the pair's translational energy on entry and exit; btab is the
@@ -744,39 +989,65 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
   // (valid for q <= 1 and levels whose spacings never grow; c = 0 gives the
   // uniform proposal) by inverting its discrete CDF, and accepted with
   // probability target / w_i.
+  //
+  // The proposed level and the acceptance are decided from single-precision
+  // estimates of c, the CDF's inverse and the power; a proposal too near a
+  // boundary (an integer of the inverse, a square root near 0, or u near the
+  // target) is decided by the form's own expressions (gibbs_trial), so every
+  // decision is theirs. A wave waits here for its slowest lane at each mode,
+  // so the length of this chain sets the time of the collision phase: in the
+  // form's own arithmetic it held two fp64 divisions and a bisection per
+  // mode, and two divisions and a square root per trial.
   double et = e_tr;
+  const double *lev = C.T.lev;
+  const float qf = (float)q;
   for (uint32_t m = 0; m < nm; ++m) {
-    const double ec = et + mode_energy(S, C.T.lev, m, lv[m * stride]);
-    const double e0 = mode_energy(S, C.T.lev, m, 0);
+    const bool bend = m < S.n_bend;
+    const double kt = S.kt[m];
+    const double *L = lev + S.lev_off[m];  // a bend reads level 0 of the array and ignores it
+    const uint32_t cur = lv[m * stride];
+    const double l0 = L[0], lc = L[bend ? 0u : cur];
+    const double e0 = bend ? 0.5 * kt : l0;
+    const double ec = et + (bend ? ((double)cur + 0.5) * kt : lc);
     const double den = ec - e0;
     if (!(den > 0.0)) continue;
-    const uint32_t top = mode_top(S, C.T.lev, m, ec);
-    double c = 0.0;
-    if (top > 0 && ((S.concave >> m) & 1u))
-      c = (q * (mode_energy(S, C.T.lev, m, top) - e0)) / ((double)top * den);
-    const double z = ((double)top + 1.0) * (1.0 - (0.5 * c) * (double)top);
-    const double h = 1.0 + 0.5 * c;
-    const double hh = h * h, c2 = 2.0 * c;
+    uint32_t top;
+    double e_top;
+    if (bend) {
+      top = bend_top(kt, S.inv[m], ec);
+      e_top = ((double)top + 0.5) * kt;
+    } else {
+      top = stretch_top(S, lev, m, ec, e_top);
+    }
+    const bool slope = top > 0 && ((S.concave >> m) & 1u);
+    const float tf = (float)top;
+    const float rden = __builtin_amdgcn_rcpf((float)den);
+    const float cf = slope ? (qf * (float)(e_top - e0)) * (rden * __builtin_amdgcn_rcpf(tf)) : 0.0f;
+    const float zf = (tf + 1.0f) * (1.0f - (0.5f * cf) * tf);
+    const float hf = 1.0f + 0.5f * cf;
+    const float hhf = hf * hf, c2f = 2.0f * cf;
     for (;;) {
       ++trials;
-      uint32_t i;
-      double w;
-      if constexpr (MIX) {
-        const float sv = rng.uniform_f() * (float)z;
-        const float k = (2.0f * sv) / ((float)h + sqrtf((float)hh - (float)c2 * sv));
-        const float fi = floorf(k);
-        i = fi > (float)top ? top : (uint32_t)fi;
-        w = (double)(1.0f - (float)c * (float)i);
-      } else {
-        const double sv = rng.uniform() * z;
-        const double k = (2.0 * sv) / (h + sqrt(hh - c2 * sv));
-        const double fi = floor(k);
-        i = fi > (double)top ? top : (uint32_t)fi;
-        w = 1.0 - c * (double)i;
+      uint64_t w1, w2;
+      rng.next_two(w1, w2);
+      const float sv = RngT<MIX>::single_of(w1) * zf;
+      const float disc = hhf - c2f * sv;
+      const float k = (sv + sv) * __builtin_amdgcn_rcpf(hf + __builtin_amdgcn_sqrtf(disc));
+      const float fl = floorf(k), fr = k - fl;
+      const float tol = kGibbsTol * (k + 1.0f);
+      bool clear = disc > kGibbsDisc && fr > tol && fr < 1.0f - tol;
+      uint32_t i = (uint32_t)fminf(fl, tf);
+      const double li = L[bend ? 0u : i];
+      double ei = bend ? ((double)i + 0.5) * kt : li;
+      const float a = RngT<MIX>::single_of(w2) * (1.0f - cf * (float)i);
+      const float est = __builtin_amdgcn_exp2f(qf * __builtin_amdgcn_logf((float)(ec - ei) * rden));
+      bool ok = ei < ec && a < est;
+      clear = clear && (!(ei < ec) || fabsf(a - est) > kGibbsBand * est + 1e-6f);
+      if (!clear) {
+        i = gibbs_level<MIX>(RngT<MIX>::exact_of(w1), slope, q, e_top - e0, top, den);
+        ei = mode_energy(S, lev, m, i);
+        ok = gibbs_accept<MIX>(RngT<MIX>::exact_of(w2), slope, q, e_top - e0, top, den, i, ec, ei);
       }
-      const double ei = mode_energy(S, C.T.lev, m, i);
-      const double ua = (double)draw<MIX>(rng);
-      const bool ok = (ei < ec) && lb_accept<MIX>(MIX ? (double)((float)ua * (float)w) : ua * w, ec - ei, den, q);
       if (ok) {
         lv[m * stride] = (uint16_t)i;
         et = ec - ei;
@@ -799,8 +1070,10 @@ __device__ __forceinline__ V3<Real<MIX>> unit_vector(RngT<MIX> &rng) {
   using R = Real<MIX>;
   R x, y, s;
   for (;;) {
-    x = R(2) * draw<MIX>(rng) - R(1);
-    y = R(2) * draw<MIX>(rng) - R(1);
+    uint64_t w1, w2;
+    rng.next_two(w1, w2);
+    x = R(2) * (R)RngT<MIX>::exact_of(w1) - R(1);
+    y = R(2) * (R)RngT<MIX>::exact_of(w2) - R(1);
     s = x * x + y * y;
     if (s < R(1)) break;
   }
@@ -877,35 +1150,28 @@ __device__ double rot_fraction(uint32_t zeta, double q, RngT<MIX> &rng) {
 
 template <bool MIX>
 struct PairLocal {
-  using R = Real<MIX>;
-  V3<R> v0, v1;
   uint32_t sp0, sp1;
-  bool dead0, dead1;
-  uint16_t *lv0, *lv1, *lvn;
+  uint16_t *lv0, *lv1, *lvn;  // quantum numbers of p, q and the product
   uint32_t ls;
-  bool born;  // a dissociation product (species nb_sp, velocity nb_v, levels lvn)
-  uint32_t nb_sp;
-  V3<R> nb_v;
-  bool has_m, m_moved;  // third body for recombination
-  uint32_t sp_m;
-  V3<R> v_m;
-  double n_cell;
-  double et_out;     // translational energy handed to the scattering (relative motions)
-  double fold_used;  // mixed form: energy owed to the cell that joined this pair
-  int32_t rec_i;  // recombination table node of the cell temperature (-1: below, -2: above)
-  double rec_f;
   double r0, r1, rn;  // rotational energies of p, q and the product (rotors only)
-  uint32_t nb_from;   // side (0: p, 1: q) whose position the product takes
-#ifdef HCAO_PHASE_CLOCKS
-  uint64_t wclk[5], wclk_t;  // collision sub-phase clocks of instrumented builds
-#endif
 };
 
+// What the collision decided for a pair: 0 scattering only, 1 dissociation,
+// 2 exchange, 3 recombination; the reaction, its side (A of a dissociation
+// or exchange, B of a recombination), the third body of a recombination (slot
+// in its cell, species) and the translational energy left to the scattering.
+struct Outcome {
+  int kind, rx;
+  uint32_t side, m, sp_m;
+  double et;
+};
+
+// a value the compiler has to take as new: what it addresses is read again
+// where it is used instead of being held in registers until then
+__device__ __forceinline__ void renew(uint32_t &x) { asm volatile("" : "+v"(x)); }
+
 __device__ __forceinline__ double vib_local(const Tab &T, uint32_t sp, const uint16_t *lv, uint32_t ls) {
-  const SpeciesTab &S = T.sp[sp];
-  double e = 0.0;
-  for (uint32_t m = 0; m < S.n_modes; ++m) e = e + mode_energy(S, T.lev, m, lv[m * ls]);
-  return e;
+  return vib_energy(T.sp[sp], T.lev, lv, ls);
 }
 
 struct Channel {
@@ -947,7 +1213,7 @@ __device__ __forceinline__ void scan_channels(const Tab &T, uint32_t sp0, uint32
             // Eq. Ecoll-diss: E_tr (+ gamma E_rot,A) + E_vib,A - sum ZPE(A, B, C) + E_A,j(0)
             const double etg = EX ? e_tr + R.gamma_rot * (side ? rot1 : rot0) : e_tr;
             const double ecoll = ((etg + evA) - R.zsum) + T.lev[SA.lev_off[m]];
-            const double eex = ecoll - SA.de[m];
+            const double eex = ecoll - SA.kt[m];
             const double pool = (etg + evA) - R.dh;
             const double left = (pool - T.sp[R.c].zpe) - T.sp[R.d].zpe;
             if (eex > 0.0 && left > 0.0 && seen < (uint32_t)kMaxChannels) {
@@ -1004,376 +1270,6 @@ __device__ __forceinline__ void scan_channels(const Tab &T, uint32_t sp0, uint32
     }
   }
   if (pass == 0) S.nch = seen;
-}
-
-// Reaction decision and application, or relaxation of both molecules, then
-// scattering, for one accepted pair held in P. Returns the reaction id or -1.
-// The outcome is decided first; the molecules to relax are then queued (at
-// most two, in draw order) and run through one sampler loop, and the
-// velocities come from at most two isotropic splits. g2 is |v_p - v_q|^2 in
-// fp64. In the mixed form, fold is energy owed to the cell's particles by
-// earlier rounding; it joins this pair's translational energy when the sum
-// stays positive.
-template <bool MIX, bool EX>
-__device__ int collide(const Ctx &C, PairLocal<MIX> &P, double g2, RngT<MIX> &rng, const double *rec,
-                       double fold) {
-  using Rl = Real<MIX>;
-  const Tab &T = C.T;
-  const uint32_t mm = T.mm;
-  const uint32_t ls = P.ls;
-  const uint32_t sp0 = P.sp0, sp1 = P.sp1;
-  const PairTab &PP = T.pair(sp0, sp1);
-  double e_tr0 = PP.hm * g2;
-  if constexpr (MIX) {
-    P.fold_used = 0.0;
-    if (fold != 0.0 && e_tr0 + fold > 0.0) {
-      e_tr0 = e_tr0 + fold;
-      P.fold_used = fold;
-    }
-  }
-  const double ev0 = vib_local(T, sp0, P.lv0, ls), ev1 = vib_local(T, sp1, P.lv1, ls);
-  P.born = false;
-  P.m_moved = false;
-
-  // outcome: 0 none, 1 dissociation, 2 exchange, 3 recombination
-  int kind = 0, rx = -1;
-  uint32_t side = 0;  // reacting side: A of dissociation/exchange, B of recombination
-  V3<Rl> vbc{Rl(0), Rl(0), Rl(0)};
-  double et = e_tr0;
-
-  // --- recombination first: B + C (+M) -> A (+M) ---
-  // (pairs that no reaction lists skip the decision; it would draw nothing)
-  for (uint32_t r = 0; PP.react && r < T.nr && kind == 0; ++r) {
-    const ReactionTab &R = T.rx[r];
-    if (R.kind != HCAO_RX_RECOMBINATION) continue;
-    uint32_t sb;
-    if (P.sp0 == (uint32_t)R.a && P.sp1 == (uint32_t)R.b)
-      sb = 0;
-    else if (P.sp1 == (uint32_t)R.a && P.sp0 == (uint32_t)R.b)
-      sb = 1;
-    else
-      continue;
-    // 53 bits in both forms: the per-collision probability can be far below
-    // the 2^-24 steps of the mixed form's single-word uniforms
-    const double u = rng.uniform53();
-    if (!P.has_m) {
-      atomicAdd(&C.ctr[HCAO_CTR_SUPPRESSED], 1ull);
-      continue;
-    }
-    const double *tab = rec + R.rec_off + (size_t)P.sp_m * T.rec_nt;
-    double prob;
-    if (P.rec_i == -1)
-      prob = tab[0];
-    else if (P.rec_i == -2)
-      prob = tab[T.rec_nt - 1];
-    else
-      prob = tab[P.rec_i] + P.rec_f * (tab[P.rec_i + 1] - tab[P.rec_i]);
-    prob = prob * P.n_cell;
-    if (prob > 1.0) prob = 1.0;
-    if (!(u < prob)) continue;
-    const V3<Rl> vb = sb ? P.v1 : P.v0, vc = sb ? P.v0 : P.v1;
-    const V3<Rl> c3 = com<MIX>(T.pair(R.a, R.b), vb, vc);
-    const double gx = (double)c3.x - (double)P.v_m.x, gy = (double)c3.y - (double)P.v_m.y,
-                 gz = (double)c3.z - (double)P.v_m.z;
-    const double e_am = T.pair(R.c, P.sp_m).hm * ((gx * gx + gy * gy) + gz * gz);
-    double pool = (((e_am + e_tr0) + (sb ? ev1 : ev0)) + (sb ? ev0 : ev1)) - R.dh;
-    double rsum = 0.0;
-    if constexpr (EX) {
-      // B's and C's rotation: kept by A's rotor, else pooled
-      rsum = (sb ? P.r1 : P.r0) + (sb ? P.r0 : P.r1);
-      if (T.sp[R.c].zeta_rot == 0) pool = pool + rsum;
-    }
-    const double e_left = pool - T.sp[R.c].zpe;
-    if (!(e_left > 0.0)) {
-      atomicAdd(&C.ctr[HCAO_CTR_SUPPRESSED], 1ull);
-      continue;
-    }
-    kind = 3;
-    rx = (int)r;
-    side = sb;
-    vbc = c3;
-    et = e_left;
-    if constexpr (EX) {
-      const double ra = T.sp[R.c].zeta_rot > 0 ? rsum : 0.0;
-      P.r0 = sb ? 0.0 : ra;
-      P.r1 = sb ? ra : 0.0;
-    }
-  }
-
-  // --- dissociation and exchange channels, competition by excess energy ---
-  // A pair none of whose channels can open skips the scan (its steric draws
-  // are passed over): the bounds are tested with a margin far above the
-  // rounding of the scan's own sums, so only pairs that certainly stay shut
-  // skip it and the result is the scan's.
-  bool may_open = false;
-  if (kind == 0 && PP.react) {
-    const PairBound &B = PP.bound;
-    for (uint32_t sd = 0; sd < 2; ++sd) {
-      const double ev = sd ? ev1 : ev0;
-      const double et = EX ? e_tr0 + (sd ? P.r1 : P.r0) : e_tr0;
-      const double scale = 1e-9 * ((fabs(et) + ev) + fabs(B.dis_c[sd] < 0.0 ? 0.0 : B.dis_c[sd]) + 1e-30);
-      if ((et + ev) + B.dis_c[sd] > -scale - 1e-9 * fabs(B.dis_c[sd])) may_open = true;
-      if (B.ex_a[sd] >= 0.0 && (et + B.ex_a[sd] * ev) - B.ex_e[sd] > -scale - 1e-9 * B.ex_e[sd]) may_open = true;
-    }
-    if (!may_open) rng.skip(B.n_steric);
-  }
-  if (kind == 0 && PP.react && may_open) {
-    uint64_t steric_ok = 0;
-    ChannelScan S;
-    S.nch = 0;
-    S.total = 0.0;
-    S.found = false;
-    S.first = S.last = S.pick = Channel{-1, 0, 0};
-    scan_channels<MIX, EX>(T, sp0, sp1, ev0, ev1, P.lv0, P.lv1, ls, e_tr0, P.r0, P.r1, rng, steric_ok, 0, 0.0, S);
-    if (S.nch > 0) {
-      Channel pick = S.first;
-      if (S.nch > 1) {
-        const double target = (double)draw<MIX>(rng) * S.total;
-        scan_channels<MIX, EX>(T, sp0, sp1, ev0, ev1, P.lv0, P.lv1, ls, e_tr0, P.r0, P.r1, rng, steric_ok, 1, target,
-                               S);
-        pick = S.found ? S.pick : S.last;
-      }
-      const ReactionTab &R = T.rx[pick.rx];
-      rx = pick.rx;
-      side = (uint32_t)pick.side;
-      const double eva = side ? ev1 : ev0, evb = side ? ev0 : ev1;
-      const double ra = side ? P.r1 : P.r0, rb = side ? P.r0 : P.r1;
-      const double grot = EX ? R.gamma_rot * ra : 0.0;
-      const double etg = EX ? e_tr0 + grot : e_tr0;
-      if (R.kind == HCAO_RX_DISSOCIATION) {
-        kind = 1;
-        et = (((etg + eva) - R.dh) - T.sp[R.c].zpe) - T.sp[R.d].zpe;
-        if constexpr (EX) {
-          // the uncoupled rotation stays with B's rotor, else is pooled
-          double keep = ra - grot;
-          if (T.sp[R.c].zeta_rot == 0) {
-            et = et + keep;
-            keep = 0.0;
-          }
-          if (side)
-            P.r1 = keep;
-          else
-            P.r0 = keep;
-          P.rn = 0.0;
-        }
-      } else {
-        kind = 2;
-        et = ((((etg + eva) + evb) - R.dh) - T.sp[R.c].zpe) - T.sp[R.d].zpe;
-        if constexpr (EX) {
-          // A's uncoupled rotation goes to C's rotor, B's to D's; else pooled
-          double keep_c = ra - grot, keep_d = rb;
-          if (T.sp[R.c].zeta_rot == 0) {
-            et = et + keep_c;
-            keep_c = 0.0;
-          }
-          if (T.sp[R.d].zeta_rot == 0) {
-            et = et + keep_d;
-            keep_d = 0.0;
-          }
-          P.r0 = side ? keep_d : keep_c;
-          P.r1 = side ? keep_c : keep_d;
-        }
-      }
-    }
-  }
-
-  HCAO_WAVE_MARK(P.wclk, kPhaseCollideDecide);
-  // --- queue the relaxations (at most two, in draw order) ---
-  uint16_t *lvj0 = nullptr, *lvj1 = nullptr;
-  uint32_t spj0 = 0, spj1 = 0;
-  double qj0 = 0.0, qj1 = 0.0;
-  uint32_t bj0 = 0, bj1 = 0;  // beta table offsets (exact sampler)
-  bool pv = false;
-  uint32_t njob = 0;
-  const ReactionTab &RX = T.rx[rx < 0 ? 0 : rx];
-  uint16_t *la = side ? P.lv1 : P.lv0;
-  uint16_t *lb = side ? P.lv0 : P.lv1;
-  uint32_t ja_sp = 0, jb_sp = 0;  // candidate jobs a and b
-  uint16_t *ja_lv = nullptr, *jb_lv = nullptr;
-  double ja_q = 0.0, jb_q = 0.0;
-  uint32_t ja_b = 0, jb_b = 0;
-  if (kind == 0) {
-    pv = true;
-    ja_sp = sp0;
-    ja_lv = P.lv0;
-    ja_q = PP.q;
-    ja_b = PP.beta_off;
-    jb_sp = sp1;
-    jb_lv = P.lv1;
-    jb_q = PP.q;
-    jb_b = T.pair(sp1, sp0).beta_off;
-  } else if (kind == 1) {
-    // A + M -> B + C + M: B takes A's slot, C is new, both from the ground state
-    const uint32_t spM = side ? sp0 : sp1;
-    zero_levels(la, ls, mm);
-    zero_levels(P.lvn, ls, mm);
-    ja_sp = (uint32_t)RX.c;
-    ja_lv = la;
-    ja_q = T.pair(RX.c, spM).q;
-    ja_b = T.pair(RX.c, spM).beta_off;
-    jb_sp = (uint32_t)RX.d;
-    jb_lv = P.lvn;
-    jb_q = T.pair(RX.d, spM).q;
-    jb_b = T.pair(RX.d, spM).beta_off;
-  } else if (kind == 2) {
-    // A + B -> C + D: C takes A's slot, D takes B's
-    zero_levels(la, ls, mm);
-    zero_levels(lb, ls, mm);
-    const double qcd = T.pair(RX.c, RX.d).q;
-    ja_sp = (uint32_t)RX.c;
-    ja_lv = la;
-    ja_q = qcd;
-    ja_b = T.pair(RX.c, RX.d).beta_off;
-    jb_sp = (uint32_t)RX.d;
-    jb_lv = lb;
-    jb_q = qcd;
-    jb_b = T.pair(RX.d, RX.c).beta_off;
-  } else {
-    // B + C (+M) -> A (+M): A takes B's slot
-    zero_levels(la, ls, mm);
-    ja_sp = (uint32_t)RX.c;
-    ja_lv = la;
-    ja_q = T.pair(RX.c, P.sp_m).q;
-    ja_b = T.pair(RX.c, P.sp_m).beta_off;
-  }
-  if (T.sp[ja_sp].n_modes > 0) {
-    lvj0 = ja_lv;
-    spj0 = ja_sp;
-    qj0 = ja_q;
-    bj0 = ja_b;
-    ++njob;
-  }
-  if (kind != 3 && T.sp[jb_sp].n_modes > 0) {
-    if (njob == 0) {
-      lvj0 = jb_lv;
-      spj0 = jb_sp;
-      qj0 = jb_q;
-      bj0 = jb_b;
-    } else {
-      lvj1 = jb_lv;
-      spj1 = jb_sp;
-      qj1 = jb_q;
-      bj1 = jb_b;
-    }
-    ++njob;
-  }
-  uint64_t tr = 0;
-  uint32_t nrel = 0, ncap = 0;
-  for (uint32_t j = 0; j < njob; ++j) {
-    const SpeciesTab &S = T.sp[j ? spj1 : spj0];
-    if (pv) {
-      const double u = (double)draw<MIX>(rng);
-      if (!(u < S.p_vib)) continue;
-      ++nrel;
-    }
-    bool capped = false;
-    const uint32_t bo = j ? bj1 : bj0;
-    tr += relax<MIX, EX>(C, S, j ? lvj1 : lvj0, ls, et, j ? qj1 : qj0, C.T.beta + (bo == 0xFFFFFFFFu ? 0u : bo), rng, capped);
-    ncap += capped ? 1u : 0u;
-  }
-  if (tr) atomicAdd(&C.ctr[HCAO_CTR_TRIALS], (unsigned long long)tr);
-  if (nrel) atomicAdd(&C.ctr[HCAO_CTR_RELAX], (unsigned long long)nrel);
-  if (ncap) atomicAdd(&C.ctr[HCAO_CTR_CAPPED], (unsigned long long)ncap);
-
-  HCAO_WAVE_MARK(P.wclk, kPhaseCollideRelax);
-  // --- rotational relaxation of each rotor in turn (non-reactive collisions) ---
-  if constexpr (EX) {
-    if (kind == 0) {
-      for (uint32_t x = 0; x < 2; ++x) {
-        const SpeciesTab &S = T.sp[x ? sp1 : sp0];
-        if (S.zeta_rot == 0) continue;
-        const double u = (double)draw<MIX>(rng);
-        if (!(u < S.p_rot)) continue;
-        const double ec = et + (x ? P.r1 : P.r0);
-        const double er = rot_fraction<MIX>(S.zeta_rot, PP.q, rng) * ec;
-        if (x)
-          P.r1 = er;
-        else
-          P.r0 = er;
-        et = ec - er;
-      }
-    }
-  }
-
-  // --- scattering ---
-  const V3<Rl> va0 = side ? P.v1 : P.v0, vb0 = side ? P.v0 : P.v1;
-  double e1 = et, e2 = 0.0;
-  if (kind == 1) {
-    // share of the translational energy in the B-C motion: density
-    // proportional to sqrt(beta (1 - beta)), by rejection
-    Rl beta;
-    for (;;) {
-      const Rl u1 = draw<MIX>(rng), u2 = draw<MIX>(rng);
-      if (u2 * Rl(0.5) < sqrt(u1 * (Rl(1) - u1))) {
-        beta = u1;
-        break;
-      }
-    }
-    e2 = (double)beta * et;
-    e1 = et - e2;
-  }
-  const uint32_t spA = side ? sp1 : sp0, spB = side ? sp0 : sp1;
-  const PairTab *t1;
-  V3<Rl> cm;
-  if (kind == 0) {
-    t1 = &PP;
-    cm = com<MIX>(PP, P.v0, P.v1);
-  } else if (kind == 1) {
-    t1 = &T.pair(spA, spB);
-    cm = com<MIX>(*t1, va0, vb0);
-  } else if (kind == 2) {
-    t1 = &T.pair(RX.c, RX.d);
-    cm = com<MIX>(T.pair(spA, spB), va0, vb0);
-  } else {
-    t1 = &T.pair(RX.c, P.sp_m);
-    cm = com<MIX>(*t1, vbc, P.v_m);
-  }
-  V3<Rl> x1, y1;
-  P.et_out = et;
-  split<MIX>(*t1, cm, e1, rng, x1, y1);
-  if (kind == 0) {
-    P.v0 = x1;
-    P.v1 = y1;
-    return -1;
-  }
-  if (kind == 1) {
-    V3<Rl> x2, y2;
-    split<MIX>(T.pair(RX.c, RX.d), x1, e2, rng, x2, y2);
-    x1 = x2;
-    P.born = true;
-    P.nb_sp = (uint32_t)RX.d;
-    P.nb_v = y2;
-    P.nb_from = side;
-    atomicAdd(&C.ctr[HCAO_CTR_BIRTHS], 1ull);
-  }
-  if (kind == 3) {
-    P.v_m = y1;
-    P.m_moved = true;
-    atomicAdd(&C.ctr[HCAO_CTR_DEATHS], 1ull);
-  }
-  const uint32_t new_a = (uint32_t)RX.c;
-  const uint32_t new_b = kind == 2 ? (uint32_t)RX.d : spB;
-  if (side) {
-    P.v1 = x1;
-    P.sp1 = new_a;
-    if (kind == 3)
-      P.dead0 = true;
-    else {
-      P.v0 = y1;
-      P.sp0 = new_b;
-    }
-  } else {
-    P.v0 = x1;
-    P.sp0 = new_a;
-    if (kind == 3)
-      P.dead1 = true;
-    else {
-      P.v1 = y1;
-      P.sp1 = new_b;
-    }
-  }
-  atomicAdd(&C.ctr[HCAO_CTR_REACTION0 + rx], 1ull);
-  return rx;
 }
 
 // Sums of m, m v_x, m v_y, m v_z and m |v|^2 over a cell's particles by one
@@ -1447,6 +1343,334 @@ struct CellHdr {
   Perm perm;
 };
 
+// Reaction decision and relaxation of one accepted pair (velocities v0, v1;
+// H its cell, k its index there, e_tr its translational energy).
+// The outcome is decided first; the molecules to relax are then taken in draw
+// order (at most two) through one sampler loop. Velocities are not changed
+// here: scatter() reads them again, so that none is held in registers while
+// the samplers run (held, they and what depends on them were spilled and
+// reloaded around every sampler).
+template <bool MIX, bool EX>
+__device__ __forceinline__ Outcome decide(const Ctx &C, PairLocal<MIX> &P, const CellHdr &H, uint32_t k, const State &st,
+                                          V3<Real<MIX>> v0, V3<Real<MIX>> v1, double e_tr0, RngT<MIX> &rng,
+                                          const double *rec HCAO_ERR_PARAM HCAO_CLK_PARAM) {
+  using Rl = Real<MIX>;
+  const Tab &T = C.T;
+  const uint32_t ls = P.ls;
+  const uint32_t sp0 = P.sp0, sp1 = P.sp1;
+  const PairTab &PP = T.pair(sp0, sp1);
+  Outcome O;
+  O.kind = 0;
+  O.rx = -1;
+  O.side = 0;
+  O.m = 0;
+  O.sp_m = 0;
+  double et = e_tr0;
+
+  // (pairs that no reaction lists skip the decision; it would draw nothing)
+  if (PP.react) {
+    const double ev0 = vib_local(T, sp0, P.lv0, ls), ev1 = vib_local(T, sp1, P.lv1, ls);
+    // --- recombination first: B + C (+M) -> A (+M) ---
+    for (uint32_t r = 0; (PP.react & kReactRecomb) && r < T.nr && O.kind == 0; ++r) {
+      const ReactionTab &R = T.rx[r];
+      if (R.kind != HCAO_RX_RECOMBINATION) continue;
+      uint32_t sb;
+      if (sp0 == (uint32_t)R.a && sp1 == (uint32_t)R.b)
+        sb = 0;
+      else if (sp1 == (uint32_t)R.a && sp0 == (uint32_t)R.b)
+        sb = 1;
+      else
+        continue;
+      // 53 bits in both forms: the per-collision probability can be far below
+      // the 2^-24 steps of the mixed form's single-word uniforms
+      const double u = rng.uniform53();
+      // third body of pair k: the particle at permutation index 2 N_cand + k
+      if (!(2 * H.ncand + k < H.n)) {
+        atomicAdd(&C.ctr[HCAO_CTR_SUPPRESSED], 1ull);
+        continue;
+      }
+      PermReg perm;
+      perm.load(H.perm);
+      const uint32_t im = perm(2 * H.ncand + k);
+      const uint64_t gm = HCAO_IDX(H.base + im, st.n_slots, err);
+      const uint32_t sp_m = st.sp[gm];
+      const double *tab = rec + R.rec_off + (size_t)sp_m * T.rec_nt;
+      double prob;
+      if (H.rec_i == -1)
+        prob = tab[0];
+      else if (H.rec_i == -2)
+        prob = tab[T.rec_nt - 1];
+      else
+        prob = tab[H.rec_i] + H.rec_f * (tab[H.rec_i + 1] - tab[H.rec_i]);
+      prob = prob * H.n_cell;
+      if (prob > 1.0) prob = 1.0;
+      if (!(u < prob)) continue;
+      const V3<Rl> c3 = com<MIX>(T.pair(R.a, R.b), sb ? v1 : v0, sb ? v0 : v1);
+      const V3<Rl> vm = ldv<MIX>(st, gm);
+      const double gx = (double)c3.x - (double)vm.x, gy = (double)c3.y - (double)vm.y,
+                   gz = (double)c3.z - (double)vm.z;
+      const double e_am = T.pair(R.c, sp_m).hm * ((gx * gx + gy * gy) + gz * gz);
+      double pool = (((e_am + e_tr0) + (sb ? ev1 : ev0)) + (sb ? ev0 : ev1)) - R.dh;
+      double rsum = 0.0;
+      if constexpr (EX) {
+        // B's and C's rotation: kept by A's rotor, else pooled
+        rsum = (sb ? P.r1 : P.r0) + (sb ? P.r0 : P.r1);
+        if (T.sp[R.c].zeta_rot == 0) pool = pool + rsum;
+      }
+      const double e_left = pool - T.sp[R.c].zpe;
+      if (!(e_left > 0.0)) {
+        atomicAdd(&C.ctr[HCAO_CTR_SUPPRESSED], 1ull);
+        continue;
+      }
+      O.kind = 3;
+      O.rx = (int)r;
+      O.side = sb;
+      O.m = im;
+      O.sp_m = sp_m;
+      et = e_left;
+      if constexpr (EX) {
+        const double ra = T.sp[R.c].zeta_rot > 0 ? rsum : 0.0;
+        P.r0 = sb ? 0.0 : ra;
+        P.r1 = sb ? ra : 0.0;
+      }
+    }
+
+    // --- dissociation and exchange channels, competition by excess energy ---
+    // A pair none of whose channels can open skips the scan (its steric draws
+    // are passed over): the bounds are tested with a margin far above the
+    // rounding of the scan's own sums, so only pairs that certainly stay shut
+    // skip it and the result is the scan's.
+    bool may_open = false;
+    if (O.kind == 0) {
+      const PairBound &B = PP.bound;
+      for (uint32_t sd = 0; sd < 2; ++sd) {
+        const double ev = sd ? ev1 : ev0;
+        const double eb = EX ? e_tr0 + (sd ? P.r1 : P.r0) : e_tr0;
+        const double scale = 1e-9 * ((fabs(eb) + ev) + fabs(B.dis_c[sd] < 0.0 ? 0.0 : B.dis_c[sd]) + 1e-30);
+        if ((eb + ev) + B.dis_c[sd] > -scale - 1e-9 * fabs(B.dis_c[sd])) may_open = true;
+        if (B.ex_a[sd] >= 0.0 && (eb + B.ex_a[sd] * ev) - B.ex_e[sd] > -scale - 1e-9 * B.ex_e[sd]) may_open = true;
+      }
+      if (!may_open) rng.skip(B.n_steric);
+    }
+    if (may_open) {
+      uint64_t steric_ok = 0;
+      ChannelScan S;
+      S.nch = 0;
+      S.total = 0.0;
+      S.found = false;
+      S.first = S.last = S.pick = Channel{-1, 0, 0};
+      scan_channels<MIX, EX>(T, sp0, sp1, ev0, ev1, P.lv0, P.lv1, ls, e_tr0, P.r0, P.r1, rng, steric_ok, 0, 0.0, S);
+      if (S.nch > 0) {
+        Channel pick = S.first;
+        if (S.nch > 1) {
+          const double target = (double)draw<MIX>(rng) * S.total;
+          scan_channels<MIX, EX>(T, sp0, sp1, ev0, ev1, P.lv0, P.lv1, ls, e_tr0, P.r0, P.r1, rng, steric_ok, 1,
+                                 target, S);
+          pick = S.found ? S.pick : S.last;
+        }
+        const ReactionTab &R = T.rx[pick.rx];
+        O.rx = pick.rx;
+        O.side = (uint32_t)pick.side;
+        const uint32_t side = O.side;
+        const double eva = side ? ev1 : ev0, evb = side ? ev0 : ev1;
+        const double ra = side ? P.r1 : P.r0, rb = side ? P.r0 : P.r1;
+        const double grot = EX ? R.gamma_rot * ra : 0.0;
+        const double etg = EX ? e_tr0 + grot : e_tr0;
+        if (R.kind == HCAO_RX_DISSOCIATION) {
+          O.kind = 1;
+          et = (((etg + eva) - R.dh) - T.sp[R.c].zpe) - T.sp[R.d].zpe;
+          if constexpr (EX) {
+            // the uncoupled rotation stays with B's rotor, else is pooled
+            double keep = ra - grot;
+            if (T.sp[R.c].zeta_rot == 0) {
+              et = et + keep;
+              keep = 0.0;
+            }
+            if (side)
+              P.r1 = keep;
+            else
+              P.r0 = keep;
+            P.rn = 0.0;
+          }
+        } else {
+          O.kind = 2;
+          et = ((((etg + eva) + evb) - R.dh) - T.sp[R.c].zpe) - T.sp[R.d].zpe;
+          if constexpr (EX) {
+            // A's uncoupled rotation goes to C's rotor, B's to D's; else pooled
+            double keep_c = ra - grot, keep_d = rb;
+            if (T.sp[R.c].zeta_rot == 0) {
+              et = et + keep_c;
+              keep_c = 0.0;
+            }
+            if (T.sp[R.d].zeta_rot == 0) {
+              et = et + keep_d;
+              keep_d = 0.0;
+            }
+            P.r0 = side ? keep_d : keep_c;
+            P.r1 = side ? keep_c : keep_d;
+          }
+        }
+      }
+    }
+  }
+
+  HCAO_WAVE_MARK(wclk, kPhaseCollideDecide);
+  // --- the molecules to relax, in draw order: species, the partner that sets
+  // the exponent, levels ---
+  uint32_t ja = sp0, jb = sp1, pa = sp1, pb = sp0;
+  uint16_t *la = P.lv0, *lb = P.lv1;
+  if (O.kind != 0) {
+    const ReactionTab &RX = T.rx[O.rx];
+    la = O.side ? P.lv1 : P.lv0;
+    ja = (uint32_t)RX.c;
+    zero_levels(la, ls, T.mm);
+    if (O.kind == 1) {
+      // A + M -> B + C + M: B takes A's slot, C is new, both from the ground state
+      lb = P.lvn;
+      zero_levels(lb, ls, T.mm);
+      jb = (uint32_t)RX.d;
+      pa = pb = O.side ? sp0 : sp1;
+    } else if (O.kind == 2) {
+      // A + B -> C + D: C takes A's slot, D takes B's
+      lb = O.side ? P.lv0 : P.lv1;
+      zero_levels(lb, ls, T.mm);
+      jb = (uint32_t)RX.d;
+      pa = jb;
+      pb = ja;
+    } else {
+      // B + C (+M) -> A (+M): A takes B's slot
+      pa = O.sp_m;
+    }
+  }
+  const uint32_t njob = O.kind == 3 ? 1u : 2u;
+  uint64_t tr = 0;
+  uint32_t nrel = 0, ncap = 0;
+  for (uint32_t j = 0; j < njob; ++j) {
+    const uint32_t sj = j ? jb : ja;
+    const SpeciesTab &S = T.sp[sj];
+    if (S.n_modes == 0) continue;
+    if (O.kind == 0) {
+      const double u = (double)draw<MIX>(rng);
+      if (!(u < S.p_vib)) continue;
+      ++nrel;
+    }
+    bool capped = false;
+    const PairTab &PJ = T.pair(sj, j ? pb : pa);
+    const uint32_t bo = PJ.beta_off;
+    tr += relax<MIX, EX>(C, S, j ? lb : la, ls, et, PJ.q, C.T.beta + (bo == 0xFFFFFFFFu ? 0u : bo), rng, capped);
+    ncap += capped ? 1u : 0u;
+  }
+  if (tr) atomicAdd(&C.ctr[HCAO_CTR_TRIALS], (unsigned long long)tr);
+  if (nrel) atomicAdd(&C.ctr[HCAO_CTR_RELAX], (unsigned long long)nrel);
+  if (ncap) atomicAdd(&C.ctr[HCAO_CTR_CAPPED], (unsigned long long)ncap);
+
+  HCAO_WAVE_MARK(wclk, kPhaseCollideRelax);
+  // --- rotational relaxation of each rotor in turn (non-reactive collisions) ---
+  if constexpr (EX) {
+    if (O.kind == 0) {
+      for (uint32_t x = 0; x < 2; ++x) {
+        const SpeciesTab &S = T.sp[x ? sp1 : sp0];
+        if (S.zeta_rot == 0) continue;
+        const double u = (double)draw<MIX>(rng);
+        if (!(u < S.p_rot)) continue;
+        const double ec = et + (x ? P.r1 : P.r0);
+        const double er = rot_fraction<MIX>(S.zeta_rot, PP.q, rng) * ec;
+        if (x)
+          P.r1 = er;
+        else
+          P.r0 = er;
+        et = ec - er;
+      }
+    }
+  }
+  O.et = et;
+  return O;
+}
+
+// Scattering and reaction application: the outgoing velocities and species
+// of the pair, the third body and the product. v0, v1 (and vm) are the
+// velocities before the collision.
+template <bool MIX>
+struct Scattered {
+  V3<Real<MIX>> v0, v1, vm, vn;
+  uint32_t sp0, sp1;
+  bool dead0, dead1;
+};
+template <bool MIX, bool EX>
+__device__ __forceinline__ Scattered<MIX> scatter(const Ctx &C, const Outcome &O, uint32_t sp0, uint32_t sp1,
+                                                  V3<Real<MIX>> v0, V3<Real<MIX>> v1, V3<Real<MIX>> vm,
+                                                  RngT<MIX> &rng) {
+  using Rl = Real<MIX>;
+  const Tab &T = C.T;
+  Scattered<MIX> F;
+  F.sp0 = sp0;
+  F.sp1 = sp1;
+  F.dead0 = F.dead1 = false;
+  F.vm = vm;
+  F.vn = V3<Rl>{Rl(0), Rl(0), Rl(0)};
+  const PairTab *t1 = &T.pair(sp0, sp1);
+  V3<Rl> cm;
+  double e1 = O.et, e2 = 0.0;
+  if (O.kind == 0) {
+    cm = com<MIX>(*t1, v0, v1);
+  } else {
+    const ReactionTab &RX = T.rx[O.rx];
+    const uint32_t side = O.side;
+    if (O.kind == 1) {
+      // share of the translational energy in the B-C motion: density
+      // proportional to sqrt(beta (1 - beta)), by rejection
+      Rl beta;
+      for (;;) {
+        const Rl u1 = draw<MIX>(rng), u2 = draw<MIX>(rng);
+        if (u2 * Rl(0.5) < sqrt(u1 * (Rl(1) - u1))) {
+          beta = u1;
+          break;
+        }
+      }
+      e2 = (double)beta * O.et;
+      e1 = O.et - e2;
+    }
+    const V3<Rl> va0 = side ? v1 : v0, vb0 = side ? v0 : v1;
+    const uint32_t spA = side ? sp1 : sp0, spB = side ? sp0 : sp1;
+    if (O.kind == 3) {
+      t1 = &T.pair(RX.c, O.sp_m);
+      cm = com<MIX>(*t1, com<MIX>(T.pair(RX.a, RX.b), va0, vb0), vm);
+    } else {
+      cm = com<MIX>(T.pair(spA, spB), va0, vb0);
+      t1 = O.kind == 1 ? &T.pair(spA, spB) : &T.pair(RX.c, RX.d);
+    }
+  }
+  V3<Rl> x1, y1;
+  split<MIX>(*t1, cm, e1, rng, x1, y1);
+  F.v0 = x1;
+  F.v1 = y1;
+  if (O.kind != 0) {
+    const ReactionTab &RX = T.rx[O.rx];
+    const uint32_t side = O.side;
+    if (O.kind == 1) {
+      V3<Rl> x2, y2;
+      split<MIX>(T.pair(RX.c, RX.d), x1, e2, rng, x2, y2);
+      x1 = x2;
+      F.vn = y2;
+      atomicAdd(&C.ctr[HCAO_CTR_BIRTHS], 1ull);
+    }
+    if (O.kind == 3) {
+      F.vm = y1;
+      y1 = side ? v0 : v1;  // C's velocity is not kept
+      atomicAdd(&C.ctr[HCAO_CTR_DEATHS], 1ull);
+    }
+    const uint32_t new_b = O.kind == 2 ? (uint32_t)RX.d : (side ? sp0 : sp1);
+    F.v0 = side ? y1 : x1;
+    F.v1 = side ? x1 : y1;
+    F.sp0 = side ? new_b : (uint32_t)RX.c;
+    F.sp1 = side ? (uint32_t)RX.c : new_b;
+    F.dead0 = O.kind == 3 && side;
+    F.dead1 = O.kind == 3 && !side;
+    atomicAdd(&C.ctr[HCAO_CTR_REACTION0 + O.rx], 1ull);
+  }
+  return F;
+}
+
 // the cell of flattened candidate j: the last cell whose range starts at or before j
 __device__ __forceinline__ uint32_t group_cell(const CellHdr *hdr, uint32_t ncell, uint32_t j) {
   uint32_t lo = 0, hi = ncell;
@@ -1459,6 +1683,18 @@ __device__ __forceinline__ uint32_t group_cell(const CellHdr *hdr, uint32_t ncel
   }
   return lo;
 }
+
+// a candidate's per-pair records: the changes of its cell's running sums and
+// the mixed form's energy defect (all 0 if it was not accepted)
+struct Records {
+  double y0, y1, y2, y3, y4, y5;
+};
+
+// an accepted pair's velocities, handed from phase A to phase B
+template <typename R>
+struct PairVel {
+  V3<R> p, q;
+};
 
 // Phase 0 stages the tables in LDS and computes each cell's NTC candidate
 // count and permutation keys (and, with recombination, the cell
@@ -1478,11 +1714,12 @@ __device__ __forceinline__ uint32_t group_cell(const CellHdr *hdr, uint32_t ncel
 // pair order, is owed to the cell and joins the translational energy of the
 // cell's pair 0 in the next step in which that pair collides.
 template <int BLOCK, bool MIX, int EX>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void k_step(StepArgs A) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_step(StepArgs A) {
   using R = Real<MIX>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ uint32_t s_nwork, s_total, s_next;
   __shared__ uint32_t s_bin[256];
+  __shared__ WorkRound s_rounds[kLdsRounds];
   const uint32_t tid = threadIdx.x;
   // the wave index is the same on every lane of a wave: held in a scalar
   // register, so that per-wave loops (one wave per cell) and what they
@@ -1494,10 +1731,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
   const uint32_t nctr = 8 + nr;
   const uint32_t c0 = A.grp[2 * blockIdx.x], c1 = A.grp[2 * blockIdx.x + 1];
   const uint32_t ncell = c1 - c0;
-  const uint64_t wbase = A.grp_work[2 * blockIdx.x];
+  const uint64_t wbase = A.grp_work[3 * blockIdx.x];
 #ifdef HCAO_PHASE_CLOCKS
   uint64_t clk_acc[kPhases] = {};
   uint64_t clk_t = clock64();
+  __shared__ unsigned long long s_wclk[5];  // collision sub-phases, summed over the workgroup's waves
+  if (tid < 5) s_wclk[tid] = 0ull;
 #endif
 
   // ---- LDS carve-up ----
@@ -1509,13 +1748,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
   ReactionTab *l_rx = reinterpret_cast<ReactionTab *>(q);
   q += sizeof(ReactionTab) * nr;
   double *l_lev = reinterpret_cast<double *>(q);
-  q += sizeof(double) * nl;
+  q += sizeof(double) * (nl ? nl : 1);  // bends read level 0 without using it
   CellHdr *hdr = reinterpret_cast<CellHdr *>(q);
   q += sizeof(CellHdr) * ncell;
   unsigned long long *l_ctr = reinterpret_cast<unsigned long long *>(q);
   q += sizeof(unsigned long long) * nctr * ncell * 2;  // per-step counters, then totals
-  uint16_t *scr = reinterpret_cast<uint16_t *>(q);  // [2 mm][BLOCK] sampler scratch
-  uint16_t *plv = scr + (size_t)2 * mm * BLOCK;      // [3 mm][BLOCK] pair levels
+  uint16_t *scr = reinterpret_cast<uint16_t *>(q);  // [2 mm][BLOCK] sampler scratch (joint and exact samplers)
+  uint16_t *plv = scr + (GT->sampler_scratch ? (size_t)2 * mm * BLOCK : 0);  // [3 mm][BLOCK] pair levels
 
   unsigned long long *l_tot = l_ctr + (size_t)nctr * ncell;  // counters summed over the launch's steps
 
@@ -1561,10 +1800,13 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
     }
   }
   const Tab T{l_sp, l_pr, l_rx, l_lev, A.beta, ns, nr, mm, GT->rec_nt};
-  const uint32_t wcap = (uint32_t)(A.grp_work[2 * blockIdx.x + 1] - wbase);
+  const uint32_t wcap = (uint32_t)(A.grp_work[3 * blockIdx.x + 1] - wbase);
   uint32_t *work_in = A.work + (size_t)kWorkWords * wbase;  // accepted pairs as found
   uint32_t *work = work_in + (size_t)kWorkFound * wcap;       // their indices sorted by key
   uint8_t *bflag = A.bflag + wbase;
+  PairVel<R> *pv = reinterpret_cast<PairVel<R> *>(A.pv) + wbase;
+  // the rounds stay in LDS where they fit (a group of up to 4,096 candidates)
+  WorkRound *rounds = wcap <= 64 * kLdsRounds ? s_rounds : A.rounds + A.grp_work[3 * blockIdx.x + 2];
   double *wdef = MIX ? A.wdef + wbase : nullptr;
   __syncthreads();
   HCAO_PHASE_MARK(kPhaseLoad);
@@ -1638,19 +1880,21 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
   for (uint32_t j0 = 0; j0 < total; j0 += BLOCK) {
     const uint32_t j = j0 + tid;
     bool acc = false;
-    uint32_t pj = 0, qj = 0, key = 0, rw1 = 0, rw2 = 0, rw3 = 0, g_acc = 0;
+    uint32_t pj = 0, qj = 0, packed = 0, rw1 = 0, rw2 = 0, rw3 = 0;
+    PairVel<R> vel{};
     if (j < total) {
       const uint32_t g = group_cell(hdr, ncell, j);
-      g_acc = g;
       const CellHdr &H = hdr[g];
       const uint32_t k = j - H.cstart;
       PermReg perm;
       perm.load(H.perm);
-      const uint32_t p = perm(2 * k), qq = perm(2 * k + 1);
+      uint32_t p, qq;
+      perm.pair(k, p, qq);
       pj = p;
       qj = qq;
       const uint64_t gp = HCAO_IDX(H.base + p, A.st.n_slots, A.err), gq = HCAO_IDX(H.base + qq, A.st.n_slots, A.err);
       const V3<R> vp = ldv<MIX>(A.st, gp), vq = ldv<MIX>(A.st, gq);
+      vel = PairVel<R>{vp, vq};
       const R dx = vp.x - vq.x, dy = vp.y - vq.y, dz = vp.z - vq.z;
       const R g2 = (dx * dx + dy * dy) + dz * dz;
       const uint32_t a = A.st.sp[gp], b = A.st.sp[gq];
@@ -1662,7 +1906,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
       rw1 = rng.w1;
       rw2 = rng.w2;
       rw3 = rng.w3;
-      bflag[HCAO_IDX(j, wcap, A.err)] = 0;
       // VHS acceptance ua < sigma g / (sigma g)_max with sigma g = C (g^2)^(1-w).
       if constexpr (MIX) {
         const float sg = (g2 > 0.0f) ? (float)PP.csg * pow_f(g2, (float)PP.esg) : 0.0f;
@@ -1689,22 +1932,27 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
       }
       const uint32_t na = T.sp[a].n_modes < 15 ? T.sp[a].n_modes : 15;
       const uint32_t nb = T.sp[b].n_modes < 15 ? T.sp[b].n_modes : 15;
-      key = 255u - (na * 16u + nb);
+      const uint32_t key = 255u - (na * 16u + nb);
+      packed = key | (g << kWorkCell) | (a << kWorkSp0) | (b << kWorkSp1);
       if (acc) atomicAdd(&s_bin[key], 1u);
     }
     const unsigned long long ma = __ballot(acc);
     uint32_t wb = 0;
     if (lane == 0 && ma) wb = atomicAdd(&s_nwork, (uint32_t)__popcll(ma));
     wb = __builtin_amdgcn_readfirstlane(wb);  // every lane is active here: lane 0's value
+    const uint32_t jr = j0 + 64 * wave;  // the wave's first candidate
+    if (lane == 0 && jr < total) rounds[HCAO_IDX(jr / 64, (wcap + 63) / 64, A.err)] = WorkRound{ma, wb, 0};
     if (acc) {
-      uint32_t *w = work_in + (size_t)kWorkFound * HCAO_IDX(wb + (uint32_t)__popcll(ma & lt), wcap, A.err);
+      const uint32_t f = (uint32_t)HCAO_IDX(wb + (uint32_t)__popcll(ma & lt), wcap, A.err);
+      uint32_t *w = work_in + (size_t)kWorkFound * f;
       w[0] = j;
       w[1] = pj;
       w[2] = qj;
-      w[3] = key | (g_acc << 8);
+      w[3] = packed;
       w[4] = rw1;
       w[5] = rw2;
       w[6] = rw3;
+      pv[f] = vel;
     }
   }
   __syncthreads();
@@ -1748,163 +1996,170 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
     const uint32_t i = c0 + lane;
     if (i < nwork) {
 #ifdef HCAO_PHASE_CLOCKS
-    PairLocal<MIX> P;
-    for (int x = 0; x < 5; ++x) P.wclk[x] = 0;
-    P.wclk_t = clock64();
+    uint64_t wclk[5] = {0, 0, 0, 0, 0}, wclk_t = clock64();  // collision sub-phase clocks
     const bool lead = lane == (uint32_t)(__ffsll((long long)__ballot(1)) - 1);
-#else
-    PairLocal<MIX> P;
 #endif
-    const uint32_t *wi = work_in + (size_t)kWorkFound * work[i];
-    const uint32_t j = wi[0], p = wi[1], qq = wi[2];
-    const uint32_t g = wi[3] >> 8;
-    const CellHdr &H = hdr[g];
-    const uint32_t k = j - H.cstart;
-    const uint64_t gp = HCAO_IDX(H.base + p, A.st.n_slots, A.err), gq = HCAO_IDX(H.base + qq, A.st.n_slots, A.err);
-    P.v0 = ldv<MIX>(A.st, gp);
-    P.v1 = ldv<MIX>(A.st, gq);
-    P.sp0 = A.st.sp[gp];
-    P.sp1 = A.st.sp[gq];
-    P.dead0 = P.dead1 = false;
+    uint32_t at = (uint32_t)HCAO_IDX(work[i], wcap, A.err);
+    PairLocal<MIX> P;
     P.ls = BLOCK;
     P.lv0 = plv + tid;
     P.lv1 = plv + (size_t)mm * BLOCK + tid;
     P.lvn = plv + (size_t)2 * mm * BLOCK + tid;
-    // quantum numbers of the species' own modes (the others are 0 in the state
-    // and nothing reads them here)
-    const uint32_t nm0 = T.sp[P.sp0].n_modes, nm1 = T.sp[P.sp1].n_modes;
-    load_levels(A.st, gp, nm0, P.lv0, BLOCK);
-    load_levels(A.st, gq, nm1, P.lv1, BLOCK);
     P.r0 = P.r1 = P.rn = 0.0;
-    if constexpr (EX >= 2) {
-      if (A.st.rot) {
-        P.r0 = A.st.rot[gp];
-        P.r1 = A.st.rot[gq];
-      }
-    }
-    P.has_m = false;
-    uint64_t gm = 0;
-    if ((T.pair(P.sp0, P.sp1).react & kReactRecomb) && 2 * H.ncand + k < H.n) {
-      // third body of pair k: the particle at permutation index 2 N_cand + k
-      PermReg perm;
-      perm.load(H.perm);
-      gm = HCAO_IDX(H.base + perm(2 * H.ncand + k), A.st.n_slots, A.err);
-      P.has_m = true;
-      P.sp_m = A.st.sp[gm];
-      P.v_m = ldv<MIX>(A.st, gm);
-    }
-    P.n_cell = H.n_cell;
-    P.rec_i = H.rec_i;
-    P.rec_f = H.rec_f;
-    // |v_p - v_q|^2 in fp64 (exact differences of fp32 velocities in the mixed form)
-    const double dx = (double)P.v0.x - (double)P.v1.x, dy = (double)P.v0.y - (double)P.v1.y,
-                 dz = (double)P.v0.z - (double)P.v1.z;
-    const double g2 = (dx * dx + dy * dy) + dz * dz;
     RngT<MIX> rng;
-    rng.open(A.seed, k, H.cell, step);
-    // resume after the acceptance draw of phase A: its block's other words
-    rng.block = 1;
-    rng.w1 = wi[4];
-    rng.w2 = wi[5];
-    rng.w3 = wi[6];
-    rng.used = MIX ? 1u : 2u;
-    unsigned long long *ctr = l_ctr + (size_t)g * nctr;
-    atomicAdd(&ctr[HCAO_CTR_COLLISIONS], 1ull);
-    Ctx C{T, ctr, scr, tid, BLOCK};
-    // mixed form: momentum of the pair (and of the third body) before the
-    // collision, in fp64 from the stored fp32 velocities
-    double mt = 0.0, px = 0.0, py = 0.0, pz = 0.0, mm3 = 0.0;
-    if constexpr (MIX) {
-      const double m0 = T.sp[P.sp0].mass, m1 = T.sp[P.sp1].mass;
-      mt = m0 + m1;
-      px = m0 * (double)P.v0.x + m1 * (double)P.v1.x;
-      py = m0 * (double)P.v0.y + m1 * (double)P.v1.y;
-      pz = m0 * (double)P.v0.z + m1 * (double)P.v1.z;
-      if (P.has_m) mm3 = T.sp[P.sp_m].mass;  // joins the sums only if the third body takes part
-    }
-    const Vec3 vm_in = P.has_m ? Vec3{(double)P.v_m.x, (double)P.v_m.y, (double)P.v_m.z} : Vec3{0.0, 0.0, 0.0};
-    // recombination: the pair's terms of its cell's running sums before the collision
-    const uint32_t sp_in0 = P.sp0, sp_in1 = P.sp1;
-    const V3<R> v_in0 = P.v0, v_in1 = P.v1;
-    HCAO_WAVE_MARK(P.wclk, kPhaseCollideGather);
-    collide<MIX, (EX >= 2)>(C, P, g2, rng, A.rec, (MIX && k == 0) ? H.defect : 0.0);
-    HCAO_WAVE_MARK(P.wclk, kPhaseCollideScatter);
-    if constexpr (MIX) {
-      // Energy audit of the fp32 kinematics: the scattering intends the
-      // kinetic energy of the total centre-of-mass motion plus the
-      // translational energy handed to it (vibrational and formation energy
-      // are bookkept in fp64 and cancel); the defect is the intended minus
-      // the stored fp32 kinetic energy, less energy owed that joined here.
-      if (P.m_moved) {
-        mt = mt + mm3;
-        px = px + mm3 * vm_in.x;
-        py = py + mm3 * vm_in.y;
-        pz = pz + mm3 * vm_in.z;
-      }
-      const double ke_int = (0.5 * ((px * px + py * py) + pz * pz)) / mt + P.et_out;
-      double ke_out = 0.0;
-      if (!P.dead0) ke_out = ke_out + kinetic(T.sp[P.sp0].mass, P.v0);
-      if (!P.dead1) ke_out = ke_out + kinetic(T.sp[P.sp1].mass, P.v1);
-      if (P.born) ke_out = ke_out + kinetic(T.sp[P.nb_sp].mass, P.nb_v);
-      if (P.m_moved) ke_out = ke_out + kinetic(T.sp[P.sp_m].mass, P.v_m);
-      wdef[HCAO_IDX(j, wcap, A.err)] = (ke_int - ke_out) - P.fold_used;
-    }
-    if (A.tdelta) {
-      // the pair's change of its cell's running sums: its particles after
-      // (p, q, the recoiling third body, the product) minus before (p, q,
-      // the third body if it took part)
-      double before[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, after[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-      add_terms(before, T.sp[sp_in0].mass, v_in0);
-      add_terms(before, T.sp[sp_in1].mass, v_in1);
-      if (P.m_moved) add_terms(before, T.sp[P.sp_m].mass, vm_in);
-      if (!P.dead0) add_terms(after, T.sp[P.sp0].mass, P.v0);
-      if (!P.dead1) add_terms(after, T.sp[P.sp1].mass, P.v1);
-      if (P.m_moved) add_terms(after, T.sp[P.sp_m].mass, P.v_m);
-      if (P.born) add_terms(after, T.sp[P.nb_sp].mass, P.nb_v);
-      const uint64_t e = HCAO_IDX(wbase + j, A.tdelta_stride, A.err);
-      for (int x = 0; x < 5; ++x) A.tdelta[(size_t)x * A.tdelta_stride + e] = after[x] - before[x];
-    }
-    stv<MIX>(A.st, gp, P.v0);
-    stv<MIX>(A.st, gq, P.v1);
-    A.st.sp[gp] = P.dead0 ? (uint8_t)kDead : (uint8_t)P.sp0;
-    A.st.sp[gq] = P.dead1 ? (uint8_t)kDead : (uint8_t)P.sp1;
-    // the new species' modes, and zeros over the modes only the old species had
-    // (a removed particle's levels are not kept)
-    if (!P.dead0) {
-      const uint32_t nn = T.sp[P.sp0].n_modes;
-      store_levels(A.st, gp, nn, nn > nm0 ? nn : nm0, P.lv0, BLOCK);
-    }
-    if (!P.dead1) {
-      const uint32_t nn = T.sp[P.sp1].n_modes;
-      store_levels(A.st, gq, nn, nn > nm1 ? nn : nm1, P.lv1, BLOCK);
-    }
-    if constexpr (EX >= 2) {
-      if (A.st.rot) {
-        A.st.rot[gp] = P.dead0 ? 0.0 : P.r0;
-        A.st.rot[gq] = P.dead1 ? 0.0 : P.r1;
-      }
-    }
-    if (P.m_moved) stv<MIX>(A.st, gm, P.v_m);
-    if (P.born) {
-      const uint64_t gb = HCAO_IDX(wbase + j, A.born.n_slots, A.err);
-      stv<MIX>(A.born, gb, P.nb_v);
-      A.born.sp[gb] = (uint8_t)P.nb_sp;
-      store_levels(A.born, gb, mm, A.born.lrow, P.lvn, BLOCK);
-      if constexpr (EX >= 1) {
-        if (A.born.rot) A.born.rot[gb] = P.rn;
-        if (A.st.px) {
-          const uint64_t gs = P.nb_from ? gq : gp;
-          A.born.px[gb] = A.st.px[gs];
-          A.born.py[gb] = A.st.py[gs];
-          A.born.pz[gb] = A.st.pz[gs];
+    Outcome O;
+    {
+      const uint32_t *wi = work_in + (size_t)kWorkFound * at;
+      const PairVel<R> vel = pv[at];
+      const V3<R> v0 = vel.p, v1 = vel.q;
+      const uint32_t packed = wi[3], g = (packed >> kWorkCell) & 63u;
+      const CellHdr &H = hdr[g];
+      const uint32_t k = wi[0] - H.cstart;
+      const uint64_t gp = HCAO_IDX(H.base + wi[1], A.st.n_slots, A.err),
+                     gq = HCAO_IDX(H.base + wi[2], A.st.n_slots, A.err);
+      P.sp0 = (packed >> kWorkSp0) & 15u;
+      P.sp1 = (packed >> kWorkSp1) & 15u;
+      // quantum numbers of the species' own modes (the others are 0 in the state
+      // and nothing reads them here)
+      load_levels(A.st, gp, T.sp[P.sp0].n_modes, P.lv0, BLOCK);
+      load_levels(A.st, gq, T.sp[P.sp1].n_modes, P.lv1, BLOCK);
+      if constexpr (EX >= 2) {
+        if (A.st.rot) {
+          P.r0 = A.st.rot[gp];
+          P.r1 = A.st.rot[gq];
         }
       }
+      rng.open(A.seed, k, H.cell, step);
+      // resume after the acceptance draw of phase A: its block's other words
+      rng.block = 1;
+      rng.w1 = wi[4];
+      rng.w2 = wi[5];
+      rng.w3 = wi[6];
+      rng.used = MIX ? 1u : 2u;
+      // |v_p - v_q|^2 in fp64 (exact differences of fp32 velocities in the mixed form)
+      const double dx = (double)v0.x - (double)v1.x, dy = (double)v0.y - (double)v1.y,
+                   dz = (double)v0.z - (double)v1.z;
+      double e_tr = T.pair(P.sp0, P.sp1).hm * ((dx * dx + dy * dy) + dz * dz);
+      // energy owed to the cell's particles by earlier rounding joins the
+      // cell's pair 0 when the sum stays positive
+      if constexpr (MIX)
+        if (k == 0 && H.defect != 0.0 && e_tr + H.defect > 0.0) e_tr = e_tr + H.defect;
+      unsigned long long *ctr = l_ctr + (size_t)g * nctr;
+      atomicAdd(&ctr[HCAO_CTR_COLLISIONS], 1ull);
+      const Ctx C{T, ctr, scr, tid, BLOCK};
+      HCAO_WAVE_MARK(wclk, kPhaseCollideGather);
+      O = decide<MIX, (EX >= 2)>(C, P, H, k, A.st, v0, v1, e_tr, rng, A.rec HCAO_ERR_ARG(A.err) HCAO_CLK_ARG);
     }
-    bflag[HCAO_IDX(j, wcap, A.err)] = (uint8_t)((P.born ? kFlagBorn : 0) | kFlagCollided);
-    HCAO_WAVE_MARK(P.wclk, kPhaseCollideWrite);
+    // the pair's entry and velocities are read again (the dense lists of the
+    // step, still in cache) rather than kept in registers through the samplers
+    renew(at);
+    {
+      const uint32_t *wi = work_in + (size_t)kWorkFound * at;
+      const PairVel<R> vel = pv[at];
+      const V3<R> v0 = vel.p, v1 = vel.q;
+      const uint32_t j = wi[0], g = (wi[3] >> kWorkCell) & 63u;
+      const CellHdr &H = hdr[g];
+      const uint64_t gp = HCAO_IDX(H.base + wi[1], A.st.n_slots, A.err),
+                     gq = HCAO_IDX(H.base + wi[2], A.st.n_slots, A.err),
+                     gm = HCAO_IDX(H.base + O.m, A.st.n_slots, A.err);
+      const bool recoil = O.kind == 3, born = O.kind == 1;
+      V3<R> vm{R(0), R(0), R(0)};
+      if (recoil) vm = ldv<MIX>(A.st, gm);
+      const Ctx C{T, l_ctr + (size_t)g * nctr, scr, tid, BLOCK};
+      const Scattered<MIX> F = scatter<MIX, (EX >= 2)>(C, O, P.sp0, P.sp1, v0, v1, vm, rng);
+      HCAO_WAVE_MARK(wclk, kPhaseCollideScatter);
+      const uint32_t nb_sp = born ? (uint32_t)T.rx[O.rx].d : 0u;
+      const double m0 = T.sp[P.sp0].mass, m1 = T.sp[P.sp1].mass;
+      if constexpr (MIX) {
+        // Energy audit of the fp32 kinematics: the scattering intends the
+        // kinetic energy of the total centre-of-mass motion plus the
+        // translational energy handed to it (vibrational and formation energy
+        // are bookkept in fp64 and cancel); the defect is the intended minus
+        // the stored fp32 kinetic energy, less energy owed that joined here.
+        double mt = m0 + m1;
+        double px = m0 * (double)v0.x + m1 * (double)v1.x;
+        double py = m0 * (double)v0.y + m1 * (double)v1.y;
+        double pz = m0 * (double)v0.z + m1 * (double)v1.z;
+        if (recoil) {
+          const double mm3 = T.sp[O.sp_m].mass;
+          mt = mt + mm3;
+          px = px + mm3 * (double)vm.x;
+          py = py + mm3 * (double)vm.y;
+          pz = pz + mm3 * (double)vm.z;
+        }
+        const double ke_int = (0.5 * ((px * px + py * py) + pz * pz)) / mt + O.et;
+        double ke_out = 0.0;
+        if (!F.dead0) ke_out = ke_out + kinetic(T.sp[F.sp0].mass, F.v0);
+        if (!F.dead1) ke_out = ke_out + kinetic(T.sp[F.sp1].mass, F.v1);
+        if (born) ke_out = ke_out + kinetic(T.sp[nb_sp].mass, F.vn);
+        if (recoil) ke_out = ke_out + kinetic(T.sp[O.sp_m].mass, F.vm);
+        double fold_used = 0.0;
+        if (j == H.cstart && H.defect != 0.0) {
+          const double dx = (double)v0.x - (double)v1.x, dy = (double)v0.y - (double)v1.y,
+                       dz = (double)v0.z - (double)v1.z;
+          const double e_tr = T.pair(P.sp0, P.sp1).hm * ((dx * dx + dy * dy) + dz * dz);
+          if (e_tr + H.defect > 0.0) fold_used = H.defect;
+        }
+        wdef[at] = (ke_int - ke_out) - fold_used;
+      }
+      if (A.tdelta) {
+        // the pair's change of its cell's running sums: its particles after
+        // (p, q, the recoiling third body, the product) minus before (p, q,
+        // the third body if it took part)
+        double before[5] = {0.0, 0.0, 0.0, 0.0, 0.0}, after[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+        add_terms(before, m0, v0);
+        add_terms(before, m1, v1);
+        if (recoil) add_terms(before, T.sp[O.sp_m].mass, vm);
+        if (!F.dead0) add_terms(after, T.sp[F.sp0].mass, F.v0);
+        if (!F.dead1) add_terms(after, T.sp[F.sp1].mass, F.v1);
+        if (recoil) add_terms(after, T.sp[O.sp_m].mass, F.vm);
+        if (born) add_terms(after, T.sp[nb_sp].mass, F.vn);
+        const uint64_t e = HCAO_IDX(wbase + at, A.tdelta_stride, A.err);
+        for (int x = 0; x < 5; ++x) A.tdelta[(size_t)x * A.tdelta_stride + e] = after[x] - before[x];
+      }
+      stv<MIX>(A.st, gp, F.v0);
+      stv<MIX>(A.st, gq, F.v1);
+      A.st.sp[gp] = F.dead0 ? (uint8_t)kDead : (uint8_t)F.sp0;
+      A.st.sp[gq] = F.dead1 ? (uint8_t)kDead : (uint8_t)F.sp1;
+      // the new species' modes, and zeros over the modes only the old species had
+      // (a removed particle's levels are not kept)
+      const uint32_t nm0 = T.sp[P.sp0].n_modes, nm1 = T.sp[P.sp1].n_modes;
+      if (!F.dead0) {
+        const uint32_t nn = T.sp[F.sp0].n_modes;
+        store_levels(A.st, gp, nn, nn > nm0 ? nn : nm0, P.lv0, BLOCK);
+      }
+      if (!F.dead1) {
+        const uint32_t nn = T.sp[F.sp1].n_modes;
+        store_levels(A.st, gq, nn, nn > nm1 ? nn : nm1, P.lv1, BLOCK);
+      }
+      if constexpr (EX >= 2) {
+        if (A.st.rot) {
+          A.st.rot[gp] = F.dead0 ? 0.0 : P.r0;
+          A.st.rot[gq] = F.dead1 ? 0.0 : P.r1;
+        }
+      }
+      if (recoil) stv<MIX>(A.st, gm, F.vm);
+      if (born) {
+        const uint64_t gb = HCAO_IDX(wbase + j, A.born.n_slots, A.err);
+        stv<MIX>(A.born, gb, F.vn);
+        A.born.sp[gb] = (uint8_t)nb_sp;
+        store_levels(A.born, gb, mm, A.born.lrow, P.lvn, BLOCK);
+        if constexpr (EX >= 1) {
+          if (A.born.rot) A.born.rot[gb] = P.rn;
+          if (A.st.px) {
+            const uint64_t gs = O.side ? gq : gp;
+            A.born.px[gb] = A.st.px[gs];
+            A.born.py[gb] = A.st.py[gs];
+            A.born.pz[gb] = A.st.pz[gs];
+          }
+        }
+      }
+      bflag[at] = born ? 1 : 0;
+    }
+    HCAO_WAVE_MARK(wclk, kPhaseCollideWrite);
 #ifdef HCAO_PHASE_CLOCKS
-    if (lead && A.clk)
-      for (int x = 0; x < 5; ++x) atomicAdd(&A.clk[kPhaseCollideGather + x], (unsigned long long)P.wclk[x]);
+    if (lead)
+      for (int x = 0; x < 5; ++x) atomicAdd(&s_wclk[x], (unsigned long long)wclk[x]);
 #endif
     }
   }
@@ -1919,31 +2174,38 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
   // has no registers to spare for it).
   const bool records = MIX || A.tdelta != nullptr;
   constexpr bool kPrefetch = MIX;
-  auto chunk_load = [&](uint32_t g, uint32_t k0, double (&y)[6], uint8_t &fl) {
+  // entry of the group's candidate j, ~0u if it was not accepted
+  auto entry_of = [&](uint32_t j) {
+    const WorkRound r = rounds[HCAO_IDX(j / 64, (wcap + 63) / 64, A.err)];
+    const uint32_t i = j & 63u;
+    return (r.mask >> i) & 1ull ? r.first + (uint32_t)__popcll(r.mask & ((1ull << i) - 1ull)) : ~0u;
+  };
+  auto chunk_load = [&](uint32_t g, uint32_t k0) {
     const CellHdr &H = hdr[g];
     const uint32_t k = k0 + lane;
-    const bool in = k < H.ncand;
-    const uint64_t e = wbase + H.cstart + k;
-    for (int x = 0; x < 6; ++x) y[x] = 0.0;
-    fl = 0;
-    const uint32_t r = (uint32_t)HCAO_IDX(H.cstart + k, in ? wcap : ~0ull, A.err);
-    if (MIX && in) fl = bflag[r];  // the mixed form's defect records need it too
-    if (A.tdelta && in) {
-      if (!MIX) fl = bflag[r];
-      for (int x = 0; x < 5; ++x) y[x] = A.tdelta[(size_t)x * A.tdelta_stride + e];
+    Records r{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    const uint32_t f = k < H.ncand ? entry_of(H.cstart + k) : ~0u;
+    if (f != ~0u) {
+      const uint32_t i = (uint32_t)HCAO_IDX(f, wcap, A.err);
+      if (A.tdelta) {
+        const uint64_t e = wbase + i;
+        r.y0 = A.tdelta[e];
+        r.y1 = A.tdelta[A.tdelta_stride + e];
+        r.y2 = A.tdelta[2 * A.tdelta_stride + e];
+        r.y3 = A.tdelta[3 * A.tdelta_stride + e];
+        r.y4 = A.tdelta[4 * A.tdelta_stride + e];
+      }
+      if (MIX) r.y5 = wdef[i];
     }
-    if (MIX && in) y[5] = wdef[r];
+    return r;
   };
-  double ny[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  uint8_t nfl = 0;
-  if (kPrefetch && records && wave < ncell) chunk_load(wave, 0, ny, nfl);
+  Records next{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  if (kPrefetch && records && wave < ncell) next = chunk_load(wave, 0);
   for (uint32_t g = wave; g < ncell; g += BLOCK / 64) {
     const CellHdr &H = hdr[g];
     const unsigned long long *in = l_ctr + (size_t)g * nctr;
-    double cy[6];
-    for (int x = 0; x < 6; ++x) cy[x] = ny[x];
-    const uint8_t cfl = nfl;
-    if (kPrefetch && records && g + BLOCK / 64 < ncell) chunk_load(g + BLOCK / 64, 0, ny, nfl);
+    const Records first = next;
+    if (kPrefetch && records && g + BLOCK / 64 < ncell) next = chunk_load(g + BLOCK / 64, 0);
     uint32_t alive = H.n;
     if (in[HCAO_CTR_DEATHS] != 0ull) {
       // stable in-place compaction: a chunk's survivors move to lower slots
@@ -1996,7 +2258,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
       uint32_t done = 0;
       for (uint32_t k0 = 0; k0 < H.ncand; k0 += 64) {
         const uint32_t k = k0 + lane;
-        const bool f = k < H.ncand && (bflag[H.cstart + k] & kFlagBorn) != 0;
+        const uint32_t e = k < H.ncand ? entry_of(H.cstart + k) : ~0u;
+        const bool f = e != ~0u && bflag[HCAO_IDX(e, wcap, A.err)] != 0;
         const unsigned long long m = __ballot(f);
         if (f) {
           const uint64_t from = HCAO_IDX(wbase + H.cstart + k, A.born.n_slots, A.err),
@@ -2021,26 +2284,22 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
     // form's energy defects, and the changes of the running sums (a
     // candidate that did not collide contributes 0). A chunk's loads are all
     // issued before any is used.
-    double dsum = 0.0, d[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (records) {
+      double d = 0.0;  // lane tree6_value: that value's sum (the defect alone: lane 0)
       for (uint32_t k0 = 0; k0 < H.ncand; k0 += 64) {
-        double y[6];
-        uint8_t fl;
-        if (kPrefetch && k0 == 0) {
-          for (int x = 0; x < 6; ++x) y[x] = cy[x];
-          fl = cfl;
+        Records r = first;
+        if (!kPrefetch || k0) r = chunk_load(g, k0);
+        if (A.tdelta) {
+          d = d + tree_sum6(r.y0, r.y1, r.y2, r.y3, r.y4, r.y5);
         } else {
-          chunk_load(g, k0, y, fl);
+          double z[1] = {r.y5};
+          tree_sum(z);
+          d = d + z[0];
         }
-        // (a record that phase B did not write is ignored)
-        if (!(fl & kFlagCollided))
-          for (int x = 0; x < (MIX ? 6 : 5); ++x) y[x] = 0.0;
-        tree_sum(y);  // only lane 0's sums are used below
-        for (int x = 0; x < 5; ++x) d[x] = d[x] + y[x];
-        dsum = dsum + y[5];
       }
-      if (A.tdelta && lane == 0)
-        for (int x = 0; x < 5; ++x) hdr[g].tsum[x] = H.tsum[x] + d[x];
+      const uint32_t x = A.tdelta ? tree6_value(lane) : (lane == 0 ? 5u : 6u);
+      if (x < 5u) hdr[g].tsum[x] = H.tsum[x] + d;
+      if (MIX && x == 5u) hdr[g].defect = H.defect + d;
     }
     unsigned long long *tot = l_tot + (size_t)g * nctr;
     for (uint32_t i = lane; i < nctr; i += 64) {
@@ -2056,7 +2315,6 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
       const double seen = __longlong_as_double((long long)H.sgbits);
       Hm.sgmax = seen > H.sgmax ? seen : H.sgmax;
       Hm.rem = H.rem_new;
-      if (MIX) Hm.defect = H.defect + dsum;
     }
   }
   __syncthreads();
@@ -2083,7 +2341,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(3))) void
 #ifdef HCAO_PHASE_CLOCKS
   HCAO_PHASE_MARK(kPhaseStore);
   if (tid == 0 && A.clk)
-    for (int k = 0; k < kPhases; ++k) atomicAdd(&A.clk[k], (unsigned long long)clk_acc[k]);
+    for (int k = 0; k < kPhases; ++k)
+      atomicAdd(&A.clk[k], k >= kPhaseCollideGather ? s_wclk[k - kPhaseCollideGather] : (unsigned long long)clk_acc[k]);
 #endif
 }
 
@@ -2110,7 +2369,7 @@ __device__ __forceinline__ void polar_normals(Rng &rng, double &n1, double &n2) 
 // the level row and the rotational energy of
 // slot g. The thermal initial state and admission through open faces draw
 // the same way.
-__device__ __forceinline__ void sample_internal(const SpeciesTab &S, const double *lev, Rng &rng, double tv,
+__device__ __forceinline__ void sample_internal(const SpeciesTab &S, const double *theta, const double *lev, Rng &rng, double tv,
                                                 double trot, const State &st, uint64_t g, uint32_t mm) {
   for (uint32_t m = 0; m < mm; ++m) {
     uint32_t l = 0;
@@ -2118,7 +2377,7 @@ __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const doubl
       if (m < S.n_bend) {
         const double r = 1.0 - rng.uniform();
         const double lg = -dlog(r);
-        double fi = floor(lg * (tv / S.theta[m]));
+        double fi = floor(lg * (tv / theta[m]));
         fi = fi > 65535.0 ? 65535.0 : fi;
         l = (uint32_t)fi;
       } else {
@@ -2190,7 +2449,7 @@ __global__ __launch_bounds__(256) void k_init(InitArgs A) {
     const uint64_t g = A.off[c] + i;
     store_vel(A.st, g, sigma * n1, sigma * n2, sigma * n3);
     A.st.sp[g] = (uint8_t)s;
-    sample_internal(S, A.lev, rng, tv, tt, A.st, g, mm);
+    sample_internal(S, T.theta[s], A.lev, rng, tv, tt, A.st, g, mm);
     if (A.st.px) {
       // spatial mode: uniform in the cell, one draw per axis
       const uint32_t ix = c % A.nx, iy = (c / A.nx) % A.ny, iz = c / (A.nx * A.ny);
@@ -2563,186 +2822,6 @@ __global__ void k_iota(uint32_t *x, uint64_t n) {
 
 
 // ---------------------------------------------------------------------------
-// Eq. recomb-correct: forward probability summed over every combination of
-// vibrational levels (set-up work, not part of the step)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ double level_above_ground(const SpeciesTab &S, const double *lev, uint32_t m, uint32_t j) {
-  return mode_energy(S, lev, m, j) - mode_energy(S, lev, m, 0);
-}
-
-template <bool WRITE>
-__global__ __launch_bounds__(256) void k_rec_enum(RecEnumArgs A) {
-  const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= A.n_prefix) return;
-  const SpeciesTab &S = A.tab->sp[A.species];
-  const uint32_t nm = S.n_modes, np = A.n_prefix_modes;
-  uint32_t j[kMaxModes];
-  double st[kMaxModes + 1];
-  uint64_t x = tid;
-  for (uint32_t m = 0; m < np; ++m) {
-    j[m] = (uint32_t)(x % A.box[m]);
-    x /= A.box[m];
-  }
-  uint32_t n = 0;
-  const uint64_t o = WRITE ? A.offset[tid] : 0;
-  auto emit = [&](double e, uint32_t code) {
-    if (WRITE) {
-      A.rec_e[o + n] = e;
-      A.rec_code[o + n] = code;
-    }
-    ++n;
-  };
-  // the prefix: valid while below de; a crossing inside it is emitted once,
-  // by the prefix whose crossing level is the first one and whose later
-  // digits are 0
-  double s = 0.0;
-  bool walk = true;
-  for (uint32_t m = 0; m < np && walk; ++m) {
-    if (m >= S.n_bend && j[m] > S.idiss[m]) {
-      walk = false;
-      break;
-    }
-    const double s2 = s + level_above_ground(S, A.lev, m, j[m]);
-    if (!(s2 < A.de)) {
-      bool first = j[m] == 0 || s + level_above_ground(S, A.lev, m, j[m] - 1) < A.de;
-      for (uint32_t k = m + 1; k < np; ++k) first = first && j[k] == 0;
-      if (first) emit(s2, m | (j[m] << 8));
-      walk = false;
-      break;
-    }
-    s = s2;
-  }
-  if (walk) {
-    if (np == nm) {
-      emit(s, kRecLeaf);
-    } else {
-      uint32_t m = np;
-      j[m] = 0;
-      st[m] = s;
-      for (;;) {
-        bool back = false;
-        if (m >= S.n_bend && j[m] > S.idiss[m]) {
-          back = true;
-        } else {
-          const double s2 = st[m] + level_above_ground(S, A.lev, m, j[m]);
-          if (!(s2 < A.de)) {
-            emit(s2, m | (j[m] << 8));
-            back = true;
-          } else if (m + 1 == nm) {
-            emit(s2, kRecLeaf);
-            ++j[m];
-          } else {
-            st[m + 1] = s2;
-            j[m + 1] = 0;
-            ++m;
-          }
-        }
-        if (back) {
-          if (m == np) break;
-          --m;
-          ++j[m];
-        }
-      }
-    }
-  }
-  if (!WRITE) A.count[tid] = n;
-}
-
-// Regularized upper incomplete gamma Q(a, x) times exp(-y), x > 0 (series
-// for the lower function below x = a + 1, Lentz's continued fraction above;
-// Press et al., Numerical Recipes 6.2); the prefactor joins exp(-y) in one
-// exponent so that small terms do not underflow early.
-__device__ double gamma_q_scaled(double a, double x, double lga, double y) {
-  const double lpre = (a * log(x) - x) - lga;
-  if (x < a + 1.0) {
-    double ap = a, del = 1.0 / a, sum = del;
-    for (int i = 1; i <= 1000; ++i) {
-      ap += 1.0;
-      del *= x / ap;
-      sum += del;
-      if (fabs(del) < fabs(sum) * 1e-17) break;
-    }
-    return (1.0 - sum * exp(lpre)) * exp(-y);
-  }
-  const double tiny = 1e-300;
-  double b = (x + 1.0) - a, c = 1.0 / tiny, d = 1.0 / b, h = d;
-  for (int i = 1; i <= 1000; ++i) {
-    const double an = -(double)i * ((double)i - a);
-    b += 2.0;
-    d = an * d + b;
-    if (fabs(d) < tiny) d = tiny;
-    c = b + an / c;
-    if (fabs(c) < tiny) c = tiny;
-    d = 1.0 / d;
-    const double del = d * c;
-    h *= del;
-    if (fabs(del - 1.0) < 1e-17) break;
-  }
-  return exp(lpre - y) * h;
-}
-
-__global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  double *tail = reinterpret_cast<double *>(smem);  // stretch levels: sum_{k >= j} exp(-beta (e_k - e_j))
-  __shared__ double s_z[kMaxModes + 1], s_bend[kMaxModes], s_red[256];
-  const SpeciesTab &S = A.tab->sp[A.species];
-  const uint32_t nm = S.n_modes, tid = threadIdx.x;
-  const double beta = 1.0 / (kBoltz * A.t[blockIdx.x]);
-  if (tid < nm) {
-    const uint32_t m = tid;
-    if (m < S.n_bend) {
-      const double z = 1.0 / (1.0 - exp(-(beta * S.kt[m])));
-      s_bend[m] = z;
-      s_z[m] = z;
-    } else {
-      // tail sums from the top level down; the partition sum is tail[0]
-      const uint32_t base = S.lev_off[m] - S.lev_off[S.n_bend];
-      const uint32_t top = S.idiss[m];
-      tail[base + top] = 1.0;
-      for (uint32_t k = top; k-- > 0;) {
-        const double step = level_above_ground(S, A.lev, m, k + 1) - level_above_ground(S, A.lev, m, k);
-        tail[base + k] = 1.0 + exp(-(beta * step)) * tail[base + k + 1];
-      }
-      s_z[m] = tail[base];
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    // s_z[m] becomes the product of the partition sums of modes m..nm-1
-    double z = 1.0;
-    s_z[nm] = 1.0;
-    for (uint32_t m = nm; m-- > 0;) {
-      z = z * s_z[m];
-      s_z[m] = z;
-    }
-  }
-  __syncthreads();
-  double acc = 0.0;
-  for (uint64_t i = tid; i < A.n_rec; i += 256) {
-    const double e = A.rec_e[i];
-    const uint32_t code = A.rec_code[i];
-    if (code == kRecLeaf) {
-      acc += gamma_q_scaled(A.a, beta * (A.de - e), A.lgamma_a, beta * e);
-    } else {
-      const uint32_t m = code & 0xFFu, jj = code >> 8;
-      const double rel = m < S.n_bend ? s_bend[m] : tail[(S.lev_off[m] - S.lev_off[S.n_bend]) + jj];
-      acc += (exp(-(beta * e)) * rel) * s_z[m + 1];
-    }
-  }
-  s_red[tid] = acc;
-  __syncthreads();
-  for (uint32_t w = 128; w > 0; w >>= 1) {
-    if (tid < w) s_red[tid] = s_red[tid] + s_red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) {
-    A.num[blockIdx.x] = s_red[0];
-    A.den[blockIdx.x] = s_z[0];
-  }
-}
-
-
-// ---------------------------------------------------------------------------
 // spatial mode: ballistic move with periodic or specular walls, then a
 // stable re-bin by (new cell, old slot) that sorts only the particles that
 // left their cell
@@ -2962,7 +3041,7 @@ __global__ __launch_bounds__(256) void k_inflow_make(InflowArgs A) {
   v[F.a] = sigma * n1;
   v[F.b] = sigma * n2;
   A.ins.sp[j] = (uint8_t)s;
-  sample_internal(S, A.lev, rng, A.t_vib, A.t_trans, A.ins, j, mm);
+  sample_internal(S, A.tab->theta[s], A.lev, rng, A.t_vib, A.t_trans, A.ins, j, mm);
   bool flip = false;
   const bool left =
       move_particle(p[0], p[1], p[2], v[0], v[1], v[2], tau * A.dt, A.len, A.periodic, A.open, flip);
@@ -3336,9 +3415,9 @@ __global__ __launch_bounds__(256) void k_rebin_admit(RebinArgs A) {
 // ---------------------------------------------------------------------------
 size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block) {
   const uint32_t ns = T.n_species, nr = T.n_reactions;
-  size_t b = sizeof(SpeciesTab) * ns + sizeof(PairTab) * ns * ns + sizeof(ReactionTab) * nr + 8 * (size_t)T.n_levels;
+  size_t b = sizeof(SpeciesTab) * ns + sizeof(PairTab) * ns * ns + sizeof(ReactionTab) * nr + 8 * (size_t)(T.n_levels ? T.n_levels : 1);
   b += sizeof(CellHdr) * max_cells + 2 * 8 * (size_t)(8 + nr) * max_cells;
-  b += (size_t)2 * (2 + 3) * (T.max_modes ? T.max_modes : 1) * block;
+  b += (size_t)2 * ((T.sampler_scratch ? 2 : 0) + 3) * (T.max_modes ? T.max_modes : 1) * block;
   return (b + 15) & ~(size_t)15;
 }
 
@@ -3541,22 +3620,6 @@ hipError_t launch_rebin_place(const RebinArgs &a, hipStream_t s) {
   hipLaunchKernelGGL(k_rebin_push, dim3(((a.n_cells + 7u) / 8u) * 8u), dim3(256), 0, s, a);
   if (a.m > a.m_real)
     hipLaunchKernelGGL(k_rebin_admit, dim3((unsigned)((a.m - a.m_real + 255) / 256)), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_rec_enum(const RecEnumArgs &a, bool write, hipStream_t s) {
-  if (a.n_prefix == 0) return hipSuccess;
-  const dim3 grid((unsigned)((a.n_prefix + 255) / 256));
-  if (write)
-    hipLaunchKernelGGL(k_rec_enum<true>, grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL(k_rec_enum<false>, grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_rec_sum(const RecSumArgs &a, uint32_t n_t, size_t lds, hipStream_t s) {
-  if (n_t == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rec_sum, dim3(n_t), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 

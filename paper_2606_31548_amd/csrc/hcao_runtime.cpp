@@ -76,7 +76,8 @@ namespace {
 
 constexpr double kB = 1.380649e-23;
 constexpr double kPi = 3.141592653589793;
-constexpr size_t kLdsBudget = 64 * 1024;  // LDS bytes per workgroup of the step kernel
+constexpr size_t kLdsBudget = 68 * 1024;  // LDS bytes per workgroup of the step kernel (64 KB of cells and tables, and the tables' single-precision columns)
+constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombination sum's stretch ladders
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
 struct SpeciesHost {
@@ -184,6 +185,8 @@ struct hcao_ctx {
   DevBuf<uint64_t> grp_work;
   DevBuf<uint8_t> bflag;
   DevBuf<double> wdef;
+  DevBuf<uint8_t> pv;         // velocities of the accepted pairs (six numbers per work entry)
+  DevBuf<WorkRound> rounds;   // accepted candidates per 64, per workgroup
   uint64_t work_entries = 0;  // entries of work / bflag / wdef
   uint32_t n_groups = 0, max_group_cells = 1;
   size_t step_lds = 0;
@@ -263,6 +266,27 @@ hcao_status build_stretch(hcao_ctx *c, double we, double xe, double de, uint32_t
   if (why) return fail(c, HCAO_EINVAL, why);
   de_out = de;
   return HCAO_OK;
+}
+
+// Closed-form inverse of a ladder E_i = a v - b v^2, v = i + 1/2, from its
+// first two spacings: v(e) = 2 t / (1 + sqrt(1 - 4 (b / a) t)), t = e / a, in
+// single precision. True when v stays within 0.4 of every level's own v for
+// energies up to 1e-6 to either side of it (the inverse grows with e, so it is
+// then within one level everywhere); the kernel settles the rest exactly.
+bool invert_ladder(const std::vector<double> &L, float &inv_a, float &x4) {
+  if (L.size() < 3) return false;
+  const double b = 0.5 * ((L[1] - L[0]) - (L[2] - L[1])), a = (L[1] - L[0]) + 2.0 * b;
+  if (!(a > 0.0) || !(b >= 0.0)) return false;
+  inv_a = (float)(1.0 / a);
+  x4 = (float)(4.0 * b / a);
+  if (!std::isfinite(inv_a)) return false;
+  for (size_t i = 0; i < L.size(); ++i)
+    for (double f : {1.0 - 1e-6, 1.0, 1.0 + 1e-6}) {
+      const float t = (float)(L[i] * f) * inv_a;
+      const float v = (t + t) / (1.0f + std::sqrt(std::max(1.0f - x4 * t, 0.0f)));
+      if (!(std::fabs(v - ((float)i + 0.5f)) < 0.4f)) return false;
+    }
+  return true;
 }
 
 // the vibrational modes of a species for the host tables
@@ -352,6 +376,8 @@ void free_state(hcao_ctx *c) {
   c->work.release();
   c->bflag.release();
   c->wdef.release();
+  c->pv.release();
+  c->rounds.release();
   c->work_entries = 0;
   c->loaded = false;
 }
@@ -454,8 +480,9 @@ hcao_status upload_vel(hcao_ctx *c, const std::vector<double> &vx, const std::ve
 // Workgroups of the step kernel: runs of consecutive cells of at most
 // kMaxGroupCells cells (fewer when the per-cell LDS records of a wide
 // workgroup would not fit) and about group_slots slots each. Workgroup w
-// takes cells [grp[2w], grp[2w+1]) and work-list entries [grp_work[2w],
-// grp_work[2w+1]) (cap/2 + 1 per cell). Workgroups are dispatched longest
+// takes cells [grp[2w], grp[2w+1]), work-list entries [grp_work[3w],
+// grp_work[3w+1]) (cap/2 + 1 per cell) and rounds from grp_work[3w+2] (one per
+// 64 work entries). Workgroups are dispatched longest
 // first (by slot capacity), so that the largest cells start earliest.
 hcao_status build_groups(hcao_ctx *c) {
   const uint32_t nc = c->cfg.n_cells;
@@ -487,11 +514,14 @@ hcao_status build_groups(hcao_ctx *c) {
   std::stable_sort(groups.begin(), groups.end(), [](const G &x, const G &y) { return x.slots > y.slots; });
   std::vector<uint32_t> grp;
   std::vector<uint64_t> gw;
+  uint64_t rounds = 0;
   for (const G &g : groups) {
     grp.push_back(g.c0);
     grp.push_back(g.c1);
     gw.push_back(g.w0);
     gw.push_back(g.w1);
+    gw.push_back(rounds);
+    rounds += (g.w1 - g.w0 + 63) / 64;
   }
   c->n_groups = (uint32_t)groups.size();
   c->max_group_cells = max_cells;
@@ -501,10 +531,12 @@ hcao_status build_groups(hcao_ctx *c) {
   if (c->work_entries != wsum) {
     HIP_TRY(c, c->work.alloc((uint64_t)kWorkWords * wsum));  // the pairs as found, then sorted
     HIP_TRY(c, c->bflag.alloc(wsum));
+    HIP_TRY(c, c->pv.alloc(wsum * 6 * (c->mixed ? sizeof(float) : sizeof(double))));
     if (c->mixed) HIP_TRY(c, c->wdef.alloc(wsum));
     if (c->tab.has_recomb) HIP_TRY(c, c->tdelta.alloc(5 * wsum));
     c->work_entries = wsum;
   }
+  if (c->rounds.n < rounds) HIP_TRY(c, c->rounds.alloc(rounds));
   HIP_TRY(c, hipMemcpyAsync(c->grp.p, grp.data(), grp.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->grp_work.p, gw.data(), gw.size() * 8, hipMemcpyHostToDevice, c->stream));
   c->step_lds = step_lds_bytes(c->tab, c->max_group_cells, c->block);
@@ -690,7 +722,7 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
       n_sl += S.idiss[m] + 1;
     }
   }
-  if (n_sl * sizeof(double) > kLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "stretch ladders too long for the exact sum");
+  if (n_sl * sizeof(double) > kRecLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "stretch ladders too long for the exact sum");
   uint64_t n_prefix = 1;
   uint32_t np = 0;
   while (np < nm && n_prefix * box[np] <= (1ull << 22)) n_prefix *= box[np++];
@@ -1003,9 +1035,11 @@ hcao_status hcao_finalize(hcao_ctx *c) {
     S.n_modes = h.n_modes;
     S.n_bend = h.d.n_bend;
     S.sampler = (uint32_t)h.sampler;
+    if (h.n_modes && h.sampler != HCAO_SAMPLER_GIBBS) T.sampler_scratch = 1;
     for (uint32_t b = 0; b < h.d.n_bend; ++b) {
-      S.theta[b] = h.theta[b];
+      T.theta[s][b] = h.theta[b];
       S.kt[b] = kB * h.theta[b];
+      S.inv[b] = (float)(1.0 / S.kt[b]);
     }
     // bends have equal spacings; a stretch qualifies when its spacings never
     // grow (Morse levels), which the Gibbs proposal's envelope needs
@@ -1015,12 +1049,13 @@ hcao_status hcao_finalize(hcao_ctx *c) {
       const uint32_t m = h.d.n_bend + j;
       S.lev_off[m] = (uint32_t)c->lev_host.size();
       S.idiss[m] = (uint32_t)h.levels[j].size() - 1;
-      S.de[m] = h.de[j];
+      S.kt[m] = h.de[j];
       const std::vector<double> &L = h.levels[j];
       bool spacing_shrinks = true;
       for (size_t i = 1; i + 1 < L.size(); ++i)
         if (!((L[i + 1] - L[i]) <= (L[i] - L[i - 1]))) spacing_shrinks = false;
       if (spacing_shrinks) S.concave |= 1u << m;
+      if (invert_ladder(L, S.inv[m], S.anharm4[m])) S.guess |= 1u << m;
       c->lev_host.insert(c->lev_host.end(), h.levels[j].begin(), h.levels[j].end());
     }
   }
@@ -1347,6 +1382,8 @@ StepArgs step_args(hcao_ctx *c, double dt) {
   a.grp_work = c->grp_work.p;
   a.work = c->work.p;
   a.bflag = c->bflag.p;
+  a.pv = c->pv.p;
+  a.rounds = c->rounds.p;
   a.wdef = c->wdef.p;
   a.tdelta = c->tab.has_recomb ? c->tdelta.p : nullptr;
   a.tdelta_stride = c->work_entries;

@@ -27,25 +27,41 @@ struct SpeciesTab {
   double mass, zpe, formation, p_vib, p_rot;
   uint32_t n_modes, n_bend, sampler;
   uint32_t concave;             // bit m: the level spacings of mode m never increase
-  uint32_t zeta_rot, pad_rot;   // rotational degrees of freedom (0, 2 or 3)
-  double kt[kMaxModes];         // bends: k_B Theta
-  double theta[kMaxModes];      // bends: Theta
-  double de[kMaxModes];         // stretches: D_e
+  uint32_t zeta_rot;            // rotational degrees of freedom (0, 2 or 3)
+  uint32_t guess;               // bit m: stretch m's ladder is inverted in closed form (inv, anharm4)
+  // (one column serves both kinds of mode where each needs a number of its own:
+  // the step kernel keeps the table in LDS, which decides how many workgroups
+  // share a CU)
+  double kt[kMaxModes];         // bends: k_B Theta; stretches: D_e
   uint32_t lev_off[kMaxModes];  // stretches: offset of level 0 in the level array
   uint32_t idiss[kMaxModes];    // stretches: top bound level
+  float inv[kMaxModes];         // bends: 1 / (k_B Theta); stretches: 1 / (h c w_e) of the ladder's parabola
+  float anharm4[kMaxModes];     // stretches: 4 x_e of the ladder's parabola
 };
 
 // PairTab::react bits
 constexpr uint32_t kReactAny = 1u;    // some reaction lists the pair (as A, or as A + B / B + C), in either order
 constexpr uint32_t kReactRecomb = 2u;  // a recombination lists it as B + C, in either order
 
-// Words per work-list entry: the pair as found (candidate j, p, q, the sort
-// key in bits 0-7 with the index of the pair's cell in its group from bit 8,
-// words 1-3 of the pair stream's first Philox block), then the sorted list
-// (the index of an entry as found).
+// Words per work-list entry: the pair as found (candidate j, p, q, packed
+// numbers, words 1-3 of the pair stream's first Philox block), then the sorted
+// list (the index of an entry as found). The packed word holds the sort key
+// (8 bits), the index of the pair's cell in its group (6) and the two species
+// (4 each).
 constexpr uint32_t kWorkFound = 7;
 constexpr uint32_t kWorkSorted = 1;
 constexpr uint32_t kWorkWords = kWorkFound + kWorkSorted;
+constexpr uint32_t kWorkCell = 8, kWorkSp0 = 14, kWorkSp1 = 18;  // first bits of the packed word's fields
+static_assert(kMaxSpecies <= 16, "work-list entries hold species in four bits");
+
+// The accepted ones of 64 consecutive candidates: bit i of mask is candidate
+// 64 r + i of the group, and the accepted candidate with b accepted ones
+// before it in the mask is entry first + b as found.
+struct alignas(16) WorkRound {
+  uint64_t mask;
+  uint32_t first, pad;
+};
+constexpr uint32_t kLdsRounds = 64;  // rounds a workgroup keeps in LDS; larger groups use their global ones
 
 // Bounds of the pair's dissociation and exchange channels, per side (0: a is
 // A, 1: b is A), for the test that lets a pair skip the channel scan when no
@@ -97,11 +113,13 @@ constexpr double kRecTmax = 5.0e4;
 
 struct Tables {
   uint32_t n_species, n_reactions, max_modes, n_levels;
-  uint32_t has_recomb, rec_nt, has_rot, pad1;
+  uint32_t has_recomb, rec_nt, has_rot;
+  uint32_t sampler_scratch;     // some molecule's sampler keeps proposals in LDS (joint, exact)
   double rec_l0, rec_inv_step;  // log T of node 0; nodes per unit of log T
   SpeciesTab sp[kMaxSpecies];
   PairTab pr[kMaxSpecies][kMaxSpecies];
   ReactionTab rx[kMaxReactions];
+  double theta[kMaxSpecies][kMaxModes];  // bends: Theta (thermal initial states)
 };
 
 // Particle state in HBM: structure of arrays, cell-major segments with
@@ -175,15 +193,12 @@ enum StepPhase {
 };
 static_assert(kPhases == HCAO_N_PHASES, "phase list and ABI disagree");
 
-// bflag bits of a candidate pair
-constexpr uint8_t kFlagBorn = 1;      // it left a dissociation product in the products staging
-constexpr uint8_t kFlagCollided = 2;  // it collided (its running-sum change is in tdelta)
-
-// Workgroup b processes the consecutive cells [grp[2b], grp[2b+1]); its work
-// list, product flags and pair energy defects are the entries
-// [grp_work[2b], grp_work[2b+1]) of work (kWorkWords words each: the pair as
-// found and its place in the sorted list) / bflag / wdef
-// (sum over its cells of cap/2 + 1 entries).
+// Workgroup b processes the consecutive cells [grp[2b], grp[2b+1]); its
+// entries of work (kWorkWords words each: the pair as found and its place in
+// the sorted list) / pv / bflag / wdef / tdelta are [grp_work[3b], grp_work[3b+1])
+// (sum over its cells of cap/2 + 1 entries), its rounds start at
+// grp_work[3b+2]. pv, bflag, wdef and tdelta are indexed by the entry as found,
+// so that a step writes and reads them as one short dense run.
 struct StepArgs {
   const Tables *tab;
   const double *lev;
@@ -195,8 +210,10 @@ struct StepArgs {
   const uint32_t *grp;
   const uint64_t *grp_work;
   uint32_t *work;
-  uint8_t *bflag;
-  double *wdef;  // mixed form: energy defect of each candidate pair, indexed like bflag
+  void *pv;        // each accepted pair's velocities as phase A read them (six numbers of the state's precision)
+  WorkRound *rounds;
+  uint8_t *bflag;  // whether the pair left a dissociation product in the products staging
+  double *wdef;    // mixed form: energy defect of each accepted pair
   double *tdelta;  // recombination: [5][tdelta_stride] each colliding pair's change of its cell's running sums
   uint64_t tdelta_stride;
   uint32_t *err;
