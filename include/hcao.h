@@ -338,6 +338,10 @@ hcao_status hcao_step(hcao_ctx *ctx, double dt, uint32_t n_steps);
  *     keeping its cells' state in LDS between them (0 = all steps of a call).
  * Defaults 64, 1024, 0; the environment variables HCAO_BLOCK,
  * HCAO_GROUP_SLOTS and HCAO_STEPS_PER_LAUNCH override them at create time.
+ * Until block or group_slots is given (here, by the autotuner or in the
+ * environment), a context with too few slots to fill the GPU at the defaults
+ * runs in smaller groups of cells and wider workgroups of the library's
+ * choice; hcao_get_launch_shape reports the defaults.
  * hcao_set_launch_shape waits for the stream; it returns HCAO_EINVAL for a
  * block size not listed or group_slots = 0. */
 typedef struct {

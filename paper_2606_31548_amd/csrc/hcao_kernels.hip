@@ -44,11 +44,7 @@ constexpr uint8_t kDead = 255;  // species byte of a particle removed by recombi
     (acc)[(k) - kPhaseCollideGather] += t_ - (acc##_t); \
     acc##_t = t_;                        \
   } while (0)
-#define HCAO_CLK_PARAM , uint64_t (&wclk)[5], uint64_t &wclk_t
-#define HCAO_CLK_ARG , wclk, wclk_t
 #else
-#define HCAO_CLK_PARAM
-#define HCAO_CLK_ARG
 #define HCAO_PHASE_MARK(k) \
   do {                     \
   } while (0)
@@ -402,6 +398,13 @@ __device__ __forceinline__ void copy_levels(const State &src, uint64_t from, con
   const uint32_t *a = reinterpret_cast<const uint32_t *>(src.lvl + from * src.lrow);
   uint32_t *b = reinterpret_cast<uint32_t *>(dst.lvl + to * dst.lrow);
   for (uint32_t w = 0; w < src.lrow / 2; ++w) b[w] = a[w];
+}
+
+// orders the LDS accesses of a wave's lanes before and after it (a wave's LDS
+// instructions complete in order; this keeps the compiler from moving them)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // The value lane + S holds, delivered to the lanes that a halving tree
@@ -955,35 +958,6 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
     }
     return trials;
   }
-  if (S.sampler == HCAO_SAMPLER_JOINT) {
-    const double e_coll = e_tr + vib_energy(S, C.T.lev, lv, stride);
-    const double denom = e_coll - S.zpe;
-    if (!(denom > 0.0)) return 0;
-    uint16_t *tops = C.scr + C.lane;
-    uint16_t *cand = C.scr + (size_t)nm * C.block + C.lane;
-    for (uint32_t m = 0; m < nm; ++m) tops[m * C.block] = (uint16_t)mode_top(S, C.T.lev, m, e_coll);
-    for (;;) {
-      ++trials;
-      double sum = 0.0;
-      for (uint32_t m = 0; m < nm; ++m) {
-        const uint32_t i = pick_level<MIX>(tops[m * C.block], rng);
-        cand[m * C.block] = (uint16_t)i;
-        sum = sum + mode_energy(S, C.T.lev, m, i);
-      }
-      const double ua = (double)draw<MIX>(rng);
-      const bool ok = (sum < e_coll) && lb_accept<MIX>(ua, e_coll - sum, denom, q);
-      if (ok) {
-        for (uint32_t m = 0; m < nm; ++m) lv[m * stride] = cand[m * C.block];
-        e_tr = e_coll - sum;
-        break;
-      }
-      if (trials >= kMaxTrials) {
-        capped = true;
-        break;
-      }
-    }
-    return trials;
-  }
   // Gibbs sweep: the level of mode m is proposed from the linear envelope
   // w_i = 1 - c i of the target ((E_c - E_i) / (E_c - E_0))^q on 0..top
   // (valid for q <= 1 and levels whose spacings never grow; c = 0 gives the
@@ -1061,6 +1035,118 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
     if (capped) break;
   }
   e_tr = et;
+  return trials;
+}
+
+// The joint sampler's molecules of a wave, one slot per lane (LDS)
+struct JointJob {
+  double e_coll, denom, q;
+  uint32_t pos, base, pair, cell;  // next word of the stream, trials done, the stream
+  uint32_t sp, owner;              // owner: slot i of a wave's lanes names its i-th unaccepted molecule's lane
+};
+
+// Joint sampler (uniform proposals over the box of levels, one acceptance of
+// the whole vector) for the lanes of a wave with job set; every lane of the
+// wave takes part. Trial t of a molecule always takes the same n_modes + 1
+// uniforms of its stream, so trials are independent work: the lanes of a wave
+// share out the next trials of the molecules still unaccepted (G = 2^sh lanes
+// each), and the first accepted trial in stream order wins, which is the one a
+// serial loop stops at. One lane per molecule keeps the whole wave until its
+// slowest molecule is accepted (a mean of 16 trials for the triatomic, about
+// 75 for the slowest of 64); shared out, 64 of them take about 25 rounds.
+template <bool MIX>
+__device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool job, uint32_t sp, uint16_t *lv,
+                                                uint32_t stride, double &e_tr, double q, RngT<MIX> &rng,
+                                                bool &capped) {
+  const double *lev = C.T.lev;
+  const uint32_t lane = C.lane & 63u, first_lane = C.lane - lane;
+  const unsigned long long lt = lane ? ((1ull << lane) - 1ull) : 0ull;
+  double e_coll = 0.0;
+  uint32_t trials = 0, nm = 0;
+  capped = false;
+  if (job) {
+    const SpeciesTab &S = C.T.sp[sp];
+    nm = S.n_modes;
+    e_coll = e_tr + vib_energy(S, lev, lv, stride);
+    const double denom = e_coll - S.zpe;
+    job = denom > 0.0;
+    if (job) {
+      for (uint32_t m = 0; m < nm; ++m) C.scr[m * C.block + C.lane] = (uint16_t)mode_top(S, lev, m, e_coll);
+      J[C.lane].e_coll = e_coll;
+      J[C.lane].denom = denom;
+      J[C.lane].q = q;
+      J[C.lane].pos = rng.used >= 4 ? 4 * rng.block : 4 * (rng.block - 1) + rng.used;  // next word of the stream
+      J[C.lane].pair = rng.pair;
+      J[C.lane].cell = rng.cell;
+      J[C.lane].sp = sp;
+    }
+  }
+  unsigned long long pend = __ballot(job);
+  while (pend) {
+    const uint32_t np = (uint32_t)__popcll(pend);
+    const uint32_t sh = 6u - (np > 1 ? 32u - (uint32_t)__builtin_clz(np - 1u) : 0u), G = 1u << sh;
+    const uint32_t rank = (uint32_t)__popcll(pend & lt);
+    if (job) {
+      J[first_lane + rank].owner = lane;
+      J[C.lane].base = trials;
+    }
+    wave_sync();
+    bool ok = false;
+    double sum = 0.0;
+    if ((lane >> sh) < np) {
+      const uint32_t o = first_lane + J[first_lane + (lane >> sh)].owner;
+      const SpeciesTab &S = C.T.sp[J[o].sp];
+      const uint32_t n = S.n_modes;
+      const uint32_t at = J[o].pos + (J[o].base + (lane & (G - 1u))) * (n + 1u) * (MIX ? 1u : 2u);
+      RngT<MIX> r = rng;
+      r.pair = J[o].pair;
+      r.cell = J[o].cell;
+      r.block = at / 4u;
+      r.used = 4;
+      if (at % 4u) {
+        r.refill();
+        r.used = at % 4u;
+      }
+      uint16_t *cand = C.scr + (size_t)n * C.block + C.lane;
+      for (uint32_t m = 0; m < n; ++m) {
+        const uint32_t i = pick_level<MIX>(C.scr[m * C.block + o], r);
+        cand[m * C.block] = (uint16_t)i;
+        sum = sum + mode_energy(S, lev, m, i);
+      }
+      const double ua = (double)draw<MIX>(r);
+      const double e = J[o].e_coll;
+      ok = sum < e && lb_accept<MIX>(ua, e - sum, J[o].denom, J[o].q);
+    }
+    const unsigned long long won = __ballot(ok);
+    const unsigned long long mine = (won >> (rank << sh)) & (G < 64u ? (1ull << G) - 1ull : ~0ull);
+    const uint32_t hit = mine ? (uint32_t)__ffsll((long long)mine) - 1u : G;
+    const uint32_t from = ((rank << sh) + hit) & 63u;
+    const double won_sum = __shfl(sum, (int)from);
+    wave_sync();
+    if (job) {
+      if (trials + hit >= kMaxTrials) {
+        // (the serial loop stops after trial kMaxTrials unless that one is accepted)
+        trials = (uint32_t)kMaxTrials;
+        capped = true;
+        job = false;
+      } else if (hit < G) {
+        trials += hit + 1u;
+        const uint16_t *cand = C.scr + (size_t)nm * C.block + first_lane + from;
+        for (uint32_t m = 0; m < nm; ++m) lv[m * stride] = cand[m * C.block];
+        e_tr = e_coll - won_sum;
+        job = false;
+      } else {
+        trials += G;
+        if (trials >= kMaxTrials) {
+          capped = true;
+          job = false;
+        }
+      }
+      if (!job) rng.skip(trials * (nm + 1u));
+    }
+    wave_sync();
+    pend = __ballot(job);
+  }
   return trials;
 }
 
@@ -1343,17 +1429,16 @@ struct CellHdr {
   Perm perm;
 };
 
-// Reaction decision and relaxation of one accepted pair (velocities v0, v1;
-// H its cell, k its index there, e_tr its translational energy).
-// The outcome is decided first; the molecules to relax are then taken in draw
-// order (at most two) through one sampler loop. Velocities are not changed
-// here: scatter() reads them again, so that none is held in registers while
-// the samplers run (held, they and what depends on them were spilled and
-// reloaded around every sampler).
+// Reaction decision of one accepted pair (velocities v0, v1; H its cell, k its
+// index there, e_tr its translational energy). The molecules to relax are then
+// taken in draw order (at most two) through one sampler loop. Velocities are
+// not changed here: scatter() reads them again, so that none is held in
+// registers while the samplers run (held, they and what depends on them were
+// spilled and reloaded around every sampler).
 template <bool MIX, bool EX>
 __device__ __forceinline__ Outcome decide(const Ctx &C, PairLocal<MIX> &P, const CellHdr &H, uint32_t k, const State &st,
                                           V3<Real<MIX>> v0, V3<Real<MIX>> v1, double e_tr0, RngT<MIX> &rng,
-                                          const double *rec HCAO_ERR_PARAM HCAO_CLK_PARAM) {
+                                          const double *rec HCAO_ERR_PARAM) {
   using Rl = Real<MIX>;
   const Tab &T = C.T;
   const uint32_t ls = P.ls;
@@ -1514,77 +1599,55 @@ __device__ __forceinline__ Outcome decide(const Ctx &C, PairLocal<MIX> &P, const
     }
   }
 
-  HCAO_WAVE_MARK(wclk, kPhaseCollideDecide);
-  // --- the molecules to relax, in draw order: species, the partner that sets
-  // the exponent, levels ---
-  uint32_t ja = sp0, jb = sp1, pa = sp1, pb = sp0;
-  uint16_t *la = P.lv0, *lb = P.lv1;
-  if (O.kind != 0) {
-    const ReactionTab &RX = T.rx[O.rx];
-    la = O.side ? P.lv1 : P.lv0;
-    ja = (uint32_t)RX.c;
-    zero_levels(la, ls, T.mm);
-    if (O.kind == 1) {
-      // A + M -> B + C + M: B takes A's slot, C is new, both from the ground state
-      lb = P.lvn;
-      zero_levels(lb, ls, T.mm);
-      jb = (uint32_t)RX.d;
-      pa = pb = O.side ? sp0 : sp1;
-    } else if (O.kind == 2) {
-      // A + B -> C + D: C takes A's slot, D takes B's
-      lb = O.side ? P.lv0 : P.lv1;
-      zero_levels(lb, ls, T.mm);
-      jb = (uint32_t)RX.d;
-      pa = jb;
-      pb = ja;
-    } else {
-      // B + C (+M) -> A (+M): A takes B's slot
-      pa = O.sp_m;
-    }
-  }
-  const uint32_t njob = O.kind == 3 ? 1u : 2u;
-  uint64_t tr = 0;
-  uint32_t nrel = 0, ncap = 0;
-  for (uint32_t j = 0; j < njob; ++j) {
-    const uint32_t sj = j ? jb : ja;
-    const SpeciesTab &S = T.sp[sj];
-    if (S.n_modes == 0) continue;
-    if (O.kind == 0) {
-      const double u = (double)draw<MIX>(rng);
-      if (!(u < S.p_vib)) continue;
-      ++nrel;
-    }
-    bool capped = false;
-    const PairTab &PJ = T.pair(sj, j ? pb : pa);
-    const uint32_t bo = PJ.beta_off;
-    tr += relax<MIX, EX>(C, S, j ? lb : la, ls, et, PJ.q, C.T.beta + (bo == 0xFFFFFFFFu ? 0u : bo), rng, capped);
-    ncap += capped ? 1u : 0u;
-  }
-  if (tr) atomicAdd(&C.ctr[HCAO_CTR_TRIALS], (unsigned long long)tr);
-  if (nrel) atomicAdd(&C.ctr[HCAO_CTR_RELAX], (unsigned long long)nrel);
-  if (ncap) atomicAdd(&C.ctr[HCAO_CTR_CAPPED], (unsigned long long)ncap);
-
-  HCAO_WAVE_MARK(wclk, kPhaseCollideRelax);
-  // --- rotational relaxation of each rotor in turn (non-reactive collisions) ---
-  if constexpr (EX) {
-    if (O.kind == 0) {
-      for (uint32_t x = 0; x < 2; ++x) {
-        const SpeciesTab &S = T.sp[x ? sp1 : sp0];
-        if (S.zeta_rot == 0) continue;
-        const double u = (double)draw<MIX>(rng);
-        if (!(u < S.p_rot)) continue;
-        const double ec = et + (x ? P.r1 : P.r0);
-        const double er = rot_fraction<MIX>(S.zeta_rot, PP.q, rng) * ec;
-        if (x)
-          P.r1 = er;
-        else
-          P.r0 = er;
-        et = ec - er;
-      }
-    }
-  }
   O.et = et;
   return O;
+}
+
+// Molecule j (0, 1) to relax after the decision, in draw order: its species,
+// the partner that sets the exponent, its levels. A reaction's products start
+// in the ground state: B takes A's slot in a dissociation and C is new, C and
+// D take A's and B's in an exchange, A takes B's in a recombination (one
+// molecule only).
+template <bool MIX>
+__device__ __forceinline__ void relax_job(const Tab &T, const PairLocal<MIX> &P, const Outcome &O, uint32_t j,
+                                          uint32_t &sp, uint32_t &partner, uint16_t *&lv) {
+  // (by value: a choice among members would put the whole struct into scratch)
+  const uint32_t sp0 = P.sp0, sp1 = P.sp1;
+  uint16_t *const lv0 = P.lv0, *const lv1 = P.lv1, *const lvn = P.lvn;
+  if (O.kind == 0) {
+    sp = j ? sp1 : sp0;
+    partner = j ? sp0 : sp1;
+    lv = j ? lv1 : lv0;
+    return;
+  }
+  const ReactionTab &RX = T.rx[O.rx];
+  const uint32_t c = (uint32_t)RX.c, d = (uint32_t)RX.d, sp_m = O.sp_m;
+  const bool b = (O.side != 0) != (j != 0);
+  lv = O.kind == 1 && j ? lvn : (b ? lv1 : lv0);
+  sp = j ? d : c;
+  partner = O.kind == 1 ? (O.side ? sp0 : sp1) : (O.kind == 2 ? (j ? c : d) : sp_m);
+  zero_levels(lv, P.ls, T.mm);
+}
+
+// rotational relaxation of each rotor of a non-reactive pair in turn
+template <bool MIX>
+__device__ __forceinline__ void relax_rotors(const Tab &T, PairLocal<MIX> &P, double &et, RngT<MIX> &rng) {
+  const double q = T.pair(P.sp0, P.sp1).q;
+  for (uint32_t x = 0; x < 2; ++x) {
+    const uint32_t sp0 = P.sp0, sp1 = P.sp1;
+    const double r0 = P.r0, r1 = P.r1;
+    const SpeciesTab &S = T.sp[x ? sp1 : sp0];
+    if (S.zeta_rot == 0) continue;
+    const double u = (double)draw<MIX>(rng);
+    if (!(u < S.p_rot)) continue;
+    const double ec = et + (x ? r1 : r0);
+    const double er = rot_fraction<MIX>(S.zeta_rot, q, rng) * ec;
+    if (x)
+      P.r1 = er;
+    else
+      P.r0 = er;
+    et = ec - er;
+  }
 }
 
 // Scattering and reaction application: the outgoing velocities and species
@@ -1714,7 +1777,7 @@ struct PairVel {
 // pair order, is owed to the cell and joins the translational energy of the
 // cell's pair 0 in the next step in which that pair collides.
 template <int BLOCK, bool MIX, int EX>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void k_step(StepArgs A) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ? 3 : 4))) void k_step(StepArgs A) {
   using R = Real<MIX>;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   __shared__ uint32_t s_nwork, s_total, s_next;
@@ -1811,6 +1874,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
   __syncthreads();
   HCAO_PHASE_MARK(kPhaseLoad);
 
+  // the joint sampler's slots lie after the pair levels
+  const bool any_joint = (GT->sampler_scratch & 2u) != 0;
+  JointJob *jobs = reinterpret_cast<JointJob *>(reinterpret_cast<unsigned char *>(plv) +
+                                                (((size_t)6 * mm * BLOCK + 7) & ~(size_t)7));
   const uint32_t step0 = A.step_dev ? *A.step_dev + A.step : A.step;
   for (uint32_t si = 0; si < A.n_steps; ++si) {
   const uint32_t step = step0 + si;
@@ -1994,21 +2061,25 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
     c0 = __builtin_amdgcn_readfirstlane(c0);  // every lane is active here: lane 0's value
     if (c0 >= nwork) break;
     const uint32_t i = c0 + lane;
-    if (i < nwork) {
+    const bool act = i < nwork;
 #ifdef HCAO_PHASE_CLOCKS
     uint64_t wclk[5] = {0, 0, 0, 0, 0}, wclk_t = clock64();  // collision sub-phase clocks
     const bool lead = lane == (uint32_t)(__ffsll((long long)__ballot(1)) - 1);
 #endif
-    uint32_t at = (uint32_t)HCAO_IDX(work[i], wcap, A.err);
+    uint32_t at = 0;
+    unsigned long long *ctr = l_ctr;
     PairLocal<MIX> P;
     P.ls = BLOCK;
     P.lv0 = plv + tid;
     P.lv1 = plv + (size_t)mm * BLOCK + tid;
     P.lvn = plv + (size_t)2 * mm * BLOCK + tid;
+    P.sp0 = P.sp1 = 0;
     P.r0 = P.r1 = P.rn = 0.0;
     RngT<MIX> rng;
-    Outcome O;
-    {
+    rng.open(A.seed, 0, 0, step);
+    Outcome O{0, -1, 0, 0, 0, 0.0};
+    if (act) {
+      at = (uint32_t)HCAO_IDX(work[i], wcap, A.err);
       const uint32_t *wi = work_in + (size_t)kWorkFound * at;
       const PairVel<R> vel = pv[at];
       const V3<R> v0 = vel.p, v1 = vel.q;
@@ -2044,12 +2115,58 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(4))) void
       // cell's pair 0 when the sum stays positive
       if constexpr (MIX)
         if (k == 0 && H.defect != 0.0 && e_tr + H.defect > 0.0) e_tr = e_tr + H.defect;
-      unsigned long long *ctr = l_ctr + (size_t)g * nctr;
+      ctr = l_ctr + (size_t)g * nctr;
       atomicAdd(&ctr[HCAO_CTR_COLLISIONS], 1ull);
       const Ctx C{T, ctr, scr, tid, BLOCK};
       HCAO_WAVE_MARK(wclk, kPhaseCollideGather);
-      O = decide<MIX, (EX >= 2)>(C, P, H, k, A.st, v0, v1, e_tr, rng, A.rec HCAO_ERR_ARG(A.err) HCAO_CLK_ARG);
+      O = decide<MIX, (EX >= 2)>(C, P, H, k, A.st, v0, v1, e_tr, rng, A.rec HCAO_ERR_ARG(A.err));
     }
+    HCAO_WAVE_MARK(wclk, kPhaseCollideDecide);
+    // the molecules to relax: the joint sampler's together, each other one in
+    // its own lane
+    {
+      const Ctx C{T, ctr, scr, tid, BLOCK};
+      uint32_t tr = 0, nrel = 0, ncap = 0;
+      for (uint32_t j = 0; j < 2; ++j) {
+        bool job = act && (j == 0 || O.kind != 3), joint = false;
+        uint32_t sj = 0, partner = 0;
+        uint16_t *lv = P.lv0;
+        if (job) {
+          relax_job<MIX>(T, P, O, j, sj, partner, lv);
+          const SpeciesTab &S = T.sp[sj];
+          job = S.n_modes > 0;
+          if (job && O.kind == 0) {
+            const double u = (double)draw<MIX>(rng);
+            job = u < S.p_vib;
+            nrel += job ? 1u : 0u;
+          }
+          if (job) {
+            joint = S.sampler == HCAO_SAMPLER_JOINT;
+            if (!joint) {
+              bool capped = false;
+              const PairTab &PJ = T.pair(sj, partner);
+              const uint32_t bo = PJ.beta_off;
+              tr += relax<MIX, (EX >= 2)>(C, S, lv, BLOCK, O.et, PJ.q, T.beta + (bo == 0xFFFFFFFFu ? 0u : bo), rng,
+                                          capped);
+              ncap += capped ? 1u : 0u;
+            }
+          }
+        }
+        if (any_joint && __ballot(joint)) {
+          bool capped;
+          const uint32_t t = relax_joint<MIX>(C, jobs, joint, sj, lv, BLOCK, O.et, T.pair(sj, partner).q, rng, capped);
+          tr += t;
+          ncap += capped ? 1u : 0u;
+        }
+      }
+      if (tr) atomicAdd(&ctr[HCAO_CTR_TRIALS], (unsigned long long)tr);
+      if (nrel) atomicAdd(&ctr[HCAO_CTR_RELAX], (unsigned long long)nrel);
+      if (ncap) atomicAdd(&ctr[HCAO_CTR_CAPPED], (unsigned long long)ncap);
+    }
+    HCAO_WAVE_MARK(wclk, kPhaseCollideRelax);
+    if (act) {
+    if constexpr (EX >= 2)
+      if (O.kind == 0) relax_rotors<MIX>(T, P, O.et, rng);
     // the pair's entry and velocities are read again (the dense lists of the
     // step, still in cache) rather than kept in registers through the samplers
     renew(at);
@@ -3418,6 +3535,7 @@ size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block) {
   size_t b = sizeof(SpeciesTab) * ns + sizeof(PairTab) * ns * ns + sizeof(ReactionTab) * nr + 8 * (size_t)(T.n_levels ? T.n_levels : 1);
   b += sizeof(CellHdr) * max_cells + 2 * 8 * (size_t)(8 + nr) * max_cells;
   b += (size_t)2 * ((T.sampler_scratch ? 2 : 0) + 3) * (T.max_modes ? T.max_modes : 1) * block;
+  if (T.sampler_scratch & 2u) b = ((b + 7) & ~(size_t)7) + sizeof(JointJob) * (size_t)block;
   return (b + 15) & ~(size_t)15;
 }
 

@@ -78,6 +78,8 @@ constexpr double kB = 1.380649e-23;
 constexpr double kPi = 3.141592653589793;
 constexpr size_t kLdsBudget = 68 * 1024;  // LDS bytes per workgroup of the step kernel (64 KB of cells and tables, and the tables' single-precision columns)
 constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombination sum's stretch ladders
+constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups, and waves, a context is spread over
+constexpr uint32_t kShapeWaves = 4096;
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
 struct SpeciesHost {
@@ -192,6 +194,8 @@ struct hcao_ctx {
   size_t step_lds = 0;
   int block = 64;
   uint32_t group_slots = 1024;  // target slot capacity per workgroup
+  bool shape_set = false;       // block or group_slots given by the caller (or the environment)
+  int run_block = 64;           // workgroup size of the launches (choose_shape)
   uint32_t step = 0;
   bool timing = false;
   double timed_ms = 0.0;
@@ -477,6 +481,31 @@ hcao_status upload_vel(hcao_ctx *c, const std::vector<double> &vx, const std::ve
   return HCAO_OK;
 }
 
+// Workgroup size and slot target of the launches. A shape the caller set is
+// taken as it is. Otherwise the default (64 lanes, 1,024 slots) holds while it
+// gives the chip enough waves; a context too small for that gets smaller
+// groups, down to one cell each, and then wider workgroups, up to one lane per
+// possible candidate pair (a fourth of the slots: half are paired, and NTC
+// tests about half of those at most once (sigma g)_max has settled).
+void choose_shape(const hcao_ctx *c, int &block, uint32_t &group_slots) {
+  block = c->block;
+  group_slots = c->group_slots;
+  if (c->shape_set) return;
+  uint64_t slots = 0;
+  uint32_t largest = 0;
+  for (uint32_t cap : c->cap_host) {
+    slots += cap;
+    largest = std::max(largest, cap);
+  }
+  if (slots >= (uint64_t)kShapeGroups * group_slots) return;
+  group_slots = (uint32_t)std::max<uint64_t>(1, slots / kShapeGroups);
+  const uint64_t groups = std::max<uint64_t>(1, slots / std::max(group_slots, largest));
+  while (block < 512 && groups * (uint64_t)block * 2 <= (uint64_t)kShapeWaves * 64 &&
+         (uint64_t)block * 4 < std::max(group_slots, largest) &&
+         step_lds_bytes(c->tab, 1, 2 * block) <= kLdsBudget)
+    block *= 2;
+}
+
 // Workgroups of the step kernel: runs of consecutive cells of at most
 // kMaxGroupCells cells (fewer when the per-cell LDS records of a wide
 // workgroup would not fit) and about group_slots slots each. Workgroup w
@@ -486,8 +515,10 @@ hcao_status upload_vel(hcao_ctx *c, const std::vector<double> &vx, const std::ve
 // first (by slot capacity), so that the largest cells start earliest.
 hcao_status build_groups(hcao_ctx *c) {
   const uint32_t nc = c->cfg.n_cells;
+  uint32_t group_slots = c->group_slots;
+  choose_shape(c, c->run_block, group_slots);
   uint32_t cell_limit = kMaxGroupCells;
-  while (cell_limit > 0 && step_lds_bytes(c->tab, cell_limit, c->block) > kLdsBudget) --cell_limit;
+  while (cell_limit > 0 && step_lds_bytes(c->tab, cell_limit, c->run_block) > kLdsBudget) --cell_limit;
   if (cell_limit == 0) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
   struct G {
     uint32_t c0, c1;
@@ -497,7 +528,7 @@ hcao_status build_groups(hcao_ctx *c) {
   uint64_t slots = 0, wsum = 0, w0 = 0;
   uint32_t in_group = 0, max_cells = 1, first = 0;
   for (uint32_t i = 0; i < nc; ++i) {
-    if (in_group > 0 && (in_group >= cell_limit || slots + c->cap_host[i] > c->group_slots)) {
+    if (in_group > 0 && (in_group >= cell_limit || slots + c->cap_host[i] > group_slots)) {
       groups.push_back(G{first, i, w0, wsum, slots});
       max_cells = std::max(max_cells, in_group);
       in_group = 0;
@@ -539,7 +570,7 @@ hcao_status build_groups(hcao_ctx *c) {
   if (c->rounds.n < rounds) HIP_TRY(c, c->rounds.alloc(rounds));
   HIP_TRY(c, hipMemcpyAsync(c->grp.p, grp.data(), grp.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->grp_work.p, gw.data(), gw.size() * 8, hipMemcpyHostToDevice, c->stream));
-  c->step_lds = step_lds_bytes(c->tab, c->max_group_cells, c->block);
+  c->step_lds = step_lds_bytes(c->tab, c->max_group_cells, c->run_block);
   if (c->step_lds > kLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
   return HCAO_OK;
 }
@@ -882,7 +913,10 @@ hcao_status hcao_create(const hcao_config *cfg, hcao_ctx **out) {
   c->stream = (hipStream_t)cfg->hip_stream;
   if (const char *b = std::getenv("HCAO_BLOCK")) {
     const int v = std::atoi(b);
-    if (v == 64 || v == 128 || v == 256 || v == 512) c->block = v;
+    if (v == 64 || v == 128 || v == 256 || v == 512) {
+      c->block = v;
+      c->shape_set = true;
+    }
   }
   if (const char *k = std::getenv("HCAO_STEPS_PER_LAUNCH")) {
     const long v = std::atol(k);
@@ -890,7 +924,10 @@ hcao_status hcao_create(const hcao_config *cfg, hcao_ctx **out) {
   }
   if (const char *g = std::getenv("HCAO_GROUP_SLOTS")) {
     const long v = std::atol(g);
-    if (v >= 1 && v <= (1L << 30)) c->group_slots = (uint32_t)v;
+    if (v >= 1 && v <= (1L << 30)) {
+      c->group_slots = (uint32_t)v;
+      c->shape_set = true;
+    }
   }
   const char *step = "hipSetDevice";
   hipError_t e = hipSetDevice(c->device);
@@ -1035,7 +1072,7 @@ hcao_status hcao_finalize(hcao_ctx *c) {
     S.n_modes = h.n_modes;
     S.n_bend = h.d.n_bend;
     S.sampler = (uint32_t)h.sampler;
-    if (h.n_modes && h.sampler != HCAO_SAMPLER_GIBBS) T.sampler_scratch = 1;
+    if (h.n_modes && h.sampler != HCAO_SAMPLER_GIBBS) T.sampler_scratch |= h.sampler == HCAO_SAMPLER_JOINT ? 3u : 1u;
     for (uint32_t b = 0; b < h.d.n_bend; ++b) {
       T.theta[s][b] = h.theta[b];
       S.kt[b] = kB * h.theta[b];
@@ -1586,7 +1623,7 @@ hcao_status issue_steps(hcao_ctx *c, double dt, uint32_t n_steps, uint32_t base,
       StepArgs a = step_args(c, dt);
       a.step = base + d;
       a.n_steps = 1;
-      HIP_TRY(c, launch_step(a, c->step_lds, c->block, c->mixed, step_level(c), c->n_groups, s));
+      HIP_TRY(c, launch_step(a, c->step_lds, c->run_block, c->mixed, step_level(c), c->n_groups, s));
     }
     if (launches) *launches = n_steps;
     return HCAO_OK;
@@ -1605,7 +1642,7 @@ hcao_status issue_steps(hcao_ctx *c, double dt, uint32_t n_steps, uint32_t base,
     const uint32_t k = std::min(n_steps - done, c->steps_per_launch);
     a.step = (step_dev ? 0u : base) + done;
     a.n_steps = k;
-    HIP_TRY(c, launch_step(a, c->step_lds, c->block, c->mixed, step_level(c),
+    HIP_TRY(c, launch_step(a, c->step_lds, c->run_block, c->mixed, step_level(c),
                            c->n_groups, s));
     done += k;
     ++n;
@@ -1738,14 +1775,17 @@ hcao_status hcao_set_launch_shape(hcao_ctx *c, const hcao_launch_shape *shape) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   const int old_block = c->block;
   const uint32_t old_slots = c->group_slots;
+  const bool old_set = c->shape_set;
   c->block = (int)b;
   c->group_slots = shape->group_slots;
+  c->shape_set = true;
   c->steps_per_launch = shape->steps_per_launch ? shape->steps_per_launch : (1u << 30);
   ++c->shape_gen;
   if (c->loaded) {
     if (hcao_status s = build_groups(c)) {
       c->block = old_block;
       c->group_slots = old_slots;
+      c->shape_set = old_set;
       (void)build_groups(c);
       return s;
     }
@@ -1880,6 +1920,7 @@ hcao_status hcao_autotune(hcao_ctx *c, double dt, uint32_t trial_steps, const ch
     Snapshot S, W;
     if (hcao_status s = snapshot(c, S, true)) return s;
     const hcao_launch_shape orig{(uint32_t)c->block, c->group_slots, spl >= (1u << 30) ? 0u : spl};
+    const bool orig_set = c->shape_set;
     const bool was_timing = c->timing;
     double best_ms = 0.0;
     // candidates are timed from a copy advanced past the first steps, whose
@@ -1925,7 +1966,14 @@ hcao_status hcao_autotune(hcao_ctx *c, double dt, uint32_t trial_steps, const ch
     c->timing = was_timing;
     const hcao_status back = snapshot(c, S, false);
     if (tried != HCAO_OK) {
-      if (c->sticky == HCAO_OK) (void)hcao_set_launch_shape(c, &orig);
+      if (c->sticky == HCAO_OK) {
+        c->shape_set = orig_set;
+        (void)hcao_set_launch_shape(c, &orig);
+        if (!orig_set) {
+          c->shape_set = false;  // the default shape again
+          (void)build_groups(c);
+        }
+      }
       return tried;
     }
     if (back != HCAO_OK) return back;

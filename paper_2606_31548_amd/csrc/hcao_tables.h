@@ -114,7 +114,7 @@ constexpr double kRecTmax = 5.0e4;
 struct Tables {
   uint32_t n_species, n_reactions, max_modes, n_levels;
   uint32_t has_recomb, rec_nt, has_rot;
-  uint32_t sampler_scratch;     // some molecule's sampler keeps proposals in LDS (joint, exact)
+  uint32_t sampler_scratch;     // 1: some molecule's sampler keeps proposals in LDS (joint, exact); 3: some uses the joint sampler
   double rec_l0, rec_inv_step;  // log T of node 0; nodes per unit of log T
   SpeciesTab sp[kMaxSpecies];
   PairTab pr[kMaxSpecies][kMaxSpecies];
