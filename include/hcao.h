@@ -463,14 +463,16 @@ hcao_status hcao_get_exact_beta(const hcao_ctx *ctx, uint32_t species, uint32_t 
  * species' vibrational levels, S_i its energy above the ground level, Q the
  * regularized upper incomplete gamma (1 for arguments <= 0); bends are
  * infinite harmonic ladders, stretches run to their top bound level. The
- * device enumerates every combination below D_e (one record each) and the
- * points where the enumeration first crosses D_e (the combinations above it
- * have Q = 1 and are summed in closed form there), then sums the records
- * for each temperature in one workgroup. Sums are in a fixed order, so
+ * device enumerates the combinations below D_e and the points where the
+ * enumeration first crosses D_e (the combinations above it have Q = 1 and are
+ * summed in closed form there), combinations that only swap levels among
+ * identical modes as one weighted entry, then sums them for each temperature
+ * in one workgroup. Sums are in a fixed order, so
  * results repeat bitwise; they match a serial sum to rounding (~1e-13
  * relative). elapsed_ms and n_records (may be NULL) receive the device
- * time and the number of records. Allocates device memory for the records
- * (16 bytes each); synchronous on the context's stream. HCAO_EUNSUPPORTED
+ * time and the number of records (one per combination and crossing).
+ * Allocates device memory for the entries (20 bytes each), which the context
+ * keeps; synchronous on the context's stream. HCAO_EUNSUPPORTED
  * if the species' stretch ladders exceed 8192 levels in total. */
 hcao_status hcao_recombination_exact(hcao_ctx *ctx, uint32_t species, double de_J, double omega, uint32_t n_t,
                                      const double *t_K, double *p_out, double *elapsed_ms, uint64_t *n_records);

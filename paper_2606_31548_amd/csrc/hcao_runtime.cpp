@@ -112,6 +112,8 @@ struct DevBuf {
     n = count;
     return hipSuccess;
   }
+  // at least count entries; what it held is kept only if it was large enough
+  hipError_t reserve(size_t count) { return count <= n && p ? hipSuccess : alloc(count); }
   void release() {
     if (p) (void)hipFree(p);
     p = nullptr;
@@ -119,9 +121,28 @@ struct DevBuf {
   }
 };
 
+// device scratch of the exact recombination sum, kept by the context
+struct RecScratch {
+  DevBuf<uint32_t> cnt, code;
+  DevBuf<uint64_t> off, stmp;
+  DevBuf<unsigned long long> full;
+  DevBuf<double> e, w, t;
+  void release() {
+    cnt.release();
+    code.release();
+    off.release();
+    stmp.release();
+    full.release();
+    e.release();
+    w.release();
+    t.release();
+  }
+};
+
 }  // namespace
 
 struct hcao_ctx {
+  RecScratch rec_scratch;
   hcao_config cfg{};
   std::vector<double> rec_host;   // recombination factors, all reactions
   std::vector<double> beta_host;  // exact sampler: beta per E' bin, per (species, LB exponent)
@@ -723,11 +744,13 @@ hcao_status read_err(hcao_ctx *c) {
   return HCAO_OK;
 }
 
-// Eq. recomb-correct on the device for species sp of the device tables:
-// every level combination below de is enumerated (count pass, scan, write
-// pass), then one workgroup per temperature sums the records. p[i] receives
-// the probability at t[i]; ms and n_rec (may be null) the device time and
-// the number of records.
+// Eq. recomb-correct on the device for species sp of the device tables: the
+// level combinations below de are enumerated (count pass, scan, write pass),
+// those that only swap levels among identical modes as one weighted record
+// (CH4: 12.0 M combinations and crossings in tens of thousands of records),
+// then one workgroup per temperature sums the records. p[i] receives the
+// probability at t[i]; ms and n_rec (may be null) the device time and the
+// number of combinations and crossings the records stand for.
 hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double omega, uint32_t n_t, const double *t,
                                   double *p, double *ms, uint64_t *n_rec) {
   const SpeciesTab &S = c->tab.sp[sp];
@@ -738,89 +761,108 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
   ea.lev = c->d_lev.p;
   ea.species = sp;
   ea.de = de;
-  // box of the prefix modes: the levels below de and the first one above
+  // the walk's units: runs of bends with one quantum, and the stretches in
+  // order, those with their predecessor's ladder marked
+  RecUnits U{};
+  auto same_ladder = [&](uint32_t x, uint32_t y) {
+    return S.idiss[x] == S.idiss[y] &&
+           std::memcmp(c->lev_host.data() + S.lev_off[x], c->lev_host.data() + S.lev_off[y],
+                       (S.idiss[x] + 1) * sizeof(double)) == 0;
+  };
+  for (uint32_t m = 0; m < nm; ++m) {
+    if (m < S.n_bend && m > 0 && S.kt[m] == S.kt[m - 1]) {
+      ++U.degree[U.n - 1];
+      continue;
+    }
+    U.mode[U.n] = m;
+    U.degree[U.n] = m < S.n_bend ? 1u : 0u;
+    U.same[U.n] = m > S.n_bend && same_ladder(m - 1, m) ? 1u : 0u;
+    ++U.n;
+  }
+  // box of a unit: the levels below de and the first one above
   uint32_t box[kMaxModes];
   size_t n_sl = 0;
-  for (uint32_t m = 0; m < nm; ++m) {
+  for (uint32_t u = 0; u < U.n; ++u) {
+    const uint32_t m = U.mode[u];
     uint32_t below = 0;
-    if (m < S.n_bend) {
+    if (U.degree[u]) {
       while (((double)below + 0.5) * S.kt[m] - 0.5 * S.kt[m] < de) ++below;
-      box[m] = below + 1;
+      box[u] = below + 1;
     } else {
       const double *L = c->lev_host.data() + S.lev_off[m];
       while (below <= S.idiss[m] && L[below] - L[0] < de) ++below;
-      box[m] = std::min(below + 1, S.idiss[m] + 1);
+      box[u] = std::min(below + 1, S.idiss[m] + 1);
       n_sl += S.idiss[m] + 1;
     }
   }
   if (n_sl * sizeof(double) > kRecLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "stretch ladders too long for the exact sum");
-  uint64_t n_prefix = 1;
-  uint32_t np = 0;
-  while (np < nm && n_prefix * box[np] <= (1ull << 22)) n_prefix *= box[np++];
-  if (np == 0) {
-    np = 1;
-    n_prefix = box[0];
-  }
-  ea.n_prefix_modes = np;
-  for (uint32_t m = 0; m < np; ++m) ea.box[m] = box[m];
+  // enough threads to fill the GPU; more only split the walk into idle prefixes
+  uint64_t n_prefix = box[0];
+  uint32_t np = 1;
+  while (np < U.n && n_prefix < (1ull << 17) && n_prefix * box[np] <= (1ull << 22)) n_prefix *= box[np++];
+  ea.units = U;
+  ea.n_prefix_units = np;
+  for (uint32_t u = 0; u < np; ++u) ea.box[u] = box[u];
   ea.n_prefix = n_prefix;
-  DevBuf<uint32_t> cnt;
-  DevBuf<uint64_t> off;
-  DevBuf<double> rec_e, d_t, d_num, d_den;
-  DevBuf<uint32_t> rec_code;
-  HIP_TRY(c, cnt.alloc(n_prefix));
-  HIP_TRY(c, off.alloc(n_prefix));
+  RecScratch &R = c->rec_scratch;
+  HIP_TRY(c, R.cnt.reserve(n_prefix));
+  HIP_TRY(c, R.off.reserve(n_prefix));
+  HIP_TRY(c, R.stmp.reserve(scan_tmp_entries(n_prefix)));
+  HIP_TRY(c, R.full.reserve(1));
+  HIP_TRY(c, R.t.reserve(3 * (size_t)n_t));
   hipEvent_t e0, e1;
   HIP_TRY(c, hipEventCreate(&e0));
   HIP_TRY(c, hipEventCreate(&e1));
   HIP_TRY(c, hipEventRecord(e0, c->stream));
-  ea.count = cnt.p;
+  HIP_TRY(c, hipMemsetAsync(R.full.p, 0, sizeof(unsigned long long), c->stream));
+  ea.count = R.cnt.p;
+  ea.n_full = R.full.p;
   HIP_TRY(c, launch_rec_enum(ea, false, c->stream));
-  DevBuf<uint64_t> stmp;
-  HIP_TRY(c, stmp.alloc(scan_tmp_entries(n_prefix)));
-  HIP_TRY(c, launch_scan_u32(cnt.p, off.p, n_prefix, stmp.p, c->stream));
+  HIP_TRY(c, launch_scan_u32(R.cnt.p, R.off.p, n_prefix, R.stmp.p, c->stream));
   uint64_t last_off = 0;
   uint32_t last_cnt = 0;
-  HIP_TRY(c, hipMemcpyAsync(&last_off, off.p + (n_prefix - 1), sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(&last_cnt, cnt.p + (n_prefix - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+  unsigned long long full = 0;
+  HIP_TRY(c, hipMemcpyAsync(&last_off, R.off.p + (n_prefix - 1), sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(&last_cnt, R.cnt.p + (n_prefix - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(&full, R.full.p, sizeof full, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   const uint64_t total = last_off + last_cnt;
-  HIP_TRY(c, rec_e.alloc(total));
-  HIP_TRY(c, rec_code.alloc(total));
-  ea.offset = off.p;
-  ea.rec_e = rec_e.p;
-  ea.rec_code = rec_code.p;
+  HIP_TRY(c, R.e.reserve(total));
+  HIP_TRY(c, R.w.reserve(total));
+  HIP_TRY(c, R.code.reserve(total));
+  ea.offset = R.off.p;
+  ea.rec_e = R.e.p;
+  ea.rec_w = R.w.p;
+  ea.rec_code = R.code.p;
   HIP_TRY(c, launch_rec_enum(ea, true, c->stream));
-  HIP_TRY(c, d_t.alloc(n_t));
-  HIP_TRY(c, d_num.alloc(n_t));
-  HIP_TRY(c, d_den.alloc(n_t));
-  HIP_TRY(c, hipMemcpyAsync(d_t.p, t, n_t * sizeof(double), hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(R.t.p, t, n_t * sizeof(double), hipMemcpyHostToDevice, c->stream));
   RecSumArgs sa{};
   sa.tab = c->d_tab.p;
   sa.lev = c->d_lev.p;
+  sa.units = U;
   sa.species = sp;
   sa.de = de;
   sa.a = 2.5 - omega;
   sa.lgamma_a = std::lgamma(sa.a);
-  sa.t = d_t.p;
-  sa.rec_e = rec_e.p;
-  sa.rec_code = rec_code.p;
+  sa.t = R.t.p;
+  sa.rec_e = R.e.p;
+  sa.rec_w = R.w.p;
+  sa.rec_code = R.code.p;
   sa.n_rec = total;
-  sa.num = d_num.p;
-  sa.den = d_den.p;
+  sa.num = R.t.p + n_t;
+  sa.den = R.t.p + 2 * (size_t)n_t;
   HIP_TRY(c, launch_rec_sum(sa, n_t, std::max<size_t>(n_sl, 1) * sizeof(double), c->stream));
   HIP_TRY(c, hipEventRecord(e1, c->stream));
-  std::vector<double> num(n_t), den(n_t);
-  HIP_TRY(c, hipMemcpyAsync(num.data(), d_num.p, n_t * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(den.data(), d_den.p, n_t * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  std::vector<double> sums(2 * (size_t)n_t);
+  HIP_TRY(c, hipMemcpyAsync(sums.data(), R.t.p + n_t, sums.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   float el = 0.0f;
   HIP_TRY(c, hipEventElapsedTime(&el, e0, e1));
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  for (uint32_t i = 0; i < n_t; ++i) p[i] = num[i] / den[i];
+  for (uint32_t i = 0; i < n_t; ++i) p[i] = sums[i] / sums[(size_t)n_t + i];
   if (ms) *ms = el;
-  if (n_rec) *n_rec = total;
+  if (n_rec) *n_rec = full;
   return HCAO_OK;
 }
 
@@ -2552,6 +2594,9 @@ void hcao_destroy(hcao_ctx *c) {
   c->d_rec.release();
   c->d_beta.release();
   c->err.release();
+  c->rec_scratch.release();
+  c->tdelta.release();
+  c->clk.release();
   c->in_rem.release();
   c->in_count.release();
   c->in_base.release();

@@ -314,39 +314,60 @@ struct RebinArgs {
 };
 
 // Forward recombination probability summed over every level combination of
-// a species (Eq. recomb-correct). Enumeration pass: thread i takes prefix i
-// of the levels of the first n_prefix_modes modes (mixed radix over box[])
-// and walks the remaining modes depth first, emitting one record per
-// combination below de (a leaf: energy above ground, code kRecLeaf) and one
-// per point where the walk first crosses de at mode m, level j (energy of
-// that partial combination, code m | j << 8). With offset == null it only
-// counts a thread's records into count[i].
+// a species (Eq. recomb-correct). Combinations that only swap levels among
+// identical modes have the same energy, so they are enumerated once, with
+// their number as a weight: the modes are walked as units, one per run of
+// degree identical bends (its state is the run's total quantum number v,
+// which C(v + degree - 1, degree - 1) combinations share) and one per stretch
+// (levels within a run of identical stretches never decrease; same marks a
+// stretch with its predecessor's ladder). Walking the units in order, a
+// prefix of units below de leaves one crossing record at the next unit
+// (energy of the prefix and the first level j that reaches de, code unit | j
+// << 8, weight of the prefix) and a full combination below de a leaf (code
+// kRecLeaf).
+//
+// Enumeration pass: thread i takes prefix i of the first n_prefix_units
+// units (mixed radix over box[]) and walks the rest depth first. With offset
+// == null it only counts a thread's records into count[i], and adds the
+// number of records an enumeration of single combinations would hold to
+// n_full.
 constexpr uint32_t kRecLeaf = 0xFFu;
+
+struct RecUnits {
+  uint32_t n;
+  uint32_t mode[kMaxModes];    // a bend of the run, or the stretch
+  uint32_t degree[kMaxModes];  // bends in the run (0: a stretch)
+  uint32_t same[kMaxModes];
+};
 
 struct RecEnumArgs {
   const Tables *tab;
   const double *lev;
-  uint32_t species, n_prefix_modes;
+  RecUnits units;
+  uint32_t species, n_prefix_units;
   uint32_t box[kMaxModes];
   uint64_t n_prefix;
   double de;
   uint32_t *count;
+  unsigned long long *n_full;
   const uint64_t *offset;
-  double *rec_e;
+  double *rec_e, *rec_w;
   uint32_t *rec_code;
 };
 
 // Sum pass: block b evaluates temperature t[b]; leaves contribute
 // Q(a, (de - e)/kT) exp(-e/kT), crossings exp(-e/kT) times the Boltzmann sum
-// of the crossing mode's levels from j up (relative to level j) times the
-// partition sums of the later modes. num[b] / den[b] is the probability.
+// of the crossing unit's levels from j up (relative to level j) times the
+// partition sums of the later units, each times its weight. num[b] / den[b]
+// is the probability.
 struct RecSumArgs {
   const Tables *tab;
   const double *lev;
+  RecUnits units;
   uint32_t species;
   double de, a, lgamma_a;
   const double *t;
-  const double *rec_e;
+  const double *rec_e, *rec_w;
   const uint32_t *rec_code;
   uint64_t n_rec;
   double *num, *den;
