@@ -144,7 +144,7 @@ double vibrational_temperature(const ModeSet &m, double e) {
 
 VibrationalThermometer::VibrationalThermometer(const ModeSet &m) : theta_(m.theta) {
   for (const std::vector<double> *L : m.ladder) ladders_.push_back(*L);
-  constexpr int kGrid = 512;
+  constexpr int kGrid = kNodes;
   const double top = std::log(1.0e6);
   for (int i = 0; i < kGrid; ++i) {
     const double lt = top * (double)i / (double)(kGrid - 1);

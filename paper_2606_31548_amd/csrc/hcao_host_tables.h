@@ -52,6 +52,9 @@ class VibrationalThermometer {
   VibrationalThermometer() = default;
   explicit VibrationalThermometer(const ModeSet &m);
   double temperature(double e) const;
+  static constexpr int kNodes = 512;  // equally spaced in log T over 1 .. 1e6 K
+  // mean energies at the nodes
+  const std::vector<double> &nodes() const { return mean_; }
 
  private:
   double mean(double t) const;  // mean_energy over the copied modes

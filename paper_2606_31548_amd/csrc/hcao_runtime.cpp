@@ -51,7 +51,13 @@ hipError_t launch_rebin_place(const RebinArgs &a, hipStream_t s);
 hipError_t launch_cell_init(const Tables *tab, const State &st, const CellArrays &cells, uint32_t n_cells,
                             hipStream_t s);
 hipError_t launch_moments(const Tables *tab, const double *lev, const State &st, const uint64_t *off,
-                          const uint32_t *cnt, double *out, uint32_t n_cells, hipStream_t s);
+                          const uint32_t *cnt, double *out, uint32_t n_cells, uint32_t ns, bool large, hipStream_t s);
+hipError_t launch_moments_sum(const double *in, const double *weight, const double *defect, double *out,
+                              uint32_t n_cells, uint32_t w, uint32_t ns, uint32_t blocks, hipStream_t s);
+hipError_t launch_thermometer(const Tables *tab, const double *lev, const double *mean, const double *in, double *t,
+                              uint32_t n_cells, uint32_t w, uint32_t ns, const uint32_t *same, hipStream_t s);
+hipError_t launch_reaction_sum(const unsigned long long *ctr, uint32_t n_cells, uint32_t nr, unsigned long long *out,
+                               hipStream_t s);
 hipError_t launch_load_check(const Tables *tab, const uint32_t *cell, const uint8_t *sp, const double *vel,
                              const uint16_t *lvl, uint64_t n, uint32_t n_cells, uint32_t *count, uint32_t *err,
                              hipStream_t s);
@@ -143,6 +149,11 @@ struct RecScratch {
 
 struct hcao_ctx {
   RecScratch rec_scratch;
+  // moments: the cells' sums, their partial totals, vibrational temperatures
+  // (scratch, kept), and the thermometer's tables
+  DevBuf<double> mom_raw, mom_part, mom_tvib, thermo_mean;
+  DevBuf<unsigned long long> rx_sum;
+  uint32_t thermo_same[kMaxSpecies] = {};
   hcao_config cfg{};
   std::vector<double> rec_host;   // recombination factors, all reactions
   std::vector<double> beta_host;  // exact sampler: beta per E' bin, per (species, LB exponent)
@@ -1141,6 +1152,18 @@ hcao_status hcao_finalize(hcao_ctx *c) {
   T.n_levels = (uint32_t)c->lev_host.size();
   c->thermo.clear();
   for (const SpeciesHost &h : c->species) c->thermo.emplace_back(modes_of(h));
+  static_assert(host::VibrationalThermometer::kNodes == (int)kThermoNodes, "thermometer tables disagree");
+  std::vector<double> nodes;
+  for (uint32_t s = 0; s < T.n_species; ++s) {
+    const std::vector<double> &m = c->thermo[s].nodes();
+    nodes.insert(nodes.end(), m.begin(), m.end());
+    const SpeciesHost &h = c->species[s];
+    c->thermo_same[s] = 0;
+    for (uint32_t j = 1; j < h.d.n_stretch; ++j)
+      if (h.levels[j] == h.levels[j - 1]) c->thermo_same[s] |= 1u << (h.d.n_bend + j);
+  }
+  HIP_TRY(c, c->thermo_mean.alloc(nodes.size()));
+  HIP_TRY(c, hipMemcpy(c->thermo_mean.p, nodes.data(), nodes.size() * sizeof(double), hipMemcpyHostToDevice));
   // VHS pair constants: sigma g = C (g^2)^(1-w), C = pi d^2 (2 k T_ref / m_r)^(w-1/2) / Gamma(5/2-w),
   // mixed-pair d, w, T_ref as species means; LB exponent 3/2 - w
   for (uint32_t a = 0; a < T.n_species; ++a)
@@ -2162,15 +2185,32 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
   if (!c) return HCAO_EINVAL;
   if (!c->loaded) return fail(c, HCAO_ESTATE, "no particles");
   const uint32_t nc = c->cfg.n_cells, ns = (uint32_t)c->species.size();
-  const uint32_t w = 6 + 3 * ns;
-  DevBuf<double> d_out;
-  HIP_TRY(c, d_out.alloc((size_t)nc * w));
-  HIP_TRY(c, launch_moments(c->d_tab.p, c->d_lev.p, state_of(c), c->off.p, c->cnt.p, d_out.p, nc, c->stream));
-  std::vector<double> raw((size_t)nc * w), df(nc);
-  HIP_TRY(c, hipMemcpyAsync(raw.data(), d_out.p, raw.size() * 8, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(df.data(), c->defect.p, nc * 8, hipMemcpyDeviceToHost, c->stream));
+  const uint32_t w = 6 + 3 * ns, cols = w + ns + 1;
+  // eight waves per cell where a cell holds more than a wave's few rounds
+  uint64_t slots = 0;
+  for (uint32_t cap : c->cap_host) slots += cap;
+  const bool large = slots > 2048ull * nc;
+  const uint32_t blocks = std::min(256u, (nc + 63u) / 64u);
+  HIP_TRY(c, c->mom_raw.reserve((size_t)nc * w));
+  HIP_TRY(c, c->mom_part.reserve((size_t)blocks * cols));
+  HIP_TRY(c, launch_moments(c->d_tab.p, c->d_lev.p, state_of(c), c->off.p, c->cnt.p, c->mom_raw.p, nc, ns, large,
+                            c->stream));
+  HIP_TRY(c, launch_moments_sum(c->mom_raw.p, c->d_weight.p, c->defect.p, c->mom_part.p, nc, w, ns, blocks, c->stream));
+  std::vector<double> part((size_t)blocks * cols), raw, df, tv;
+  if (per_cell) {
+    HIP_TRY(c, c->mom_tvib.reserve((size_t)nc * ns));
+    HIP_TRY(c, launch_thermometer(c->d_tab.p, c->d_lev.p, c->thermo_mean.p, c->mom_raw.p, c->mom_tvib.p, nc, w, ns,
+                                  c->thermo_same, c->stream));
+    raw.resize((size_t)nc * w);
+    df.resize(nc);
+    tv.resize((size_t)nc * ns);
+    HIP_TRY(c, hipMemcpyAsync(raw.data(), c->mom_raw.p, raw.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(df.data(), c->defect.p, nc * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(tv.data(), c->mom_tvib.p, tv.size() * 8, hipMemcpyDeviceToHost, c->stream));
+  }
+  HIP_TRY(c, hipMemcpyAsync(part.data(), c->mom_part.p, part.size() * 8, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  auto fill = [&](hcao_moments &M, const double *r, double vol, double wgt) {
+  auto fill = [&](hcao_moments &M, const double *r, const double *t_vib, double vol, double wgt) {
     std::memset(&M, 0, sizeof(M));
     for (int k = 0; k < 3; ++k) M.momentum[k] = r[k];
     const double mass = r[4];
@@ -2185,7 +2225,7 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
       ntot += k;
       M.E_vib_J[s] = r[6 + ns + s];
       if (vol > 0.0) M.number_density[s] = (double)k * wgt / vol;
-      M.T_vib_K[s] = k ? c->thermo[s].temperature(r[6 + ns + s] / (double)k) : 0.0;
+      M.T_vib_K[s] = t_vib ? t_vib[s] : (k ? c->thermo[s].temperature(r[6 + ns + s] / (double)k) : 0.0);
       M.E_rot_J[s] = r[6 + 2 * ns + s];
       const uint32_t z = c->species[s].d.zeta_rot;
       M.T_rot_K[s] = (k && z) ? (2.0 * M.E_rot_J[s]) / ((double)z * kB * (double)k) : 0.0;
@@ -2193,24 +2233,20 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
     M.n_total = ntot;
     M.T_trans_K = ntot ? 2.0 * M.E_trans_J / (3.0 * kB * (double)ntot) : 0.0;
   };
-  std::vector<double> sum(w, 0.0);
-  double vol_tot = 0.0, def_tot = 0.0;
-  std::vector<double> dens(ns, 0.0);
-  for (uint32_t i = 0; i < nc; ++i) {
-    const double *r = raw.data() + (size_t)i * w;
-    if (per_cell) {
-      fill(per_cell[i], r, c->volume[i], c->weight[i]);
+  if (per_cell)
+    for (uint32_t i = 0; i < nc; ++i) {
+      fill(per_cell[i], raw.data() + (size_t)i * w, tv.data() + (size_t)i * ns, c->volume[i], c->weight[i]);
       per_cell[i].E_defect_J = df[i];
     }
-    def_tot += df[i];
-    for (uint32_t k = 0; k < w; ++k) sum[k] += r[k];
-    vol_tot += c->volume[i];
-    for (uint32_t s = 0; s < ns; ++s) dens[s] += r[6 + s] * c->weight[i];
-  }
   if (total) {
-    fill(*total, sum.data(), 0.0, 0.0);
-    for (uint32_t s = 0; s < ns; ++s) total->number_density[s] = dens[s] / vol_tot;
-    total->E_defect_J = def_tot;
+    std::vector<double> sum(cols, 0.0);
+    for (uint32_t b = 0; b < blocks; ++b)
+      for (uint32_t k = 0; k < cols; ++k) sum[k] += part[(size_t)b * cols + k];
+    double vol_tot = 0.0;
+    for (uint32_t i = 0; i < nc; ++i) vol_tot += c->volume[i];
+    fill(*total, sum.data(), nullptr, 0.0, 0.0);
+    for (uint32_t s = 0; s < ns; ++s) total->number_density[s] = sum[w + s] / vol_tot;
+    total->E_defect_J = sum[w + ns];
   }
   return HCAO_OK;
 }
@@ -2219,13 +2255,18 @@ hcao_status hcao_read_reaction_counts(hcao_ctx *c, uint64_t *counts) {
   if (!c || !counts) return HCAO_EINVAL;
   if (!c->loaded) return fail(c, HCAO_ESTATE, "no particles");
   const uint32_t nc = c->cfg.n_cells;
-  std::vector<uint64_t> ctr((size_t)nc * kNumCtr);
-  if (hcao_status s = hcao_read_cell_state(c, nullptr, nullptr, ctr.data())) return s;
-  for (size_t r = 0; r < c->reactions.size(); ++r) {
-    uint64_t t = 0;
-    for (uint32_t i = 0; i < nc; ++i) t += ctr[(size_t)i * kNumCtr + HCAO_CTR_REACTION0 + r];
-    counts[r] = t;
+  const uint32_t nr = (uint32_t)c->reactions.size();
+  if (nr == 0) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return HCAO_OK;
   }
+  unsigned long long sums[kMaxReactions];
+  HIP_TRY(c, c->rx_sum.reserve(kMaxReactions));
+  HIP_TRY(c, hipMemsetAsync(c->rx_sum.p, 0, nr * sizeof(unsigned long long), c->stream));
+  HIP_TRY(c, launch_reaction_sum(c->ctr.p, nc, nr, c->rx_sum.p, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(sums, c->rx_sum.p, nr * sizeof(unsigned long long), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (uint32_t r = 0; r < nr; ++r) counts[r] = sums[r];
   return HCAO_OK;
 }
 
@@ -2595,6 +2636,11 @@ void hcao_destroy(hcao_ctx *c) {
   c->d_beta.release();
   c->err.release();
   c->rec_scratch.release();
+  c->mom_raw.release();
+  c->mom_part.release();
+  c->mom_tvib.release();
+  c->thermo_mean.release();
+  c->rx_sum.release();
   c->tdelta.release();
   c->clk.release();
   c->in_rem.release();

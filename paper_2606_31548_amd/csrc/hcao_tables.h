@@ -107,6 +107,7 @@ constexpr uint32_t kExactNBeta = 960u;  // beta grid (1 + (j mod 16) / 16) 2^(40
 // bytes of the fixed device array behind the allocation-free step
 constexpr uint64_t kStaticScratchBytes = HCAO_STATIC_SCRATCH_BYTES;
 
+constexpr uint32_t kThermoNodes = 512;  // mean energies per species over log T, 1 .. 1e6 K
 constexpr uint32_t kRecNodes = 1024;
 constexpr double kRecTmin = 100.0;
 constexpr double kRecTmax = 5.0e4;
