@@ -3093,6 +3093,42 @@ __global__ __launch_bounds__(256) void k_load_place(PlaceArgs A) {
   }
 }
 
+// Particles [p0, p1) of the canonical order into dense arrays (what a reader
+// wants of a cell-padded state): workgroup b packs cell c0 + b, whose first
+// particle has index start[c]. Levels in rows of mm.
+struct PackArgs {
+  State st;
+  const uint64_t *off, *start;
+  const uint32_t *cnt;
+  uint8_t *sp;
+  double *vel;
+  uint16_t *lvl;
+  uint64_t p0, p1;
+  uint32_t c0, mm;
+};
+__global__ __launch_bounds__(256) void k_pack(PackArgs A) {
+  const uint32_t c = A.c0 + blockIdx.x, n = A.cnt[c], mm = A.mm;
+  const uint64_t base = A.off[c], first = A.start[c];
+  if (first >= A.p1 || first + n <= A.p0) return;
+  const uint32_t i0 = first < A.p0 ? (uint32_t)(A.p0 - first) : 0u;
+  const uint32_t i1 = first + n > A.p1 ? (uint32_t)(A.p1 - first) : n;
+  const uint64_t to = first + i0 - A.p0;  // of particle i0
+  for (uint32_t i = i0 + threadIdx.x; i < i1; i += 256) {
+    const uint64_t j = to + (i - i0);
+    const Vec3 v = load_vel(A.st, base + i);
+    A.vel[3 * j] = v.x;
+    A.vel[3 * j + 1] = v.y;
+    A.vel[3 * j + 2] = v.z;
+    A.sp[j] = A.st.sp[base + i];
+  }
+  // levels number by number, so that a wave's stores are consecutive
+  const uint64_t nl = (uint64_t)(i1 - i0) * mm;
+  for (uint64_t f = threadIdx.x; f < nl; f += 256) {
+    const uint64_t i = f / mm;
+    A.lvl[to * mm + f] = A.st.lvl[(base + i0 + i) * A.st.lrow + (f - i * mm)];
+  }
+}
+
 // advances the device step index after the launches of a graph replay
 __global__ void k_advance(uint32_t *step, uint32_t n) {
   if (threadIdx.x == 0) step[0] = step[0] + n;
@@ -3824,6 +3860,15 @@ hipError_t launch_reaction_sum(const unsigned long long *ctr, uint32_t n_cells, 
                                hipStream_t s) {
   const uint32_t blocks = (n_cells + 255u) / 256u;
   hipLaunchKernelGGL(k_reaction_sum, dim3(blocks < 256u ? blocks : 256u), dim3(256), 0, s, ctr, n_cells, nr, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack(const State &st, const uint64_t *off, const uint64_t *start, const uint32_t *cnt, uint8_t *sp,
+                       double *vel, uint16_t *lvl, uint64_t p0, uint64_t p1, uint32_t c0, uint32_t c1, uint32_t mm,
+                       hipStream_t s) {
+  if (c1 <= c0 || p1 <= p0) return hipSuccess;
+  PackArgs a{st, off, start, cnt, sp, vel, lvl, p0, p1, c0, mm};
+  hipLaunchKernelGGL(k_pack, dim3(c1 - c0), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

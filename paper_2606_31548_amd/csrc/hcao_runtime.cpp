@@ -56,6 +56,9 @@ hipError_t launch_moments_sum(const double *in, const double *weight, const doub
                               uint32_t n_cells, uint32_t w, uint32_t ns, uint32_t blocks, hipStream_t s);
 hipError_t launch_thermometer(const Tables *tab, const double *lev, const double *mean, const double *in, double *t,
                               uint32_t n_cells, uint32_t w, uint32_t ns, const uint32_t *same, hipStream_t s);
+hipError_t launch_pack(const State &st, const uint64_t *off, const uint64_t *start, const uint32_t *cnt, uint8_t *sp,
+                       double *vel, uint16_t *lvl, uint64_t p0, uint64_t p1, uint32_t c0, uint32_t c1, uint32_t mm,
+                       hipStream_t s);
 hipError_t launch_reaction_sum(const unsigned long long *ctr, uint32_t n_cells, uint32_t nr, unsigned long long *out,
                                hipStream_t s);
 hipError_t launch_load_check(const Tables *tab, const uint32_t *cell, const uint8_t *sp, const double *vel,
@@ -108,8 +111,9 @@ struct DevBuf {
   T *p = nullptr;
   size_t n = 0;
   hipError_t alloc(size_t count) {
-    release();
     if (count == 0) count = 1;
+    if (p && n == count) return hipSuccess;
+    release();
     hipError_t e = hipMalloc((void **)&p, count * sizeof(T));
     if (e != hipSuccess) {
       p = nullptr;
@@ -145,10 +149,45 @@ struct RecScratch {
   }
 };
 
+// device scratch of the host transfers (load and read-back), kept by the
+// context while it is small
+struct LoadScratch {
+  DevBuf<uint32_t> cell, count, keys_tmp, idx, idx_tmp, hist;
+  DevBuf<uint8_t> sp;
+  DevBuf<double> vel, pos, rot;
+  DevBuf<uint16_t> lvl;
+  DevBuf<uint64_t> offs, packed, stmp;
+  size_t bytes() const {
+    return 4 * (cell.n + count.n + keys_tmp.n + idx.n + idx_tmp.n + hist.n) + sp.n + 8 * (vel.n + pos.n + rot.n) +
+           2 * lvl.n + 8 * (offs.n + packed.n + stmp.n);
+  }
+  void release() {
+    cell.release();
+    count.release();
+    keys_tmp.release();
+    idx.release();
+    idx_tmp.release();
+    hist.release();
+    sp.release();
+    vel.release();
+    pos.release();
+    rot.release();
+    lvl.release();
+    offs.release();
+    packed.release();
+    stmp.release();
+  }
+  void trim() {
+    if (bytes() > (512u << 20)) release();
+  }
+};
+constexpr uint64_t kPackChunk = 4u << 20;  // particles a read-back packs at once
+
 }  // namespace
 
 struct hcao_ctx {
   RecScratch rec_scratch;
+  LoadScratch io;
   // moments: the cells' sums, their partial totals, vibrational temperatures
   // (scratch, kept), and the thermometer's tables
   DevBuf<double> mom_raw, mom_part, mom_tvib, thermo_mean;
@@ -659,8 +698,13 @@ hipError_t grow_ins(hcao_ctx *c, uint64_t n) {
 // (capacities from caps, else the default headroom) and sets the offsets.
 hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
                         const std::vector<uint32_t> *caps = nullptr) {
-  free_state(c);
   const uint32_t nc = c->cfg.n_cells;
+  // a state of the same size takes the same arrays (allocating and freeing
+  // them cost a fifth of a load of a million particles)
+  uint64_t want = 0;
+  for (uint32_t i = 0; i < nc; ++i) want += caps ? (*caps)[i] : default_cap(c, counts[i]);
+  if (want != c->total_slots || !c->sp.p) free_state(c);
+  c->loaded = false;
   c->cap_host.assign(nc, 0);
   c->off_host.assign(nc + 1, 0);
   uint64_t tot = 0;
@@ -1354,7 +1398,8 @@ hcao_status hcao_load_particles(hcao_ctx *c, uint64_t n, const uint32_t *cell, c
         return fail(c, HCAO_EINVAL, "rotational energy must be finite, >= 0, and 0 without a rotor");
     }
   }
-  DevBuf<double> d_pos;
+  LoadScratch &S = c->io;
+  DevBuf<double> &d_pos = S.pos, &d_rot = S.rot;
   if (c->spatial) {
     if (n && !pos) return fail(c, HCAO_EINVAL, "the spatial mode needs positions");
     for (uint64_t i = 0; i < n; ++i) {
@@ -1368,24 +1413,24 @@ hcao_status hcao_load_particles(hcao_ctx *c, uint64_t n, const uint32_t *cell, c
       if (ijk[0] + c->grid[0] * (ijk[1] + c->grid[1] * ijk[2]) != cell[i])
         return fail(c, HCAO_EINVAL, "position not in the particle's cell");
     }
-    HIP_TRY(c, d_pos.alloc(3 * n));
+    HIP_TRY(c, d_pos.reserve(3 * n));
     if (n) HIP_TRY(c, hipMemcpyAsync(d_pos.p, pos, 3 * n * sizeof(double), hipMemcpyHostToDevice, c->stream));
   }
-  DevBuf<double> d_rot;
   if (rot && c->tab.has_rot) {
-    HIP_TRY(c, d_rot.alloc(n));
+    HIP_TRY(c, d_rot.reserve(n));
     if (n) HIP_TRY(c, hipMemcpyAsync(d_rot.p, rot, n * sizeof(double), hipMemcpyHostToDevice, c->stream));
   }
-  DevBuf<uint32_t> d_cell, d_count, keys_tmp, idx, idx_tmp, hist;
-  DevBuf<uint8_t> d_sp;
-  DevBuf<double> d_vel;
-  DevBuf<uint16_t> d_lvl;
-  DevBuf<uint64_t> offs, packed;
-  HIP_TRY(c, d_cell.alloc(n));
-  HIP_TRY(c, d_sp.alloc(n));
-  HIP_TRY(c, d_vel.alloc(3 * n));
-  HIP_TRY(c, d_lvl.alloc(n * mm));
-  HIP_TRY(c, d_count.alloc(nc));
+  DevBuf<uint32_t> &d_cell = S.cell, &d_count = S.count, &keys_tmp = S.keys_tmp, &idx = S.idx, &idx_tmp = S.idx_tmp,
+                   &hist = S.hist;
+  DevBuf<uint8_t> &d_sp = S.sp;
+  DevBuf<double> &d_vel = S.vel;
+  DevBuf<uint16_t> &d_lvl = S.lvl;
+  DevBuf<uint64_t> &offs = S.offs, &packed = S.packed, &stmp = S.stmp;
+  HIP_TRY(c, d_cell.reserve(n));
+  HIP_TRY(c, d_sp.reserve(n));
+  HIP_TRY(c, d_vel.reserve(3 * n));
+  HIP_TRY(c, d_lvl.reserve(n * mm));
+  HIP_TRY(c, d_count.reserve(nc));
   HIP_TRY(c, hipMemsetAsync(d_count.p, 0, nc * sizeof(uint32_t), c->stream));
   HIP_TRY(c, hipMemsetAsync(c->err.p, 0, sizeof(uint32_t), c->stream));
   if (n) {
@@ -1408,25 +1453,25 @@ hcao_status hcao_load_particles(hcao_ctx *c, uint64_t n, const uint32_t *cell, c
   // stable counting sort by cell, then placement into the padded layout
   uint32_t key_bits = 0;
   while (key_bits < 32 && ((uint64_t)1 << key_bits) < nc) ++key_bits;
-  HIP_TRY(c, keys_tmp.alloc(n));
-  HIP_TRY(c, idx.alloc(n));
-  HIP_TRY(c, idx_tmp.alloc(n));
-  HIP_TRY(c, hist.alloc(sort_hist_entries(n)));
-  HIP_TRY(c, offs.alloc(sort_hist_entries(n)));
-  HIP_TRY(c, packed.alloc(nc));
+  HIP_TRY(c, keys_tmp.reserve(n));
+  HIP_TRY(c, idx.reserve(n));
+  HIP_TRY(c, idx_tmp.reserve(n));
+  HIP_TRY(c, hist.reserve(sort_hist_entries(n)));
+  HIP_TRY(c, offs.reserve(sort_hist_entries(n)));
+  HIP_TRY(c, packed.reserve(nc));
   bool in_tmp = false;
-  DevBuf<uint64_t> stmp;
-  HIP_TRY(c, stmp.alloc(std::max(scan_tmp_entries(sort_hist_entries(n)), scan_tmp_entries(nc))));
+  HIP_TRY(c, stmp.reserve(std::max(scan_tmp_entries(sort_hist_entries(n)), scan_tmp_entries(nc))));
   HIP_TRY(c, launch_sort(d_cell.p, idx.p, keys_tmp.p, idx_tmp.p, hist.p, offs.p, stmp.p, n, key_bits, c->stream,
                          in_tmp));
   HIP_TRY(c, launch_scan_u32(c->cnt.p, packed.p, nc, stmp.p, c->stream));
   const uint32_t *sk = in_tmp ? keys_tmp.p : d_cell.p;
   const uint32_t *si = in_tmp ? idx_tmp.p : idx.p;
-  HIP_TRY(c, launch_place(c->d_tab.p, sk, si, packed.p, c->off.p, d_sp.p, d_vel.p, d_lvl.p, d_rot.p, d_pos.p,
+  HIP_TRY(c, launch_place(c->d_tab.p, sk, si, packed.p, c->off.p, d_sp.p, d_vel.p, d_lvl.p,
+                          rot && c->tab.has_rot ? d_rot.p : nullptr, c->spatial ? d_pos.p : nullptr,
                           state_of(c), n, c->stream));
   HIP_TRY(c, launch_cell_init(c->d_tab.p, state_of(c), cells_of(c), nc, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  d_cell.release();
+  S.trim();
   c->step = 0;
   c->loaded = true;
   return HCAO_OK;
@@ -1461,6 +1506,9 @@ hcao_status hcao_init_thermal(hcao_ctx *c, const uint32_t *counts, const double 
                          c->grid, c->len, c->stream));
   HIP_TRY(c, launch_cell_init(c->d_tab.p, state_of(c), cells_of(c), nc, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  d_counts.release();
+  d_tt.release();
+  d_tv.release();
   c->step = 0;
   c->loaded = true;
   return HCAO_OK;
@@ -2125,30 +2173,37 @@ hcao_status hcao_read_cell_particles(hcao_ctx *c, uint32_t cell, uint32_t max_n,
 hcao_status hcao_read_particles(hcao_ctx *c, uint8_t *species, double *vel, uint16_t *levels) {
   if (!c || !species || !vel || !levels) return HCAO_EINVAL;
   if (!c->loaded) return fail(c, HCAO_ESTATE, "no particles");
-  const uint64_t tot = c->total_slots;
   const uint32_t nc = c->cfg.n_cells, mm = c->max_modes ? c->max_modes : 1;
-  std::vector<double> vx(tot), vy(tot), vz(tot);
-  std::vector<uint8_t> sp(tot);
-  const uint32_t lr = level_row(c->max_modes);
-  std::vector<uint16_t> lv(tot * lr);
   std::vector<uint32_t> cnt(nc);
-  if (hcao_status s = download_vel(c, vx, vy, vz)) return s;
-  HIP_TRY(c, hipMemcpyAsync(sp.data(), c->sp.p, tot, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(lv.data(), c->lvl.p, tot * lr * 2, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipMemcpyAsync(cnt.data(), c->cnt.p, nc * 4, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  uint64_t j = 0;
-  for (uint32_t cell = 0; cell < nc; ++cell) {
-    const uint64_t b = c->off_host[cell];
-    for (uint32_t i = 0; i < cnt[cell]; ++i, ++j) {
-      const uint64_t g = b + i;
-      species[j] = sp[g];
-      vel[3 * j] = vx[g];
-      vel[3 * j + 1] = vy[g];
-      vel[3 * j + 2] = vz[g];
-      for (uint32_t m = 0; m < mm; ++m) levels[j * mm + m] = lv[g * lr + m];
-    }
+  std::vector<uint64_t> start(nc + 1, 0);
+  for (uint32_t i = 0; i < nc; ++i) start[i + 1] = start[i] + cnt[i];
+  const uint64_t tot = start[nc];
+  if (tot == 0) return HCAO_OK;
+  // packed on the device and copied straight into the caller's arrays, a
+  // bounded number of particles at a time
+  LoadScratch &S = c->io;
+  const uint64_t chunk = std::min<uint64_t>(tot, kPackChunk);
+  HIP_TRY(c, S.packed.reserve(nc));
+  HIP_TRY(c, S.sp.reserve(chunk));
+  HIP_TRY(c, S.vel.reserve(3 * chunk));
+  HIP_TRY(c, S.lvl.reserve(chunk * mm));
+  HIP_TRY(c, hipMemcpyAsync(S.packed.p, start.data(), nc * sizeof(uint64_t), hipMemcpyHostToDevice, c->stream));
+  uint32_t c0 = 0;
+  for (uint64_t p0 = 0; p0 < tot; p0 += chunk) {
+    const uint64_t p1 = std::min(tot, p0 + chunk), n = p1 - p0;
+    while (start[c0 + 1] <= p0) ++c0;
+    uint32_t c1 = c0 + 1;
+    while (c1 < nc && start[c1] < p1) ++c1;
+    HIP_TRY(c, launch_pack(state_of(c), c->off.p, S.packed.p, c->cnt.p, S.sp.p, S.vel.p, S.lvl.p, p0, p1, c0, c1, mm,
+                           c->stream));
+    HIP_TRY(c, hipMemcpyAsync(species + p0, S.sp.p, n, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(vel + 3 * p0, S.vel.p, 3 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(levels + p0 * mm, S.lvl.p, n * mm * sizeof(uint16_t), hipMemcpyDeviceToHost, c->stream));
   }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  S.trim();
   return HCAO_OK;
 }
 
@@ -2636,6 +2691,7 @@ void hcao_destroy(hcao_ctx *c) {
   c->d_beta.release();
   c->err.release();
   c->rec_scratch.release();
+  c->io.release();
   c->mom_raw.release();
   c->mom_part.release();
   c->mom_tvib.release();
