@@ -1040,9 +1040,9 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
 
 // The joint sampler's molecules of a wave, one slot per lane (LDS)
 struct JointJob {
-  double e_coll, denom, q;
-  uint32_t pos, base, pair, cell;  // next word of the stream, trials done, the stream
-  uint32_t sp, owner;              // owner: slot i of a wave's lanes names its i-th unaccepted molecule's lane
+  double e_coll, q;
+  uint32_t pos, pair, cell;  // first word of the next trial, the stream
+  uint16_t sp, owner;        // owner: slot i of a wave's lanes names its i-th unaccepted molecule's lane
 };
 
 // Joint sampler (uniform proposals over the box of levels, one acceptance of
@@ -1073,12 +1073,11 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
     if (job) {
       for (uint32_t m = 0; m < nm; ++m) C.scr[m * C.block + C.lane] = (uint16_t)mode_top(S, lev, m, e_coll);
       J[C.lane].e_coll = e_coll;
-      J[C.lane].denom = denom;
       J[C.lane].q = q;
       J[C.lane].pos = rng.used >= 4 ? 4 * rng.block : 4 * (rng.block - 1) + rng.used;  // next word of the stream
       J[C.lane].pair = rng.pair;
       J[C.lane].cell = rng.cell;
-      J[C.lane].sp = sp;
+      J[C.lane].sp = (uint16_t)sp;
     }
   }
   unsigned long long pend = __ballot(job);
@@ -1087,8 +1086,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
     const uint32_t sh = 6u - (np > 1 ? 32u - (uint32_t)__builtin_clz(np - 1u) : 0u), G = 1u << sh;
     const uint32_t rank = (uint32_t)__popcll(pend & lt);
     if (job) {
-      J[first_lane + rank].owner = lane;
-      J[C.lane].base = trials;
+      J[first_lane + rank].owner = (uint16_t)lane;
     }
     wave_sync();
     bool ok = false;
@@ -1097,7 +1095,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
       const uint32_t o = first_lane + J[first_lane + (lane >> sh)].owner;
       const SpeciesTab &S = C.T.sp[J[o].sp];
       const uint32_t n = S.n_modes;
-      const uint32_t at = J[o].pos + (J[o].base + (lane & (G - 1u))) * (n + 1u) * (MIX ? 1u : 2u);
+      const uint32_t at = J[o].pos + (lane & (G - 1u)) * (n + 1u) * (MIX ? 1u : 2u);
       RngT<MIX> r = rng;
       r.pair = J[o].pair;
       r.cell = J[o].cell;
@@ -1115,7 +1113,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
       }
       const double ua = (double)draw<MIX>(r);
       const double e = J[o].e_coll;
-      ok = sum < e && lb_accept<MIX>(ua, e - sum, J[o].denom, J[o].q);
+      ok = sum < e && lb_accept<MIX>(ua, e - sum, e - S.zpe, J[o].q);
     }
     const unsigned long long won = __ballot(ok);
     const unsigned long long mine = (won >> (rank << sh)) & (G < 64u ? (1ull << G) - 1ull : ~0ull);
@@ -1137,6 +1135,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
         job = false;
       } else {
         trials += G;
+        J[C.lane].pos += G * (nm + 1u) * (MIX ? 1u : 2u);
         if (trials >= kMaxTrials) {
           capped = true;
           job = false;
@@ -1753,6 +1752,15 @@ struct Records {
   double y0, y1, y2, y3, y4, y5;
 };
 
+// Phase C lists the step's products (candidate of each) in LDS while they are
+// few; with more of them it looks at every candidate's flag instead.
+constexpr uint32_t kBornList = 128;
+// A cell with more candidates than this has its per-pair records reduced by
+// all waves of the workgroup, chunk by chunk, before one wave adds up the
+// chunks (a wave takes a microsecond per chunk: a cell of 100,000 particles
+// has 600, which kept the other waves waiting for half of the step).
+constexpr uint32_t kBigCell = 512;
+
 // an accepted pair's velocities, handed from phase A to phase B
 template <typename R>
 struct PairVel {
@@ -1783,6 +1791,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
   __shared__ uint32_t s_nwork, s_total, s_next;
   __shared__ uint32_t s_bin[256];
   __shared__ WorkRound s_rounds[kLdsRounds];
+  __shared__ uint32_t s_nborn, s_born[kBornList];
+  __shared__ uint32_t s_big;
   const uint32_t tid = threadIdx.x;
   // the wave index is the same on every lane of a wave: held in a scalar
   // register, so that per-wave loops (one wave per cell) and what they
@@ -1926,12 +1936,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
   __syncthreads();
   HCAO_PHASE_MARK(kPhaseNtc);
   if (tid == 0) {
-    uint32_t acc = 0;
+    uint32_t acc = 0, most = 0;
     for (uint32_t g = 0; g < ncell; ++g) {
+      const uint32_t n = hdr[g].ncand;
       hdr[g].cstart = acc;
-      acc += hdr[g].ncand;
+      acc += n;
+      most = n > most ? n : most;
     }
     s_total = acc;
+    s_nborn = 0;
+    s_big = most > kBigCell ? 1u : 0u;
     s_nwork = 0;
     s_next = 0;
   }
@@ -2055,13 +2069,20 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
   // Waves take 64 consecutive pairs of the sorted list at a time from a
   // shared counter, so that a wave that drew light pairs takes the next
   // block instead of waiting at the barrier for one that drew heavy ones.
+  // (With the joint sampler, whose lanes share the work of fewer pairs, the
+  // blocks are as even as the waves can take them.)
+  uint32_t take = 64;
+  if (any_joint) {
+    const uint32_t per = (nwork + BLOCK / 64 - 1) / (BLOCK / 64), rounds_b = (per + 63) / 64;
+    if (rounds_b) take = (per + rounds_b - 1) / rounds_b;
+  }
   for (;;) {
     uint32_t c0 = 0;
-    if (lane == 0) c0 = atomicAdd(&s_next, 64u);
+    if (lane == 0) c0 = atomicAdd(&s_next, take);
     c0 = __builtin_amdgcn_readfirstlane(c0);  // every lane is active here: lane 0's value
     if (c0 >= nwork) break;
     const uint32_t i = c0 + lane;
-    const bool act = i < nwork;
+    const bool act = lane < take && i < nwork;
 #ifdef HCAO_PHASE_CLOCKS
     uint64_t wclk[5] = {0, 0, 0, 0, 0}, wclk_t = clock64();  // collision sub-phase clocks
     const bool lead = lane == (uint32_t)(__ffsll((long long)__ballot(1)) - 1);
@@ -2272,6 +2293,10 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
         }
       }
       bflag[at] = born ? 1 : 0;
+      if (born) {
+        const uint32_t b = atomicAdd(&s_nborn, 1u);
+        if (b < kBornList) s_born[b] = j;
+      }
     }
     HCAO_WAVE_MARK(wclk, kPhaseCollideWrite);
 #ifdef HCAO_PHASE_CLOCKS
@@ -2316,6 +2341,45 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
     }
     return r;
   };
+  // the product of candidate j to slot `slot`
+  auto place_born = [&](uint32_t j, uint64_t slot) {
+    const uint64_t from = HCAO_IDX(wbase + j, A.born.n_slots, A.err), to = HCAO_IDX(slot, A.st.n_slots, A.err);
+    stv<MIX>(A.st, to, ldv<MIX>(A.born, from));
+    A.st.sp[to] = A.born.sp[from];
+    copy_levels(A.born, from, A.st, to);
+    if constexpr (EX >= 1) {
+      if (A.st.rot) A.st.rot[to] = A.born.rot[from];
+      if (A.st.px) {
+        A.st.px[to] = A.born.px[from];
+        A.st.py[to] = A.born.py[from];
+        A.st.pz[to] = A.born.pz[from];
+      }
+    }
+  };
+  // one chunk's sums: value tree6_value(lane) (the defect alone: lane 0)
+  auto chunk_sum = [&](const Records &r) {
+    if (A.tdelta) return tree_sum6(r.y0, r.y1, r.y2, r.y3, r.y4, r.y5);
+    double z[1] = {r.y5};
+    tree_sum(z);
+    return z[0];
+  };
+  const uint32_t vx = A.tdelta ? tree6_value(lane) : (lane == 0 ? 5u : 6u);
+  // chunk sums of big cells, in the memory of the pairs' velocities (free
+  // from here to the next step): six numbers per chunk
+  double *chunks = reinterpret_cast<double *>(pv);
+  const bool big = records && s_big != 0;
+  if (big) {
+    for (uint32_t g = 0; g < ncell; ++g) {
+      const uint32_t nc = hdr[g].ncand;
+      if (nc <= kBigCell) continue;
+      double *to = chunks + 6 * (size_t)(hdr[g].cstart / 64 + g);
+      for (uint32_t h = wave; h * 64 < nc; h += BLOCK / 64) {
+        const double d = chunk_sum(chunk_load(g, h * 64));
+        if (vx < 6u) to[6 * (size_t)h + vx] = d;
+      }
+    }
+    __syncthreads();
+  }
   Records next{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   if (kPrefetch && records && wave < ncell) next = chunk_load(wave, 0);
   for (uint32_t g = wave; g < ncell; g += BLOCK / 64) {
@@ -2371,7 +2435,16 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
     }
     const uint32_t births = (uint32_t)in[HCAO_CTR_BIRTHS];
     const bool overflow = alive + births > H.cap;
-    if (births && !overflow) {
+    if (births && !overflow && s_nborn <= kBornList) {
+      const uint32_t nb = s_nborn;
+      for (uint32_t e = lane; e < nb; e += 64) {
+        const uint32_t j = s_born[e];
+        if (j < H.cstart || j - H.cstart >= H.ncand) continue;
+        uint32_t rank = 0;  // products of the cell from earlier pairs
+        for (uint32_t t = 0; t < nb; ++t) rank += s_born[t] >= H.cstart && s_born[t] < j ? 1u : 0u;
+        place_born(j, H.base + alive + rank);
+      }
+    } else if (births && !overflow) {
       uint32_t done = 0;
       for (uint32_t k0 = 0; k0 < H.ncand; k0 += 64) {
         const uint32_t k = k0 + lane;
@@ -2379,19 +2452,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
         const bool f = e != ~0u && bflag[HCAO_IDX(e, wcap, A.err)] != 0;
         const unsigned long long m = __ballot(f);
         if (f) {
-          const uint64_t from = HCAO_IDX(wbase + H.cstart + k, A.born.n_slots, A.err),
-                         to = HCAO_IDX(H.base + alive + done + (uint32_t)__popcll(m & lt), A.st.n_slots, A.err);
-          stv<MIX>(A.st, to, ldv<MIX>(A.born, from));
-          A.st.sp[to] = A.born.sp[from];
-          copy_levels(A.born, from, A.st, to);
-          if constexpr (EX >= 1) {
-            if (A.st.rot) A.st.rot[to] = A.born.rot[from];
-            if (A.st.px) {
-              A.st.px[to] = A.born.px[from];
-              A.st.py[to] = A.born.py[from];
-              A.st.pz[to] = A.born.pz[from];
-            }
-          }
+          place_born(H.cstart + k, H.base + alive + done + (uint32_t)__popcll(m & lt));
         }
         done += (uint32_t)__popcll(m);
       }
@@ -2402,21 +2463,28 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
     // candidate that did not collide contributes 0). A chunk's loads are all
     // issued before any is used.
     if (records) {
-      double d = 0.0;  // lane tree6_value: that value's sum (the defect alone: lane 0)
-      for (uint32_t k0 = 0; k0 < H.ncand; k0 += 64) {
-        Records r = first;
-        if (!kPrefetch || k0) r = chunk_load(g, k0);
-        if (A.tdelta) {
-          d = d + tree_sum6(r.y0, r.y1, r.y2, r.y3, r.y4, r.y5);
-        } else {
-          double z[1] = {r.y5};
-          tree_sum(z);
-          d = d + z[0];
+      double d = 0.0;  // sum of the lane's value
+      if (big && H.ncand > kBigCell) {
+        const double *from = chunks + 6 * (size_t)(H.cstart / 64 + g) + (vx < 6u ? vx : 0u);
+        const uint32_t nch = (H.ncand + 63) / 64;
+        uint32_t h = 0;
+        for (; h + 16 <= nch; h += 16) {  // sixteen loads in flight, added in order
+          double y[16];
+#pragma unroll
+          for (int x = 0; x < 16; ++x) y[x] = from[6 * (size_t)(h + x)];
+#pragma unroll
+          for (int x = 0; x < 16; ++x) d = d + y[x];
+        }
+        for (; h < nch; ++h) d = d + from[6 * (size_t)h];
+      } else {
+        for (uint32_t k0 = 0; k0 < H.ncand; k0 += 64) {
+          Records r = first;
+          if (!kPrefetch || k0) r = chunk_load(g, k0);
+          d = d + chunk_sum(r);
         }
       }
-      const uint32_t x = A.tdelta ? tree6_value(lane) : (lane == 0 ? 5u : 6u);
-      if (x < 5u) hdr[g].tsum[x] = H.tsum[x] + d;
-      if (MIX && x == 5u) hdr[g].defect = H.defect + d;
+      if (vx < 5u && A.tdelta) hdr[g].tsum[vx] = H.tsum[vx] + d;
+      if (MIX && vx == 5u) hdr[g].defect = H.defect + d;
     }
     unsigned long long *tot = l_tot + (size_t)g * nctr;
     for (uint32_t i = lane; i < nctr; i += 64) {
@@ -3748,6 +3816,12 @@ static hipError_t launch_step_t(const StepArgs &a, size_t lds, int block, uint32
     case 128: hipLaunchKernelGGL((k_step<128, MIX, EX>), dim3(n_groups), dim3(128), lds, s, a); break;
     case 256: hipLaunchKernelGGL((k_step<256, MIX, EX>), dim3(n_groups), dim3(256), lds, s, a); break;
     case 512: hipLaunchKernelGGL((k_step<512, MIX, EX>), dim3(n_groups), dim3(512), lds, s, a); break;
+    case 1024:
+      if constexpr (EX == 0) {
+        hipLaunchKernelGGL((k_step<1024, MIX, EX>), dim3(n_groups), dim3(1024), lds, s, a);
+        break;
+      }
+      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -3791,6 +3865,11 @@ static hipError_t set_lds_limit_level(int bytes) {
                        (const void *)k_step<256, MIX, EX>, (const void *)k_step<512, MIX, EX>};
   for (const void *f : fns) {
     const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (r != hipSuccess) e = r;
+  }
+  if constexpr (EX == 0) {
+    const hipError_t r =
+        hipFuncSetAttribute((const void *)k_step<1024, MIX, EX>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
     if (r != hipSuccess) e = r;
   }
   return e;

@@ -552,6 +552,8 @@ hcao_status upload_vel(hcao_ctx *c, const std::vector<double> &vx, const std::ve
   return HCAO_OK;
 }
 
+int step_level(const hcao_ctx *c);
+
 // Workgroup size and slot target of the launches. A shape the caller set is
 // taken as it is. Otherwise the default (64 lanes, 1,024 slots) holds while it
 // gives the chip enough waves; a context too small for that gets smaller
@@ -571,7 +573,8 @@ void choose_shape(const hcao_ctx *c, int &block, uint32_t &group_slots) {
   if (slots >= (uint64_t)kShapeGroups * group_slots) return;
   group_slots = (uint32_t)std::max<uint64_t>(1, slots / kShapeGroups);
   const uint64_t groups = std::max<uint64_t>(1, slots / std::max(group_slots, largest));
-  while (block < 512 && groups * (uint64_t)block * 2 <= (uint64_t)kShapeWaves * 64 &&
+  const int widest = step_level(c) == 0 ? 1024 : 512;  // (the widest form is built for the plain step only)
+  while (block < widest && groups * (uint64_t)block * 2 <= (uint64_t)kShapeWaves * 64 &&
          (uint64_t)block * 4 < std::max(group_slots, largest) &&
          step_lds_bytes(c->tab, 1, 2 * block) <= kLdsBudget)
     block *= 2;
