@@ -22,7 +22,7 @@ namespace hcao {
 namespace {
 
 constexpr double kBoltz = 1.380649e-23;
-constexpr uint8_t kDead = 255;  // species byte of a particle removed by recombination
+constexpr uint32_t kDead = 255;  // species of a particle removed by recombination
 
 // Instrumented builds (HCAO_PHASE_CLOCKS) let thread 0 of every step
 // workgroup sum the shader clock spent between the barriers that end each
@@ -249,40 +249,55 @@ __device__ __forceinline__ uint64_t checked_index(uint64_t i, uint64_t n, uint32
 #define HCAO_ERR_ARG(e)
 #endif
 
+// a particle's velocity and species
+template <typename R>
+struct BodyOf {
+  V3<R> v;
+  uint32_t sp;
+};
 template <bool MIX>
-__device__ __forceinline__ V3<Real<MIX>> ldv(const State &s, uint64_t i) {
+__device__ __forceinline__ BodyOf<Real<MIX>> ldb(const State &s, uint64_t i) {
+  if constexpr (MIX) {
+    const Body32 b = s.b32[i];
+    return {{b.x, b.y, b.z}, b.sp};
+  } else {
+    const Body64 b = s.b64[i];
+    return {{b.x, b.y, b.z}, (uint32_t)b.sp};
+  }
+}
+template <bool MIX>
+__device__ __forceinline__ void stb(const State &s, uint64_t i, V3<Real<MIX>> v, uint32_t sp) {
   if constexpr (MIX)
-    return V3<float>{s.fx[i], s.fy[i], s.fz[i]};
+    s.b32[i] = Body32{v.x, v.y, v.z, sp};
   else
-    return V3<double>{s.vx[i], s.vy[i], s.vz[i]};
+    s.b64[i] = Body64{v.x, v.y, v.z, sp};
 }
 template <bool MIX>
 __device__ __forceinline__ void stv(const State &s, uint64_t i, V3<Real<MIX>> v) {
   if constexpr (MIX) {
-    s.fx[i] = v.x;
-    s.fy[i] = v.y;
-    s.fz[i] = v.z;
+    s.b32[i].x = v.x;
+    s.b32[i].y = v.y;
+    s.b32[i].z = v.z;
   } else {
-    s.vx[i] = v.x;
-    s.vy[i] = v.y;
-    s.vz[i] = v.z;
+    s.b64[i].x = v.x;
+    s.b64[i].y = v.y;
+    s.b64[i].z = v.z;
   }
 }
 // the same for kernels that serve both forms (the set that is not null)
-__device__ __forceinline__ Vec3 load_vel(const State &s, uint64_t i) {
-  if (s.fx) return Vec3{(double)s.fx[i], (double)s.fy[i], (double)s.fz[i]};
-  return Vec3{s.vx[i], s.vy[i], s.vz[i]};
-}
-__device__ __forceinline__ void store_vel(const State &s, uint64_t i, double x, double y, double z) {
-  if (s.fx) {
-    s.fx[i] = (float)x;
-    s.fy[i] = (float)y;
-    s.fz[i] = (float)z;
-  } else {
-    s.vx[i] = x;
-    s.vy[i] = y;
-    s.vz[i] = z;
+__device__ __forceinline__ BodyOf<double> load_body(const State &s, uint64_t i) {
+  if (s.b32) {
+    const Body32 b = s.b32[i];
+    return {{(double)b.x, (double)b.y, (double)b.z}, b.sp};
   }
+  const Body64 b = s.b64[i];
+  return {{b.x, b.y, b.z}, (uint32_t)b.sp};
+}
+__device__ __forceinline__ void store_body(const State &s, uint64_t i, double x, double y, double z, uint32_t sp) {
+  if (s.b32)
+    s.b32[i] = Body32{(float)x, (float)y, (float)z, sp};
+  else
+    s.b64[i] = Body64{x, y, z, sp};
 }
 
 // ---------------------------------------------------------------------------
@@ -1377,11 +1392,11 @@ __device__ void cell_sums(const State &st, const SpeciesTab *spt, uint64_t base,
       vx[u] = vy[u] = vz[u] = 0.0;
       if (i < n) {
         const uint64_t g = base + i;
-        m[u] = spt[st.sp[g]].mass;
-        const V3<Real<MIX>> v = ldv<MIX>(st, g);
-        vx[u] = v.x;
-        vy[u] = v.y;
-        vz[u] = v.z;
+        const BodyOf<Real<MIX>> b = ldb<MIX>(st, g);
+        m[u] = spt[b.sp].mass;
+        vx[u] = b.v.x;
+        vy[u] = b.v.y;
+        vz[u] = b.v.z;
       }
     }
 #pragma unroll
@@ -1477,7 +1492,8 @@ __device__ __forceinline__ Outcome decide(const Ctx &C, PairLocal<MIX> &P, const
       perm.load(H.perm);
       const uint32_t im = perm(2 * H.ncand + k);
       const uint64_t gm = HCAO_IDX(H.base + im, st.n_slots, err);
-      const uint32_t sp_m = st.sp[gm];
+      const BodyOf<Rl> third = ldb<MIX>(st, gm);
+      const uint32_t sp_m = third.sp;
       const double *tab = rec + R.rec_off + (size_t)sp_m * T.rec_nt;
       double prob;
       if (H.rec_i == -1)
@@ -1490,7 +1506,7 @@ __device__ __forceinline__ Outcome decide(const Ctx &C, PairLocal<MIX> &P, const
       if (prob > 1.0) prob = 1.0;
       if (!(u < prob)) continue;
       const V3<Rl> c3 = com<MIX>(T.pair(R.a, R.b), sb ? v1 : v0, sb ? v0 : v1);
-      const V3<Rl> vm = ldv<MIX>(st, gm);
+      const V3<Rl> vm = third.v;
       const double gx = (double)c3.x - (double)vm.x, gy = (double)c3.y - (double)vm.y,
                    gz = (double)c3.z - (double)vm.z;
       const double e_am = T.pair(R.c, sp_m).hm * ((gx * gx + gy * gy) + gz * gz);
@@ -1974,11 +1990,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
       pj = p;
       qj = qq;
       const uint64_t gp = HCAO_IDX(H.base + p, A.st.n_slots, A.err), gq = HCAO_IDX(H.base + qq, A.st.n_slots, A.err);
-      const V3<R> vp = ldv<MIX>(A.st, gp), vq = ldv<MIX>(A.st, gq);
+      const BodyOf<R> bp = ldb<MIX>(A.st, gp), bq = ldb<MIX>(A.st, gq);
+      const V3<R> vp = bp.v, vq = bq.v;
       vel = PairVel<R>{vp, vq};
       const R dx = vp.x - vq.x, dy = vp.y - vq.y, dz = vp.z - vq.z;
       const R g2 = (dx * dx + dy * dy) + dz * dz;
-      const uint32_t a = A.st.sp[gp], b = A.st.sp[gq];
+      const uint32_t a = bp.sp, b = bq.sp;
       const PairTab &PP = T.pair(a, b);
       RngT<MIX> rng;
       rng.open(A.seed, k, H.cell, step);
@@ -2202,7 +2219,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
                      gm = HCAO_IDX(H.base + O.m, A.st.n_slots, A.err);
       const bool recoil = O.kind == 3, born = O.kind == 1;
       V3<R> vm{R(0), R(0), R(0)};
-      if (recoil) vm = ldv<MIX>(A.st, gm);
+      if (recoil) vm = ldb<MIX>(A.st, gm).v;
       const Ctx C{T, l_ctr + (size_t)g * nctr, scr, tid, BLOCK};
       const Scattered<MIX> F = scatter<MIX, (EX >= 2)>(C, O, P.sp0, P.sp1, v0, v1, vm, rng);
       HCAO_WAVE_MARK(wclk, kPhaseCollideScatter);
@@ -2255,10 +2272,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
         const uint64_t e = HCAO_IDX(wbase + at, A.tdelta_stride, A.err);
         for (int x = 0; x < 5; ++x) A.tdelta[(size_t)x * A.tdelta_stride + e] = after[x] - before[x];
       }
-      stv<MIX>(A.st, gp, F.v0);
-      stv<MIX>(A.st, gq, F.v1);
-      A.st.sp[gp] = F.dead0 ? (uint8_t)kDead : (uint8_t)F.sp0;
-      A.st.sp[gq] = F.dead1 ? (uint8_t)kDead : (uint8_t)F.sp1;
+      stb<MIX>(A.st, gp, F.v0, F.dead0 ? kDead : F.sp0);
+      stb<MIX>(A.st, gq, F.v1, F.dead1 ? kDead : F.sp1);
       // the new species' modes, and zeros over the modes only the old species had
       // (a removed particle's levels are not kept)
       const uint32_t nm0 = T.sp[P.sp0].n_modes, nm1 = T.sp[P.sp1].n_modes;
@@ -2279,8 +2294,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
       if (recoil) stv<MIX>(A.st, gm, F.vm);
       if (born) {
         const uint64_t gb = HCAO_IDX(wbase + j, A.born.n_slots, A.err);
-        stv<MIX>(A.born, gb, F.vn);
-        A.born.sp[gb] = (uint8_t)nb_sp;
+        stb<MIX>(A.born, gb, F.vn, nb_sp);
         store_levels(A.born, gb, mm, A.born.lrow, P.lvn, BLOCK);
         if constexpr (EX >= 1) {
           if (A.born.rot) A.born.rot[gb] = P.rn;
@@ -2344,8 +2358,8 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
   // the product of candidate j to slot `slot`
   auto place_born = [&](uint32_t j, uint64_t slot) {
     const uint64_t from = HCAO_IDX(wbase + j, A.born.n_slots, A.err), to = HCAO_IDX(slot, A.st.n_slots, A.err);
-    stv<MIX>(A.st, to, ldv<MIX>(A.born, from));
-    A.st.sp[to] = A.born.sp[from];
+    const BodyOf<R> b = ldb<MIX>(A.born, from);
+    stb<MIX>(A.st, to, b.v, b.sp);
     copy_levels(A.born, from, A.st, to);
     if constexpr (EX >= 1) {
       if (A.st.rot) A.st.rot[to] = A.born.rot[from];
@@ -2395,19 +2409,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
       for (uint32_t i0 = 0; i0 < H.n; i0 += 64) {
         const uint32_t i = i0 + lane;
         const uint64_t src = HCAO_IDX(H.base + i, A.st.n_slots, A.err);
-        const bool live = i < H.n && A.st.sp[src] != kDead;
+        BodyOf<R> b{{R(0), R(0), R(0)}, kDead};
+        if (i < H.n) b = ldb<MIX>(A.st, src);
+        const bool live = b.sp != kDead;
         const unsigned long long m = __ballot(live);
         const uint64_t dst = HCAO_IDX(H.base + kept + (uint32_t)__popcll(m & lt), A.st.n_slots, A.err);
-        V3<R> v{R(0), R(0), R(0)};
-        uint8_t spv = 0;
-        if (live) {
-          v = ldv<MIX>(A.st, src);
-          spv = A.st.sp[src];
-        }
-        if (live) {
-          stv<MIX>(A.st, dst, v);
-          A.st.sp[dst] = spv;
-        }
+        if (live) stb<MIX>(A.st, dst, b.v, b.sp);
         if (live) copy_levels(A.st, src, A.st, dst);
         if constexpr (EX >= 1) {
           if (A.st.rot) {
@@ -2632,8 +2639,7 @@ __global__ __launch_bounds__(256) void k_init(InitArgs A) {
     polar_normals(rng, n3, n4);
     const double sigma = sqrt((kBoltz * tt) / S.mass);
     const uint64_t g = A.off[c] + i;
-    store_vel(A.st, g, sigma * n1, sigma * n2, sigma * n3);
-    A.st.sp[g] = (uint8_t)s;
+    store_body(A.st, g, sigma * n1, sigma * n2, sigma * n3, s);
     sample_internal(S, T.theta[s], A.lev, rng, tv, tt, A.st, g, mm);
     if (A.st.px) {
       // spatial mode: uniform in the cell, one draw per axis
@@ -2669,17 +2675,17 @@ __global__ __launch_bounds__(256) void k_cell_init(CellInitArgs A) {
   double vmax2 = 0.0;
   uint32_t mask = 0;
   for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-    const Vec3 v = load_vel(A.st, base + i);
-    const double v2 = (v.x * v.x + v.y * v.y) + v.z * v.z;
+    const BodyOf<double> b = load_body(A.st, base + i);
+    const double v2 = (b.v.x * b.v.x + b.v.y * b.v.y) + b.v.z * b.v.z;
     vmax2 = v2 > vmax2 ? v2 : vmax2;
-    mask |= 1u << A.st.sp[base + i];
+    mask |= 1u << b.sp;
   }
   atomicMax(&s_v, (unsigned long long)__double_as_longlong(vmax2));
   atomicOr(&s_mask, mask);
   if (A.cells.tsum && threadIdx.x < 64) {
     // the running sums of the cell temperature start from the particles
     double sums[5];
-    if (A.st.fx)
+    if (A.st.b32)
       cell_sums<true>(A.st, A.tab->sp, base, n, threadIdx.x, sums);
     else
       cell_sums<false>(A.st, A.tab->sp, base, n, threadIdx.x, sums);
@@ -2750,12 +2756,14 @@ __global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void k_moments(Momen
     const uint32_t i = i0 + lane;
     const bool in = i < n;
     const uint64_t g = base + (in ? i : 0u);
-    const uint32_t s = in ? A.st.sp[g] : ~0u;
+    BodyOf<double> b{{0.0, 0.0, 0.0}, ~0u};
+    if (in) b = load_body(A.st, g);
+    const uint32_t s = b.sp;
     double ev = 0.0, er = 0.0;
     if (in) {
       const SpeciesTab &S = T.sp[s];
       const double m = S.mass;
-      const Vec3 v = load_vel(A.st, g);
+      const Vec3 v = b.v;
       acc[0] += m * v.x;
       acc[1] += m * v.y;
       acc[2] += m * v.z;
@@ -3150,8 +3158,7 @@ __global__ __launch_bounds__(256) void k_load_place(PlaceArgs A) {
   const uint64_t src = A.sorted_idx[j];
   const uint64_t g = A.off[c] + (j - A.packed_start[c]);
   const uint32_t mm = A.tab->max_modes;
-  store_vel(A.st, g, A.vel[3 * src], A.vel[3 * src + 1], A.vel[3 * src + 2]);
-  A.st.sp[g] = A.sp[src];
+  store_body(A.st, g, A.vel[3 * src], A.vel[3 * src + 1], A.vel[3 * src + 2], A.sp[src]);
   for (uint32_t m = 0; m < A.st.lrow; ++m) A.st.lvl[g * A.st.lrow + m] = m < mm ? A.lvl[src * mm + m] : (uint16_t)0;
   if (A.st.rot) A.st.rot[g] = A.rot ? A.rot[src] : 0.0;
   if (A.st.px) {
@@ -3183,11 +3190,11 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs A) {
   const uint64_t to = first + i0 - A.p0;  // of particle i0
   for (uint32_t i = i0 + threadIdx.x; i < i1; i += 256) {
     const uint64_t j = to + (i - i0);
-    const Vec3 v = load_vel(A.st, base + i);
-    A.vel[3 * j] = v.x;
-    A.vel[3 * j + 1] = v.y;
-    A.vel[3 * j + 2] = v.z;
-    A.sp[j] = A.st.sp[base + i];
+    const BodyOf<double> b = load_body(A.st, base + i);
+    A.vel[3 * j] = b.v.x;
+    A.vel[3 * j + 1] = b.v.y;
+    A.vel[3 * j + 2] = b.v.z;
+    A.sp[j] = (uint8_t)b.sp;
   }
   // levels number by number, so that a wave's stores are consecutive
   const uint64_t nl = (uint64_t)(i1 - i0) * mm;
@@ -3285,7 +3292,7 @@ __global__ __launch_bounds__(256) void k_move(MoveArgs A) {
     bool mover = false, stayer = false;
     uint32_t key = 0;
     if (i < n) {
-      const Vec3 v = load_vel(A.st, g);
+      const Vec3 v = load_body(A.st, g).v;
       double vx = v.x, vy = v.y, vz = v.z;
       double x = A.st.px[g], y = A.st.py[g], z = A.st.pz[g];
       bool flip = false;
@@ -3427,12 +3434,11 @@ __global__ __launch_bounds__(256) void k_inflow_make(InflowArgs A) {
   p[F.b] = ((double)F.ib + ub) * F.db;
   v[F.a] = sigma * n1;
   v[F.b] = sigma * n2;
-  A.ins.sp[j] = (uint8_t)s;
   sample_internal(S, A.tab->theta[s], A.lev, rng, A.t_vib, A.t_trans, A.ins, j, mm);
   bool flip = false;
   const bool left =
       move_particle(p[0], p[1], p[2], v[0], v[1], v[2], tau * A.dt, A.len, A.periodic, A.open, flip);
-  store_vel(A.ins, j, v[0], v[1], v[2]);
+  store_body(A.ins, j, v[0], v[1], v[2], s);
   A.ins.px[j] = p[0];
   A.ins.py[j] = p[1];
   A.ins.pz[j] = p[2];
@@ -3476,16 +3482,10 @@ __global__ __launch_bounds__(256) void k_run_starts(const uint32_t *key, uint64_
 }
 
 __device__ __forceinline__ void copy_particle(const State &s, const State &d, uint64_t from, uint64_t to, uint32_t mm) {
-  if (s.fx) {
-    d.fx[to] = s.fx[from];
-    d.fy[to] = s.fy[from];
-    d.fz[to] = s.fz[from];
-  } else {
-    d.vx[to] = s.vx[from];
-    d.vy[to] = s.vy[from];
-    d.vz[to] = s.vz[from];
-  }
-  d.sp[to] = s.sp[from];
+  if (s.b32)
+    d.b32[to] = s.b32[from];
+  else
+    d.b64[to] = s.b64[from];
   copy_levels(s, from, d, to);
   if (s.rot) d.rot[to] = s.rot[from];
   d.px[to] = s.px[from];
@@ -3562,13 +3562,12 @@ __device__ __forceinline__ uint64_t entry_slot(const RebinArgs &A, uint64_t m) {
 // arithmetic as the move pass)
 __device__ __forceinline__ void copy_moved(const RebinArgs &A, uint64_t from, uint64_t to) {
   const State &s = A.src, &d = A.dst;
-  const Vec3 v = load_vel(s, from);
-  double vx = v.x, vy = v.y, vz = v.z;
+  const BodyOf<double> b = load_body(s, from);
+  double vx = b.v.x, vy = b.v.y, vz = b.v.z;
   double x = s.px[from], y = s.py[from], z = s.pz[from];
   bool flip = false;
   move_particle(x, y, z, vx, vy, vz, A.dt, A.len, A.periodic, A.open, flip);
-  store_vel(d, to, vx, vy, vz);
-  d.sp[to] = s.sp[from];
+  store_body(d, to, vx, vy, vz, b.sp);
   copy_levels(s, from, d, to);
   if (s.rot) d.rot[to] = s.rot[from];
   d.px[to] = x;
@@ -3630,7 +3629,7 @@ __global__ __launch_bounds__(256) void k_rebin_push(RebinArgs A) {
       copy_moved(A, HCAO_IDX(from, S.n_slots, A.err), HCAO_IDX(to, D.n_slots, A.err));
     }
   } else {
-    const bool f32 = S.fx != nullptr, rot = S.rot != nullptr;
+    const bool f32 = S.b32 != nullptr, rot = S.rot != nullptr;
     uint64_t rp[kPer][3], rv[kPer][3], rr[kPer];
     uint8_t rs[kPer];
 #pragma unroll
@@ -3642,16 +3641,19 @@ __global__ __launch_bounds__(256) void k_rebin_push(RebinArgs A) {
         rp[q][1] = reinterpret_cast<const uint64_t *>(S.py)[g];
         rp[q][2] = reinterpret_cast<const uint64_t *>(S.pz)[g];
         if (f32) {
-          rv[q][0] = reinterpret_cast<const uint32_t *>(S.fx)[g];
-          rv[q][1] = reinterpret_cast<const uint32_t *>(S.fy)[g];
-          rv[q][2] = reinterpret_cast<const uint32_t *>(S.fz)[g];
+          const uint4 b = reinterpret_cast<const uint4 *>(S.b32)[g];
+          rv[q][0] = b.x;
+          rv[q][1] = b.y;
+          rv[q][2] = b.z;
+          rs[q] = (uint8_t)b.w;
         } else {
-          rv[q][0] = reinterpret_cast<const uint64_t *>(S.vx)[g];
-          rv[q][1] = reinterpret_cast<const uint64_t *>(S.vy)[g];
-          rv[q][2] = reinterpret_cast<const uint64_t *>(S.vz)[g];
+          const Body64 b = S.b64[g];
+          rv[q][0] = (uint64_t)__double_as_longlong(b.x);
+          rv[q][1] = (uint64_t)__double_as_longlong(b.y);
+          rv[q][2] = (uint64_t)__double_as_longlong(b.z);
+          rs[q] = (uint8_t)b.sp;
         }
         rr[q] = rot ? reinterpret_cast<const uint64_t *>(S.rot)[g] : 0u;
-        rs[q] = S.sp[g];
       }
     }
     // the step's move (positions, and velocities a specular face reversed);
@@ -3745,17 +3747,13 @@ __global__ __launch_bounds__(256) void k_rebin_push(RebinArgs A) {
       reinterpret_cast<uint64_t *>(D.px)[to] = s_pos[0][i];
       reinterpret_cast<uint64_t *>(D.py)[to] = s_pos[1][i];
       reinterpret_cast<uint64_t *>(D.pz)[to] = s_pos[2][i];
-      if (f32) {
-        reinterpret_cast<uint32_t *>(D.fx)[to] = (uint32_t)s_vel[0][i];
-        reinterpret_cast<uint32_t *>(D.fy)[to] = (uint32_t)s_vel[1][i];
-        reinterpret_cast<uint32_t *>(D.fz)[to] = (uint32_t)s_vel[2][i];
-      } else {
-        reinterpret_cast<uint64_t *>(D.vx)[to] = s_vel[0][i];
-        reinterpret_cast<uint64_t *>(D.vy)[to] = s_vel[1][i];
-        reinterpret_cast<uint64_t *>(D.vz)[to] = s_vel[2][i];
-      }
+      if (f32)
+        reinterpret_cast<uint4 *>(D.b32)[to] =
+            make_uint4((uint32_t)s_vel[0][i], (uint32_t)s_vel[1][i], (uint32_t)s_vel[2][i], s_sp[i]);
+      else
+        D.b64[to] = Body64{__longlong_as_double((long long)s_vel[0][i]), __longlong_as_double((long long)s_vel[1][i]),
+                           __longlong_as_double((long long)s_vel[2][i]), s_sp[i]};
       if (rot) reinterpret_cast<uint64_t *>(D.rot)[to] = s_rot[i];
-      D.sp[to] = s_sp[i];
     }
     // level rows through LDS (over the staged positions and velocities, read
     // for the last time above), written dword by dword in output order, so
@@ -3847,7 +3845,7 @@ hipError_t launch_step(const StepArgs &a, size_t lds, int block, bool mixed, int
 // step call. Host code never passes the array's name to a kernel: it uses
 // the device address that static_scratch_address() returns for the current
 // device.
-static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticArrayBytes];
 
 hipError_t static_scratch_address(void **ptr) { return hipGetSymbolAddress(ptr, HIP_SYMBOL(scratch)); }
 
@@ -4041,7 +4039,7 @@ hipError_t launch_inflow_make(const InflowArgs &a, hipStream_t s) {
   const uint64_t n = a.n_ins;
   if (n == 0 || a.face_base[6] == 0 || a.n_species == 0) return hipSuccess;
   if (!a.tab || !a.lev || !a.count || !a.ibase || !a.mbase || !a.mkey || !a.mslot || !a.flux || !a.err ||
-      !a.ins.sp || !a.ins.lvl || !a.ins.px || !a.ins.py || !a.ins.pz || (!a.ins.vx && !a.ins.fx))
+      !a.ins.lvl || !a.ins.px || !a.ins.py || !a.ins.pz || (!a.ins.b64 && !a.ins.b32))
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_inflow_make, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();

@@ -218,9 +218,7 @@ struct hcao_ctx {
   std::vector<uint32_t> cap_host;
   std::vector<uint64_t> off_host;
   bool mixed = false;                         // fp32 velocities (mixed form)
-  DevBuf<double> vx, vy, vz, bvx, bvy, bvz;  // fp64 form
-  DevBuf<float> fx, fy, fz, bfx, bfy, bfz;   // mixed form
-  DevBuf<uint8_t> sp, bsp;
+  DevBuf<uint8_t> body, bbody;  // Body64 records (fp64 form) or Body32 (mixed form)
   DevBuf<uint16_t> lvl, blvl;
   DevBuf<double> rot, brot;  // rotational energies (only when some species has a rotor)
   // spatial mode: positions, and the re-bin's sort buffers (all slots)
@@ -243,9 +241,8 @@ struct hcao_ctx {
   DevBuf<uint64_t> in_base;
   DevBuf<unsigned long long> flux;
   uint64_t ins_cap = 0;
-  DevBuf<double> ivx, ivy, ivz, irot, ipx, ipy, ipz;
-  DevBuf<float> ifx, ify, ifz;
-  DevBuf<uint8_t> isp;
+  DevBuf<double> irot, ipx, ipy, ipz;
+  DevBuf<uint8_t> ibody;
   DevBuf<uint16_t> ilvl;
   DevBuf<uint64_t> off;
   DevBuf<uint32_t> cnt, cap;
@@ -379,13 +376,7 @@ double host_mode_energy(const SpeciesHost &s, uint32_t m, uint32_t i) {
 }
 
 void release_ins(hcao_ctx *c) {
-  c->ivx.release();
-  c->ivy.release();
-  c->ivz.release();
-  c->ifx.release();
-  c->ify.release();
-  c->ifz.release();
-  c->isp.release();
+  c->ibody.release();
   c->ilvl.release();
   c->irot.release();
   c->ipx.release();
@@ -395,21 +386,9 @@ void release_ins(hcao_ctx *c) {
 }
 
 void free_state(hcao_ctx *c) {
-  c->vx.release();
-  c->vy.release();
-  c->vz.release();
-  c->fx.release();
-  c->fy.release();
-  c->fz.release();
-  c->sp.release();
+  c->body.release();
+  c->bbody.release();
   c->lvl.release();
-  c->bvx.release();
-  c->bvy.release();
-  c->bvz.release();
-  c->bfx.release();
-  c->bfy.release();
-  c->bfz.release();
-  c->bsp.release();
   c->blvl.release();
   c->rot.release();
   c->brot.release();
@@ -462,23 +441,34 @@ uint32_t default_cap(const hcao_ctx *c, uint32_t n) {
   return n + n / 4 + 32;
 }
 
+size_t body_bytes(const hcao_ctx *c) { return c->mixed ? sizeof(Body32) : sizeof(Body64); }
+
+State state_over(const hcao_ctx *c, uint8_t *body, uint16_t *lvl, double *rot, double *px, double *py, double *pz) {
+  State s{};
+  (c->mixed ? (void *&)s.b32 : (void *&)s.b64) = body;
+  s.lvl = lvl;
+  s.rot = rot;
+  s.px = px;
+  s.py = py;
+  s.pz = pz;
+  s.lrow = level_row(c->max_modes);
+  return s;
+}
+
 // staging state of the admissions through open faces (stride ins_cap)
 State ins_state(hcao_ctx *c) {
-  State s{c->ivx.p, c->ivy.p, c->ivz.p, c->ifx.p, c->ify.p, c->ifz.p, c->isp.p, c->ilvl.p, c->irot.p,
-          c->ipx.p, c->ipy.p, c->ipz.p, level_row(c->max_modes)};
+  State s = state_over(c, c->ibody.p, c->ilvl.p, c->irot.p, c->ipx.p, c->ipy.p, c->ipz.p);
   set_slots(s, c->ins_cap);
   return s;
 }
 
 State state_of(hcao_ctx *c) {
-  State s{c->vx.p, c->vy.p, c->vz.p, c->fx.p, c->fy.p, c->fz.p, c->sp.p, c->lvl.p, c->rot.p,
-          c->px.p, c->py.p, c->pz.p, level_row(c->max_modes)};
+  State s = state_over(c, c->body.p, c->lvl.p, c->rot.p, c->px.p, c->py.p, c->pz.p);
   set_slots(s, c->total_slots);
   return s;
 }
 State staging_of(hcao_ctx *c) {
-  State s{c->bvx.p, c->bvy.p, c->bvz.p, c->bfx.p, c->bfy.p, c->bfz.p, c->bsp.p, c->blvl.p, c->brot.p,
-          c->bpx.p, c->bpy.p, c->bpz.p, level_row(c->max_modes)};
+  State s = state_over(c, c->bbody.p, c->blvl.p, c->brot.p, c->bpx.p, c->bpy.p, c->bpz.p);
   set_slots(s, c->total_slots);
   return s;
 }
@@ -488,66 +478,50 @@ CellArrays cells_of(hcao_ctx *c) {
                     c->cfg.n_cells};
 }
 
-// velocity arrays of the context's precision (three, fp64 or fp32)
-hipError_t alloc_vel(hcao_ctx *c, DevBuf<double> &x, DevBuf<double> &y, DevBuf<double> &z, DevBuf<float> &fx,
-                     DevBuf<float> &fy, DevBuf<float> &fz, uint64_t n) {
-  hipError_t e;
-  if (c->mixed) {
-    if ((e = fx.alloc(n)) != hipSuccess) return e;
-    if ((e = fy.alloc(n)) != hipSuccess) return e;
-    return fz.alloc(n);
-  }
-  if ((e = x.alloc(n)) != hipSuccess) return e;
-  if ((e = y.alloc(n)) != hipSuccess) return e;
-  return z.alloc(n);
-}
-
-// all velocity slots as fp64 (synchronous)
-hcao_status download_vel(hcao_ctx *c, std::vector<double> &vx, std::vector<double> &vy, std::vector<double> &vz) {
-  const uint64_t tot = c->total_slots;
-  vx.resize(tot);
-  vy.resize(tot);
-  vz.resize(tot);
-  if (c->mixed) {
-    std::vector<float> fx(tot), fy(tot), fz(tot);
-    HIP_TRY(c, hipMemcpyAsync(fx.data(), c->fx.p, tot * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(fy.data(), c->fy.p, tot * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(fz.data(), c->fz.p, tot * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (uint64_t i = 0; i < tot; ++i) {
-      vx[i] = fx[i];
-      vy[i] = fy[i];
-      vz[i] = fz[i];
-    }
-    return HCAO_OK;
-  }
-  HIP_TRY(c, hipMemcpyAsync(vx.data(), c->vx.p, tot * 8, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(vy.data(), c->vy.p, tot * 8, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(vz.data(), c->vz.p, tot * 8, hipMemcpyDeviceToHost, c->stream));
+// velocities (as fp64) and species of n slots from slot `first` on
+// (synchronous)
+hcao_status download_bodies(hcao_ctx *c, uint64_t first, uint64_t n, double *vx, double *vy, double *vz, uint8_t *sp) {
+  const size_t b = body_bytes(c);
+  std::vector<uint8_t> raw(n * b);
+  HIP_TRY(c, hipMemcpyAsync(raw.data(), c->body.p + first * b, n * b, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  for (uint64_t i = 0; i < n; ++i) {
+    if (c->mixed) {
+      Body32 x;
+      std::memcpy(&x, raw.data() + i * b, b);
+      vx[i] = x.x;
+      vy[i] = x.y;
+      vz[i] = x.z;
+      sp[i] = (uint8_t)x.sp;
+    } else {
+      Body64 x;
+      std::memcpy(&x, raw.data() + i * b, b);
+      vx[i] = x.x;
+      vy[i] = x.y;
+      vz[i] = x.z;
+      sp[i] = (uint8_t)x.sp;
+    }
+  }
   return HCAO_OK;
 }
 
-// all velocity slots from fp64 (rounded to fp32 in the mixed form; synchronous)
-hcao_status upload_vel(hcao_ctx *c, const std::vector<double> &vx, const std::vector<double> &vy,
-                       const std::vector<double> &vz) {
+// all slots from fp64 velocities (rounded to fp32 in the mixed form) and
+// species (synchronous)
+hcao_status upload_bodies(hcao_ctx *c, const std::vector<double> &vx, const std::vector<double> &vy,
+                          const std::vector<double> &vz, const std::vector<uint8_t> &sp) {
   const uint64_t tot = c->total_slots;
-  if (c->mixed) {
-    std::vector<float> fx(tot), fy(tot), fz(tot);
-    for (uint64_t i = 0; i < tot; ++i) {
-      fx[i] = (float)vx[i];
-      fy[i] = (float)vy[i];
-      fz[i] = (float)vz[i];
+  const size_t b = body_bytes(c);
+  std::vector<uint8_t> raw(tot * b);
+  for (uint64_t i = 0; i < tot; ++i) {
+    if (c->mixed) {
+      const Body32 x{(float)vx[i], (float)vy[i], (float)vz[i], sp[i]};
+      std::memcpy(raw.data() + i * b, &x, b);
+    } else {
+      const Body64 x{vx[i], vy[i], vz[i], sp[i]};
+      std::memcpy(raw.data() + i * b, &x, b);
     }
-    HIP_TRY(c, hipMemcpyAsync(c->fx.p, fx.data(), tot * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->fy.p, fy.data(), tot * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(c->fz.p, fz.data(), tot * 4, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return HCAO_OK;
   }
-  HIP_TRY(c, hipMemcpyAsync(c->vx.p, vx.data(), tot * 8, hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->vy.p, vy.data(), tot * 8, hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->vz.p, vz.data(), tot * 8, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(c->body.p, raw.data(), raw.size(), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return HCAO_OK;
 }
@@ -686,8 +660,7 @@ hipError_t grow_ins(hcao_ctx *c, uint64_t n) {
   const uint32_t mm = c->max_modes ? c->max_modes : 1;
   release_ins(c);
   hipError_t e;
-  if ((e = alloc_vel(c, c->ivx, c->ivy, c->ivz, c->ifx, c->ify, c->ifz, cap)) != hipSuccess) return e;
-  if ((e = c->isp.alloc(cap)) != hipSuccess) return e;
+  if ((e = c->ibody.alloc(cap * body_bytes(c))) != hipSuccess) return e;
   if ((e = c->ilvl.alloc(cap * level_row(mm))) != hipSuccess) return e;
   if (c->tab.has_rot && (e = c->irot.alloc(cap)) != hipSuccess) return e;
   if ((e = c->ipx.alloc(cap)) != hipSuccess) return e;
@@ -706,7 +679,7 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   // them cost a fifth of a load of a million particles)
   uint64_t want = 0;
   for (uint32_t i = 0; i < nc; ++i) want += caps ? (*caps)[i] : default_cap(c, counts[i]);
-  if (want != c->total_slots || !c->sp.p) free_state(c);
+  if (want != c->total_slots || !c->body.p) free_state(c);
   c->loaded = false;
   c->cap_host.assign(nc, 0);
   c->off_host.assign(nc + 1, 0);
@@ -723,8 +696,7 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   // the spatial re-bin keeps old slots as 32-bit indices
   if (c->spatial && tot > 0xFFFFFFFFull) return fail(c, HCAO_EINVAL, "spatial mode holds at most 2^32 - 1 slots");
   const uint32_t mm = c->max_modes ? c->max_modes : 1;
-  HIP_TRY(c, alloc_vel(c, c->vx, c->vy, c->vz, c->fx, c->fy, c->fz, tot));
-  HIP_TRY(c, c->sp.alloc(tot));
+  HIP_TRY(c, c->body.alloc(tot * body_bytes(c)));
   HIP_TRY(c, c->lvl.alloc(tot * level_row(mm)));
   if (c->tab.has_rot) {
     HIP_TRY(c, c->rot.alloc(tot));
@@ -774,8 +746,7 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   HIP_TRY(c, hipMemcpyAsync(c->d_weight.p, c->weight.data(), nc * sizeof(double), hipMemcpyHostToDevice,
                             c->stream));
   // products staging (indexed like the state)
-  HIP_TRY(c, alloc_vel(c, c->bvx, c->bvy, c->bvz, c->bfx, c->bfy, c->bfz, tot));
-  HIP_TRY(c, c->bsp.alloc(tot));
+  HIP_TRY(c, c->bbody.alloc(tot * body_bytes(c)));
   HIP_TRY(c, c->blvl.alloc(tot * level_row(mm)));
   if (hcao_status st = build_groups(c)) return st;
   HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1666,13 +1637,7 @@ hcao_status move_rebin(hcao_ctx *c, double dt, uint32_t step, hipStream_t s) {
   r.sidx = in_tmp ? c->mv_sidx_tmp.p : c->mv_sidx.p;
   r.slot = in_tmp ? c->mv_sidx.p : c->mv_sidx_tmp.p;  // the sort's other index buffer is free now
   HIP_TRY(c, launch_rebin_place(r, s));
-  std::swap(c->vx, c->bvx);
-  std::swap(c->vy, c->bvy);
-  std::swap(c->vz, c->bvz);
-  std::swap(c->fx, c->bfx);
-  std::swap(c->fy, c->bfy);
-  std::swap(c->fz, c->bfz);
-  std::swap(c->sp, c->bsp);
+  std::swap(c->body, c->bbody);
   std::swap(c->lvl, c->blvl);
   std::swap(c->rot, c->brot);
   std::swap(c->px, c->bpx);
@@ -1697,37 +1662,32 @@ struct StepScratch {
 
 // Carves the allocation-free step's scratch out of the fixed array at base
 // (256-byte aligned pieces, products staged per work entry); returns the
-// bytes it needs.
+// bytes it needs by the count that the limit is on.
 uint64_t static_layout(const hcao_ctx *c, unsigned char *base, StepScratch &out) {
   const uint64_t w = c->work_entries;
   const uint32_t mm = c->max_modes ? c->max_modes : 1;
-  uint64_t at = 0;
-  auto take = [&](uint64_t bytes) {
+  uint64_t at = 0, need = 0;
+  auto pad = [](uint64_t bytes) { return (bytes + 255) & ~uint64_t(255); };
+  auto take = [&](uint64_t bytes, uint64_t counted) {
     unsigned char *p = base + at;
-    at += (bytes + 255) & ~uint64_t(255);
+    at += pad(bytes);
+    need += counted;
     return p;
   };
+  auto piece = [&](uint64_t bytes) { return take(bytes, pad(bytes)); };
   out = StepScratch{};
-  out.work = reinterpret_cast<uint32_t *>(take((uint64_t)kWorkWords * w * sizeof(uint32_t)));
-  out.bflag = take(w);
-  if (c->mixed) out.wdef = reinterpret_cast<double *>(take(w * sizeof(double)));
-  if (c->tab.has_recomb) out.tdelta = reinterpret_cast<double *>(take(5 * w * sizeof(double)));
-  State &b = out.born;
-  if (c->mixed) {
-    b.fx = reinterpret_cast<float *>(take(w * sizeof(float)));
-    b.fy = reinterpret_cast<float *>(take(w * sizeof(float)));
-    b.fz = reinterpret_cast<float *>(take(w * sizeof(float)));
-  } else {
-    b.vx = reinterpret_cast<double *>(take(w * sizeof(double)));
-    b.vy = reinterpret_cast<double *>(take(w * sizeof(double)));
-    b.vz = reinterpret_cast<double *>(take(w * sizeof(double)));
-  }
-  b.sp = take(w);
-  set_slots(b, w);
-  b.lrow = level_row(mm);
-  b.lvl = reinterpret_cast<uint16_t *>(take(w * b.lrow * sizeof(uint16_t)));
-  if (c->tab.has_rot) b.rot = reinterpret_cast<double *>(take(w * sizeof(double)));
-  return at;
+  out.work = reinterpret_cast<uint32_t *>(piece((uint64_t)kWorkWords * w * sizeof(uint32_t)));
+  out.bflag = piece(w);
+  if (c->mixed) out.wdef = reinterpret_cast<double *>(piece(w * sizeof(double)));
+  if (c->tab.has_recomb) out.tdelta = reinterpret_cast<double *>(piece(5 * w * sizeof(double)));
+  // a staged product counts as three velocity numbers and a species byte
+  unsigned char *body = take(w * body_bytes(c), 3 * pad(w * (c->mixed ? sizeof(float) : sizeof(double))) + pad(w));
+  unsigned char *lvl = piece(w * level_row(mm) * sizeof(uint16_t));
+  unsigned char *rot = c->tab.has_rot ? piece(w * sizeof(double)) : nullptr;
+  out.born = state_over(c, body, reinterpret_cast<uint16_t *>(lvl), reinterpret_cast<double *>(rot), nullptr, nullptr,
+                        nullptr);
+  set_slots(out.born, w);
+  return need <= kStaticScratchBytes && at <= kStaticArrayBytes ? need : std::max(need, kStaticScratchBytes + 1);
 }
 
 hcao_status issue_steps(hcao_ctx *c, double dt, uint32_t n_steps, uint32_t base, uint32_t *step_dev,
@@ -1915,9 +1875,8 @@ namespace {
 
 // Device copy of everything a step changes, for the autotuner's trials.
 struct Snapshot {
-  DevBuf<double> vx, vy, vz, sgmax, rem, defect, rot, tsum;
-  DevBuf<float> fx, fy, fz;
-  DevBuf<uint8_t> sp;
+  DevBuf<double> sgmax, rem, defect, rot, tsum;
+  DevBuf<uint8_t> body;
   DevBuf<uint16_t> lvl;
   DevBuf<uint32_t> cnt, err;
   DevBuf<unsigned long long> ctr;
@@ -1928,18 +1887,12 @@ struct Snapshot {
   // the copy is freed when it goes out of scope (early returns included);
   // hipFree waits for work still using it
   ~Snapshot() {
-    vx.release();
-    vy.release();
-    vz.release();
+    body.release();
     sgmax.release();
     rem.release();
     defect.release();
     rot.release();
     tsum.release();
-    fx.release();
-    fy.release();
-    fz.release();
-    sp.release();
     lvl.release();
     cnt.release();
     err.release();
@@ -1961,13 +1914,7 @@ hipError_t dcopy(DevBuf<T> &dst, const DevBuf<T> &src, bool alloc, hipStream_t s
 hcao_status snapshot(hcao_ctx *c, Snapshot &S, bool take) {
   hipStream_t st = c->stream;
 #define SNAP(f) HIP_TRY(c, take ? dcopy(S.f, c->f, true, st) : dcopy(c->f, S.f, false, st))
-  SNAP(vx);
-  SNAP(vy);
-  SNAP(vz);
-  SNAP(fx);
-  SNAP(fy);
-  SNAP(fz);
-  SNAP(sp);
+  SNAP(body);
   SNAP(rot);
   SNAP(lvl);
   SNAP(cnt);
@@ -2149,19 +2096,7 @@ hcao_status hcao_read_cell_particles(hcao_ctx *c, uint32_t cell, uint32_t max_n,
   std::vector<double> v(3 * (size_t)k);
   const uint32_t lr = level_row(c->max_modes);
   std::vector<uint16_t> lv((size_t)k * lr);
-  if (c->mixed) {
-    std::vector<float> f(3 * (size_t)k);
-    HIP_TRY(c, hipMemcpyAsync(f.data(), c->fx.p + b, k * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(f.data() + k, c->fy.p + b, k * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(f.data() + 2 * (size_t)k, c->fz.p + b, k * 4, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    for (size_t i = 0; i < v.size(); ++i) v[i] = f[i];
-  } else {
-    HIP_TRY(c, hipMemcpyAsync(v.data(), c->vx.p + b, k * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(v.data() + k, c->vy.p + b, k * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(v.data() + 2 * (size_t)k, c->vz.p + b, k * 8, hipMemcpyDeviceToHost, c->stream));
-  }
-  HIP_TRY(c, hipMemcpyAsync(species, c->sp.p + b, k, hipMemcpyDeviceToHost, c->stream));
+  if (hcao_status s = download_bodies(c, b, k, v.data(), v.data() + k, v.data() + 2 * (size_t)k, species)) return s;
   HIP_TRY(c, hipMemcpyAsync(lv.data(), c->lvl.p + b * lr, (size_t)k * lr * 2, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   for (uint32_t i = 0; i < k; ++i) {
@@ -2536,14 +2471,13 @@ hcao_status hcao_save(hcao_ctx *c, const char *path) {
   if (hcao_status s = hcao_sync(c)) return s;
   const uint64_t tot = c->total_slots;
   const uint32_t nc = c->cfg.n_cells, mm = c->max_modes ? c->max_modes : 1;
-  std::vector<double> vx, vy, vz, sg(nc), rm(nc), df(nc), ts(c->tsum.p ? 5 * (size_t)nc : 0);
+  std::vector<double> vx(tot), vy(tot), vz(tot), sg(nc), rm(nc), df(nc), ts(c->tsum.p ? 5 * (size_t)nc : 0);
   std::vector<uint8_t> sp(tot);
   std::vector<uint16_t> lv(tot * mm);
   std::vector<uint32_t> cnt(nc);
   std::vector<unsigned long long> ctr((size_t)nc * kNumCtr);
-  if (hcao_status s = download_vel(c, vx, vy, vz)) return s;
+  if (hcao_status s = download_bodies(c, 0, tot, vx.data(), vy.data(), vz.data(), sp.data())) return s;
   HIP_TRY(c, hipMemcpy(df.data(), c->defect.p, nc * 8, hipMemcpyDeviceToHost));
-  HIP_TRY(c, hipMemcpy(sp.data(), c->sp.p, tot, hipMemcpyDeviceToHost));
   {
     // the file holds n x max_modes rows; the device rows are level_row long
     const uint32_t lr = level_row(c->max_modes);
@@ -2651,9 +2585,8 @@ hcao_status hcao_restore(hcao_ctx *c, const char *path) {
   for (uint32_t v : capv) t2 += v;
   if (t2 != tot) return fail(c, HCAO_EINVAL, "checkpoint capacities inconsistent");
   if (hcao_status st = alloc_state(c, cnt, &capv)) return st;
-  if (hcao_status s = upload_vel(c, vx, vy, vz)) return s;
+  if (hcao_status s = upload_bodies(c, vx, vy, vz, sp)) return s;
   HIP_TRY(c, hipMemcpy(c->defect.p, df.data(), nc * 8, hipMemcpyHostToDevice));
-  HIP_TRY(c, hipMemcpy(c->sp.p, sp.data(), tot, hipMemcpyHostToDevice));
   {
     const uint32_t lr = level_row(c->max_modes);
     std::vector<uint16_t> rows(tot * lr, 0);

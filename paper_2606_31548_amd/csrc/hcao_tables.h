@@ -106,6 +106,10 @@ constexpr uint32_t kExactNBeta = 960u;  // beta grid (1 + (j mod 16) / 16) 2^(40
 
 // bytes of the fixed device array behind the allocation-free step
 constexpr uint64_t kStaticScratchBytes = HCAO_STATIC_SCRATCH_BYTES;
+// The limit counts a staged product's velocity and species at their own size;
+// the records that hold them are up to 7 bytes larger (for at most 128 MiB / 62
+// entries).
+constexpr uint64_t kStaticArrayBytes = kStaticScratchBytes + (16u << 20);
 
 constexpr uint32_t kThermoNodes = 512;  // mean energies per species over log T, 1 .. 1e6 K
 constexpr uint32_t kRecNodes = 1024;
@@ -123,17 +127,25 @@ struct Tables {
   double theta[kMaxSpecies][kMaxModes];  // bends: Theta (thermal initial states)
 };
 
-// Particle state in HBM: structure of arrays, cell-major segments with
-// per-cell slot capacity. Slot i of cell c lives at index off[c] + i. The
+// Particle state in HBM, cell-major segments with per-cell slot capacity: slot
+// i of cell c lives at index off[c] + i. Velocity and species are one record
+// (16 bytes in the mixed form, 32 in the fp64 form: one access, one line, for
+// what every candidate test gathers; as separate arrays they were four). The
 // quantum numbers of a slot are one row of lrow uint16 (lrow = max_modes
-// rounded up to even, so rows are dword aligned): mode m at lvl[index *
-// lrow + m], modes the species does not have (and the padding) 0.
-// Velocities are fp64 (vx, vy, vz) in the fp64 form and fp32 (fx, fy, fz)
-// in the mixed form; the other set is null.
+// rounded up to even, so rows are dword aligned): mode m at lvl[index * lrow +
+// m], modes the species does not have (and the padding) 0. Positions and
+// rotational energies are arrays of their own.
+struct alignas(16) Body32 {
+  float x, y, z;
+  uint32_t sp;
+};
+struct alignas(16) Body64 {
+  double x, y, z;
+  uint64_t sp;
+};
 struct State {
-  double *vx, *vy, *vz;
-  float *fx, *fy, *fz;
-  uint8_t *sp;
+  Body64 *b64;      // fp64 form, else null
+  Body32 *b32;      // mixed form, else null
   uint16_t *lvl;
   double *rot;      // rotational energy [J]; null when no species has a rotor
   double *px, *py, *pz;  // positions [m]; null outside the spatial mode
