@@ -173,6 +173,13 @@ struct RngT {
     else
       return (float)(uint32_t)(w >> 32) * 0x1p-32f;
   }
+  // the next uniform's word
+  __device__ __forceinline__ uint64_t next_word() {
+    if constexpr (MIX)
+      return next32();
+    else
+      return next64();
+  }
   // passes over the next n uniforms of this form without using them (blocks
   // wholly passed over are not computed)
   __device__ __forceinline__ void skip(uint32_t n) {
@@ -778,37 +785,45 @@ __device__ __forceinline__ bool below_exp_neg(double u, double a) {
   return u < dexp(-a);
 }
 
-// Exact sampler, level proposal of one mode: the geometric level
-// floor(-ln(1 - u) / c) with c = beta * slope. Returns false when it lies
-// above top (the caller draws again). The fp64 form decides floor() as the
-// fp64 expression -dlog(1 - u) / c does: an fp32 estimate far enough from
-// an integer settles it, else the fp64 expression is evaluated.
+// Exact sampler, level proposal of one mode in the form's own arithmetic: the
+// geometric level floor(-ln(1 - u) / c) with c = beta * slope. Returns false
+// when it lies above top (the caller draws again).
 template <bool MIX>
-__device__ __forceinline__ bool geometric_level(RngT<MIX> &rng, double c, uint32_t top, uint32_t &i) {
-  const float ftop1 = (float)top + 1.0f;
+__device__ __forceinline__ bool geometric_exact(double u, double c, uint32_t top, uint32_t &i) {
   if constexpr (MIX) {
-    const float u = rng.uniform_f();
-    const float x = -__builtin_amdgcn_logf(1.0f - u) * (0.69314718f / (float)c);
-    if (!(x < ftop1)) return false;
+    const float x = -__builtin_amdgcn_logf(1.0f - (float)u) * (0.69314718f / (float)c);
+    if (!(x < (float)top + 1.0f)) return false;
     i = (uint32_t)floorf(x);
     return true;
   } else {
-    const double u = rng.uniform();
-    const double v = 1.0 - u;
-    const float k = (float)(0.6931471805599453 / c);
-    const float xe = -__builtin_amdgcn_logf((float)v) * k;
-    const float band = 1e-5f * (xe + 1.0f) + 1e-6f * k;
-    if (xe >= ftop1 + band) return false;
-    const float fl = floorf(xe);
-    if (xe - fl > band && (fl + 1.0f) - xe > band) {
-      i = (uint32_t)fl;
-      return true;
-    }
-    const double x = -dlog(v) / c;
+    const double x = -dlog(1.0 - u) / c;
     if (!(x < (double)top + 1.0)) return false;
     i = (uint32_t)floor(x);
     return true;
   }
+}
+// The same from a single-precision estimate with k = ln 2 / c (to 1e-6): clear
+// is set when it settles the level, which is then the one geometric_exact
+// gives; ok tells whether the level is at most top.
+template <bool MIX>
+__device__ __forceinline__ bool geometric_estimate(uint64_t w, float k, uint32_t top, uint32_t &i, bool &clear) {
+  float v;
+  bool fine = true;
+  if constexpr (MIX) {
+    v = 1.0f - RngT<MIX>::single_of(w);
+  } else {
+    const uint32_t h = ~(uint32_t)(w >> 32);
+    fine = h >= (1u << 21);  // 1 - u to 5e-7
+    v = (float)h * 0x1p-32f;
+  }
+  const float ftop1 = (float)top + 1.0f;
+  const float x = -__builtin_amdgcn_logf(v) * k;
+  const float band = 1e-5f * (x + 1.0f) + 2e-6f * k;
+  const float fl = floorf(x);
+  i = (uint32_t)fminf(fl, (float)top);
+  const bool above = x >= ftop1 + band;
+  clear = fine && (above || (x - fl > band && (fl + 1.0f) - x > band && x < ftop1 - band));
+  return !above;
 }
 
 // Exact sampler, slope of the geometric proposal of mode m on 0..top: the
@@ -900,31 +915,70 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
     if (beta * ep < q) beta = q / ep;
     uint16_t *tops = C.scr + C.lane;
     uint16_t *cand = C.scr + (size_t)nm * C.block + C.lane;
+    const double *lev = C.T.lev;
     for (uint32_t m = 0; m < nm; ++m)
-      tops[m * C.block] = (uint16_t)mode_top(S, C.T.lev, m, ep + mode_energy(S, C.T.lev, m, 0));
+      tops[m * C.block] = (uint16_t)mode_top(S, lev, m, ep + mode_energy(S, lev, m, 0));
+    // Levels, thinning and acceptance are decided from single-precision
+    // estimates; only a decision near its boundary evaluates the form's own
+    // expressions (each mode's draw took three fp64 divisions before).
+    const float bf = (float)beta, kb = 0.69314718f * __builtin_amdgcn_rcpf(bf);
+    const float rq = __builtin_amdgcn_rcpf((float)q), qf = (float)q;
     for (;;) {
       double sum = 0.0;
       for (uint32_t m = 0; m < nm && !capped; ++m) {
         const uint32_t top = tops[m * C.block];
+        const bool bend = m < S.n_bend;
+        const double kt = S.kt[m];
+        const double *L = lev + S.lev_off[m];  // a bend reads level 0 of the array and ignores it
+        const double l0 = L[0];
+        const double e0 = bend ? 0.5 * kt : l0;
         uint32_t i = 0;
+        double de = 0.0;  // E_i - E_0
         if (top > 0) {
-          const double sl = exact_slope(S, C.T.lev, m, top);
-          const double c = beta * sl;
+          // the slope to 1e-6: 1 / slope of a bend is tabulated, a stretch's
+          // chord is divided in single precision
+          const bool chord = !bend && ((S.concave >> m) & 1u);
+          float slf = 0.0f, inv = S.inv[m];
+          if (!bend) {
+            slf = chord ? (float)(L[top] - l0) * __builtin_amdgcn_rcpf((float)top) : (float)exact_slope(S, lev, m, top);
+            inv = __builtin_amdgcn_rcpf(slf);
+          }
+          const float k = kb * inv;
           for (;;) {
             ++trials;
             if (trials >= kMaxTrials) {
               capped = true;
               break;
             }
-            if (!geometric_level<MIX>(rng, c, top, i)) continue;
-            if (m >= S.n_bend && i > 0) {
-              const double d = (mode_energy(S, C.T.lev, m, i) - mode_energy(S, C.T.lev, m, 0)) - sl * (double)i;
-              if (d > 0.0) {
-                bool keep;
-                if constexpr (MIX)
-                  keep = rng.uniform_f() < __builtin_amdgcn_exp2f(-(float)(beta * d) * 1.44269504f);
-                else
-                  keep = below_exp_neg(rng.uniform(), beta * d);
+            const uint64_t w = rng.next_word();
+            bool clear;
+            bool ok = geometric_estimate<MIX>(w, k, top, i, clear);
+            if (!clear)
+              ok = geometric_exact<MIX>(RngT<MIX>::exact_of(w), beta * exact_slope(S, lev, m, top), top, i);
+            if (!ok) continue;
+            const double li = L[bend ? 0u : i];
+            de = (bend ? ((double)i + 0.5) * kt : li) - e0;
+            if (!bend && i > 0) {
+              const float def = (float)de;
+              float df = def - slf * (float)i;
+              const bool sure = fabsf(df) > 1e-5f * def;
+              double d = 0.0;
+              if (!sure) {
+                d = de - exact_slope(S, lev, m, top) * (double)i;
+                df = d > 0.0 ? 1.0f : -1.0f;
+              }
+              if (df > 0.0f) {
+                const uint64_t w2 = rng.next_word();
+                const float est = __builtin_amdgcn_exp2f(-(bf * df) * 1.44269504f);
+                const float u2 = RngT<MIX>::single_of(w2);
+                bool keep = u2 < est;
+                if (!sure || fabsf(u2 - est) <= 1e-4f * est + 1e-6f) {
+                  d = de - exact_slope(S, lev, m, top) * (double)i;
+                  if constexpr (MIX)
+                    keep = u2 < __builtin_amdgcn_exp2f(-(float)(beta * d) * 1.44269504f);
+                  else
+                    keep = below_exp_neg(RngT<MIX>::exact_of(w2), beta * d);
+                }
                 if (!keep) continue;
               }
             }
@@ -932,28 +986,34 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
           }
         }
         cand[m * C.block] = (uint16_t)i;
-        sum = sum + (mode_energy(S, C.T.lev, m, i) - mode_energy(S, C.T.lev, m, 0));
+        sum = sum + (capped ? mode_energy(S, lev, m, i) - e0 : de);
       }
       if (capped) break;
       ++trials;
       if (sum < ep) {
-        const double y = (beta * (ep - sum)) / q;
-        bool ok;
-        if constexpr (MIX) {
-          const float yf = (float)y, qf = (float)q;
-          const float ex = qf * ((__builtin_amdgcn_logf(yf) * 0.69314718f + 1.0f) - yf);
-          ok = rng.uniform_f() < __builtin_amdgcn_exp2f(ex * 1.44269504f);
-        } else {
-          const double ua = rng.uniform();
-          const float yf = (float)y, qf = (float)q;
-          const float ex = qf * ((__builtin_amdgcn_logf(yf) * 0.69314718f + 1.0f) - yf);
-          const double est = (double)__builtin_amdgcn_exp2f(ex * 1.44269504f);
-          if (ua < est * (1.0 - kFilter))
-            ok = true;
-          else if (ua > est * (1.0 + kFilter))
-            ok = false;
-          else
-            ok = ua < dexp(q * ((dlog(y) + 1.0) - y));
+        const uint64_t w = rng.next_word();
+        const float yf = (bf * (float)(ep - sum)) * rq;
+        const float ex = qf * ((__builtin_amdgcn_logf(yf) * 0.69314718f + 1.0f) - yf);
+        const float est = __builtin_amdgcn_exp2f(ex * 1.44269504f);
+        const float ua = RngT<MIX>::single_of(w);
+        bool ok = ua < est;
+        // (the estimate of ex is within 2e-6 (1 + |ex|) of the exact one)
+        if (!(fabsf(ua - est) > (1e-5f + 4e-6f * fabsf(ex)) * est + 1e-6f)) {
+          const double y = (beta * (ep - sum)) / q;
+          const float y2 = (float)y;
+          const float ex2 = qf * ((__builtin_amdgcn_logf(y2) * 0.69314718f + 1.0f) - y2);
+          if constexpr (MIX) {
+            ok = ua < __builtin_amdgcn_exp2f(ex2 * 1.44269504f);
+          } else {
+            const double u = RngT<MIX>::exact_of(w);
+            const double est2 = (double)__builtin_amdgcn_exp2f(ex2 * 1.44269504f);
+            if (u < est2 * (1.0 - kFilter))
+              ok = true;
+            else if (u > est2 * (1.0 + kFilter))
+              ok = false;
+            else
+              ok = u < dexp(q * ((dlog(y) + 1.0) - y));
+          }
         }
         if (ok) {
           double ev = 0.0;
@@ -2567,11 +2627,20 @@ __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const doubl
     uint32_t l = 0;
     if (m < S.n_modes) {
       if (m < S.n_bend) {
+        // floor(-ln(1 - u) T / Theta): a single-precision estimate settles it
+        // unless it lies near an integer
         const double r = 1.0 - rng.uniform();
-        const double lg = -dlog(r);
-        double fi = floor(lg * (tv / theta[m]));
-        fi = fi > 65535.0 ? 65535.0 : fi;
-        l = (uint32_t)fi;
+        const double ratio = tv / theta[m];
+        const float k = (float)(ratio * 0.6931471805599453), x = -__builtin_amdgcn_logf((float)r) * k;
+        const float fl = floorf(x), band = 1e-5f * (x + 1.0f) + 1e-6f * k;
+        if (x - fl > band && (fl + 1.0f) - x > band && fl < 65000.0f) {
+          l = (uint32_t)fl;
+        } else {
+          const double lg = -dlog(r);
+          double fi = floor(lg * ratio);
+          fi = fi > 65535.0 ? 65535.0 : fi;
+          l = (uint32_t)fi;
+        }
       } else {
         const uint32_t top = S.idiss[m];
         const double *L = lev + S.lev_off[m];
@@ -2582,7 +2651,7 @@ __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const doubl
           j = j > top ? top : j;
           const double u2 = rng.uniform();
           const double xx = (L[j] - L[0]) / kt;
-          if (u2 < dexp(-xx)) {
+          if (below_exp_neg(u2, xx)) {
             l = j;
             break;
           }
@@ -2979,62 +3048,75 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_hist(const uint32_t *keys, 
   for (uint32_t b = threadIdx.x; b < bins; b += kSortBlock) hist[(uint64_t)b * n_tiles + blockIdx.x] = s_h[b];
 }
 
-// Multi-block exclusive scan of u32 into u64: each 1024-thread block scans
-// a chunk of kScanChunk entries (16 per thread) and leaves its total in
-// bsum; one block then scans the totals; a third pass adds each chunk's
-// offset. Integer sums, so the result does not depend on the split.
-constexpr int kScanPer = 16;
-constexpr uint64_t kScanChunk = 1024 * kScanPer;
+// Multi-block exclusive scan of u32 into u64: each 256-thread block scans a
+// chunk of kScanChunk entries (four neighbours per thread and round, scanned by
+// wave shuffles) and leaves its total in bsum; a second pass adds the totals of
+// the chunks before. Integer sums, so the result does not depend on the split.
+// (A block of 1,024 threads with 16 neighbours each, two barriers per doubling
+// and a launch of its own for the totals took 26 us for the smallest scan.)
+constexpr int kScanRounds = 4;
+constexpr uint64_t kScanChunk = 256 * 4 * kScanRounds;
 
-__global__ __launch_bounds__(1024) void k_scan_chunk(const uint32_t *in, uint64_t *out, uint64_t n, uint64_t *bsum) {
-  __shared__ uint64_t s_part[1024];
-  const uint64_t b0 = (uint64_t)blockIdx.x * kScanChunk + (uint64_t)threadIdx.x * kScanPer;
-  uint64_t sum = 0;
-  for (int k = 0; k < kScanPer; ++k)
-    if (b0 + k < n) sum += in[b0 + k];
-  s_part[threadIdx.x] = sum;
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {
-    const uint64_t v = (int)threadIdx.x >= d ? s_part[threadIdx.x - d] : 0;
-    __syncthreads();
-    s_part[threadIdx.x] += v;
-    __syncthreads();
+__device__ __forceinline__ uint64_t wave_inclusive(uint64_t v, uint32_t lane) {
+  for (uint32_t d = 1; d < 64; d <<= 1) {
+    const uint64_t o = __shfl_up(v, d);
+    if (lane >= d) v += o;
   }
-  uint64_t acc = s_part[threadIdx.x] - sum;
-  for (int k = 0; k < kScanPer; ++k)
-    if (b0 + k < n) {
-      out[b0 + k] = acc;
-      acc += in[b0 + k];
-    }
-  if (threadIdx.x == 1023) bsum[blockIdx.x] = s_part[1023];
+  return v;
 }
 
-__global__ __launch_bounds__(1024) void k_scan_top(uint64_t *bsum, uint64_t nb) {
-  __shared__ uint64_t s_part[1024];
-  const uint64_t b0 = (uint64_t)threadIdx.x * kScanPer;
-  uint64_t sum = 0;
-  for (int k = 0; k < kScanPer; ++k)
-    if (b0 + k < nb) sum += bsum[b0 + k];
-  s_part[threadIdx.x] = sum;
-  __syncthreads();
-  for (int d = 1; d < 1024; d <<= 1) {
-    const uint64_t v = (int)threadIdx.x >= d ? s_part[threadIdx.x - d] : 0;
-    __syncthreads();
-    s_part[threadIdx.x] += v;
-    __syncthreads();
+__global__ __launch_bounds__(256) void k_scan_chunk(const uint32_t *in, uint64_t *out, uint64_t n, uint64_t *bsum) {
+  __shared__ uint64_t s_wave[kScanRounds][4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+  const uint64_t b0 = (uint64_t)blockIdx.x * kScanChunk + 4 * tid;
+  uint32_t x[kScanRounds][4];
+  uint64_t sum[kScanRounds], inc[kScanRounds];
+#pragma unroll
+  for (int r = 0; r < kScanRounds; ++r) {
+    const uint64_t i = b0 + 1024u * r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[r][k] = i + k < n ? in[i + k] : 0u;
+    sum[r] = ((uint64_t)x[r][0] + x[r][1]) + ((uint64_t)x[r][2] + x[r][3]);
   }
-  uint64_t acc = s_part[threadIdx.x] - sum;
-  for (int k = 0; k < kScanPer; ++k)
-    if (b0 + k < nb) {
-      const uint64_t v = bsum[b0 + k];
-      bsum[b0 + k] = acc;
-      acc += v;
+#pragma unroll
+  for (int r = 0; r < kScanRounds; ++r) {
+    inc[r] = wave_inclusive(sum[r], lane);
+    if (lane == 63) s_wave[r][wave] = inc[r];
+  }
+  __syncthreads();
+  uint64_t run = 0;
+#pragma unroll
+  for (int r = 0; r < kScanRounds; ++r) {
+    uint64_t acc = run;
+#pragma unroll
+    for (uint32_t w = 0; w < 4; ++w) {
+      const uint64_t t = s_wave[r][w];
+      if (w < wave) acc += t;
+      run += t;
     }
+    acc += inc[r] - sum[r];
+    const uint64_t i = b0 + 1024u * r;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (i + k < n) out[i + k] = acc;
+      acc += x[r][k];
+    }
+  }
+  if (tid == 0) bsum[blockIdx.x] = run;
 }
 
+// adds the totals of the earlier chunks to every chunk but the first
 __global__ __launch_bounds__(256) void k_scan_add(uint64_t *out, uint64_t n, const uint64_t *bsum) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) out[i] += bsum[i / kScanChunk];
+  __shared__ uint64_t s_wave[4];
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, chunk = blockIdx.x + 1;
+  uint64_t v = 0;
+  for (uint32_t b = tid; b < chunk; b += 256) v += bsum[b];
+  for (int d = 32; d > 0; d >>= 1) v += __shfl_down(v, d);
+  if (lane == 0) s_wave[tid >> 6] = v;
+  __syncthreads();
+  v = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
+  const uint64_t b0 = (uint64_t)chunk * kScanChunk;
+  for (uint64_t i = b0 + tid; i < b0 + kScanChunk && i < n; i += 256) out[i] += v;
 }
 
 __global__ __launch_bounds__(kSortBlock) void k_sort_scatter(const uint32_t *keys_in, const uint32_t *idx_in,
@@ -3057,7 +3139,7 @@ __global__ __launch_bounds__(kSortBlock) void k_sort_scatter(const uint32_t *key
   for (int it = 0; it < kSortItems; ++it) {
     const uint64_t i = t0 + (uint64_t)it * kSortBlock + tid;
     kr[it] = i < n ? keys_in[i] : 0u;
-    ir[it] = i < n ? idx_in[i] : 0u;
+    ir[it] = idx_in ? (i < n ? idx_in[i] : 0u) : (uint32_t)i;  // the first pass: entry i is entry i
   }
 #pragma unroll
   for (int it = 0; it < kSortItems; ++it) {
@@ -3951,17 +4033,13 @@ hipError_t launch_pack(const State &st, const uint64_t *off, const uint64_t *sta
 
 uint64_t scan_tmp_entries(uint64_t n) { return (n + kScanChunk - 1) / kScanChunk + 1; }
 
-// exclusive scan; tmp holds scan_tmp_entries(n) entries (at most
-// kScanChunk chunks, i.e. n <= 2^28)
+// exclusive scan; tmp holds scan_tmp_entries(n) entries
 hipError_t launch_scan_u32(const uint32_t *in, uint64_t *out, uint64_t n, uint64_t *tmp, hipStream_t s) {
   if (n == 0) return hipSuccess;
   const uint64_t nb = (n + kScanChunk - 1) / kScanChunk;
-  if (nb > kScanChunk) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_scan_chunk, dim3((unsigned)nb), dim3(1024), 0, s, in, out, n, tmp);
-  if (nb > 1) {
-    hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(1024), 0, s, tmp, nb);
-    hipLaunchKernelGGL(k_scan_add, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, out, n, tmp);
-  }
+  if (nb > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_scan_chunk, dim3((unsigned)nb), dim3(256), 0, s, in, out, n, tmp);
+  if (nb > 1) hipLaunchKernelGGL(k_scan_add, dim3((unsigned)(nb - 1)), dim3(256), 0, s, out, n, tmp);
   return hipGetLastError();
 }
 
@@ -3987,7 +4065,10 @@ hipError_t launch_sort(uint32_t *keys, uint32_t *idx, uint32_t *keys_tmp, uint32
   result_in_tmp = false;
   if (n == 0) return hipSuccess;
   const uint32_t tiles = (uint32_t)((n + kSortTile - 1) / kSortTile);
-  hipLaunchKernelGGL(k_iota, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, idx, n);
+  if (key_bits == 0) {  // one key: nothing to sort
+    hipLaunchKernelGGL(k_iota, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, idx, n);
+    return hipGetLastError();
+  }
   uint32_t *kin = keys, *iin = idx, *kout = keys_tmp, *iout = idx_tmp;
   if (key_bits > 32) return hipErrorInvalidValue;
   const uint32_t passes = (key_bits + kSortMaxBits - 1) / kSortMaxBits;
@@ -3996,8 +4077,8 @@ hipError_t launch_sort(uint32_t *keys, uint32_t *idx, uint32_t *keys_tmp, uint32
     hipLaunchKernelGGL(k_sort_hist, dim3(tiles), dim3(kSortBlock), 0, s, kin, n, shift, bits, hist, tiles);
     const hipError_t e = launch_scan_u32(hist, offs, (uint64_t)(1u << bits) * tiles, scan_tmp, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sort_scatter, dim3(tiles), dim3(kSortBlock), 0, s, kin, iin, kout, iout, n, shift, bits,
-                       offs, tiles);
+    hipLaunchKernelGGL(k_sort_scatter, dim3(tiles), dim3(kSortBlock), 0, s, kin, shift ? iin : nullptr, kout, iout, n,
+                       shift, bits, offs, tiles);
     uint32_t *tk = kin, *ti = iin;
     kin = kout;
     iin = iout;
