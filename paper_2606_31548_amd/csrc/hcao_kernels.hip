@@ -842,6 +842,11 @@ __device__ __forceinline__ double exact_slope(const SpeciesTab &S, const double 
   return sl;
 }
 
+// a value the compiler has to take as new: what depends on it is read or
+// computed again where it is used, instead of being held in registers from an
+// earlier use or hoisted out of the branch that needs it
+__device__ __forceinline__ void renew(uint32_t &x) { asm volatile("" : "+v"(x)); }
+
 // Gibbs proposal and acceptance in the form's own arithmetic. de_top = E_top
 // - E_0, den = E_c - E_0; slope tells whether the linear envelope applies.
 __device__ __forceinline__ double gibbs_slope(bool slope, double q, double de_top, uint32_t top, double den) {
@@ -953,8 +958,11 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
             const uint64_t w = rng.next_word();
             bool clear;
             bool ok = geometric_estimate<MIX>(w, k, top, i, clear);
-            if (!clear)
-              ok = geometric_exact<MIX>(RngT<MIX>::exact_of(w), beta * exact_slope(S, lev, m, top), top, i);
+            if (!clear) {
+              uint32_t t = top;  // (taken as new: the slope's division would be hoisted to every mode)
+              renew(t);
+              ok = geometric_exact<MIX>(RngT<MIX>::exact_of(w), beta * exact_slope(S, lev, m, t), t, i);
+            }
             if (!ok) continue;
             const double li = L[bend ? 0u : i];
             de = (bend ? ((double)i + 0.5) * kt : li) - e0;
@@ -964,7 +972,9 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
               const bool sure = fabsf(df) > 1e-5f * def;
               double d = 0.0;
               if (!sure) {
-                d = de - exact_slope(S, lev, m, top) * (double)i;
+                uint32_t t = top;
+                renew(t);
+                d = de - exact_slope(S, lev, m, t) * (double)i;
                 df = d > 0.0 ? 1.0f : -1.0f;
               }
               if (df > 0.0f) {
@@ -973,7 +983,9 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
                 const float u2 = RngT<MIX>::single_of(w2);
                 bool keep = u2 < est;
                 if (!sure || fabsf(u2 - est) <= 1e-4f * est + 1e-6f) {
-                  d = de - exact_slope(S, lev, m, top) * (double)i;
+                  uint32_t t = top;
+                  renew(t);
+                  d = de - exact_slope(S, lev, m, t) * (double)i;
                   if constexpr (MIX)
                     keep = u2 < __builtin_amdgcn_exp2f(-(float)(beta * d) * 1.44269504f);
                   else
@@ -1084,18 +1096,22 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
       const float k = (sv + sv) * __builtin_amdgcn_rcpf(hf + __builtin_amdgcn_sqrtf(disc));
       const float fl = floorf(k), fr = k - fl;
       const float tol = kGibbsTol * (k + 1.0f);
-      bool clear = disc > kGibbsDisc && fr > tol && fr < 1.0f - tol;
+      bool clear = (disc > kGibbsDisc) & (fr > tol) & (fr < 1.0f - tol);
       uint32_t i = (uint32_t)fminf(fl, tf);
       const double li = L[bend ? 0u : i];
       double ei = bend ? ((double)i + 0.5) * kt : li;
       const float a = RngT<MIX>::single_of(w2) * (1.0f - cf * (float)i);
       const float est = __builtin_amdgcn_exp2f(qf * __builtin_amdgcn_logf((float)(ec - ei) * rden));
-      bool ok = ei < ec && a < est;
-      clear = clear && (!(ei < ec) || fabsf(a - est) > kGibbsBand * est + 1e-6f);
+      const bool below = ei < ec;
+      bool ok = below & (a < est);
+      clear = clear & (!below | (fabsf(a - est) > kGibbsBand * est + 1e-6f));
       if (!clear) {
-        i = gibbs_level<MIX>(RngT<MIX>::exact_of(w1), slope, q, e_top - e0, top, den);
+        // (top taken as new: its divisions would be hoisted to every mode)
+        uint32_t t = top;
+        renew(t);
+        i = gibbs_level<MIX>(RngT<MIX>::exact_of(w1), slope, q, e_top - e0, t, den);
         ei = mode_energy(S, lev, m, i);
-        ok = gibbs_accept<MIX>(RngT<MIX>::exact_of(w2), slope, q, e_top - e0, top, den, i, ec, ei);
+        ok = gibbs_accept<MIX>(RngT<MIX>::exact_of(w2), slope, q, e_top - e0, t, den, i, ec, ei);
       }
       if (ok) {
         lv[m * stride] = (uint16_t)i;
@@ -1325,10 +1341,6 @@ struct Outcome {
   uint32_t side, m, sp_m;
   double et;
 };
-
-// a value the compiler has to take as new: what it addresses is read again
-// where it is used instead of being held in registers until then
-__device__ __forceinline__ void renew(uint32_t &x) { asm volatile("" : "+v"(x)); }
 
 __device__ __forceinline__ double vib_local(const Tab &T, uint32_t sp, const uint16_t *lv, uint32_t ls) {
   return vib_energy(T.sp[sp], T.lev, lv, ls);
