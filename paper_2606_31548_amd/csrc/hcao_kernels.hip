@@ -3371,61 +3371,63 @@ __device__ __forceinline__ uint32_t axis_index(double x, double len, uint32_t n)
   return (uint32_t)f;
 }
 
-// one workgroup of four waves per cell; ranks in slot order come from
-// ballots within a wave and the per-wave totals in LDS
+// one wave per cell, four cells per workgroup; ranks in slot order come from
+// ballots. Bandwidth bound; kMovePer slots per lane are loaded together. (8.0 M
+// particles in the mixed form, 200 per cell: 110 us with a workgroup of four
+// waves per cell, which meets twice per 256 slots, 91 like this, 119 with four
+// slots per lane; 67.1 M in fp64, 256 per cell: 1.01, 1.05 and 1.08 ms.)
+constexpr uint32_t kMovePer = 2;
 __global__ __launch_bounds__(256) void k_move(MoveArgs A) {
-  __shared__ uint32_t s_wave[2][4];
-  const uint32_t c = blockIdx.x, tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+  const uint32_t c = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  if (c >= A.n_cells) return;
   const uint64_t base = A.off[c];
   const uint32_t n = A.cnt[c], top = A.cap[c] - 1u;
   const uint64_t below_lane = (1ull << lane) - 1ull;
   uint32_t run_s = 0, run_m = 0;
-  for (uint32_t i0 = 0; i0 < n; i0 += 256) {
-    const uint32_t i = i0 + tid;
-    const uint64_t g = base + i;
-    bool mover = false, stayer = false;
-    uint32_t key = 0;
-    if (i < n) {
-      const Vec3 v = load_body(A.st, g).v;
-      double vx = v.x, vy = v.y, vz = v.z;
-      double x = A.st.px[g], y = A.st.py[g], z = A.st.pz[g];
-      bool flip = false;
-      // the moved state is not stored: the place pass moves the particle
-      // again as it copies it (the same arithmetic, so the same bits)
-      if (!move_particle(x, y, z, vx, vy, vz, A.dt, A.len, A.periodic, A.open, flip)) {
-        key = axis_index(x, A.len[0], A.nx) +
-              A.nx * (axis_index(y, A.len[1], A.ny) + A.ny * axis_index(z, A.len[2], A.nz));
-        mover = key != c;
-        stayer = !mover;
+  for (uint32_t i0 = 0; i0 < n; i0 += 64 * kMovePer) {
+    Vec3 v[kMovePer];
+    double x[kMovePer], y[kMovePer], z[kMovePer];
+#pragma unroll
+    for (uint32_t q = 0; q < kMovePer; ++q) {
+      const uint32_t i = i0 + 64 * q + lane;
+      if (i < n) {
+        const uint64_t g = base + i;
+        v[q] = load_body(A.st, g).v;
+        x[q] = A.st.px[g];
+        y[q] = A.st.py[g];
+        z[q] = A.st.pz[g];
       }
     }
-    const uint64_t bm = __ballot(mover), bs = __ballot(stayer);
-    if (lane == 0) {
-      s_wave[0][wv] = (uint32_t)__popcll(bs);
-      s_wave[1][wv] = (uint32_t)__popcll(bm);
-    }
-    __syncthreads();
-    uint32_t pre_s = run_s, pre_m = run_m;
-    for (uint32_t w = 0; w < 4; ++w) {
-      const uint32_t ns = s_wave[0][w], nm = s_wave[1][w];
-      if (w < wv) {
-        pre_s += ns;
-        pre_m += nm;
+#pragma unroll
+    for (uint32_t q = 0; q < kMovePer; ++q) {
+      const uint32_t i = i0 + 64 * q + lane;
+      bool mover = false, stayer = false;
+      uint32_t key = 0;
+      if (i < n) {
+        bool flip = false;
+        // the moved state is not stored: the place pass moves the particle
+        // again as it copies it (the same arithmetic, so the same bits)
+        if (!move_particle(x[q], y[q], z[q], v[q].x, v[q].y, v[q].z, A.dt, A.len, A.periodic, A.open, flip)) {
+          key = axis_index(x[q], A.len[0], A.nx) +
+                A.nx * (axis_index(y[q], A.len[1], A.ny) + A.ny * axis_index(z[q], A.len[2], A.nz));
+          mover = key != c;
+          stayer = !mover;
+        }
       }
-      run_s += ns;
-      run_m += nm;
+      const uint64_t bm = __ballot(mover), bs = __ballot(stayer);
+      // stayer ranks count up from the first slot, mover ranks down from the
+      // last: together they never pass n <= cap entries
+      if (mover) {
+        const uint64_t at = base + top - (run_m + (uint32_t)__popcll(bm & below_lane));
+        A.list[at] = i;
+        A.key[at] = key;
+      }
+      if (stayer) A.list[base + run_s + (uint32_t)__popcll(bs & below_lane)] = i;
+      run_s += (uint32_t)__popcll(bs);
+      run_m += (uint32_t)__popcll(bm);
     }
-    // stayer ranks count up from the first slot, mover ranks down from the
-    // last: together they never pass n <= cap entries
-    if (mover) {
-      const uint64_t at = base + top - (pre_m + (uint32_t)__popcll(bm & below_lane));
-      A.list[at] = i;
-      A.key[at] = key;
-    }
-    if (stayer) A.list[base + pre_s + (uint32_t)__popcll(bs & below_lane)] = i;
-    __syncthreads();
   }
-  if (tid == 0) {
+  if (lane == 0) {
     A.n_stay[c] = run_s;
     A.n_move[c] = run_m;
     const uint32_t gone = n - run_s - run_m;
@@ -3681,10 +3683,15 @@ __device__ __forceinline__ void copy_moved(const RebinArgs &A, uint64_t from, ui
 // (issued first, so that the loads overlap the ranking) and then LDS, and
 // written from there in output order; its level rows (4 to 32 bytes each)
 // follow as one run of dwords, read in order and written dword by dword in
-// output order. Larger cells copy each particle directly. The old count is read before the new one is written (only this
-// workgroup touches cnt[j]). Workgroups go to the eight XCDs in turn, so
-// the grid (a multiple of 8) gives each XCD one contiguous range of cells:
-// movers go to neighbouring cells, whose lines are then in the same L2.
+// output order. Larger cells copy each particle directly. The old count is
+// read before the new one is written (only this workgroup touches cnt[j]).
+// Workgroups go to the eight XCDs in turn; each XCD takes kPushRun
+// consecutive cells at a time, since movers go to neighbouring cells, whose
+// lines are then in the same L2, and so that the XCDs together work through
+// one region of the grid (67.1 M particles in fp64: 3.10 ms with an eighth
+// of the grid per XCD, 2.98 with runs of 256 cells). A grid's last, incomplete
+// round of runs is shared out evenly.
+constexpr uint32_t kPushRun = 256;
 __global__ __launch_bounds__(256) void k_rebin_push(RebinArgs A) {
   constexpr uint32_t kPer = (kStageSlots + 255u) / 256u;  // staged slots per thread
   constexpr uint32_t kPerL = (kStageSlots * (kMaxModes / 2) + 255u) / 256u;  // staged level dwords per thread
@@ -3699,7 +3706,9 @@ __global__ __launch_bounds__(256) void k_rebin_push(RebinArgs A) {
   __shared__ uint16_t s_src[kStageSlots], s_msrc[kStageSlots];
   __shared__ uint8_t s_sp[kStageSlots];
   const uint32_t per_xcd = gridDim.x >> 3;
-  const uint32_t j = (blockIdx.x & 7u) * per_xcd + (blockIdx.x >> 3);
+  const uint32_t xcd = blockIdx.x & 7u, turn = blockIdx.x >> 3, whole = per_xcd / kPushRun * kPushRun;
+  const uint32_t j = turn < whole ? (turn / kPushRun * 8u + xcd) * kPushRun + turn % kPushRun
+                                  : whole * 8u + xcd * (per_xcd - whole) + (turn - whole);
   if (j >= A.n_cells) return;
   const uint32_t tid = threadIdx.x;
   const uint64_t base = A.off[j], mb = A.mbase[j];
@@ -4108,7 +4117,7 @@ hipError_t launch_move(const MoveArgs &a, hipStream_t s) {
   if (a.n_cells == 0) return hipSuccess;
   if (!a.off || !a.cnt || !a.cap || !a.key || !a.list || !a.n_stay || !a.n_move || !a.st.px || !a.st.py || !a.st.pz)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_move, dim3(a.n_cells), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_move, dim3((a.n_cells + 3u) / 4u), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
