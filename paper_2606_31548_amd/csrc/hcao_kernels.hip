@@ -2633,8 +2633,16 @@ __device__ __forceinline__ void polar_normals(Rng &rng, double &n1, double &n2) 
 // the level row and the rotational energy of
 // slot g. The thermal initial state and admission through open faces draw
 // the same way.
+//
+// LANES (a power of two) consecutive lanes may share one molecule, all with
+// its state: lane i of them then tests the stretch trial that lies i further
+// in the stream (a trial is two uniforms, one block), and the first accepted
+// one is the sampler's, as is the stream position after it.
+template <uint32_t LANES>
 __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const double *theta, const double *lev, Rng &rng, double tv,
                                                 double trot, const State &st, uint64_t g, uint32_t mm) {
+  const uint32_t sub = threadIdx.x & (LANES - 1u), lane0 = (threadIdx.x & 63u) - sub;
+  const bool writer = sub == 0;
   for (uint32_t m = 0; m < mm; ++m) {
     uint32_t l = 0;
     if (m < S.n_modes) {
@@ -2658,21 +2666,48 @@ __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const doubl
         const double *L = lev + S.lev_off[m];
         const double kt = kBoltz * tv;
         for (;;) {
-          const double u = rng.uniform();
+          Rng r = rng;
+          if (LANES > 1 && sub > 0) {
+            // trial sub: as many blocks further on, with the words that the
+            // trial before it left
+            r.block += sub;
+            if (r.used == 2) {
+              r.block -= 1;
+              r.refill();
+              r.used = 2;
+            }
+          }
+          const double u = r.uniform();
           uint32_t j = (uint32_t)floor(u * (double)(top + 1));
           j = j > top ? top : j;
-          const double u2 = rng.uniform();
+          const double u2 = r.uniform();
           const double xx = (L[j] - L[0]) / kt;
-          if (below_exp_neg(u2, xx)) {
-            l = j;
-            break;
+          const bool ok = below_exp_neg(u2, xx);
+          if constexpr (LANES == 1) {
+            rng = r;
+            if (ok) {
+              l = j;
+              break;
+            }
+          } else {
+            const uint32_t hit = (uint32_t)(__ballot(ok) >> lane0) & ((1u << LANES) - 1u);
+            const int src = (int)lane0 + (hit ? __ffs((int)hit) - 1 : (int)LANES - 1);
+            rng.block = __shfl(r.block, src);
+            rng.used = __shfl(r.used, src);
+            rng.w0 = __shfl(r.w0, src);
+            rng.w1 = __shfl(r.w1, src);
+            rng.w2 = __shfl(r.w2, src);
+            rng.w3 = __shfl(r.w3, src);
+            l = __shfl(j, src);
+            if (hit) break;
           }
         }
       }
     }
-    st.lvl[g * st.lrow + m] = (uint16_t)l;
+    if (writer) st.lvl[g * st.lrow + m] = (uint16_t)l;
   }
-  for (uint32_t m = mm; m < st.lrow; ++m) st.lvl[g * st.lrow + m] = 0;
+  if (writer)
+    for (uint32_t m = mm; m < st.lrow; ++m) st.lvl[g * st.lrow + m] = 0;
   if (st.rot) {
     double e = 0.0;
     if (S.zeta_rot > 0) {
@@ -2684,7 +2719,7 @@ __device__ __forceinline__ void sample_internal(const SpeciesTab &S, const doubl
       }
       e = (kBoltz * trot) * gm;
     }
-    st.rot[g] = e;
+    if (writer) st.rot[g] = e;
   }
 }
 
@@ -2721,7 +2756,7 @@ __global__ __launch_bounds__(256) void k_init(InitArgs A) {
     const double sigma = sqrt((kBoltz * tt) / S.mass);
     const uint64_t g = A.off[c] + i;
     store_body(A.st, g, sigma * n1, sigma * n2, sigma * n3, s);
-    sample_internal(S, T.theta[s], A.lev, rng, tv, tt, A.st, g, mm);
+    sample_internal<1>(S, T.theta[s], A.lev, rng, tv, tt, A.st, g, mm);
     if (A.st.px) {
       // spatial mode: uniform in the cell, one draw per axis
       const uint32_t ix = c % A.nx, iy = (c / A.nx) % A.ny, iz = c / (A.nx * A.ny);
@@ -3491,9 +3526,35 @@ __global__ __launch_bounds__(256) void k_inflow_count(InflowArgs A) {
 // sqrt(-2 ln(1 - u)); tangential speeds, a polar normal pair times sigma;
 // the flight fraction tau; the place on the face cell, uniform per
 // tangential axis; levels and rotation as the thermal initial state draws
-// them; then a move over tau dt
-__global__ __launch_bounds__(256) void k_inflow_make(InflowArgs A) {
-  const uint64_t j = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// them; then a move over tau dt.
+//
+// A step may admit too few molecules to fill the chip, and each is one long
+// chain of draws, mostly rejected stretch proposals: LANES lanes share a
+// molecule and its trials, and the tables come from LDS. 20,000 admissions of a
+// step of the 45 x 33 x 27 channel: 150 us with a lane each and the tables in
+// memory, 134 with the tables in LDS, 61 with four lanes. Lanes are shared
+// while the chip has room for them; with 1, 4 and 8 lanes, 7,600 admissions
+// take 106, 48 and 34 us, 108,500 take 165, 142 and 206, 244,000 take 249, 247
+// and 400, 549,000 take 357, 492 and 760.
+constexpr uint64_t kInflowEight = 16384, kInflowFour = 196608;  // the most admissions that take so many lanes
+constexpr uint32_t kInflowLevels = 4096;  // levels staged in LDS at most (32 KB); larger ladders are read from memory
+template <uint32_t LANES>
+__global__ __launch_bounds__(64) void k_inflow_make(InflowArgs A) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  SpeciesTab *l_sp = reinterpret_cast<SpeciesTab *>(smem);
+  double *l_theta = reinterpret_cast<double *>(l_sp + A.n_species), *l_lev = l_theta + A.n_species * kMaxModes;
+  {
+    const uint64_t *src = reinterpret_cast<const uint64_t *>(A.tab->sp);
+    uint64_t *dst = reinterpret_cast<uint64_t *>(l_sp);
+    for (uint32_t i = threadIdx.x; i < A.n_species * sizeof(SpeciesTab) / 8; i += blockDim.x) dst[i] = src[i];
+    for (uint32_t i = threadIdx.x; i < A.n_species * kMaxModes; i += blockDim.x)
+      l_theta[i] = A.tab->theta[i / kMaxModes][i % kMaxModes];
+    for (uint32_t i = threadIdx.x; i < A.n_levels; i += blockDim.x) l_lev[i] = A.lev[i];
+  }
+  __syncthreads();
+  const double *lev = A.n_levels ? l_lev : A.lev;
+  const uint64_t j = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) / LANES;
+  const bool writer = (threadIdx.x & (LANES - 1u)) == 0;
   if (j >= A.n_ins) return;
   if (j >= A.cap_ins) {
     atomicOr(A.err, kErrCapacity);
@@ -3512,7 +3573,7 @@ __global__ __launch_bounds__(256) void k_inflow_make(InflowArgs A) {
   const uint32_t i = (uint32_t)(j - A.ibase[t]);
   const uint32_t gfc = (uint32_t)(t / ns), s = (uint32_t)(t % ns);
   const FaceCell F = face_cell(A, gfc);
-  const SpeciesTab &S = A.tab->sp[s];
+  const SpeciesTab &S = l_sp[s];
   const uint32_t mm = A.tab->max_modes;
   const double sigma = sqrt((kBoltz * A.t_trans) / S.mass);
   Rng rng;
@@ -3530,10 +3591,11 @@ __global__ __launch_bounds__(256) void k_inflow_make(InflowArgs A) {
   p[F.b] = ((double)F.ib + ub) * F.db;
   v[F.a] = sigma * n1;
   v[F.b] = sigma * n2;
-  sample_internal(S, A.tab->theta[s], A.lev, rng, A.t_vib, A.t_trans, A.ins, j, mm);
+  sample_internal<LANES>(S, l_theta + s * kMaxModes, lev, rng, A.t_vib, A.t_trans, A.ins, j, mm);
   bool flip = false;
   const bool left =
       move_particle(p[0], p[1], p[2], v[0], v[1], v[2], tau * A.dt, A.len, A.periodic, A.open, flip);
+  if (!writer) return;
   store_body(A.ins, j, v[0], v[1], v[2], s);
   A.ins.px[j] = p[0];
   A.ins.py[j] = p[1];
@@ -4143,7 +4205,17 @@ hipError_t launch_inflow_make(const InflowArgs &a, hipStream_t s) {
   if (!a.tab || !a.lev || !a.count || !a.ibase || !a.mbase || !a.mkey || !a.mslot || !a.flux || !a.err ||
       !a.ins.lvl || !a.ins.px || !a.ins.py || !a.ins.pz || (!a.ins.b64 && !a.ins.b32))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_inflow_make, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+  InflowArgs b = a;
+  if (b.n_levels > kInflowLevels) b.n_levels = 0;
+  const size_t lds = b.n_species * (sizeof(SpeciesTab) + kMaxModes * 8) + (size_t)b.n_levels * 8;
+  const uint32_t lanes = n <= kInflowEight ? 8u : n <= kInflowFour ? 4u : 1u;
+  const dim3 grid((unsigned)((n * lanes + 63) / 64));
+  if (lanes == 8)
+    hipLaunchKernelGGL(k_inflow_make<8>, grid, dim3(64), lds, s, b);
+  else if (lanes == 4)
+    hipLaunchKernelGGL(k_inflow_make<4>, grid, dim3(64), lds, s, b);
+  else
+    hipLaunchKernelGGL(k_inflow_make<1>, grid, dim3(64), lds, s, b);
   return hipGetLastError();
 }
 

@@ -1573,6 +1573,7 @@ hcao_status move_rebin(hcao_ctx *c, double dt, uint32_t step, hipStream_t s) {
     in.periodic = c->periodic;
     in.open = c->open_faces;
     in.n_species = ns;
+  in.n_levels = c->tab.n_levels;
     in.step = step;
     HIP_TRY(c, launch_inflow_count(in, s));
     // the entry past the last (face cell, species) stays zero: the scan's

@@ -284,6 +284,7 @@ struct InflowArgs {
   uint64_t n_ins;              // admissions of the step (make pass)
   uint32_t face_base[7];
   uint32_t nx, ny, nz, n_cells, periodic, open, n_species, step;
+  uint32_t n_levels;           // entries of lev
 };
 
 // Spatial mode, re-bin after the move pass. The new order of cell k is the
