@@ -7,13 +7,17 @@
 #include <rocprofiler-sdk-roctx/roctx.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <limits>
 #include <mutex>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <vector>
 
 #include "hcao.h"
@@ -183,11 +187,40 @@ struct LoadScratch {
 };
 constexpr uint64_t kPackChunk = 4u << 20;  // particles a read-back packs at once
 
+// pinned slots of large read-backs, one per thread that empties them, kept by
+// the context from its first one
+struct HostStage {
+  static constexpr size_t kSlots = 4, kSlotBytes = 2u << 20;
+  static constexpr size_t kMin = 4u << 20;  // smaller copies go straight to the caller's memory
+  unsigned char *p = nullptr;
+  hipEvent_t ev[kSlots] = {};
+  // false (and no error left behind) when they cannot be had
+  bool ready() {
+    if (p) return true;
+    bool ok = hipHostMalloc((void **)&p, kSlots * kSlotBytes, hipHostMallocDefault) == hipSuccess;
+    for (size_t i = 0; ok && i < kSlots; ++i) ok = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming) == hipSuccess;
+    if (!ok) {
+      (void)hipGetLastError();
+      release();
+    }
+    return ok;
+  }
+  void release() {
+    for (hipEvent_t &e : ev) {
+      if (e) (void)hipEventDestroy(e);
+      e = nullptr;
+    }
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+  }
+};
+
 }  // namespace
 
 struct hcao_ctx {
   RecScratch rec_scratch;
   LoadScratch io;
+  HostStage stage;
   // moments: the cells' sums, their partial totals, vibrational temperatures
   // (scratch, kept), and the thermometer's tables
   DevBuf<double> mom_raw, mom_part, mom_tvib, thermo_mean;
@@ -329,6 +362,81 @@ hcao_status hip_fail(hcao_ctx *c, hipError_t e, const char *what) {
     hipError_t e_ = (expr);                              \
     if (e_ != hipSuccess) return hip_fail(ctx, e_, #expr); \
   } while (0)
+
+// Device memory to the caller's pageable memory, behind the stream's work; a
+// large copy has ended when this returns, a small one when the stream has.
+// The runtime's own path to pageable memory is one thread that copies out of
+// pinned memory and takes the page faults of a fresh array, at 11 GB/s; here
+// the copy engine fills pinned slots and four threads empty them.
+hcao_status copy_out(hcao_ctx *c, void *dst, const void *src, size_t bytes) {
+  constexpr size_t S = HostStage::kSlots, B = HostStage::kSlotBytes;
+  if (bytes < HostStage::kMin || !c->stage.ready()) {
+    HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
+    return HCAO_OK;
+  }
+  HostStage &H = c->stage;
+  const size_t n = (bytes + B - 1) / B;
+  auto size_of = [&](size_t k) { return std::min(B, bytes - k * B); };
+  std::mutex mu;
+  std::condition_variable cv;
+  size_t arrived = 0;                  // chunks that are in their slots (chunk k in slot k mod S)
+  std::array<size_t, S> emptied = {};  // times each slot was emptied
+  bool stop = false;
+  auto work = [&](size_t t) {
+    for (size_t k = t; k < n; k += S) {
+      {
+        std::unique_lock<std::mutex> lk(mu);
+        cv.wait(lk, [&] { return stop || arrived > k; });
+        if (arrived <= k) return;
+      }
+      std::memcpy((unsigned char *)dst + k * B, H.p + t * B, size_of(k));
+      std::lock_guard<std::mutex> lk(mu);
+      ++emptied[t];
+      cv.notify_all();
+    }
+  };
+  std::array<std::thread, S> threads;
+  auto finish = [&] {
+    {
+      std::lock_guard<std::mutex> lk(mu);
+      stop = true;
+    }
+    cv.notify_all();
+    for (std::thread &t : threads)
+      if (t.joinable()) t.join();
+  };
+  try {
+    for (size_t t = 0; t < S; ++t) threads[t] = std::thread(work, t);
+  } catch (const std::system_error &) {  // no thread to be had
+    finish();
+    HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
+    return HCAO_OK;
+  }
+  hipError_t e = hipSuccess;
+  size_t queued = 0;
+  for (size_t k = 0; k < n && e == hipSuccess; ++k) {
+    for (; e == hipSuccess && queued < n && queued < k + S; ++queued) {
+      const size_t slot = queued % S;
+      {
+        std::unique_lock<std::mutex> lk(mu);
+        if (queued > k && emptied[slot] < queued / S) break;  // its turn comes with a later chunk
+        cv.wait(lk, [&] { return emptied[slot] >= queued / S; });
+      }
+      e = hipMemcpyAsync(H.p + slot * B, (const unsigned char *)src + queued * B, size_of(queued),
+                         hipMemcpyDeviceToHost, c->stream);
+      if (e == hipSuccess) e = hipEventRecord(H.ev[slot], c->stream);
+    }
+    if (e == hipSuccess) e = hipEventSynchronize(H.ev[k % S]);
+    if (e == hipSuccess) {
+      std::lock_guard<std::mutex> lk(mu);
+      arrived = k + 1;
+      cv.notify_all();
+    }
+  }
+  finish();
+  if (e != hipSuccess) return hip_fail(c, e, "read-back");
+  return HCAO_OK;
+}
 
 // Level ladder of one stretch: explicit energies, or the Morse ladder of
 // (w_e, x_e) capped at D_e (D_e = h c w_e / (4 x_e) when not given).
@@ -2137,9 +2245,9 @@ hcao_status hcao_read_particles(hcao_ctx *c, uint8_t *species, double *vel, uint
     while (c1 < nc && start[c1] < p1) ++c1;
     HIP_TRY(c, launch_pack(state_of(c), c->off.p, S.packed.p, c->cnt.p, S.sp.p, S.vel.p, S.lvl.p, p0, p1, c0, c1, mm,
                            c->stream));
-    HIP_TRY(c, hipMemcpyAsync(species + p0, S.sp.p, n, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(vel + 3 * p0, S.vel.p, 3 * n * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(levels + p0 * mm, S.lvl.p, n * mm * sizeof(uint16_t), hipMemcpyDeviceToHost, c->stream));
+    if (hcao_status st = copy_out(c, species + p0, S.sp.p, n)) return st;
+    if (hcao_status st = copy_out(c, vel + 3 * p0, S.vel.p, 3 * n * sizeof(double))) return st;
+    if (hcao_status st = copy_out(c, levels + p0 * mm, S.lvl.p, n * mm * sizeof(uint16_t))) return st;
   }
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   S.trim();
@@ -2169,7 +2277,7 @@ hcao_status hcao_read_cell_state(hcao_ctx *c, double *sgmax, double *rem, uint64
   if (sgmax) HIP_TRY(c, hipMemcpyAsync(sgmax, c->sgmax.p, nc * 8, hipMemcpyDeviceToHost, c->stream));
   if (rem) HIP_TRY(c, hipMemcpyAsync(rem, c->rem.p, nc * 8, hipMemcpyDeviceToHost, c->stream));
   if (counters)
-    HIP_TRY(c, hipMemcpyAsync(counters, c->ctr.p, (size_t)nc * kNumCtr * 8, hipMemcpyDeviceToHost, c->stream));
+    if (hcao_status st = copy_out(c, counters, c->ctr.p, (size_t)nc * kNumCtr * 8)) return st;
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return HCAO_OK;
 }
@@ -2629,6 +2737,7 @@ void hcao_destroy(hcao_ctx *c) {
   c->err.release();
   c->rec_scratch.release();
   c->io.release();
+  c->stage.release();
   c->mom_raw.release();
   c->mom_part.release();
   c->mom_tvib.release();

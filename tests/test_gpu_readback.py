@@ -5,8 +5,16 @@ import numpy as np
 import pytest
 
 from paper_2606_31548_amd import workloads as W
+from test_gpu_parity import _compare_state
 
 pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hc():
+    from paper_2606_31548_amd import hcao
+    hcao.load_library()
+    return hcao
 
 
 def _state(counts, seed):
@@ -46,3 +54,19 @@ def test_cell_longer_than_a_chunk():
     g.load_particles(cell, sp, vel, lv)
     c, s, v, l = g.read_particles()
     assert np.array_equal(c, counts) and np.array_equal(s, sp) and np.array_equal(v, vel) and np.array_equal(l, lv)
+
+
+@pytest.mark.parametrize("cells,per_cell", [(13107, 8), (13108, 14), (30001, 23)])
+def test_large_reads_match_the_oracle(orc, hc, cells, per_cell):
+    """Counters just below and above the 4 MiB from which a read goes through
+    pinned slots, and reads of more 2 MiB chunks than there are slots, the
+    last one ragged."""
+    wl = W.methane_argon(n_cells=cells, per_cell=per_cell, seed=5)
+    o, g = orc.from_workload(wl), hc.from_workload(wl)
+    o.init_thermal(wl.counts, wl.t_trans, wl.t_vib)
+    g.init_thermal(wl.counts, wl.t_trans, wl.t_vib)
+    for n in (1, 2):  # the second read takes the slots of the first
+        o.step(wl.dt, n)
+        g.step(wl.dt, n)
+        g.sync()
+        _compare_state(o, g, f"{cells} cells")
