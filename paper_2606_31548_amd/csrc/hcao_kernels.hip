@@ -107,7 +107,7 @@ struct RngT {
   // word i of the current block, selected by value: a conditional over the
   // members themselves becomes a choice of addresses, which put the whole
   // generator into scratch memory (every draw of the mixed form then waited
-  // for memory: 0.52 against 0.38 ms per step of 65,536 cells)
+  // for memory: 0.52 against 0.43 ms per step of 65,536 cells)
   __device__ __forceinline__ uint32_t word(uint32_t i) const {
     const uint32_t x0 = w0, x1 = w1, x2 = w2, x3 = w3;
     const uint32_t lo = (i & 1u) ? x1 : x0, hi = (i & 1u) ? x3 : x2;
@@ -1846,7 +1846,8 @@ constexpr uint32_t kBornList = 128;
 // A cell with more candidates than this has its per-pair records reduced by
 // all waves of the workgroup, chunk by chunk, before one wave adds up the
 // chunks (a wave takes a microsecond per chunk: a cell of 100,000 particles
-// has 600, which kept the other waves waiting for half of the step).
+// has 600, which kept the other waves waiting for half of the step; at 512
+// candidates the extra barrier costs what eight chunks do).
 constexpr uint32_t kBigCell = 512;
 
 // an accepted pair's velocities, handed from phase A to phase B
@@ -1872,6 +1873,20 @@ struct PairVel {
 // (the audit of its particles before and after); the cell's sum, reduced in
 // pair order, is owed to the cell and joins the translational energy of the
 // cell's pair 0 in the next step in which that pair collides.
+//
+// What bounds it: vector arithmetic, where there are cells enough to fill the
+// chip (the pairs' samplers, then the permutation and the generator: about
+// 19,000 vector instructions per seven cells of 256 particles and step; the
+// issue slots are 85% busy). It was bound by cache lines before: 262,144 cells
+// of 256, 50 steps, 92.9 ms mixed and 108 fp64, now 62.6 and 77. Velocity and
+// species are therefore one record; an accepted pair's velocities go from
+// phase A to B, and from B's decision to its scattering, through a dense list
+// that stays in cache; per-pair records are dense by entry. Four waves per SIMD
+// (128 registers; three with the exact sampler, which needs 136) came with
+// that: alone they gained nothing. Few cells: bound by the chain of a step's
+// phases, so groups get smaller and workgroups wider (choose_shape). Large
+// cells (4,096 reservoirs of 1,000 to 100,000 particles, 25 steps: 101 to 45
+// ms): the candidates' gathers land on scattered lines.
 template <int BLOCK, bool MIX, int EX>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ? 3 : 4))) void k_step(StepArgs A) {
   using R = Real<MIX>;
@@ -2849,7 +2864,8 @@ struct MomentArgs {
 // per workgroup), eight for large ones. NS: a bound of the species count, so
 // that the per-species sums stay in registers. One workgroup of 256 threads
 // per cell, each sum reduced through LDS with nine barriers, took 7.0 ms for
-// 262,144 cells of 256 particles (three times the time its arithmetic needs).
+// 262,144 cells of 256 particles; with a wave per cell the whole read of the
+// moments takes 1.1, most of it the pass over the state.
 template <int NS, int WAVES>
 __global__ __launch_bounds__(WAVES == 1 ? 256 : 64 * WAVES) void k_moments(MomentArgs A) {
   constexpr int kW = 6 + 2 * NS;  // per-lane sums: the common ones, E_vib and E_rot per species
@@ -2967,7 +2983,8 @@ __global__ __launch_bounds__(256) void k_moments_sum(MomentSumArgs A) {
 // Boltzmann mean energy above the ground levels equals the species' mean, by
 // the Illinois form of regula falsi in log T between two nodes of a table of
 // means (512 nodes over 1 .. 1e6 K, equally spaced in log T). One thread
-// each; on the host the same took 2.4 us per cell and species.
+// each; on the host the same took 2.4 us per cell and species (the moments of
+// 12,345 cells: 28.6 ms, now 1.9).
 struct ThermoArgs {
   const Tables *tab;
   const double *lev;
@@ -3534,7 +3551,7 @@ __global__ __launch_bounds__(256) void k_inflow_count(InflowArgs A) {
 // step of the 45 x 33 x 27 channel: 150 us with a lane each and the tables in
 // memory, 134 with the tables in LDS, 61 with four lanes. Lanes are shared
 // while the chip has room for them; with 1, 4 and 8 lanes, 7,600 admissions
-// take 106, 48 and 34 us, 108,500 take 165, 142 and 206, 244,000 take 249, 247
+// take 106, 48 and 34 us, 108,500 take 165, 142 and 206, 244,000 take 240, 247
 // and 400, 549,000 take 357, 492 and 760.
 constexpr uint64_t kInflowEight = 16384, kInflowFour = 196608;  // the most admissions that take so many lanes
 constexpr uint32_t kInflowLevels = 4096;  // levels staged in LDS at most (32 KB); larger ladders are read from memory

@@ -367,7 +367,9 @@ hcao_status hip_fail(hcao_ctx *c, hipError_t e, const char *what) {
 // large copy has ended when this returns, a small one when the stream has.
 // The runtime's own path to pageable memory is one thread that copies out of
 // pinned memory and takes the page faults of a fresh array, at 11 GB/s; here
-// the copy engine fills pinned slots and four threads empty them.
+// the copy engine fills pinned slots and four threads empty them (the 84 MB of
+// counters of 262,144 cells: 8.2 ms, now 3.1; 21 MB: 1.55, now 1.03). Small
+// copies gain nothing from the threads' start and end.
 hcao_status copy_out(hcao_ctx *c, void *dst, const void *src, size_t bytes) {
   constexpr size_t S = HostStage::kSlots, B = HostStage::kSlotBytes;
   if (bytes < HostStage::kMin || !c->stage.ready()) {
@@ -642,6 +644,10 @@ int step_level(const hcao_ctx *c);
 // groups, down to one cell each, and then wider workgroups, up to one lane per
 // possible candidate pair (a fourth of the slots: half are paired, and NTC
 // tests about half of those at most once (sigma g)_max has settled).
+// Methane/argon, 256 particles per cell, us per step: 4,096 cells 34 with the
+// default, 54 with a cell per group; 1,500 cells 28 to 30 with the default, 25
+// with smaller groups. One reservoir of 10,000 particles, 20 steps: 13.6 ms
+// with 64 lanes, 2.4 with 256, 1.4 with 1,024.
 void choose_shape(const hcao_ctx *c, int &block, uint32_t &group_slots) {
   block = c->block;
   group_slots = c->group_slots;
