@@ -1878,7 +1878,7 @@ struct PairVel {
 // chip (the pairs' samplers, then the permutation and the generator: about
 // 19,000 vector instructions per seven cells of 256 particles and step; the
 // issue slots are 85% busy). It was bound by cache lines before: 262,144 cells
-// of 256, 50 steps, 92.9 ms mixed and 108 fp64, now 62.6 and 77. Velocity and
+// of 256, 50 steps, 93 ms mixed and 101 fp64, now 63 and 73. Velocity and
 // species are therefore one record; an accepted pair's velocities go from
 // phase A to B, and from B's decision to its scattering, through a dense list
 // that stays in cache; per-pair records are dense by entry. Four waves per SIMD
