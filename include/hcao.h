@@ -381,8 +381,9 @@ hcao_status hcao_step_graph(hcao_ctx *ctx, double dt, uint32_t n_steps);
  * hipMalloc): the same n_steps steps as hcao_step, with bitwise the same
  * result, but the step's work lists, pair flags, pair energy defects and
  * products staging live in one fixed device array of
- * HCAO_STATIC_SCRATCH_BYTES that the library holds on each GPU it runs on
- * until the process ends, not in the context's buffers. The call allocates
+ * HCAO_STATIC_SCRATCH_BYTES (and 16 MiB by which the records of staged
+ * products may exceed the need stated here) that the library holds on each GPU
+ * it runs on until the process ends, not in the context's buffers. The call allocates
  * and frees nothing. Its need is about 30 + 3 b_v + 2 max_modes bytes per
  * work entry (b_v = 8 fp64, 4 mixed; 8 more in the mixed form, 8 more with
  * rotors and 40 more with a recombination reaction; work entries = sum over cells of capacity / 2 + 1, e.g.
