@@ -1145,6 +1145,11 @@ struct JointJob {
 // serial loop stops at. One lane per molecule keeps the whole wave until its
 // slowest molecule is accepted (a mean of 16 trials for the triatomic, about
 // 75 for the slowest of 64); shared out, 64 of them take about 25 rounds.
+//
+// A molecule's tops are rows 0 .. n_modes - 1 of its owner's column of the
+// scratch; a trial's proposals are rows max_modes on of the column of the lane
+// that tests it. A lane may test a molecule with fewer modes than the one it
+// owns, whose tops must outlast the test.
 template <bool MIX>
 __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool job, uint32_t sp, uint16_t *lv,
                                                 uint32_t stride, double &e_tr, double q, RngT<MIX> &rng,
@@ -1196,7 +1201,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
         r.refill();
         r.used = at % 4u;
       }
-      uint16_t *cand = C.scr + (size_t)n * C.block + C.lane;
+      uint16_t *cand = C.scr + (size_t)C.T.mm * C.block + C.lane;
       for (uint32_t m = 0; m < n; ++m) {
         const uint32_t i = pick_level<MIX>(C.scr[m * C.block + o], r);
         cand[m * C.block] = (uint16_t)i;
@@ -1220,7 +1225,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
         job = false;
       } else if (hit < G) {
         trials += hit + 1u;
-        const uint16_t *cand = C.scr + (size_t)nm * C.block + first_lane + from;
+        const uint16_t *cand = C.scr + (size_t)C.T.mm * C.block + first_lane + from;
         for (uint32_t m = 0; m < nm; ++m) lv[m * stride] = cand[m * C.block];
         e_tr = e_coll - won_sum;
         job = false;
