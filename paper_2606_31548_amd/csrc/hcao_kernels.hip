@@ -1131,10 +1131,12 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
 
 // The joint sampler's molecules of a wave, one slot per lane (LDS)
 struct JointJob {
-  double e_coll, q;
+  double e_coll;
   uint32_t pos, pair, cell;  // first word of the next trial, the stream
-  uint16_t sp, owner;        // owner: slot i of a wave's lanes names its i-th unaccepted molecule's lane
+  uint8_t sp, pr;            // the molecule's species, the pair table entry of its exponent
+  uint16_t owner;            // slot i of a wave's lanes names its i-th unaccepted molecule's lane
 };
+static_assert(sizeof(JointJob) == 24 && kMaxSpecies * kMaxSpecies <= 256, "the joint sampler's LDS slots");
 
 // Joint sampler (uniform proposals over the box of levels, one acceptance of
 // the whole vector) for the lanes of a wave with job set; every lane of the
@@ -1151,8 +1153,8 @@ struct JointJob {
 // that tests it. A lane may test a molecule with fewer modes than the one it
 // owns, whose tops must outlast the test.
 template <bool MIX>
-__device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool job, uint32_t sp, uint16_t *lv,
-                                                uint32_t stride, double &e_tr, double q, RngT<MIX> &rng,
+__device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool job, uint32_t sp, uint32_t partner,
+                                                uint16_t *lv, uint32_t stride, double &e_tr, RngT<MIX> &rng,
                                                 bool &capped) {
   const double *lev = C.T.lev;
   const uint32_t lane = C.lane & 63u, first_lane = C.lane - lane;
@@ -1169,11 +1171,11 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
     if (job) {
       for (uint32_t m = 0; m < nm; ++m) C.scr[m * C.block + C.lane] = (uint16_t)mode_top(S, lev, m, e_coll);
       J[C.lane].e_coll = e_coll;
-      J[C.lane].q = q;
       J[C.lane].pos = rng.used >= 4 ? 4 * rng.block : 4 * (rng.block - 1) + rng.used;  // next word of the stream
       J[C.lane].pair = rng.pair;
       J[C.lane].cell = rng.cell;
-      J[C.lane].sp = (uint16_t)sp;
+      J[C.lane].sp = (uint8_t)sp;
+      J[C.lane].pr = (uint8_t)(sp * C.T.ns + partner);
     }
   }
   unsigned long long pend = __ballot(job);
@@ -1209,7 +1211,7 @@ __device__ __forceinline__ uint32_t relax_joint(const Ctx &C, JointJob *J, bool 
       }
       const double ua = (double)draw<MIX>(r);
       const double e = J[o].e_coll;
-      ok = sum < e && lb_accept<MIX>(ua, e - sum, e - S.zpe, J[o].q);
+      ok = sum < e && lb_accept<MIX>(ua, e - sum, e - S.zpe, C.T.pr[J[o].pr].q);
     }
     const unsigned long long won = __ballot(ok);
     const unsigned long long mine = (won >> (rank << sh)) & (G < 64u ? (1ull << G) - 1ull : ~0ull);
@@ -2284,7 +2286,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(EX >= 2 ?
         }
         if (any_joint && __ballot(joint)) {
           bool capped;
-          const uint32_t t = relax_joint<MIX>(C, jobs, joint, sj, lv, BLOCK, O.et, T.pair(sj, partner).q, rng, capped);
+          const uint32_t t = relax_joint<MIX>(C, jobs, joint, sj, partner, lv, BLOCK, O.et, rng, capped);
           tr += t;
           ncap += capped ? 1u : 0u;
         }
@@ -3985,12 +3987,17 @@ __global__ __launch_bounds__(256) void k_rebin_admit(RebinArgs A) {
 // ---------------------------------------------------------------------------
 // launch wrappers (host side)
 // ---------------------------------------------------------------------------
+// the joint sampler's part of step_lds_bytes
+size_t step_joint_lds_bytes(const Tables &T, int block) {
+  return T.sampler_scratch & 2u ? sizeof(JointJob) * (size_t)block : 0;
+}
+
 size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block) {
   const uint32_t ns = T.n_species, nr = T.n_reactions;
   size_t b = sizeof(SpeciesTab) * ns + sizeof(PairTab) * ns * ns + sizeof(ReactionTab) * nr + 8 * (size_t)(T.n_levels ? T.n_levels : 1);
   b += sizeof(CellHdr) * max_cells + 2 * 8 * (size_t)(8 + nr) * max_cells;
   b += (size_t)2 * ((T.sampler_scratch ? 2 : 0) + 3) * (T.max_modes ? T.max_modes : 1) * block;
-  if (T.sampler_scratch & 2u) b = ((b + 7) & ~(size_t)7) + sizeof(JointJob) * (size_t)block;
+  b = ((b + 7) & ~(size_t)7) + step_joint_lds_bytes(T, block);
   return (b + 15) & ~(size_t)15;
 }
 

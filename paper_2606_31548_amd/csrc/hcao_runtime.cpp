@@ -39,6 +39,7 @@ struct Range {
 namespace hcao {
 // kernels (hcao_kernels.hip)
 size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block);
+size_t step_joint_lds_bytes(const Tables &T, int block);
 hipError_t launch_step(const StepArgs &a, size_t lds, int block, bool mixed, int level, uint32_t n_groups,
                        hipStream_t s);
 hipError_t set_step_lds_limit(size_t bytes);
@@ -89,7 +90,12 @@ namespace {
 
 constexpr double kB = 1.380649e-23;
 constexpr double kPi = 3.141592653589793;
-constexpr size_t kLdsBudget = 68 * 1024;  // LDS bytes per workgroup of the step kernel (64 KB of cells and tables, and the tables' single-precision columns)
+// LDS bytes per workgroup of the step kernel: 68 KB of cells, tables and
+// levels, and the joint sampler's slots besides (24 bytes per lane, 12 KB at
+// 512 lanes: two such workgroups still share a CU's 160 KB). What a context
+// may hold does not depend on its sampler's slots.
+constexpr size_t kLdsBudget = 68 * 1024;
+constexpr size_t kJointLdsMost = 24 * 1024;  // 1,024 lanes
 constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombination sum's stretch ladders
 constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups, and waves, a context is spread over
 constexpr uint32_t kShapeWaves = 4096;
@@ -638,6 +644,10 @@ hcao_status upload_bodies(hcao_ctx *c, const std::vector<double> &vx, const std:
 
 int step_level(const hcao_ctx *c);
 
+bool lds_fits(const hcao_ctx *c, uint32_t cells, int block) {
+  return step_lds_bytes(c->tab, cells, block) - step_joint_lds_bytes(c->tab, block) <= kLdsBudget;
+}
+
 // Workgroup size and slot target of the launches. A shape the caller set is
 // taken as it is. Otherwise the default (64 lanes, 1,024 slots) holds while it
 // gives the chip enough waves; a context too small for that gets smaller
@@ -664,7 +674,7 @@ void choose_shape(const hcao_ctx *c, int &block, uint32_t &group_slots) {
   const int widest = step_level(c) == 0 ? 1024 : 512;  // (the widest form is built for the plain step only)
   while (block < widest && groups * (uint64_t)block * 2 <= (uint64_t)kShapeWaves * 64 &&
          (uint64_t)block * 4 < std::max(group_slots, largest) &&
-         step_lds_bytes(c->tab, 1, 2 * block) <= kLdsBudget)
+         lds_fits(c, 1, 2 * block))
     block *= 2;
 }
 
@@ -680,7 +690,7 @@ hcao_status build_groups(hcao_ctx *c) {
   uint32_t group_slots = c->group_slots;
   choose_shape(c, c->run_block, group_slots);
   uint32_t cell_limit = kMaxGroupCells;
-  while (cell_limit > 0 && step_lds_bytes(c->tab, cell_limit, c->run_block) > kLdsBudget) --cell_limit;
+  while (cell_limit > 0 && !lds_fits(c, cell_limit, c->run_block)) --cell_limit;
   if (cell_limit == 0) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
   struct G {
     uint32_t c0, c1;
@@ -733,7 +743,8 @@ hcao_status build_groups(hcao_ctx *c) {
   HIP_TRY(c, hipMemcpyAsync(c->grp.p, grp.data(), grp.size() * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->grp_work.p, gw.data(), gw.size() * 8, hipMemcpyHostToDevice, c->stream));
   c->step_lds = step_lds_bytes(c->tab, c->max_group_cells, c->run_block);
-  if (c->step_lds > kLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
+  if (!lds_fits(c, c->max_group_cells, c->run_block))
+    return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
   return HCAO_OK;
 }
 
@@ -1464,7 +1475,7 @@ hcao_status hcao_finalize(hcao_ctx *c) {
   if (!c->lev_host.empty())
     HIP_TRY(c, hipMemcpyAsync(c->d_lev.p, c->lev_host.data(), c->lev_host.size() * sizeof(double),
                               hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, set_step_lds_limit(kLdsBudget));
+  HIP_TRY(c, set_step_lds_limit(kLdsBudget + kJointLdsMost));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->finalized = true;
   return HCAO_OK;

@@ -1,0 +1,49 @@
+"""Launch shapes at the edge of a workgroup's LDS: what a context may hold does
+not depend on the joint sampler's own slots."""
+import numpy as np
+import pytest
+
+from paper_2606_31548_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hc():
+    from paper_2606_31548_amd import hcao
+    hcao.load_library()
+    return hcao
+
+
+def _state(g):
+    return (*g.read_particles(), *g.cell_state())
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("how", ["call", "environment"])
+def test_joint_sampler_in_the_widest_workgroup(orc, hc, monkeypatch, precision, how):
+    """The five-species methane chemistry (54 KB of cells, tables and levels at
+    512 lanes) with a joint-sampled species besides."""
+    wl = W.methane_chemistry(n_cells=5, per_cell=301, t=15000.0)
+    wl.species[W.CH3].sampler = W.SAMPLER_JOINT
+    runs = []
+    for block in (64, 512):
+        if how == "environment":
+            monkeypatch.setenv("HCAO_BLOCK", str(block))
+            monkeypatch.setenv("HCAO_GROUP_SLOTS", "2048")
+        g = hc.from_workload(wl, precision=precision)
+        if how == "call":
+            g.set_launch_shape(block, 2048)
+        g.init_thermal(wl.counts, wl.t_trans, wl.t_vib)
+        g.step(wl.dt, 5)
+        runs.append(_state(g))
+        g.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*runs))
+    if precision == 0:
+        o = orc.from_workload(wl)
+        o.init_thermal(wl.counts, wl.t_trans, wl.t_vib)
+        o.step(wl.dt, 5)
+        oc, osp, ov, ol = o.read_all()
+        c, s, v, l = runs[1][:4]
+        assert np.array_equal(c, oc) and np.array_equal(s, osp) and np.array_equal(l, ol)
+        assert np.array_equal(v.view(np.uint64), ov.view(np.uint64))
