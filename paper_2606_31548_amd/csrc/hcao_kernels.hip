@@ -16,6 +16,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "hcao_tables.h"
 
 namespace hcao {
@@ -4002,6 +4004,38 @@ size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block) {
 }
 
 template <bool MIX, int EX>
+static const void *step_kernel(int block) {
+  switch (block) {
+    case 64: return (const void *)k_step<64, MIX, EX>;
+    case 128: return (const void *)k_step<128, MIX, EX>;
+    case 256: return (const void *)k_step<256, MIX, EX>;
+    case 512: return (const void *)k_step<512, MIX, EX>;
+    case 1024:
+      if constexpr (EX == 0) return (const void *)k_step<1024, MIX, EX>;
+      return nullptr;
+    default: return nullptr;
+  }
+}
+
+// Step workgroups of this size that a CU holds at once (0: not launchable).
+// LDS is given out in pieces of 1,280 bytes (160 KB / 128), which the
+// occupancy query does not count.
+int step_blocks_per_cu(size_t lds, int block, bool mixed, int level) {
+  const void *f = level >= 2 ? (mixed ? step_kernel<true, 2>(block) : step_kernel<false, 2>(block))
+                  : level == 1 ? (mixed ? step_kernel<true, 1>(block) : step_kernel<false, 1>(block))
+                               : (mixed ? step_kernel<true, 0>(block) : step_kernel<false, 0>(block));
+  int n = 0;
+  hipFuncAttributes at{};
+  if (!f || hipFuncGetAttributes(&at, f) != hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, block, lds) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  constexpr size_t kPiece = 1280, kPieces = 128;
+  return std::min(n, (int)(kPieces / ((at.sharedSizeBytes + lds + kPiece - 1) / kPiece)));
+}
+
+template <bool MIX, int EX>
 static hipError_t launch_step_t(const StepArgs &a, size_t lds, int block, uint32_t n_groups, hipStream_t s) {
   switch (block) {
     case 64: hipLaunchKernelGGL((k_step<64, MIX, EX>), dim3(n_groups), dim3(64), lds, s, a); break;
@@ -4049,19 +4083,14 @@ hipError_t launch_advance(uint32_t *step, uint32_t n, hipStream_t s) {
 }
 
 // the dynamic LDS limit of every k_step instantiation the launcher can pick
-// (block sizes 64..512, both precisions, levels 0..2)
+// (block sizes 64..512, both precisions, levels 0..2, and 1,024 at level 0)
 template <bool MIX, int EX>
 static hipError_t set_lds_limit_level(int bytes) {
   hipError_t e = hipSuccess;
-  const void *fns[] = {(const void *)k_step<64, MIX, EX>, (const void *)k_step<128, MIX, EX>,
-                       (const void *)k_step<256, MIX, EX>, (const void *)k_step<512, MIX, EX>};
-  for (const void *f : fns) {
-    const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (r != hipSuccess) e = r;
-  }
-  if constexpr (EX == 0) {
+  for (int block = 64; block <= 1024; block *= 2) {
+    const void *f = step_kernel<MIX, EX>(block);
     const hipError_t r =
-        hipFuncSetAttribute((const void *)k_step<1024, MIX, EX>, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        f ? hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) : hipSuccess;
     if (r != hipSuccess) e = r;
   }
   return e;

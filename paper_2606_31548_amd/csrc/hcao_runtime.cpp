@@ -40,6 +40,7 @@ namespace hcao {
 // kernels (hcao_kernels.hip)
 size_t step_lds_bytes(const Tables &T, uint32_t max_cells, int block);
 size_t step_joint_lds_bytes(const Tables &T, int block);
+int step_blocks_per_cu(size_t lds, int block, bool mixed, int level);
 hipError_t launch_step(const StepArgs &a, size_t lds, int block, bool mixed, int level, uint32_t n_groups,
                        hipStream_t s);
 hipError_t set_step_lds_limit(size_t bytes);
@@ -97,8 +98,7 @@ constexpr double kPi = 3.141592653589793;
 constexpr size_t kLdsBudget = 68 * 1024;
 constexpr size_t kJointLdsMost = 24 * 1024;  // 1,024 lanes
 constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombination sum's stretch ladders
-constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups, and waves, a context is spread over
-constexpr uint32_t kShapeWaves = 4096;
+constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups a small context is spread over
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
 struct SpeciesHost {
@@ -648,60 +648,27 @@ bool lds_fits(const hcao_ctx *c, uint32_t cells, int block) {
   return step_lds_bytes(c->tab, cells, block) - step_joint_lds_bytes(c->tab, block) <= kLdsBudget;
 }
 
-// Workgroup size and slot target of the launches. A shape the caller set is
-// taken as it is. Otherwise the default (64 lanes, 1,024 slots) holds while it
-// gives the chip enough waves; a context too small for that gets smaller
-// groups, down to one cell each, and then wider workgroups, up to one lane per
-// possible candidate pair (a fourth of the slots: half are paired, and NTC
-// tests about half of those at most once (sigma g)_max has settled).
-// Methane/argon, 256 particles per cell, us per step: 4,096 cells 34 with the
-// default, 54 with a cell per group; 1,500 cells 28 to 30 with the default, 25
-// with smaller groups. One reservoir of 10,000 particles, 20 steps: 13.6 ms
-// with 64 lanes, 2.4 with 256, 1.4 with 1,024.
-void choose_shape(const hcao_ctx *c, int &block, uint32_t &group_slots) {
-  block = c->block;
-  group_slots = c->group_slots;
-  if (c->shape_set) return;
-  uint64_t slots = 0;
-  uint32_t largest = 0;
-  for (uint32_t cap : c->cap_host) {
-    slots += cap;
-    largest = std::max(largest, cap);
-  }
-  if (slots >= (uint64_t)kShapeGroups * group_slots) return;
-  group_slots = (uint32_t)std::max<uint64_t>(1, slots / kShapeGroups);
-  const uint64_t groups = std::max<uint64_t>(1, slots / std::max(group_slots, largest));
-  const int widest = step_level(c) == 0 ? 1024 : 512;  // (the widest form is built for the plain step only)
-  while (block < widest && groups * (uint64_t)block * 2 <= (uint64_t)kShapeWaves * 64 &&
-         (uint64_t)block * 4 < std::max(group_slots, largest) &&
-         lds_fits(c, 1, 2 * block))
-    block *= 2;
-}
+// a workgroup's run of cells [c0, c1), its work-list entries and its slots
+struct Group {
+  uint32_t c0, c1;
+  uint64_t w0, w1, slots;
+};
 
-// Workgroups of the step kernel: runs of consecutive cells of at most
-// kMaxGroupCells cells (fewer when the per-cell LDS records of a wide
-// workgroup would not fit) and about group_slots slots each. Workgroup w
-// takes cells [grp[2w], grp[2w+1]), work-list entries [grp_work[3w],
-// grp_work[3w+1]) (cap/2 + 1 per cell) and rounds from grp_work[3w+2] (one per
-// 64 work entries). Workgroups are dispatched longest
-// first (by slot capacity), so that the largest cells start earliest.
-hcao_status build_groups(hcao_ctx *c) {
+// Runs of consecutive cells of at most kMaxGroupCells cells (fewer when the
+// per-cell LDS records of a wide workgroup would not fit) and about
+// group_slots slots each; empty when not even one cell fits.
+std::vector<Group> pack_groups(const hcao_ctx *c, int block, uint32_t group_slots, uint32_t &max_cells) {
   const uint32_t nc = c->cfg.n_cells;
-  uint32_t group_slots = c->group_slots;
-  choose_shape(c, c->run_block, group_slots);
   uint32_t cell_limit = kMaxGroupCells;
-  while (cell_limit > 0 && !lds_fits(c, cell_limit, c->run_block)) --cell_limit;
-  if (cell_limit == 0) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
-  struct G {
-    uint32_t c0, c1;
-    uint64_t w0, w1, slots;
-  };
-  std::vector<G> groups;
+  while (cell_limit > 0 && !lds_fits(c, cell_limit, block)) --cell_limit;
+  std::vector<Group> groups;
+  if (cell_limit == 0) return groups;
   uint64_t slots = 0, wsum = 0, w0 = 0;
-  uint32_t in_group = 0, max_cells = 1, first = 0;
+  uint32_t in_group = 0, first = 0;
+  max_cells = 1;
   for (uint32_t i = 0; i < nc; ++i) {
     if (in_group > 0 && (in_group >= cell_limit || slots + c->cap_host[i] > group_slots)) {
-      groups.push_back(G{first, i, w0, wsum, slots});
+      groups.push_back(Group{first, i, w0, wsum, slots});
       max_cells = std::max(max_cells, in_group);
       in_group = 0;
       slots = 0;
@@ -712,13 +679,75 @@ hcao_status build_groups(hcao_ctx *c) {
     slots += c->cap_host[i];
     wsum += c->cap_host[i] / 2 + 1;
   }
-  groups.push_back(G{first, nc, w0, wsum, slots});
+  groups.push_back(Group{first, nc, w0, wsum, slots});
   max_cells = std::max(max_cells, in_group);
-  std::stable_sort(groups.begin(), groups.end(), [](const G &x, const G &y) { return x.slots > y.slots; });
+  return groups;
+}
+
+// Workgroup size and cells of the launches. A shape the caller set is taken as
+// it is. Otherwise a context starts from the default (64 lanes, 1,024 slots).
+// One of fewer than kShapeGroups such groups is spread over that many, down to
+// one cell each, and its workgroups are widened up to one lane per possible
+// candidate pair (a fourth of the slots: half are paired, and NTC tests about
+// half of those at most once (sigma g)_max has settled). Larger ones keep the
+// default's groups and are widened where a cell is large: while a lane has
+// sixteen slots. Either way the chip has to hold all workgroups at once, counted
+// as packed: a second round of them costs as much as the first.
+// us per step in fp64: 2,975 chemistry cells of 256 particles 45 in 1,488 groups
+// of 64 or 128 lanes, 68 in 2,975 groups (2,560 fit), and 1,536 of them 38 in
+// 128 lanes, 64 in 256; 1,500 methane/argon cells 28 with the default, 25 with
+// smaller groups; 200 reservoirs of 10,000 particles 345 with 64 lanes, 64 with
+// 512. One reservoir of 10,000 particles, 20 steps: 13.6 ms with 64 lanes, 2.4
+// with 256, 1.4 with 1,024.
+std::vector<Group> choose_shape(const hcao_ctx *c, int &block, uint32_t &max_cells) {
+  block = c->block;
+  std::vector<Group> groups = pack_groups(c, block, c->group_slots, max_cells);
+  if (c->shape_set || groups.empty()) return groups;
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return groups;
+  }
+  const int level = step_level(c);
+  auto resident = [&](size_t n, int lanes, uint32_t cells) {
+    return n <= (size_t)cus * step_blocks_per_cu(step_lds_bytes(c->tab, cells, lanes), lanes, c->mixed, level);
+  };
+  uint64_t slots = 0;
+  for (uint32_t cap : c->cap_host) slots += cap;
+  const bool small = slots < (uint64_t)kShapeGroups * c->group_slots;
+  if (small) {
+    uint32_t cells = 1;
+    std::vector<Group> smaller =
+        pack_groups(c, block, (uint32_t)std::max<uint64_t>(1, slots / kShapeGroups), cells);
+    if (resident(smaller.size(), block, cells)) {
+      groups = std::move(smaller);
+      max_cells = cells;
+    }
+  }
+  uint64_t largest = 0;
+  for (const Group &g : groups) largest = std::max(largest, g.slots);
+  const int widest = level == 0 ? 1024 : 512;  // (the widest form is built for the plain step only)
+  while (block < widest && (small ? 4 * (uint64_t)block < largest : 16 * (uint64_t)block <= largest) &&
+         lds_fits(c, max_cells, 2 * block) && resident(groups.size(), 2 * block, max_cells))
+    block *= 2;
+  return groups;
+}
+
+// Workgroups of the step kernel (choose_shape). Workgroup w takes cells
+// [grp[2w], grp[2w+1]), work-list entries [grp_work[3w], grp_work[3w+1])
+// (cap/2 + 1 per cell) and rounds from grp_work[3w+2] (one per 64 work
+// entries). Workgroups are dispatched longest first (by slot capacity), so
+// that the largest cells start earliest.
+hcao_status build_groups(hcao_ctx *c) {
+  uint32_t max_cells = 1;
+  std::vector<Group> groups = choose_shape(c, c->run_block, max_cells);
+  if (groups.empty()) return fail(c, HCAO_EUNSUPPORTED, "step kernel LDS budget exceeded");
+  const uint64_t wsum = groups.back().w1;
+  std::stable_sort(groups.begin(), groups.end(), [](const Group &x, const Group &y) { return x.slots > y.slots; });
   std::vector<uint32_t> grp;
   std::vector<uint64_t> gw;
   uint64_t rounds = 0;
-  for (const G &g : groups) {
+  for (const Group &g : groups) {
     grp.push_back(g.c0);
     grp.push_back(g.c1);
     gw.push_back(g.w0);
