@@ -338,10 +338,11 @@ hcao_status hcao_step(hcao_ctx *ctx, double dt, uint32_t n_steps);
  *     keeping its cells' state in LDS between them (0 = all steps of a call).
  * Defaults 64, 1024, 0; the environment variables HCAO_BLOCK,
  * HCAO_GROUP_SLOTS and HCAO_STEPS_PER_LAUNCH override them at create time.
- * Until block or group_slots is given (here, by the autotuner or in the
- * environment), a context with too few slots to fill the GPU at the defaults
- * runs in smaller groups of cells and wider workgroups of the library's
- * choice; hcao_get_launch_shape reports the defaults.
+ * Block 64 with group_slots 1024 asks for the automatic choice: those, or, for
+ * a context that does not fill the GPU with them, smaller groups of cells and
+ * wider workgroups (up to 1,024 lanes). hcao_get_launch_shape reports the shape
+ * as set, so setting what it returned changes nothing. Any other shape is taken
+ * as it is.
  * hcao_set_launch_shape waits for the stream; it returns HCAO_EINVAL for a
  * block size not listed or group_slots = 0. */
 typedef struct {
@@ -353,10 +354,10 @@ hcao_status hcao_get_launch_shape(const hcao_ctx *ctx, hcao_launch_shape *shape)
 hcao_status hcao_set_launch_shape(hcao_ctx *ctx, const hcao_launch_shape *shape);
 
 /* Autotuner of the launch shape: times trial_steps steps of every candidate
- * (block 64, 128, 256 x group_slots 256 .. 6144) from a device copy of the
- * current state advanced by max(trial_steps, 10) steps (so that the first
- * steps' settling (sigma g)_max does not decide), puts the state back, and
- * keeps the fastest candidate. Trials shorter than one launch
+ * (block 64, 128, 256 x group_slots 256 .. 6144, the automatic choice among
+ * them as 64 x 1024) from a device copy of the current state advanced by
+ * max(trial_steps, 10) steps (so that the first steps' settling (sigma g)_max
+ * does not decide), puts the state back, and keeps the fastest candidate. Trials shorter than one launch
  * (steps_per_launch) weigh a launch's start and tail more than the timed
  * configuration does and can prefer larger workgroups (on the 67 M-particle
  * chemistry: 5-step trials choose 4096 slots, 50-step trials 2048, the

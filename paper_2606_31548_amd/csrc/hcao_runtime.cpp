@@ -98,6 +98,8 @@ constexpr double kPi = 3.141592653589793;
 constexpr size_t kLdsBudget = 68 * 1024;
 constexpr size_t kJointLdsMost = 24 * 1024;  // 1,024 lanes
 constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombination sum's stretch ladders
+constexpr int kDefaultBlock = 64;  // launch shape; the pair of them stands for the automatic choice (choose_shape)
+constexpr uint32_t kDefaultSlots = 1024;
 constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups a small context is spread over
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
@@ -299,9 +301,8 @@ struct hcao_ctx {
   uint64_t work_entries = 0;  // entries of work / bflag / wdef
   uint32_t n_groups = 0, max_group_cells = 1;
   size_t step_lds = 0;
-  int block = 64;
-  uint32_t group_slots = 1024;  // target slot capacity per workgroup
-  bool shape_set = false;       // block or group_slots given by the caller (or the environment)
+  int block = kDefaultBlock;
+  uint32_t group_slots = kDefaultSlots;  // target slot capacity per workgroup
   int run_block = 64;           // workgroup size of the launches (choose_shape)
   uint32_t step = 0;
   bool timing = false;
@@ -684,25 +685,30 @@ std::vector<Group> pack_groups(const hcao_ctx *c, int block, uint32_t group_slot
   return groups;
 }
 
-// Workgroup size and cells of the launches. A shape the caller set is taken as
-// it is. Otherwise a context starts from the default (64 lanes, 1,024 slots).
-// One of fewer than kShapeGroups such groups is spread over that many, down to
-// one cell each, and its workgroups are widened up to one lane per possible
-// candidate pair (a fourth of the slots: half are paired, and NTC tests about
-// half of those at most once (sigma g)_max has settled). Larger ones keep the
-// default's groups and are widened where a cell is large: while a lane has
-// sixteen slots. Either way the chip has to hold all workgroups at once, counted
-// as packed: a second round of them costs as much as the first.
+// Workgroup size and cells of the launches. A shape other than the default (64
+// lanes, 1,024 slots) is taken as it is. The default stands for the library's
+// choice, however it was set, so that a program that sets what it read (or what
+// the autotuner chose) gets the same launches again.
+//
+// The choice starts from the default's groups. A context of fewer than
+// kShapeGroups of them is spread over that many, down to one cell each, and its
+// workgroups are widened up to one lane per possible candidate pair (a fourth of
+// the slots: half are paired, and NTC tests about half of those at most once
+// (sigma g)_max has settled). Larger ones keep the default's groups and are
+// widened where a cell is large: while a lane has sixteen slots. Either way the
+// chip has to hold all workgroups at once, counted as packed: a second round of
+// them costs as much as the first.
+//
 // us per step in fp64: 2,975 chemistry cells of 256 particles 45 in 1,488 groups
 // of 64 or 128 lanes, 68 in 2,975 groups (2,560 fit), and 1,536 of them 38 in
 // 128 lanes, 64 in 256; 1,500 methane/argon cells 28 with the default, 25 with
-// smaller groups; 200 reservoirs of 10,000 particles 345 with 64 lanes, 64 with
+// smaller groups; 200 reservoirs of 10,000 particles 342 with 64 lanes, 63 with
 // 512. One reservoir of 10,000 particles, 20 steps: 13.6 ms with 64 lanes, 2.4
 // with 256, 1.4 with 1,024.
 std::vector<Group> choose_shape(const hcao_ctx *c, int &block, uint32_t &max_cells) {
   block = c->block;
   std::vector<Group> groups = pack_groups(c, block, c->group_slots, max_cells);
-  if (c->shape_set || groups.empty()) return groups;
+  if (block != kDefaultBlock || c->group_slots != kDefaultSlots || groups.empty()) return groups;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
     (void)hipGetLastError();
@@ -1138,10 +1144,7 @@ hcao_status hcao_create(const hcao_config *cfg, hcao_ctx **out) {
   c->stream = (hipStream_t)cfg->hip_stream;
   if (const char *b = std::getenv("HCAO_BLOCK")) {
     const int v = std::atoi(b);
-    if (v == 64 || v == 128 || v == 256 || v == 512) {
-      c->block = v;
-      c->shape_set = true;
-    }
+    if (v == 64 || v == 128 || v == 256 || v == 512) c->block = v;
   }
   if (const char *k = std::getenv("HCAO_STEPS_PER_LAUNCH")) {
     const long v = std::atol(k);
@@ -1149,10 +1152,7 @@ hcao_status hcao_create(const hcao_config *cfg, hcao_ctx **out) {
   }
   if (const char *g = std::getenv("HCAO_GROUP_SLOTS")) {
     const long v = std::atol(g);
-    if (v >= 1 && v <= (1L << 30)) {
-      c->group_slots = (uint32_t)v;
-      c->shape_set = true;
-    }
+    if (v >= 1 && v <= (1L << 30)) c->group_slots = (uint32_t)v;
   }
   const char *step = "hipSetDevice";
   hipError_t e = hipSetDevice(c->device);
@@ -2006,17 +2006,14 @@ hcao_status hcao_set_launch_shape(hcao_ctx *c, const hcao_launch_shape *shape) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   const int old_block = c->block;
   const uint32_t old_slots = c->group_slots;
-  const bool old_set = c->shape_set;
   c->block = (int)b;
   c->group_slots = shape->group_slots;
-  c->shape_set = true;
   c->steps_per_launch = shape->steps_per_launch ? shape->steps_per_launch : (1u << 30);
   ++c->shape_gen;
   if (c->loaded) {
     if (hcao_status s = build_groups(c)) {
       c->block = old_block;
       c->group_slots = old_slots;
-      c->shape_set = old_set;
       (void)build_groups(c);
       return s;
     }
@@ -2138,7 +2135,6 @@ hcao_status hcao_autotune(hcao_ctx *c, double dt, uint32_t trial_steps, const ch
     Snapshot S, W;
     if (hcao_status s = snapshot(c, S, true)) return s;
     const hcao_launch_shape orig{(uint32_t)c->block, c->group_slots, spl >= (1u << 30) ? 0u : spl};
-    const bool orig_set = c->shape_set;
     const bool was_timing = c->timing;
     double best_ms = 0.0;
     // candidates are timed from a copy advanced past the first steps, whose
@@ -2151,6 +2147,7 @@ hcao_status hcao_autotune(hcao_ctx *c, double dt, uint32_t trial_steps, const ch
       HIP_TRY(c, hipStreamSynchronize(c->stream));
       if (hcao_status e = read_err(c)) return e;
       if (hcao_status s = snapshot(c, W, true)) return s;
+      // (the default among them times the automatic choice)
       const uint32_t blocks[] = {64, 128, 256};
       const uint32_t slots[] = {256, 512, 1024, 1536, 2048, 2560, 3072, 3584, 4096, 6144};
       for (uint32_t b : blocks) {
@@ -2184,14 +2181,7 @@ hcao_status hcao_autotune(hcao_ctx *c, double dt, uint32_t trial_steps, const ch
     c->timing = was_timing;
     const hcao_status back = snapshot(c, S, false);
     if (tried != HCAO_OK) {
-      if (c->sticky == HCAO_OK) {
-        c->shape_set = orig_set;
-        (void)hcao_set_launch_shape(c, &orig);
-        if (!orig_set) {
-          c->shape_set = false;  // the default shape again
-          (void)build_groups(c);
-        }
-      }
+      if (c->sticky == HCAO_OK) (void)hcao_set_launch_shape(c, &orig);
       return tried;
     }
     if (back != HCAO_OK) return back;

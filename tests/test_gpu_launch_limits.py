@@ -76,3 +76,37 @@ def test_automatic_shape_fits_the_chip(hc, cells, per_cell, exact):
             times.append(g.kernel_time()[0])
         best.append(min(times))
     assert best[0] < 1.2 * best[1], best
+
+
+def _step_ms(g, wl, steps=20):
+    g.step(wl.dt, steps)
+    g.sync()
+    times = []
+    for _ in range(5):
+        g.set_timing(True)
+        g.step(wl.dt, steps)
+        g.sync()
+        times.append(g.kernel_time()[0])
+    return min(times)
+
+
+def test_default_shape_can_be_read_set_and_tuned(hc):
+    """One reservoir, which the default shape runs 1,024 lanes wide: setting the
+    shape that was read, going back to it and tuning keep that speed (256 lanes
+    take 1.7 times as long, 64 take six times)."""
+    wl = W.triatomic_reservoir(10000, seed=4)
+    g = hc.from_workload(wl)
+    g.init_thermal(wl.counts, wl.t_trans, wl.t_vib)
+    g.step(wl.dt, 20)
+    first = _step_ms(g, wl)
+    shape = g.launch_shape()
+    assert shape == {"block": 64, "group_slots": 1024, "steps_per_launch": 0}
+    g.set_launch_shape(**shape)
+    assert _step_ms(g, wl) < 1.15 * first
+    g.set_launch_shape(128, 2560)
+    g.set_launch_shape(**shape)
+    assert _step_ms(g, wl) < 1.15 * first
+    tuned = g.autotune(wl.dt, trial_steps=20)
+    assert _step_ms(g, wl) < 1.15 * first
+    g.set_launch_shape(**tuned)
+    assert _step_ms(g, wl) < 1.15 * first
