@@ -3432,25 +3432,24 @@ __device__ __forceinline__ uint32_t axis_index(double x, double len, uint32_t n)
   return (uint32_t)f;
 }
 
-// one wave per cell, four cells per workgroup; ranks in slot order come from
-// ballots. Bandwidth bound; kMovePer slots per lane are loaded together. (8.0 M
-// particles in the mixed form, 200 per cell: 110 us with a workgroup of four
-// waves per cell, which meets twice per 256 slots, 91 like this, 119 with four
-// slots per lane; 67.1 M in fp64, 256 per cell: 1.01, 1.05 and 1.08 ms.)
-constexpr uint32_t kMovePer = 2;
-__global__ __launch_bounds__(256) void k_move(MoveArgs A) {
-  const uint32_t c = blockIdx.x * 4u + (threadIdx.x >> 6), lane = threadIdx.x & 63u;
-  if (c >= A.n_cells) return;
+// The move of one cell by WAVES waves (wave w of them): slots in chunks of 64
+// PER per wave, ranks in slot order from ballots and, with several waves,
+// their totals of the chunk in LDS (s_cnt, used in turn so that one barrier per
+// chunk does).
+template <uint32_t WAVES, uint32_t PER>
+__device__ __forceinline__ void move_cell(const MoveArgs &A, uint32_t c, uint32_t w, uint32_t lane,
+                                          uint32_t (*s_cnt)[2][4], uint32_t &turn) {
   const uint64_t base = A.off[c];
   const uint32_t n = A.cnt[c], top = A.cap[c] - 1u;
   const uint64_t below_lane = (1ull << lane) - 1ull;
   uint32_t run_s = 0, run_m = 0;
-  for (uint32_t i0 = 0; i0 < n; i0 += 64 * kMovePer) {
-    Vec3 v[kMovePer];
-    double x[kMovePer], y[kMovePer], z[kMovePer];
+  for (uint32_t i0 = 0; i0 < n; i0 += 64 * PER * WAVES) {
+    Vec3 v[PER];
+    double x[PER], y[PER], z[PER];
+    const uint32_t first = i0 + 64 * PER * w + lane;
 #pragma unroll
-    for (uint32_t q = 0; q < kMovePer; ++q) {
-      const uint32_t i = i0 + 64 * q + lane;
+    for (uint32_t q = 0; q < PER; ++q) {
+      const uint32_t i = first + 64 * q;
       if (i < n) {
         const uint64_t g = base + i;
         v[q] = load_body(A.st, g).v;
@@ -3459,40 +3458,97 @@ __global__ __launch_bounds__(256) void k_move(MoveArgs A) {
         z[q] = A.st.pz[g];
       }
     }
+    uint64_t bm[PER], bs[PER];
+    uint32_t key[PER], ms = 0, ss = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < kMovePer; ++q) {
-      const uint32_t i = i0 + 64 * q + lane;
+    for (uint32_t q = 0; q < PER; ++q) {
+      const uint32_t i = first + 64 * q;
       bool mover = false, stayer = false;
-      uint32_t key = 0;
+      key[q] = 0;
       if (i < n) {
         bool flip = false;
         // the moved state is not stored: the place pass moves the particle
         // again as it copies it (the same arithmetic, so the same bits)
         if (!move_particle(x[q], y[q], z[q], v[q].x, v[q].y, v[q].z, A.dt, A.len, A.periodic, A.open, flip)) {
-          key = axis_index(x[q], A.len[0], A.nx) +
-                A.nx * (axis_index(y[q], A.len[1], A.ny) + A.ny * axis_index(z[q], A.len[2], A.nz));
-          mover = key != c;
+          key[q] = axis_index(x[q], A.len[0], A.nx) +
+                   A.nx * (axis_index(y[q], A.len[1], A.ny) + A.ny * axis_index(z[q], A.len[2], A.nz));
+          mover = key[q] != c;
           stayer = !mover;
         }
       }
-      const uint64_t bm = __ballot(mover), bs = __ballot(stayer);
-      // stayer ranks count up from the first slot, mover ranks down from the
-      // last: together they never pass n <= cap entries
-      if (mover) {
-        const uint64_t at = base + top - (run_m + (uint32_t)__popcll(bm & below_lane));
-        A.list[at] = i;
-        A.key[at] = key;
+      bm[q] = __ballot(mover);
+      bs[q] = __ballot(stayer);
+      ms += (uint32_t)__popcll(bm[q]);
+      ss += (uint32_t)__popcll(bs[q]);
+    }
+    uint32_t pre_s = run_s, pre_m = run_m;
+    if constexpr (WAVES > 1) {
+      uint32_t(*t)[4] = s_cnt[turn & 1u];
+      ++turn;
+      if (lane == 0) {
+        t[0][w] = ss;
+        t[1][w] = ms;
       }
-      if (stayer) A.list[base + run_s + (uint32_t)__popcll(bs & below_lane)] = i;
-      run_s += (uint32_t)__popcll(bs);
-      run_m += (uint32_t)__popcll(bm);
+      __syncthreads();
+#pragma unroll
+      for (uint32_t u = 0; u < WAVES; ++u) {
+        if (u < w) {
+          pre_s += t[0][u];
+          pre_m += t[1][u];
+        }
+        run_s += t[0][u];
+        run_m += t[1][u];
+      }
+    } else {
+      run_s += ss;
+      run_m += ms;
+    }
+    // stayer ranks count up from the first slot, mover ranks down from the
+    // last: together they never pass n <= cap entries
+#pragma unroll
+    for (uint32_t q = 0; q < PER; ++q) {
+      const uint32_t i = first + 64 * q;
+      if ((bm[q] >> lane) & 1ull) {
+        const uint64_t at = base + top - (pre_m + (uint32_t)__popcll(bm[q] & below_lane));
+        A.list[at] = i;
+        A.key[at] = key[q];
+      }
+      if ((bs[q] >> lane) & 1ull) A.list[base + pre_s + (uint32_t)__popcll(bs[q] & below_lane)] = i;
+      pre_s += (uint32_t)__popcll(bs[q]);
+      pre_m += (uint32_t)__popcll(bm[q]);
     }
   }
-  if (lane == 0) {
+  if (lane == 0 && w == 0) {
     A.n_stay[c] = run_s;
     A.n_move[c] = run_m;
     const uint32_t gone = n - run_s - run_m;
     if (gone && A.flux) atomicAdd(&A.flux[1], (unsigned long long)gone);
+  }
+}
+
+// Bandwidth bound. CELLS 1: four waves per cell, one slot per lane and chunk.
+// CELLS 4: one wave per cell with two slots per lane, for many small cells; a
+// cell of more than kMoveBig particles still takes the workgroup's four waves.
+// us with CELLS 1 and 4: fp64, 262,144 cells of 100: 559, 401; of 256: 855, 850;
+// 40,095 of 200: 108, 114; 32,768 of 600: 245, 263. Mixed, 262,144 of 256: 886,
+// 713; 40,095 of 200: 107, 100; 32,768 of 400: 151, 151; of 600: 210, 217. Few
+// cells leave the chip idle in fours: 4,096 of 100 10.9, 10.6; 1,728 of 200 8.1,
+// 10.4; 512 of 600 8.3, 18; 64 of 100,000 634, 2,519.
+constexpr uint32_t kMoveBig = 1024;      // particles
+constexpr uint32_t kMoveManyCells = 4096;
+constexpr uint32_t kMoveSmall64 = 160, kMoveSmall32 = 384;  // mean particles per cell, fp64 and mixed form
+template <uint32_t CELLS>
+__global__ __launch_bounds__(256) void k_move(MoveArgs A) {
+  __shared__ uint32_t s_cnt[2][2][4];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
+  const uint32_t c0 = blockIdx.x * CELLS;
+  uint32_t turn = 0;
+  if constexpr (CELLS == 1) {
+    move_cell<4, 1>(A, c0, wave, lane, s_cnt, turn);
+  } else {
+    if (c0 + wave < A.n_cells && A.cnt[c0 + wave] <= kMoveBig) move_cell<1, 2>(A, c0 + wave, 0, lane, s_cnt, turn);
+    for (uint32_t q = 0; q < CELLS && c0 + q < A.n_cells; ++q)
+      if (A.cnt[c0 + q] > kMoveBig) move_cell<4, 1>(A, c0 + q, wave, lane, s_cnt, turn);
   }
 }
 
@@ -4237,7 +4293,11 @@ hipError_t launch_move(const MoveArgs &a, hipStream_t s) {
   if (a.n_cells == 0) return hipSuccess;
   if (!a.off || !a.cnt || !a.cap || !a.key || !a.list || !a.n_stay || !a.n_move || !a.st.px || !a.st.py || !a.st.pz)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_move, dim3((a.n_cells + 3u) / 4u), dim3(256), 0, s, a);
+  const uint64_t small = a.st.b32 ? kMoveSmall32 : kMoveSmall64;
+  if (a.n_cells >= kMoveManyCells && a.particles <= small * a.n_cells)
+    hipLaunchKernelGGL(k_move<4>, dim3((a.n_cells + 3u) / 4u), dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_move<1>, dim3(a.n_cells), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

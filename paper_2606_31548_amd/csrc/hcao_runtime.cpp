@@ -256,6 +256,7 @@ struct hcao_ctx {
   DevBuf<double> d_lev;
   // particle state
   uint64_t total_slots = 0;
+  uint64_t loaded_particles = 0;  // of the last load, init or restore
   std::vector<uint32_t> cap_host;
   std::vector<uint64_t> off_host;
   bool mixed = false;                         // fp32 velocities (mixed form)
@@ -853,6 +854,8 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   }
   c->off_host[nc] = tot;
   c->total_slots = tot;
+  c->loaded_particles = 0;
+  for (uint32_t n : counts) c->loaded_particles += n;
   // the spatial re-bin keeps old slots as 32-bit indices
   if (c->spatial && tot > 0xFFFFFFFFull) return fail(c, HCAO_EINVAL, "spatial mode holds at most 2^32 - 1 slots");
   const uint32_t mm = c->max_modes ? c->max_modes : 1;
@@ -1686,6 +1689,7 @@ hcao_status move_rebin(hcao_ctx *c, double dt, uint32_t step, hipStream_t s) {
   m.off = c->off.p;
   m.cnt = c->cnt.p;
   m.cap = c->cap.p;
+  m.particles = c->loaded_particles;
   m.n_cells = nc;
   m.nx = c->grid[0];
   m.ny = c->grid[1];

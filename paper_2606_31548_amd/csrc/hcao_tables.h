@@ -250,6 +250,7 @@ struct MoveArgs {
   State st;
   const uint64_t *off;
   const uint32_t *cnt, *cap;
+  uint64_t particles;  // in the box when it was loaded
   uint32_t n_cells, nx, ny, nz, periodic, open;
   double len[3];
   double dt;
