@@ -57,7 +57,8 @@ hipError_t launch_rebin_place(const RebinArgs &a, hipStream_t s);
 hipError_t launch_cell_init(const Tables *tab, const State &st, const CellArrays &cells, uint32_t n_cells,
                             hipStream_t s);
 hipError_t launch_moments(const Tables *tab, const double *lev, const State &st, const uint64_t *off,
-                          const uint32_t *cnt, double *out, uint32_t n_cells, uint32_t ns, bool large, hipStream_t s);
+                          const uint32_t *cnt, const uint32_t *cap, double *out, uint32_t n_cells, uint32_t ns,
+                          bool large, const uint32_t *list, uint32_t n_list, hipStream_t s);
 hipError_t launch_moments_sum(const double *in, const double *weight, const double *defect, double *out,
                               uint32_t n_cells, uint32_t w, uint32_t ns, uint32_t blocks, hipStream_t s);
 hipError_t launch_thermometer(const Tables *tab, const double *lev, const double *mean, const double *in, double *t,
@@ -288,6 +289,8 @@ struct hcao_ctx {
   DevBuf<uint16_t> ilvl;
   DevBuf<uint64_t> off;
   DevBuf<uint32_t> cnt, cap;
+  DevBuf<uint32_t> large_cells;  // cells of more than kMomentsLarge slots, where the mean cell has fewer
+  uint32_t n_large = 0;
   DevBuf<double> d_volume, d_weight, sgmax, rem, defect;
   DevBuf<double> tsum;    // recombination: running sums of the cell temperature [5][n_cells]
   DevBuf<double> tdelta;  // recombination: each work entry's change of the running sums [5][work_entries]
@@ -536,6 +539,7 @@ void free_state(hcao_ctx *c) {
   c->off.release();
   c->cnt.release();
   c->cap.release();
+  c->large_cells.release();
   c->d_volume.release();
   c->d_weight.release();
   c->sgmax.release();
@@ -908,11 +912,22 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
                             c->stream));
   HIP_TRY(c, hipMemcpyAsync(c->d_weight.p, c->weight.data(), nc * sizeof(double), hipMemcpyHostToDevice,
                             c->stream));
+  std::vector<uint32_t> large;
+  if (tot <= (uint64_t)kMomentsLarge * nc)
+    for (uint32_t i = 0; i < nc; ++i)
+      if (c->cap_host[i] > kMomentsLarge) large.push_back(i);
+  c->n_large = 0;
+  if (!large.empty()) {
+    HIP_TRY(c, c->large_cells.alloc(large.size()));
+    HIP_TRY(c, hipMemcpyAsync(c->large_cells.p, large.data(), large.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
+                              c->stream));
+  }
   // products staging (indexed like the state)
   HIP_TRY(c, c->bbody.alloc(tot * body_bytes(c)));
   HIP_TRY(c, c->blvl.alloc(tot * level_row(mm)));
   if (hcao_status st = build_groups(c)) return st;
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  c->n_large = (uint32_t)large.size();
   return HCAO_OK;
 }
 
@@ -2329,14 +2344,12 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
   const uint32_t nc = c->cfg.n_cells, ns = (uint32_t)c->species.size();
   const uint32_t w = 6 + 3 * ns, cols = w + ns + 1;
   // eight waves per cell where a cell holds more than a wave's few rounds
-  uint64_t slots = 0;
-  for (uint32_t cap : c->cap_host) slots += cap;
-  const bool large = slots > 2048ull * nc;
+  const bool large = c->total_slots > (uint64_t)kMomentsLarge * nc;
   const uint32_t blocks = std::min(256u, (nc + 63u) / 64u);
   HIP_TRY(c, c->mom_raw.reserve((size_t)nc * w));
   HIP_TRY(c, c->mom_part.reserve((size_t)blocks * cols));
-  HIP_TRY(c, launch_moments(c->d_tab.p, c->d_lev.p, state_of(c), c->off.p, c->cnt.p, c->mom_raw.p, nc, ns, large,
-                            c->stream));
+  HIP_TRY(c, launch_moments(c->d_tab.p, c->d_lev.p, state_of(c), c->off.p, c->cnt.p, c->cap.p, c->mom_raw.p, nc, ns,
+                            large, c->n_large ? c->large_cells.p : nullptr, c->n_large, c->stream));
   HIP_TRY(c, launch_moments_sum(c->mom_raw.p, c->d_weight.p, c->defect.p, c->mom_part.p, nc, w, ns, blocks, c->stream));
   std::vector<double> part((size_t)blocks * cols), raw, df, tv;
   if (per_cell) {

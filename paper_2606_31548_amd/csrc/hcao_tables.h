@@ -111,6 +111,7 @@ constexpr uint64_t kStaticScratchBytes = HCAO_STATIC_SCRATCH_BYTES;
 // entries).
 constexpr uint64_t kStaticArrayBytes = kStaticScratchBytes + (16u << 20);
 
+constexpr uint32_t kMomentsLarge = 2048;  // slots: the moments of a larger cell take eight waves
 constexpr uint32_t kThermoNodes = 512;  // mean energies per species over log T, 1 .. 1e6 K
 constexpr uint32_t kRecNodes = 1024;
 constexpr double kRecTmin = 100.0;
