@@ -173,6 +173,86 @@ __global__ __launch_bounds__(256) void k_rec_enum(RecEnumArgs A) {
   }
 }
 
+// The same where no two modes are alike: every unit is one mode and every weight
+// 1. The walk meets each crossing as it counts a mode's levels up, needs no
+// search for it and carries only energies, and more threads share it (seven
+// modes, 4.9 M records, 256 temperatures: 129 ms with the walk above, 118
+// with this one; nine modes, 12.6 M: 431, 339).
+template <bool WRITE>
+__global__ __launch_bounds__(256) void k_rec_enum_distinct(RecEnumArgs A) {
+  const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (tid >= A.n_prefix) return;
+  const SpeciesTab &S = A.tab->sp[A.species];
+  const uint32_t nm = A.units.n, np = A.n_prefix_units;
+  uint32_t j[kMaxModes];
+  double st[kMaxModes + 1];
+  uint64_t x = tid;
+  for (uint32_t m = 0; m < np; ++m) {
+    j[m] = (uint32_t)(x % A.box[m]);
+    x /= A.box[m];
+  }
+  uint32_t n = 0;
+  const uint64_t o = WRITE ? A.offset[tid] : 0;
+  auto emit = [&](double e, uint32_t code) {
+    if (WRITE) {
+      A.rec_e[o + n] = e;
+      A.rec_code[o + n] = code;
+    }
+    ++n;
+  };
+  // the prefix: valid while below de; a crossing inside it is emitted once,
+  // by the prefix whose crossing level is the first one and whose later
+  // digits are 0
+  double s = 0.0;
+  bool walk = true;
+  for (uint32_t m = 0; m < np && walk; ++m) {
+    if (m >= S.n_bend && j[m] > S.idiss[m]) {
+      walk = false;
+      break;
+    }
+    const double s2 = s + level_above_ground(S, A.lev, m, j[m]);
+    if (!(s2 < A.de)) {
+      bool first = j[m] == 0 || s + level_above_ground(S, A.lev, m, j[m] - 1) < A.de;
+      for (uint32_t k = m + 1; k < np; ++k) first = first && j[k] == 0;
+      if (first) emit(s2, m | (j[m] << 8));
+      walk = false;
+      break;
+    }
+    s = s2;
+  }
+  if (walk && np == nm) emit(s, kRecLeaf);
+  if (walk && np < nm) {
+    uint32_t m = np;
+    j[m] = 0;
+    st[m] = s;
+    for (;;) {
+      bool back = false;
+      if (m >= S.n_bend && j[m] > S.idiss[m]) {
+        back = true;
+      } else {
+        const double s2 = st[m] + level_above_ground(S, A.lev, m, j[m]);
+        if (!(s2 < A.de)) {
+          emit(s2, m | (j[m] << 8));
+          back = true;
+        } else if (m + 1 == nm) {
+          emit(s2, kRecLeaf);
+          ++j[m];
+        } else {
+          st[m + 1] = s2;
+          j[m + 1] = 0;
+          ++m;
+        }
+      }
+      if (back) {
+        if (m == np) break;
+        --m;
+        ++j[m];
+      }
+    }
+  }
+  if (!WRITE) A.count[tid] = n;
+}
+
 // Regularized upper incomplete gamma Q(a, x) times exp(-y), x > 0 (series
 // for the lower function below x = a + 1, Lentz's continued fraction above;
 // Press et al., Numerical Recipes 6.2); the prefactor joins exp(-y) in one
@@ -206,6 +286,9 @@ __device__ double gamma_q_scaled(double a, double x, double lga, double y) {
   return exp(lpre - y) * h;
 }
 
+// (without WEIGHTED the units are the modes, every record's weight is 1 and
+// rec_w is not read)
+template <bool WEIGHTED>
 __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   double *tail = reinterpret_cast<double *>(smem);  // stretch levels: sum_{k >= j} exp(-beta (e_k - e_j))
@@ -214,8 +297,8 @@ __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
   const uint32_t nu = A.units.n, tid = threadIdx.x;
   const double beta = 1.0 / (kBoltz * A.t[blockIdx.x]);
   if (tid < nu) {
-    const uint32_t m = A.units.mode[tid], d = A.units.degree[tid];
-    if (d) {
+    const uint32_t m = WEIGHTED ? A.units.mode[tid] : tid, d = WEIGHTED ? A.units.degree[tid] : 1u;
+    if (WEIGHTED ? d > 0 : m < S.n_bend) {
       const double z = 1.0 / (1.0 - exp(-(beta * S.kt[m])));  // of one bend
       s_bend[tid] = z;
       double zz = 1.0;
@@ -246,8 +329,19 @@ __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
   __syncthreads();
   double acc = 0.0;
   for (uint64_t i = tid; i < A.n_rec; i += 256) {
-    const double e = A.rec_e[i], w = A.rec_w[i];
+    const double e = A.rec_e[i];
     const uint32_t code = A.rec_code[i];
+    if constexpr (!WEIGHTED) {
+      if (code == kRecLeaf) {
+        acc += gamma_q_scaled(A.a, beta * (A.de - e), A.lgamma_a, beta * e);
+      } else {
+        const uint32_t m = code & 0xFFu, jj = code >> 8;
+        const double rel = m < S.n_bend ? s_bend[m] : tail[(S.lev_off[m] - S.lev_off[S.n_bend]) + jj];
+        acc += (exp(-(beta * e)) * rel) * s_z[m + 1];
+      }
+      continue;
+    }
+    const double w = A.rec_w[i];
     if (code == kRecLeaf) {
       acc += w * gamma_q_scaled(A.a, beta * (A.de - e), A.lgamma_a, beta * e);
     } else {
@@ -286,16 +380,25 @@ __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
 hipError_t launch_rec_enum(const RecEnumArgs &a, bool write, hipStream_t s) {
   if (a.n_prefix == 0) return hipSuccess;
   const dim3 grid((unsigned)((a.n_prefix + 255) / 256));
-  if (write)
+  if (!a.n_full) {
+    if (write)
+      hipLaunchKernelGGL(k_rec_enum_distinct<true>, grid, dim3(256), 0, s, a);
+    else
+      hipLaunchKernelGGL(k_rec_enum_distinct<false>, grid, dim3(256), 0, s, a);
+  } else if (write) {
     hipLaunchKernelGGL(k_rec_enum<true>, grid, dim3(256), 0, s, a);
-  else
+  } else {
     hipLaunchKernelGGL(k_rec_enum<false>, grid, dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 
 hipError_t launch_rec_sum(const RecSumArgs &a, uint32_t n_t, size_t lds, hipStream_t s) {
   if (n_t == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_rec_sum, dim3(n_t), dim3(256), lds, s, a);
+  if (a.rec_w)
+    hipLaunchKernelGGL(k_rec_sum<true>, dim3(n_t), dim3(256), lds, s, a);
+  else
+    hipLaunchKernelGGL(k_rec_sum<false>, dim3(n_t), dim3(256), lds, s, a);
   return hipGetLastError();
 }
 

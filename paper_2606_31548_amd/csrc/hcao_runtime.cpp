@@ -1014,10 +1014,14 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
     }
   }
   if (n_sl * sizeof(double) > kRecLdsBudget) return fail(c, HCAO_EUNSUPPORTED, "stretch ladders too long for the exact sum");
+  bool weighted = U.n < nm;
+  for (uint32_t u = 0; u < U.n; ++u) weighted = weighted || U.same[u];
   // enough threads to fill the GPU; more only split the walk into idle prefixes
+  // (single combinations are so many that the longest walks count)
+  const uint64_t enough = 1ull << (weighted ? 17 : 22);
   uint64_t n_prefix = box[0];
   uint32_t np = 1;
-  while (np < U.n && n_prefix < (1ull << 17) && n_prefix * box[np] <= (1ull << 22)) n_prefix *= box[np++];
+  while (np < U.n && n_prefix < enough && n_prefix * box[np] <= (1ull << 22)) n_prefix *= box[np++];
   ea.units = U;
   ea.n_prefix_units = np;
   for (uint32_t u = 0; u < np; ++u) ea.box[u] = box[u];
@@ -1032,9 +1036,9 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
   HIP_TRY(c, hipEventCreate(&e0));
   HIP_TRY(c, hipEventCreate(&e1));
   HIP_TRY(c, hipEventRecord(e0, c->stream));
-  HIP_TRY(c, hipMemsetAsync(R.full.p, 0, sizeof(unsigned long long), c->stream));
+  if (weighted) HIP_TRY(c, hipMemsetAsync(R.full.p, 0, sizeof(unsigned long long), c->stream));
   ea.count = R.cnt.p;
-  ea.n_full = R.full.p;
+  ea.n_full = weighted ? R.full.p : nullptr;
   HIP_TRY(c, launch_rec_enum(ea, false, c->stream));
   HIP_TRY(c, launch_scan_u32(R.cnt.p, R.off.p, n_prefix, R.stmp.p, c->stream));
   uint64_t last_off = 0;
@@ -1042,15 +1046,16 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
   unsigned long long full = 0;
   HIP_TRY(c, hipMemcpyAsync(&last_off, R.off.p + (n_prefix - 1), sizeof(uint64_t), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipMemcpyAsync(&last_cnt, R.cnt.p + (n_prefix - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(&full, R.full.p, sizeof full, hipMemcpyDeviceToHost, c->stream));
+  if (weighted) HIP_TRY(c, hipMemcpyAsync(&full, R.full.p, sizeof full, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   const uint64_t total = last_off + last_cnt;
+  if (!weighted) full = total;
   HIP_TRY(c, R.e.reserve(total));
-  HIP_TRY(c, R.w.reserve(total));
+  if (weighted) HIP_TRY(c, R.w.reserve(total));
   HIP_TRY(c, R.code.reserve(total));
   ea.offset = R.off.p;
   ea.rec_e = R.e.p;
-  ea.rec_w = R.w.p;
+  ea.rec_w = weighted ? R.w.p : nullptr;
   ea.rec_code = R.code.p;
   HIP_TRY(c, launch_rec_enum(ea, true, c->stream));
   HIP_TRY(c, hipMemcpyAsync(R.t.p, t, n_t * sizeof(double), hipMemcpyHostToDevice, c->stream));
@@ -1064,7 +1069,7 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
   sa.lgamma_a = std::lgamma(sa.a);
   sa.t = R.t.p;
   sa.rec_e = R.e.p;
-  sa.rec_w = R.w.p;
+  sa.rec_w = ea.rec_w;
   sa.rec_code = R.code.p;
   sa.n_rec = total;
   sa.num = R.t.p + n_t;

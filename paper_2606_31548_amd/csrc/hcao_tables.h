@@ -346,7 +346,8 @@ struct RebinArgs {
 // units (mixed radix over box[]) and walks the rest depth first. With offset
 // == null it only counts a thread's records into count[i], and adds the
 // number of records an enumeration of single combinations would hold to
-// n_full.
+// n_full. Where no two modes are alike the units are the modes, every weight
+// is 1, and n_full and rec_w are null.
 constexpr uint32_t kRecLeaf = 0xFFu;
 
 struct RecUnits {
