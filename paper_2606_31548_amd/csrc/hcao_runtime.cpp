@@ -783,6 +783,7 @@ hcao_status build_groups(hcao_ctx *c) {
   HIP_TRY(c, c->grp.alloc(grp.size()));
   HIP_TRY(c, c->grp_work.alloc(gw.size()));
   if (c->work_entries != wsum) {
+    c->work_entries = 0;  // (until all of them are there: a failed allocation leaves some at another size)
     HIP_TRY(c, c->work.alloc((uint64_t)kWorkWords * wsum));  // the pairs as found, then sorted
     HIP_TRY(c, c->bflag.alloc(wsum));
     HIP_TRY(c, c->pv.alloc(wsum * 6 * (c->mixed ? sizeof(float) : sizeof(double))));
