@@ -13,10 +13,10 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <limits>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -431,7 +431,7 @@ hcao_status copy_out(hcao_ctx *c, void *dst, const void *src, size_t bytes) {
   };
   try {
     for (size_t t = 0; t < S; ++t) threads[t] = std::thread(work, t);
-  } catch (const std::system_error &) {  // no thread to be had
+  } catch (const std::exception &) {  // no thread to be had, or no memory for it
     finish();
     HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
     return HCAO_OK;
