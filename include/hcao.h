@@ -473,8 +473,9 @@ hcao_status hcao_get_exact_beta(const hcao_ctx *ctx, uint32_t species, uint32_t 
  * results repeat bitwise; they match a serial sum to rounding (~1e-13
  * relative). elapsed_ms and n_records (may be NULL) receive the device
  * time and the number of records (one per combination and crossing).
- * Allocates device memory for the entries (20 bytes each), which the context
- * keeps; synchronous on the context's stream. HCAO_EUNSUPPORTED
+ * Allocates device memory for the entries (20 bytes each; 12 where no two modes
+ * are alike), which the context keeps up to 512 MiB; synchronous on the
+ * context's stream. HCAO_EUNSUPPORTED
  * if the species' stretch ladders exceed 8192 levels in total. */
 hcao_status hcao_recombination_exact(hcao_ctx *ctx, uint32_t species, double de_J, double omega, uint32_t n_t,
                                      const double *t_K, double *p_out, double *elapsed_ms, uint64_t *n_records);

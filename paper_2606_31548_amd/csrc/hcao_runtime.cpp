@@ -144,12 +144,19 @@ struct DevBuf {
   }
 };
 
-// device scratch of the exact recombination sum, kept by the context
+constexpr size_t kScratchKept = 512u << 20;  // bytes of scratch a context keeps from one call for the next, per kind
+
+// device scratch of the exact recombination sum, kept by the context while it
+// is small
 struct RecScratch {
   DevBuf<uint32_t> cnt, code;
   DevBuf<uint64_t> off, stmp;
   DevBuf<unsigned long long> full;
   DevBuf<double> e, w, t;
+  size_t bytes() const { return 4 * (cnt.n + code.n) + 8 * (off.n + stmp.n + full.n + e.n + w.n + t.n); }
+  void trim() {
+    if (bytes() > kScratchKept) release();
+  }
   void release() {
     cnt.release();
     code.release();
@@ -191,7 +198,7 @@ struct LoadScratch {
     stmp.release();
   }
   void trim() {
-    if (bytes() > (512u << 20)) release();
+    if (bytes() > kScratchKept) release();
   }
 };
 constexpr uint64_t kPackChunk = 4u << 20;  // particles a read-back packs at once
@@ -1087,6 +1094,7 @@ hcao_status exact_rec_probability(hcao_ctx *c, uint32_t sp, double de, double om
   for (uint32_t i = 0; i < n_t; ++i) p[i] = sums[i] / sums[(size_t)n_t + i];
   if (ms) *ms = el;
   if (n_rec) *n_rec = full;
+  R.trim();
   return HCAO_OK;
 }
 
