@@ -3366,6 +3366,28 @@ __global__ __launch_bounds__(256) void k_pack(PackArgs A) {
   }
 }
 
+// The records of n slots from slot `first` on as arrays of fp64 velocities,
+// species and level rows of mm (a checkpoint's form), and back. On the host the
+// same took a third of a save or restore.
+__global__ __launch_bounds__(256) void k_slots_out(State st, uint64_t first, uint64_t n, uint32_t mm, double *vel,
+                                                   uint8_t *sp, uint16_t *lvl) {
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  const BodyOf<double> b = load_body(st, first + i);
+  vel[i] = b.v.x;
+  vel[n + i] = b.v.y;
+  vel[2 * n + i] = b.v.z;
+  sp[i] = (uint8_t)b.sp;
+  for (uint32_t m = 0; m < mm; ++m) lvl[i * mm + m] = st.lvl[(first + i) * st.lrow + m];
+}
+__global__ __launch_bounds__(256) void k_slots_in(State st, uint64_t first, uint64_t n, uint32_t mm, const double *vel,
+                                                  const uint8_t *sp, const uint16_t *lvl) {
+  const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  store_body(st, first + i, vel[i], vel[n + i], vel[2 * n + i], sp[i]);
+  for (uint32_t m = 0; m < st.lrow; ++m) st.lvl[(first + i) * st.lrow + m] = m < mm ? lvl[i * mm + m] : (uint16_t)0;
+}
+
 // advances the device step index after the launches of a graph replay
 __global__ void k_advance(uint32_t *step, uint32_t n) {
   if (threadIdx.x == 0) step[0] = step[0] + n;
@@ -4230,6 +4252,20 @@ hipError_t launch_pack(const State &st, const uint64_t *off, const uint64_t *sta
   if (c1 <= c0 || p1 <= p0) return hipSuccess;
   PackArgs a{st, off, start, cnt, sp, vel, lvl, p0, p1, c0, mm};
   hipLaunchKernelGGL(k_pack, dim3(c1 - c0), dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_slots_out(const State &st, uint64_t first, uint64_t n, uint32_t mm, double *vel, uint8_t *sp,
+                            uint16_t *lvl, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_slots_out, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, st, first, n, mm, vel, sp, lvl);
+  return hipGetLastError();
+}
+
+hipError_t launch_slots_in(const State &st, uint64_t first, uint64_t n, uint32_t mm, const double *vel,
+                           const uint8_t *sp, const uint16_t *lvl, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_slots_in, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, st, first, n, mm, vel, sp, lvl);
   return hipGetLastError();
 }
 

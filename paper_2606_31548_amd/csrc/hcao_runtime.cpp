@@ -66,6 +66,10 @@ hipError_t launch_thermometer(const Tables *tab, const double *lev, const double
 hipError_t launch_pack(const State &st, const uint64_t *off, const uint64_t *start, const uint32_t *cnt, uint8_t *sp,
                        double *vel, uint16_t *lvl, uint64_t p0, uint64_t p1, uint32_t c0, uint32_t c1, uint32_t mm,
                        hipStream_t s);
+hipError_t launch_slots_out(const State &st, uint64_t first, uint64_t n, uint32_t mm, double *vel, uint8_t *sp,
+                            uint16_t *lvl, hipStream_t s);
+hipError_t launch_slots_in(const State &st, uint64_t first, uint64_t n, uint32_t mm, const double *vel,
+                           const uint8_t *sp, const uint16_t *lvl, hipStream_t s);
 hipError_t launch_reaction_sum(const unsigned long long *ctr, uint32_t n_cells, uint32_t nr, unsigned long long *out,
                                hipStream_t s);
 hipError_t launch_load_check(const Tables *tab, const uint32_t *cell, const uint8_t *sp, const double *vel,
@@ -618,51 +622,60 @@ CellArrays cells_of(hcao_ctx *c) {
                     c->cfg.n_cells};
 }
 
-// velocities (as fp64) and species of n slots from slot `first` on
-// (synchronous)
-hcao_status download_bodies(hcao_ctx *c, uint64_t first, uint64_t n, double *vx, double *vy, double *vz, uint8_t *sp) {
-  const size_t b = body_bytes(c);
-  std::vector<uint8_t> raw(n * b);
-  HIP_TRY(c, hipMemcpyAsync(raw.data(), c->body.p + first * b, n * b, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (uint64_t i = 0; i < n; ++i) {
-    if (c->mixed) {
-      Body32 x;
-      std::memcpy(&x, raw.data() + i * b, b);
-      vx[i] = x.x;
-      vy[i] = x.y;
-      vz[i] = x.z;
-      sp[i] = (uint8_t)x.sp;
-    } else {
-      Body64 x;
-      std::memcpy(&x, raw.data() + i * b, b);
-      vx[i] = x.x;
-      vy[i] = x.y;
-      vz[i] = x.z;
-      sp[i] = (uint8_t)x.sp;
-    }
-  }
+// a checkpoint's arrays of the slots: fp64 velocities, species, and level rows
+// of max_modes (the device's rows are level_row long)
+struct SlotArrays {
+  std::vector<double> vx, vy, vz;
+  std::vector<uint8_t> sp;
+  std::vector<uint16_t> lv;
+  SlotArrays(uint64_t slots, uint32_t mm) : vx(slots), vy(slots), vz(slots), sp(slots), lv(slots * mm) {}
+};
+
+// the device scratch of a conversion of slots, and how many take it at a time
+hcao_status slot_scratch(hcao_ctx *c, uint32_t mm, uint64_t &chunk) {
+  chunk = std::min<uint64_t>(c->total_slots, kPackChunk);
+  HIP_TRY(c, c->io.vel.reserve(3 * chunk));
+  HIP_TRY(c, c->io.sp.reserve(chunk));
+  HIP_TRY(c, c->io.lvl.reserve(chunk * mm));
   return HCAO_OK;
 }
 
-// all slots from fp64 velocities (rounded to fp32 in the mixed form) and
-// species (synchronous)
-hcao_status upload_bodies(hcao_ctx *c, const std::vector<double> &vx, const std::vector<double> &vy,
-                          const std::vector<double> &vz, const std::vector<uint8_t> &sp) {
-  const uint64_t tot = c->total_slots;
-  const size_t b = body_bytes(c);
-  std::vector<uint8_t> raw(tot * b);
-  for (uint64_t i = 0; i < tot; ++i) {
-    if (c->mixed) {
-      const Body32 x{(float)vx[i], (float)vy[i], (float)vz[i], sp[i]};
-      std::memcpy(raw.data() + i * b, &x, b);
-    } else {
-      const Body64 x{vx[i], vy[i], vz[i], sp[i]};
-      std::memcpy(raw.data() + i * b, &x, b);
-    }
+// synchronous, as is the way back
+hcao_status download_slots(hcao_ctx *c, uint32_t mm, SlotArrays &A) {
+  LoadScratch &S = c->io;
+  uint64_t chunk = 0;
+  if (hcao_status s = slot_scratch(c, mm, chunk)) return s;
+  for (uint64_t p = 0; p < c->total_slots; p += chunk) {
+    const uint64_t n = std::min(chunk, c->total_slots - p);
+    HIP_TRY(c, launch_slots_out(state_of(c), p, n, mm, S.vel.p, S.sp.p, S.lvl.p, c->stream));
+    double *const to[] = {A.vx.data() + p, A.vy.data() + p, A.vz.data() + p};
+    for (int k = 0; k < 3; ++k)
+      if (hcao_status s = copy_out(c, to[k], S.vel.p + k * n, n * sizeof(double))) return s;
+    if (hcao_status s = copy_out(c, A.sp.data() + p, S.sp.p, n)) return s;
+    if (hcao_status s = copy_out(c, A.lv.data() + p * mm, S.lvl.p, n * mm * sizeof(uint16_t))) return s;
   }
-  HIP_TRY(c, hipMemcpyAsync(c->body.p, raw.data(), raw.size(), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
+  S.trim();
+  return HCAO_OK;
+}
+
+// (velocities rounded to fp32 in the mixed form)
+hcao_status upload_slots(hcao_ctx *c, uint32_t mm, const SlotArrays &A) {
+  LoadScratch &S = c->io;
+  uint64_t chunk = 0;
+  if (hcao_status s = slot_scratch(c, mm, chunk)) return s;
+  for (uint64_t p = 0; p < c->total_slots; p += chunk) {
+    const uint64_t n = std::min(chunk, c->total_slots - p);
+    const double *const from[] = {A.vx.data() + p, A.vy.data() + p, A.vz.data() + p};
+    for (int k = 0; k < 3; ++k)
+      HIP_TRY(c, hipMemcpyAsync(S.vel.p + k * n, from[k], n * sizeof(double), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(S.sp.p, A.sp.data() + p, n, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(S.lvl.p, A.lv.data() + p * mm, n * mm * sizeof(uint16_t), hipMemcpyHostToDevice,
+                              c->stream));
+    HIP_TRY(c, launch_slots_in(state_of(c), p, n, mm, S.vel.p, S.sp.p, S.lvl.p, c->stream));
+  }
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  S.trim();
   return HCAO_OK;
 }
 
@@ -2282,18 +2295,30 @@ hcao_status hcao_read_cell_particles(hcao_ctx *c, uint32_t cell, uint32_t max_n,
   if (n_out) *n_out = n;
   const uint32_t k = std::min(n, max_n);
   if (k == 0) return HCAO_OK;
-  std::vector<double> v(3 * (size_t)k);
+  const size_t bb = body_bytes(c);
   const uint32_t lr = level_row(c->max_modes);
+  std::vector<uint8_t> raw(k * bb);
   std::vector<uint16_t> lv((size_t)k * lr);
-  if (hcao_status s = download_bodies(c, b, k, v.data(), v.data() + k, v.data() + 2 * (size_t)k, species)) return s;
+  HIP_TRY(c, hipMemcpyAsync(raw.data(), c->body.p + b * bb, k * bb, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipMemcpyAsync(lv.data(), c->lvl.p + b * lr, (size_t)k * lr * 2, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  for (uint32_t i = 0; i < k; ++i) {
-    vel[3 * i] = v[i];
-    vel[3 * i + 1] = v[k + i];
-    vel[3 * i + 2] = v[2 * (size_t)k + i];
-    for (uint32_t m = 0; m < mm; ++m) levels[(size_t)i * mm + m] = lv[(size_t)i * lr + m];
-  }
+  auto put = [&](const auto *body) {
+    for (size_t i = 0; i < k; ++i) {
+      vel[3 * i] = body[i].x;
+      vel[3 * i + 1] = body[i].y;
+      vel[3 * i + 2] = body[i].z;
+      species[i] = (uint8_t)body[i].sp;
+    }
+  };
+  if (c->mixed)
+    put(reinterpret_cast<const Body32 *>(raw.data()));
+  else
+    put(reinterpret_cast<const Body64 *>(raw.data()));
+  if (lr == mm)
+    std::memcpy(levels, lv.data(), lv.size() * sizeof(uint16_t));
+  else
+    for (size_t i = 0; i < k; ++i)
+      for (uint32_t m = 0; m < mm; ++m) levels[i * mm + m] = lv[i * lr + m];
   return HCAO_OK;
 }
 
@@ -2658,21 +2683,12 @@ hcao_status hcao_save(hcao_ctx *c, const char *path) {
   if (hcao_status s = hcao_sync(c)) return s;
   const uint64_t tot = c->total_slots;
   const uint32_t nc = c->cfg.n_cells, mm = c->max_modes ? c->max_modes : 1;
-  std::vector<double> vx(tot), vy(tot), vz(tot), sg(nc), rm(nc), df(nc), ts(c->tsum.p ? 5 * (size_t)nc : 0);
-  std::vector<uint8_t> sp(tot);
-  std::vector<uint16_t> lv(tot * mm);
+  SlotArrays A(tot, mm);
+  std::vector<double> sg(nc), rm(nc), df(nc), ts(c->tsum.p ? 5 * (size_t)nc : 0);
   std::vector<uint32_t> cnt(nc);
   std::vector<unsigned long long> ctr((size_t)nc * kNumCtr);
-  if (hcao_status s = download_bodies(c, 0, tot, vx.data(), vy.data(), vz.data(), sp.data())) return s;
+  if (hcao_status s = download_slots(c, mm, A)) return s;
   HIP_TRY(c, hipMemcpy(df.data(), c->defect.p, nc * 8, hipMemcpyDeviceToHost));
-  {
-    // the file holds n x max_modes rows; the device rows are level_row long
-    const uint32_t lr = level_row(c->max_modes);
-    std::vector<uint16_t> rows(tot * lr);
-    HIP_TRY(c, hipMemcpy(rows.data(), c->lvl.p, tot * lr * 2, hipMemcpyDeviceToHost));
-    for (uint64_t g = 0; g < tot; ++g)
-      for (uint32_t m = 0; m < mm; ++m) lv[g * mm + m] = rows[g * lr + m];
-  }
   HIP_TRY(c, hipMemcpy(cnt.data(), c->cnt.p, nc * 4, hipMemcpyDeviceToHost));
   HIP_TRY(c, hipMemcpy(sg.data(), c->sgmax.p, nc * 8, hipMemcpyDeviceToHost));
   HIP_TRY(c, hipMemcpy(rm.data(), c->rem.p, nc * 8, hipMemcpyDeviceToHost));
@@ -2709,11 +2725,11 @@ hcao_status hcao_save(hcao_ctx *c, const char *path) {
   ok = ok && std::fwrite(rm.data(), 8, nc, f) == nc;
   ok = ok && std::fwrite(df.data(), 8, nc, f) == nc;
   ok = ok && std::fwrite(ctr.data(), 8, ctr.size(), f) == ctr.size();
-  ok = ok && std::fwrite(vx.data(), 8, tot, f) == tot;
-  ok = ok && std::fwrite(vy.data(), 8, tot, f) == tot;
-  ok = ok && std::fwrite(vz.data(), 8, tot, f) == tot;
-  ok = ok && std::fwrite(sp.data(), 1, tot, f) == tot;
-  ok = ok && std::fwrite(lv.data(), 2, lv.size(), f) == lv.size();
+  ok = ok && std::fwrite(A.vx.data(), 8, tot, f) == tot;
+  ok = ok && std::fwrite(A.vy.data(), 8, tot, f) == tot;
+  ok = ok && std::fwrite(A.vz.data(), 8, tot, f) == tot;
+  ok = ok && std::fwrite(A.sp.data(), 1, tot, f) == tot;
+  ok = ok && std::fwrite(A.lv.data(), 2, A.lv.size(), f) == A.lv.size();
   ok = ok && std::fwrite(rt.data(), 8, rt.size(), f) == rt.size();
   ok = ok && std::fwrite(pos.data(), 8, pos.size(), f) == pos.size();
   ok = ok && std::fwrite(irem.data(), 8, irem.size(), f) == irem.size();
@@ -2741,21 +2757,20 @@ hcao_status hcao_restore(hcao_ctx *c, const char *path) {
   }
   const uint64_t tot = hdr[3];
   std::vector<uint32_t> capv(nc), cnt(nc);
-  std::vector<double> sg(nc), rm(nc), df(nc), vx(tot), vy(tot), vz(tot);
+  SlotArrays A(tot, mm);
+  std::vector<double> sg(nc), rm(nc), df(nc);
   std::vector<unsigned long long> ctr((size_t)nc * kNumCtr);
-  std::vector<uint8_t> sp(tot);
-  std::vector<uint16_t> lv(tot * mm);
   bool ok = std::fread(capv.data(), 4, nc, f) == nc;
   ok = ok && std::fread(cnt.data(), 4, nc, f) == nc;
   ok = ok && std::fread(sg.data(), 8, nc, f) == nc;
   ok = ok && std::fread(rm.data(), 8, nc, f) == nc;
   ok = ok && std::fread(df.data(), 8, nc, f) == nc;
   ok = ok && std::fread(ctr.data(), 8, ctr.size(), f) == ctr.size();
-  ok = ok && std::fread(vx.data(), 8, tot, f) == tot;
-  ok = ok && std::fread(vy.data(), 8, tot, f) == tot;
-  ok = ok && std::fread(vz.data(), 8, tot, f) == tot;
-  ok = ok && std::fread(sp.data(), 1, tot, f) == tot;
-  ok = ok && std::fread(lv.data(), 2, lv.size(), f) == lv.size();
+  ok = ok && std::fread(A.vx.data(), 8, tot, f) == tot;
+  ok = ok && std::fread(A.vy.data(), 8, tot, f) == tot;
+  ok = ok && std::fread(A.vz.data(), 8, tot, f) == tot;
+  ok = ok && std::fread(A.sp.data(), 1, tot, f) == tot;
+  ok = ok && std::fread(A.lv.data(), 2, A.lv.size(), f) == A.lv.size();
   std::vector<double> rt(c->tab.has_rot ? tot : 0);
   ok = ok && std::fread(rt.data(), 8, rt.size(), f) == rt.size();
   std::vector<double> pos(c->spatial ? 3 * tot : 0);
@@ -2772,15 +2787,8 @@ hcao_status hcao_restore(hcao_ctx *c, const char *path) {
   for (uint32_t v : capv) t2 += v;
   if (t2 != tot) return fail(c, HCAO_EINVAL, "checkpoint capacities inconsistent");
   if (hcao_status st = alloc_state(c, cnt, &capv)) return st;
-  if (hcao_status s = upload_bodies(c, vx, vy, vz, sp)) return s;
+  if (hcao_status s = upload_slots(c, mm, A)) return s;
   HIP_TRY(c, hipMemcpy(c->defect.p, df.data(), nc * 8, hipMemcpyHostToDevice));
-  {
-    const uint32_t lr = level_row(c->max_modes);
-    std::vector<uint16_t> rows(tot * lr, 0);
-    for (uint64_t g = 0; g < tot; ++g)
-      for (uint32_t m = 0; m < mm; ++m) rows[g * lr + m] = lv[g * mm + m];
-    HIP_TRY(c, hipMemcpy(c->lvl.p, rows.data(), tot * lr * 2, hipMemcpyHostToDevice));
-  }
   HIP_TRY(c, hipMemcpy(c->sgmax.p, sg.data(), nc * 8, hipMemcpyHostToDevice));
   HIP_TRY(c, hipMemcpy(c->rem.p, rm.data(), nc * 8, hipMemcpyHostToDevice));
   HIP_TRY(c, hipMemcpy(c->ctr.p, ctr.data(), ctr.size() * 8, hipMemcpyHostToDevice));
