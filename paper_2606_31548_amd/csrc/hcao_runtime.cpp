@@ -106,6 +106,10 @@ constexpr size_t kRecLdsBudget = 64 * 1024;  // LDS bytes of the exact recombina
 constexpr int kDefaultBlock = 64;  // launch shape; the pair of them stands for the automatic choice (choose_shape)
 constexpr uint32_t kDefaultSlots = 1024;
 constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups a small context is spread over
+// Cells whose counters are summed on the host: one small copy, where the device
+// takes a fill, a kernel and a copy (us on the host and the device: 64 cells 19,
+// 29; 512 21, 30; 1,024 31, 30).
+constexpr uint32_t kCountersOnHost = 512;
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
 struct SpeciesHost {
@@ -2463,6 +2467,16 @@ hcao_status hcao_read_reaction_counts(hcao_ctx *c, uint64_t *counts) {
   const uint32_t nr = (uint32_t)c->reactions.size();
   if (nr == 0) {
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return HCAO_OK;
+  }
+  if (nc <= kCountersOnHost) {
+    std::vector<unsigned long long> ctr((size_t)nc * kNumCtr);
+    HIP_TRY(c, hipMemcpyAsync(ctr.data(), c->ctr.p, ctr.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    for (uint32_t r = 0; r < nr; ++r) {
+      counts[r] = 0;
+      for (uint32_t i = 0; i < nc; ++i) counts[r] += ctr[(size_t)i * kNumCtr + HCAO_CTR_REACTION0 + r];
+    }
     return HCAO_OK;
   }
   unsigned long long sums[kMaxReactions];
