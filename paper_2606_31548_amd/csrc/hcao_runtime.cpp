@@ -110,6 +110,11 @@ constexpr uint32_t kShapeGroups = 1024;  // default shape: workgroups a small co
 // takes a fill, a kernel and a copy (us on the host and the device: 64 cells 19,
 // 29; 512 21, 30; 1,024 31, 30).
 constexpr uint32_t kCountersOnHost = 512;
+// Vibrational temperatures (cells times species) inverted on the host: one at a
+// time, about 2 us each, where the device takes as long for one as for
+// thousands (the moments of one methane/argon cell 88 and 141 us on the host and
+// the device, of 12 cells 149 and 152, of 24 about 200 and 158).
+constexpr uint64_t kThermoOnHost = 64;
 constexpr uint32_t kMaxGroupCells = 64;   // cells per workgroup at most
 
 struct SpeciesHost {
@@ -245,9 +250,9 @@ struct hcao_ctx {
   RecScratch rec_scratch;
   LoadScratch io;
   HostStage stage;
-  // moments: the cells' sums, their partial totals, vibrational temperatures
+  // moments: the cells' sums and their partial totals, vibrational temperatures
   // (scratch, kept), and the thermometer's tables
-  DevBuf<double> mom_raw, mom_part, mom_tvib, thermo_mean;
+  DevBuf<double> mom_raw, mom_tvib, thermo_mean;
   DevBuf<unsigned long long> rx_sum;
   uint32_t thermo_same[kMaxSpecies] = {};
   hcao_config cfg{};
@@ -2400,24 +2405,30 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
   // eight waves per cell where a cell holds more than a wave's few rounds
   const bool large = c->total_slots > (uint64_t)kMomentsLarge * nc;
   const uint32_t blocks = std::min(256u, (nc + 63u) / 64u);
-  HIP_TRY(c, c->mom_raw.reserve((size_t)nc * w));
-  HIP_TRY(c, c->mom_part.reserve((size_t)blocks * cols));
+  // the cells' rows and, behind them, the partial totals: one copy brings both
+  const size_t rows = (size_t)nc * w, parts = (size_t)blocks * cols;
+  HIP_TRY(c, c->mom_raw.reserve(rows + parts));
   HIP_TRY(c, launch_moments(c->d_tab.p, c->d_lev.p, state_of(c), c->off.p, c->cnt.p, c->cap.p, c->mom_raw.p, nc, ns,
                             large, c->n_large ? c->large_cells.p : nullptr, c->n_large, c->stream));
-  HIP_TRY(c, launch_moments_sum(c->mom_raw.p, c->d_weight.p, c->defect.p, c->mom_part.p, nc, w, ns, blocks, c->stream));
-  std::vector<double> part((size_t)blocks * cols), raw, df, tv;
+  HIP_TRY(c, launch_moments_sum(c->mom_raw.p, c->d_weight.p, c->defect.p, c->mom_raw.p + rows, nc, w, ns, blocks,
+                                c->stream));
+  std::vector<double> raw((per_cell ? rows : 0) + parts), df, tv;
+  const double *const part = raw.data() + (raw.size() - parts);
   if (per_cell) {
-    HIP_TRY(c, c->mom_tvib.reserve((size_t)nc * ns));
-    HIP_TRY(c, launch_thermometer(c->d_tab.p, c->d_lev.p, c->thermo_mean.p, c->mom_raw.p, c->mom_tvib.p, nc, w, ns,
-                                  c->thermo_same, c->stream));
-    raw.resize((size_t)nc * w);
+    const bool on_host = (uint64_t)nc * ns <= kThermoOnHost;
+    if (!on_host) {
+      HIP_TRY(c, c->mom_tvib.reserve((size_t)nc * ns));
+      HIP_TRY(c, launch_thermometer(c->d_tab.p, c->d_lev.p, c->thermo_mean.p, c->mom_raw.p, c->mom_tvib.p, nc, w, ns,
+                                    c->thermo_same, c->stream));
+      tv.resize((size_t)nc * ns);
+    }
     df.resize(nc);
-    tv.resize((size_t)nc * ns);
-    HIP_TRY(c, hipMemcpyAsync(raw.data(), c->mom_raw.p, raw.size() * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipMemcpyAsync(df.data(), c->defect.p, nc * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(tv.data(), c->mom_tvib.p, tv.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    if (!on_host)
+      HIP_TRY(c, hipMemcpyAsync(tv.data(), c->mom_tvib.p, tv.size() * 8, hipMemcpyDeviceToHost, c->stream));
   }
-  HIP_TRY(c, hipMemcpyAsync(part.data(), c->mom_part.p, part.size() * 8, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(raw.data(), c->mom_raw.p + (rows + parts - raw.size()), raw.size() * 8,
+                            hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   auto fill = [&](hcao_moments &M, const double *r, const double *t_vib, double vol, double wgt) {
     std::memset(&M, 0, sizeof(M));
@@ -2444,7 +2455,8 @@ hcao_status hcao_read_moments(hcao_ctx *c, hcao_moments *per_cell, hcao_moments 
   };
   if (per_cell)
     for (uint32_t i = 0; i < nc; ++i) {
-      fill(per_cell[i], raw.data() + (size_t)i * w, tv.data() + (size_t)i * ns, c->volume[i], c->weight[i]);
+      fill(per_cell[i], raw.data() + (size_t)i * w, tv.empty() ? nullptr : tv.data() + (size_t)i * ns, c->volume[i],
+           c->weight[i]);
       per_cell[i].E_defect_J = df[i];
     }
   if (total) {
@@ -2839,7 +2851,6 @@ void hcao_destroy(hcao_ctx *c) {
   c->io.release();
   c->stage.release();
   c->mom_raw.release();
-  c->mom_part.release();
   c->mom_tvib.release();
   c->thermo_mean.release();
   c->rx_sum.release();
