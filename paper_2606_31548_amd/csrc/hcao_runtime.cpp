@@ -620,9 +620,10 @@ State state_of(hcao_ctx *c) {
   set_slots(s, c->total_slots);
   return s;
 }
+uint64_t staged_slots(const hcao_ctx *c) { return c->spatial ? c->total_slots : c->work_entries; }
 State staging_of(hcao_ctx *c) {
   State s = state_over(c, c->bbody.p, c->blvl.p, c->brot.p, c->bpx.p, c->bpy.p, c->bpz.p);
-  set_slots(s, c->total_slots);
+  set_slots(s, staged_slots(c));
   return s;
 }
 CellArrays cells_of(hcao_ctx *c) {
@@ -908,7 +909,6 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   HIP_TRY(c, c->lvl.alloc(tot * level_row(mm)));
   if (c->tab.has_rot) {
     HIP_TRY(c, c->rot.alloc(tot));
-    HIP_TRY(c, c->brot.alloc(tot));
     HIP_TRY(c, hipMemsetAsync(c->rot.p, 0, tot * sizeof(double), c->stream));
   }
   if (c->spatial) {
@@ -963,10 +963,13 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
     HIP_TRY(c, hipMemcpyAsync(c->large_cells.p, large.data(), large.size() * sizeof(uint32_t), hipMemcpyHostToDevice,
                               c->stream));
   }
-  // products staging (indexed like the state)
-  HIP_TRY(c, c->bbody.alloc(tot * body_bytes(c)));
-  HIP_TRY(c, c->blvl.alloc(tot * level_row(mm)));
   if (hcao_status st = build_groups(c)) return st;
+  // products staging: a row per work entry; in the spatial mode the re-bin's
+  // second copy of the state serves
+  const uint64_t staged = staged_slots(c);
+  HIP_TRY(c, c->bbody.alloc(staged * body_bytes(c)));
+  HIP_TRY(c, c->blvl.alloc(staged * level_row(mm)));
+  if (c->tab.has_rot) HIP_TRY(c, c->brot.alloc(staged));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->n_large = (uint32_t)large.size();
   return HCAO_OK;
