@@ -389,12 +389,6 @@ __device__ __forceinline__ double dpow(double x, double y) {
   return dexp(y * dlog(x));
 }
 
-// Exact comparisons against a power through a single-precision filter.
-// est = 2^(y log2 x) from the hardware log2/exp2 (v_log_f32, v_exp_f32) is
-// within 5e-6 of x^y for x in [2^-53, 2^64] and y in (0, 1] (measured over
-// 1.7e7 operands); a decision further than kFilter from est is the one the
-// fp64 power gives, and only the band in between evaluates dpow. The
-// result of every comparison is therefore that of the fp64 expression.
 // Quantum numbers of slot i, a row of s.lrow uint16 read and written as
 // dwords (two modes each). load_levels unpacks the first n modes to
 // dst[m * ds]; store_levels packs src[m * ss] for m < n and zeros for
@@ -506,6 +500,12 @@ __device__ __forceinline__ uint32_t tree6_value(uint32_t lane) {
   return lane == 0 ? 0u : lane == 32 ? 1u : lane == 16 ? 2u : lane == 48 ? 3u : lane == 8 ? 4u : lane == 40 ? 5u : 6u;
 }
 
+// Exact comparisons against a power through a single-precision filter.
+// est = 2^(y log2 x) from the hardware log2/exp2 (v_log_f32, v_exp_f32) is
+// within 5e-6 of x^y for x in [2^-53, 2^64] and y in (0, 1] (measured over
+// 1.7e7 operands); a decision further than kFilter from est is the one the
+// fp64 power gives, and only the band in between evaluates dpow. The
+// result of every comparison is therefore that of the fp64 expression.
 constexpr double kFilter = 1e-4;
 
 __device__ __forceinline__ double pow_estimate(double x, double y) {
@@ -1056,11 +1056,11 @@ __device__ uint32_t relax(const Ctx &C, const SpeciesTab &S, uint16_t *lv, uint3
   // The proposed level and the acceptance are decided from single-precision
   // estimates of c, the CDF's inverse and the power; a proposal too near a
   // boundary (an integer of the inverse, a square root near 0, or u near the
-  // target) is decided by the form's own expressions (gibbs_trial), so every
-  // decision is theirs. A wave waits here for its slowest lane at each mode,
-  // so the length of this chain sets the time of the collision phase: in the
-  // form's own arithmetic it held two fp64 divisions and a bisection per
-  // mode, and two divisions and a square root per trial.
+  // target) is decided by the form's own expressions (gibbs_level and
+  // gibbs_accept), so every decision is theirs. A wave waits here for its
+  // slowest lane at each mode, so the length of this chain sets the time of the
+  // collision phase: in the form's own arithmetic it held two fp64 divisions and
+  // a bisection per mode, and two divisions and a square root per trial.
   double et = e_tr;
   const double *lev = C.T.lev;
   const float qf = (float)q;
@@ -1885,8 +1885,8 @@ struct PairVel {
 //
 // What bounds it: vector arithmetic, where there are cells enough to fill the
 // chip (the pairs' samplers, then the permutation and the generator: about
-// 19,000 vector instructions per seven cells of 256 particles and step; the
-// issue slots are 85% busy). It was bound by cache lines before: 262,144 cells
+// 19,000 vector instructions per seven cells of 256 particles and step; in the
+// mixed form the issue slots are 93% busy). It was bound by cache lines before: 262,144 cells
 // of 256, 50 steps, 93 ms mixed and 101 fp64, now 63 and 73. Velocity and
 // species are therefore one record; an accepted pair's velocities go from
 // phase A to B, and from B's decision to its scattering, through a dense list
@@ -3103,8 +3103,8 @@ __global__ __launch_bounds__(256) void k_reaction_sum(const unsigned long long *
 }
 
 // ---------------------------------------------------------------------------
-// stable counting sort of particles by cell (LSD radix, 8-bit digits):
-// per-tile digit histograms, one exclusive scan in digit-major order, and a
+// stable counting sort of particles by cell (LSD radix, passes of equal digit
+// width up to 9 bits): per-tile digit histograms, one exclusive scan in digit-major order, and a
 // stable scatter that ranks equal digits inside a wavefront with ballots.
 // ---------------------------------------------------------------------------
 constexpr int kSortBlock = 256;

@@ -1,8 +1,8 @@
 // hcao_runtime.cpp -- host runtime behind the C ABI of include/hcao.h.
 //
 // Builds the species, pair and reaction tables on the host, owns the
-// device buffers of the structure-of-arrays particle state, and issues the
-// gfx950 kernels of hcao_kernels.hip on the context's stream.
+// device buffers of the particle state, and issues the gfx950 kernels of
+// hcao_kernels.hip and hcao_recombination.hip on the context's stream.
 #include <hip/hip_runtime.h>
 #include <rocprofiler-sdk-roctx/roctx.h>
 
@@ -1796,7 +1796,7 @@ hcao_status move_rebin(hcao_ctx *c, double dt, uint32_t step, hipStream_t s) {
     in.periodic = c->periodic;
     in.open = c->open_faces;
     in.n_species = ns;
-  in.n_levels = c->tab.n_levels;
+    in.n_levels = c->tab.n_levels;
     in.step = step;
     HIP_TRY(c, launch_inflow_count(in, s));
     // the entry past the last (face cell, species) stays zero: the scan's

@@ -259,14 +259,14 @@ struct MoveArgs {
   unsigned long long *flux;  // [2]: admitted, left (null without open faces)
 };
 
-// Spatial mode, admission through open faces; one thread per (face cell,
-// species), face cells numbered over all six faces (face f = 2 axis + side
-// starts at face_base[f]). The count pass sets count[t] = floor(x) with x =
-// ((flux_s A) dt) / F_N + rem[t] and keeps the fraction in rem[t]; the make
-// pass (one thread per admission) writes admission j of the step (j =
-// ibase[t] + i) to slot j of the staging state ins and to the mover list at movers + j with the virtual
-// old slot tot + j and its new cell (n_cells if it leaves again during its
-// partial flight).
+// Spatial mode, admission through open faces; the count pass takes one thread
+// per (face cell, species), face cells numbered over all six faces (face f = 2
+// axis + side starts at face_base[f]). It sets count[t] = floor(x) with x =
+// ((flux_s A) dt) / F_N + rem[t] and keeps the fraction in rem[t]; the make pass
+// (one, four or eight lanes per admission) writes admission j of the step (j =
+// ibase[t] + i) to slot j of the staging state ins and to the mover list at
+// movers + j with the virtual old slot tot + j and its new cell (n_cells if it
+// leaves again during its partial flight).
 struct InflowArgs {
   const Tables *tab;
   const double *lev;
