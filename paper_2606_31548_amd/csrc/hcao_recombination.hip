@@ -329,25 +329,16 @@ __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
   __syncthreads();
   double acc = 0.0;
   for (uint64_t i = tid; i < A.n_rec; i += 256) {
-    const double e = A.rec_e[i];
+    const double e = A.rec_e[i], w = WEIGHTED ? A.rec_w[i] : 1.0;
     const uint32_t code = A.rec_code[i];
-    if constexpr (!WEIGHTED) {
-      if (code == kRecLeaf) {
-        acc += gamma_q_scaled(A.a, beta * (A.de - e), A.lgamma_a, beta * e);
-      } else {
-        const uint32_t m = code & 0xFFu, jj = code >> 8;
-        const double rel = m < S.n_bend ? s_bend[m] : tail[(S.lev_off[m] - S.lev_off[S.n_bend]) + jj];
-        acc += (exp(-(beta * e)) * rel) * s_z[m + 1];
-      }
-      continue;
-    }
-    const double w = A.rec_w[i];
     if (code == kRecLeaf) {
       acc += w * gamma_q_scaled(A.a, beta * (A.de - e), A.lgamma_a, beta * e);
     } else {
-      const uint32_t u = code & 0xFFu, jj = code >> 8, d = A.units.degree[u], m = A.units.mode[u];
+      const uint32_t u = code & 0xFFu, jj = code >> 8, d = WEIGHTED ? A.units.degree[u] : (u < S.n_bend ? 1u : 0u);
       double rel;
-      if (d) {
+      if (!WEIGHTED && d) {
+        rel = s_bend[u];
+      } else if (d) {
         // R_d(v) = sum_k C(v + k + d - 1, d - 1) r^k by R_d(v) = (C(v + d - 2,
         // d - 1) + R_{d-1}(v)) / (1 - r), R_1 = 1 / (1 - r): no term cancels
         const double z = s_bend[u];
@@ -358,6 +349,7 @@ __global__ __launch_bounds__(256) void k_rec_sum(RecSumArgs A) {
           rel = (g + rel) * z;
         }
       } else {
+        const uint32_t m = WEIGHTED ? A.units.mode[u] : u;
         rel = tail[(S.lev_off[m] - S.lev_off[S.n_bend]) + jj];
       }
       acc += w * ((exp(-(beta * e)) * rel) * s_z[u + 1]);
