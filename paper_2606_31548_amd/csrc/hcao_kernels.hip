@@ -3465,24 +3465,49 @@ __device__ __forceinline__ uint32_t axis_index(double x, double len, uint32_t n)
   return (uint32_t)f;
 }
 
-// The move of one cell by WAVES waves (wave w of them): slots in chunks of 64
-// PER per wave, ranks in slot order from ballots and, with several waves,
-// their totals of the chunk in LDS (s_cnt, used in turn so that one barrier per
-// chunk does).
-template <uint32_t WAVES, uint32_t PER>
-__device__ __forceinline__ void move_cell(const MoveArgs &A, uint32_t c, uint32_t w, uint32_t lane,
-                                          uint32_t (*s_cnt)[2][4], uint32_t &turn) {
+// a moved particle's new cell; false if it left through an open face. The moved
+// state is not stored: the place pass moves the particle again as it copies it
+// (the same arithmetic, so the same bits)
+__device__ __forceinline__ bool moved_cell(const MoveArgs &A, double x, double y, double z, Vec3 v, uint32_t &key) {
+  bool flip = false;
+  if (move_particle(x, y, z, v.x, v.y, v.z, A.dt, A.len, A.periodic, A.open, flip)) return false;
+  key = axis_index(x, A.len[0], A.nx) + A.nx * (axis_index(y, A.len[1], A.ny) + A.ny * axis_index(z, A.len[2], A.nz));
+  return true;
+}
+
+// stayer ranks count up from the cell's first slot, mover ranks down from its
+// last: together they never pass n <= cap entries
+__device__ __forceinline__ void list_particle(const MoveArgs &A, uint64_t base, uint32_t top, uint32_t i, uint32_t key,
+                                              bool mover, bool stayer, uint32_t rank_m, uint32_t rank_s) {
+  if (mover) {
+    const uint64_t at = base + top - rank_m;
+    A.list[at] = i;
+    A.key[at] = key;
+  }
+  if (stayer) A.list[base + rank_s] = i;
+}
+
+__device__ __forceinline__ void finish_cell(const MoveArgs &A, uint32_t c, uint32_t n, uint32_t stay, uint32_t move) {
+  A.n_stay[c] = stay;
+  A.n_move[c] = move;
+  const uint32_t gone = n - stay - move;
+  if (gone && A.flux) atomicAdd(&A.flux[1], (unsigned long long)gone);
+}
+
+// The move of one cell by a wave, two slots per lane loaded together; ranks in
+// slot order come from ballots.
+__device__ __forceinline__ void move_cell_wave(const MoveArgs &A, uint32_t c, uint32_t n, uint32_t lane) {
+  constexpr uint32_t kPer = 2;
   const uint64_t base = A.off[c];
-  const uint32_t n = A.cnt[c], top = A.cap[c] - 1u;
+  const uint32_t top = A.cap[c] - 1u;
   const uint64_t below_lane = (1ull << lane) - 1ull;
   uint32_t run_s = 0, run_m = 0;
-  for (uint32_t i0 = 0; i0 < n; i0 += 64 * PER * WAVES) {
-    Vec3 v[PER];
-    double x[PER], y[PER], z[PER];
-    const uint32_t first = i0 + 64 * PER * w + lane;
+  for (uint32_t i0 = 0; i0 < n; i0 += 64 * kPer) {
+    Vec3 v[kPer];
+    double x[kPer], y[kPer], z[kPer];
 #pragma unroll
-    for (uint32_t q = 0; q < PER; ++q) {
-      const uint32_t i = first + 64 * q;
+    for (uint32_t q = 0; q < kPer; ++q) {
+      const uint32_t i = i0 + 64 * q + lane;
       if (i < n) {
         const uint64_t g = base + i;
         v[q] = load_body(A.st, g).v;
@@ -3491,97 +3516,89 @@ __device__ __forceinline__ void move_cell(const MoveArgs &A, uint32_t c, uint32_
         z[q] = A.st.pz[g];
       }
     }
-    uint64_t bm[PER], bs[PER];
-    uint32_t key[PER], ms = 0, ss = 0;
 #pragma unroll
-    for (uint32_t q = 0; q < PER; ++q) {
-      const uint32_t i = first + 64 * q;
-      bool mover = false, stayer = false;
-      key[q] = 0;
-      if (i < n) {
-        bool flip = false;
-        // the moved state is not stored: the place pass moves the particle
-        // again as it copies it (the same arithmetic, so the same bits)
-        if (!move_particle(x[q], y[q], z[q], v[q].x, v[q].y, v[q].z, A.dt, A.len, A.periodic, A.open, flip)) {
-          key[q] = axis_index(x[q], A.len[0], A.nx) +
-                   A.nx * (axis_index(y[q], A.len[1], A.ny) + A.ny * axis_index(z[q], A.len[2], A.nz));
-          mover = key[q] != c;
-          stayer = !mover;
-        }
-      }
-      bm[q] = __ballot(mover);
-      bs[q] = __ballot(stayer);
-      ms += (uint32_t)__popcll(bm[q]);
-      ss += (uint32_t)__popcll(bs[q]);
-    }
-    uint32_t pre_s = run_s, pre_m = run_m;
-    if constexpr (WAVES > 1) {
-      uint32_t(*t)[4] = s_cnt[turn & 1u];
-      ++turn;
-      if (lane == 0) {
-        t[0][w] = ss;
-        t[1][w] = ms;
-      }
-      __syncthreads();
-#pragma unroll
-      for (uint32_t u = 0; u < WAVES; ++u) {
-        if (u < w) {
-          pre_s += t[0][u];
-          pre_m += t[1][u];
-        }
-        run_s += t[0][u];
-        run_m += t[1][u];
-      }
-    } else {
-      run_s += ss;
-      run_m += ms;
-    }
-    // stayer ranks count up from the first slot, mover ranks down from the
-    // last: together they never pass n <= cap entries
-#pragma unroll
-    for (uint32_t q = 0; q < PER; ++q) {
-      const uint32_t i = first + 64 * q;
-      if ((bm[q] >> lane) & 1ull) {
-        const uint64_t at = base + top - (pre_m + (uint32_t)__popcll(bm[q] & below_lane));
-        A.list[at] = i;
-        A.key[at] = key[q];
-      }
-      if ((bs[q] >> lane) & 1ull) A.list[base + pre_s + (uint32_t)__popcll(bs[q] & below_lane)] = i;
-      pre_s += (uint32_t)__popcll(bs[q]);
-      pre_m += (uint32_t)__popcll(bm[q]);
+    for (uint32_t q = 0; q < kPer; ++q) {
+      const uint32_t i = i0 + 64 * q + lane;
+      uint32_t key = 0;
+      const bool here = i < n && moved_cell(A, x[q], y[q], z[q], v[q], key);
+      const bool mover = here && key != c, stayer = here && key == c;
+      const uint64_t bm = __ballot(mover), bs = __ballot(stayer);
+      list_particle(A, base, top, i, key, mover, stayer, run_m + (uint32_t)__popcll(bm & below_lane),
+                    run_s + (uint32_t)__popcll(bs & below_lane));
+      run_s += (uint32_t)__popcll(bs);
+      run_m += (uint32_t)__popcll(bm);
     }
   }
-  if (lane == 0 && w == 0) {
-    A.n_stay[c] = run_s;
-    A.n_move[c] = run_m;
-    const uint32_t gone = n - run_s - run_m;
-    if (gone && A.flux) atomicAdd(&A.flux[1], (unsigned long long)gone);
-  }
+  if (lane == 0) finish_cell(A, c, n, run_s, run_m);
 }
 
-// Bandwidth bound. CELLS 1: four waves per cell, one slot per lane and chunk.
-// CELLS 4: one wave per cell with two slots per lane, for many small cells; a
-// cell of more than kMoveBig particles still takes the workgroup's four waves.
-// us with CELLS 1 and 4: fp64, 262,144 cells of 100: 559, 401; of 256: 855, 850;
-// 40,095 of 200: 108, 114; 32,768 of 600: 245, 263. Mixed, 262,144 of 256: 886,
-// 713; 40,095 of 200: 107, 100; 32,768 of 400: 151, 151; of 600: 210, 217. Few
-// cells leave the chip idle in fours: 4,096 of 100 10.9, 10.6; 1,728 of 200 8.1,
-// 10.4; 512 of 600 8.3, 18; 64 of 100,000 634, 2,519.
+// The same by the four waves of a workgroup, one slot per lane; the waves' totals
+// of a chunk meet in LDS (s_cnt, used in turn so that one barrier per chunk does).
+__device__ __forceinline__ void move_cell_group(const MoveArgs &A, uint32_t c, uint32_t n, uint32_t w, uint32_t lane,
+                                                uint32_t (*s_cnt)[2][4], uint32_t &turn) {
+  const uint64_t base = A.off[c];
+  const uint32_t top = A.cap[c] - 1u;
+  const uint64_t below_lane = (1ull << lane) - 1ull;
+  uint32_t run_s = 0, run_m = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += 256) {
+    const uint32_t i = i0 + 64 * w + lane;
+    const uint64_t g = base + i;
+    uint32_t key = 0;
+    const bool here = i < n && moved_cell(A, A.st.px[g], A.st.py[g], A.st.pz[g], load_body(A.st, g).v, key);
+    const bool mover = here && key != c, stayer = here && key == c;
+    const uint64_t bm = __ballot(mover), bs = __ballot(stayer);
+    uint32_t(*t)[4] = s_cnt[turn & 1u];
+    ++turn;
+    if (lane == 0) {
+      t[0][w] = (uint32_t)__popcll(bs);
+      t[1][w] = (uint32_t)__popcll(bm);
+    }
+    __syncthreads();
+    uint32_t pre_s = run_s, pre_m = run_m;
+#pragma unroll
+    for (uint32_t u = 0; u < 4; ++u) {
+      if (u < w) {
+        pre_s += t[0][u];
+        pre_m += t[1][u];
+      }
+      run_s += t[0][u];
+      run_m += t[1][u];
+    }
+    list_particle(A, base, top, i, key, mover, stayer, pre_m + (uint32_t)__popcll(bm & below_lane),
+                  pre_s + (uint32_t)__popcll(bs & below_lane));
+  }
+  if (lane == 0 && w == 0) finish_cell(A, c, n, run_s, run_m);
+}
+
+// Bandwidth bound. CELLS 1: four waves per cell. CELLS 4: one wave per cell, for
+// many small cells; with BIG, a cell of more than kMoveBig particles still takes
+// the workgroup's four waves (boxes without such a cell do without the test: 98
+// and 102 us for the channel of 40,095 cells of 200).
+// us with CELLS 1 and 4: fp64, 262,144 cells of 100: 559, 350; of 256: 827, 892;
+// 40,095 of 200: 110, 115; 32,768 of 600: 242, 276. Mixed, 262,144 of 256: 886,
+// 679; 40,095 of 200: 107, 91; 32,768 of 400: 131, 142; of 600: 188, 210. Few
+// cells leave the chip idle in fours: 4,096 of 100 10.9, 9.3; 1,728 of 200 7.9,
+// 9.5; 512 of 600 7.5, 18; 64 of 100,000 600, 2,800.
 constexpr uint32_t kMoveBig = 1024;      // particles
 constexpr uint32_t kMoveManyCells = 4096;
-constexpr uint32_t kMoveSmall64 = 160, kMoveSmall32 = 384;  // mean particles per cell, fp64 and mixed form
-template <uint32_t CELLS>
+constexpr uint32_t kMoveSmall64 = 160, kMoveSmall32 = 300;  // mean particles per cell, fp64 and mixed form
+template <uint32_t CELLS, bool BIG>
 __global__ __launch_bounds__(256) void k_move(MoveArgs A) {
-  __shared__ uint32_t s_cnt[2][2][4];
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63u;
-  const uint32_t c0 = blockIdx.x * CELLS;
-  uint32_t turn = 0;
-  if constexpr (CELLS == 1) {
-    move_cell<4, 1>(A, c0, wave, lane, s_cnt, turn);
-  } else {
-    if (c0 + wave < A.n_cells && A.cnt[c0 + wave] <= kMoveBig) move_cell<1, 2>(A, c0 + wave, 0, lane, s_cnt, turn);
-    for (uint32_t q = 0; q < CELLS && c0 + q < A.n_cells; ++q)
-      if (A.cnt[c0 + q] > kMoveBig) move_cell<4, 1>(A, c0 + q, wave, lane, s_cnt, turn);
+  const uint32_t c0 = blockIdx.x * CELLS, own = c0 + wave;
+  if constexpr (CELLS > 1) {
+    if (own < A.n_cells) {
+      const uint32_t n = A.cnt[own];
+      if (!BIG || n <= kMoveBig) move_cell_wave(A, own, n, lane);
+    }
+  }
+  if constexpr (BIG) {
+    __shared__ uint32_t s_cnt[2][2][4];
+    uint32_t turn = 0;
+    for (uint32_t q = 0; q < CELLS && c0 + q < A.n_cells; ++q) {
+      const uint32_t n = A.cnt[c0 + q];
+      if (CELLS == 1 || n > kMoveBig) move_cell_group(A, c0 + q, n, wave, lane, s_cnt, turn);
+    }
   }
 }
 
@@ -4339,10 +4356,13 @@ hipError_t launch_move(const MoveArgs &a, hipStream_t s) {
   if (!a.off || !a.cnt || !a.cap || !a.key || !a.list || !a.n_stay || !a.n_move || !a.st.px || !a.st.py || !a.st.pz)
     return hipErrorInvalidValue;
   const uint64_t small = a.st.b32 ? kMoveSmall32 : kMoveSmall64;
-  if (a.n_cells >= kMoveManyCells && a.particles <= small * a.n_cells)
-    hipLaunchKernelGGL(k_move<4>, dim3((a.n_cells + 3u) / 4u), dim3(256), 0, s, a);
+  const dim3 fours((a.n_cells + 3u) / 4u);
+  if (a.n_cells < kMoveManyCells || a.particles > small * a.n_cells)
+    hipLaunchKernelGGL((k_move<1, true>), dim3(a.n_cells), dim3(256), 0, s, a);
+  else if (a.largest > kMoveBig)
+    hipLaunchKernelGGL((k_move<4, true>), fours, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL(k_move<1>, dim3(a.n_cells), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_move<4, false>), fours, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

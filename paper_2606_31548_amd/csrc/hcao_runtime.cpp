@@ -278,6 +278,7 @@ struct hcao_ctx {
   // particle state
   uint64_t total_slots = 0;
   uint64_t loaded_particles = 0;  // of the last load, init or restore
+  uint32_t largest_cap = 0;       // largest slot capacity of a cell
   std::vector<uint32_t> cap_host;
   std::vector<uint64_t> off_host;
   bool mixed = false;                         // fp32 velocities (mixed form)
@@ -902,6 +903,7 @@ hcao_status alloc_state(hcao_ctx *c, const std::vector<uint32_t> &counts,
   c->total_slots = tot;
   c->loaded_particles = 0;
   for (uint32_t n : counts) c->loaded_particles += n;
+  c->largest_cap = *std::max_element(c->cap_host.begin(), c->cap_host.end());
   // the spatial re-bin keeps old slots as 32-bit indices
   if (c->spatial && tot > 0xFFFFFFFFull) return fail(c, HCAO_EINVAL, "spatial mode holds at most 2^32 - 1 slots");
   const uint32_t mm = c->max_modes ? c->max_modes : 1;
@@ -1755,6 +1757,7 @@ hcao_status move_rebin(hcao_ctx *c, double dt, uint32_t step, hipStream_t s) {
   m.cnt = c->cnt.p;
   m.cap = c->cap.p;
   m.particles = c->loaded_particles;
+  m.largest = c->largest_cap;
   m.n_cells = nc;
   m.nx = c->grid[0];
   m.ny = c->grid[1];

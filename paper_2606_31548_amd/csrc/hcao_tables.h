@@ -252,6 +252,7 @@ struct MoveArgs {
   const uint64_t *off;
   const uint32_t *cnt, *cap;
   uint64_t particles;  // in the box when it was loaded
+  uint32_t largest;    // largest slot capacity of a cell
   uint32_t n_cells, nx, ny, nz, periodic, open;
   double len[3];
   double dt;

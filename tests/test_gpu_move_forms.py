@@ -28,12 +28,13 @@ def _box(grid, per_cell, sizes, faces):
 
 
 # at least 4,096 small cells: a wave per cell (chunks of 128), four waves above 1,024 particles (chunks of 256);
-# fewer: four waves per cell
+# fewer: four waves per cell; no cell above 1,024 slots: a wave per cell without the test for it
 _MANY = ((16, 16, 17), 24, {0: 0, 3: 127, 9: 128, 13: 129, 1000: 1024, 1001: 1025, 2003: 1281, 4000: 3001, 4351: 1300})
+_SMALL = ((16, 16, 17), 24, {0: 0, 3: 127, 9: 128, 13: 129, 1000: 257, 4351: 385})
 _FEW = ((5, 4, 3), 90, {0: 0, 7: 255, 20: 256, 31: 257, 44: 513, 59: 2001})
 
 
-@pytest.mark.parametrize("grid,per_cell,sizes", [_MANY, _FEW])
+@pytest.mark.parametrize("grid,per_cell,sizes", [_MANY, _SMALL, _FEW])
 @pytest.mark.parametrize("faces", [0, 3])
 def test_move_forms_parity(orc, hc, grid, per_cell, sizes, faces):
     wl = _box(grid, per_cell, sizes, faces)
@@ -50,7 +51,7 @@ def test_move_forms_parity(orc, hc, grid, per_cell, sizes, faces):
         assert np.array_equal(a.view(np.uint64), g.read_positions().view(np.uint64))
 
 
-@pytest.mark.parametrize("grid,per_cell,sizes", [_MANY, _FEW])
+@pytest.mark.parametrize("grid,per_cell,sizes", [_MANY, _SMALL, _FEW])
 def test_move_forms_mixed(hc, grid, per_cell, sizes):
     """The mixed form: no particle lost or doubled, each in its cell."""
     wl = _box(grid, per_cell, sizes, 0)
